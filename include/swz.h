@@ -128,6 +128,8 @@ int swz_pid_map_persistent_device(int grid_m, int grid_n, int num_xcd, int group
  *   Defaults: num_xcd detected, group_m = 4, tile 256x256x64; when the 256x256 tile grid would have at
  *   most half as many tiles as the device has compute units, 128x256x64, and at most a quarter, 128x128x64
  *   (the chip is then better filled by more and smaller tiles; the result bits do not depend on the tile shape).
+ *   Small and narrow products go further: a tile the library chose may be computed by several workgroups (sub-tiles of
+ *   32x32 to 128x128) that all run on the XCD the map gives the tile; plan, map and bits are those of the tile.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null pointer, M/N/K < 1, unknown mode), UNSUPPORTED (other dtype,
  * K or N not a multiple of 8, misaligned pointer), OVERFLOW (tile count >= 2^31 or a
@@ -136,7 +138,7 @@ int swz_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_
              hipStream_t stream);
 
 /* swz_gemm (paper: Appendix "Case Study: GEMM Swizzling") with explicit tile shape / group_m /
- * num_xcd / launch style (null params = all defaults); persistent = 1 is the launch style of the
+ * num_xcd / launch style (null params = all defaults; a tile named here is always one workgroup); persistent = 1 is the launch style of the
  * paper's own listing (as many workgroups as compute units, each looping over tiles).
  * UNSUPPORTED for tile rows or columns other than 128 or 256, or bk other than 64.  The persistent launch computes
  * every tile with the same instruction sequence, so its C is bit-identical to the default launch. */
@@ -201,7 +203,8 @@ int swz_layernorm(const void* in, const void* gamma, const void* beta, void* out
  * an instantiation of the same kernel that also takes time stamps, so that what bounds the kernel
  * (clock under load, cycles per K step, when each XCD finishes) can be read per workgroup.  The
  * stamps are kept in scalar registers while the tile is computed and written once at its end: the
- * loop's instruction stream is the product kernel's.  C is computed as by swz_gemm_ex.
+ * loop's instruction stream is the product kernel's.  One workgroup per tile of the plan, also where
+ * swz_gemm_ex would cut the tile into sub-tiles.  C is computed as by swz_gemm_ex.
  *   probe       : DEVICE buffer, 8-byte aligned, of probe_words >= 16 * grid_m * grid_n 64-bit words;
  *                 workgroup w (hardware id) writes words 16w .. 16w+15:
  *                 0,1  shader clock counter / constant 100 MHz counter at kernel entry

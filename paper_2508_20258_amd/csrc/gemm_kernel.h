@@ -174,6 +174,79 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
   (f(std::integral_constant<int, Is>{}), ...);
 }
 
+// The TM x TN blocks of 16 x 16 a wave has accumulated -> bf16 (nearest even) -> C, first row row_base, first
+// column col_base; rows >= M and columns >= N are left out.
+template <int TM, int TN>
+__device__ __forceinline__ void store_wave_tile(const f32x4 (&acc)[TM][TN], uint16_t* __restrict__ C, int M, int N,
+                                                int row_base, int col_base, int lane) {
+  // Lane (r = lane % 16, g = lane / 16) holds, for every block (bi, bj), C[16 bi + r][16 bj + 4 g + 0..3]:
+  // 8 bytes once converted.  v_permlane16_swap exchanges the odd 16-lane rows of one register with the
+  // even rows of another; applied to the registers of blocks bj = 2p and 2p + 1 it leaves every lane with
+  // 16 contiguous bytes: lanes g = 0, 2 hold columns 0..7, 8..15 of block 2p, lanes g = 1, 3 those of block
+  // 2p + 1, so the four lanes of a row cover 64 contiguous bytes.
+  // A wave with one column block has nothing to pair: it stores its 8 bytes per lane.
+  const int er = lane & 15, eg = lane >> 4;
+  const int ecol = col_base + ((eg & 1) ? 16 + 4 * (eg - 1) : 4 * eg);     // + 32 p
+  static_assert(TN == 1 || TN == 2 || TN == 4, "the register epilogue pairs up column blocks");
+#pragma unroll
+  for (int bi = 0; bi < TM; ++bi) {
+    if constexpr (TN == 1) {
+      bf16x4 c4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c4[e] = (__bf16)acc[bi][0][e];
+      const int row = row_base + 16 * bi + er, col = col_base + 4 * eg;
+      if (row < M && col < N) __builtin_nontemporal_store(c4, reinterpret_cast<bf16x4*>(C + (size_t)row * N + col));
+      continue;
+    }
+    u32x4 chunk[TN > 1 ? TN / 2 : 1];
+#pragma unroll
+    for (int p = 0; p < TN / 2; ++p) {
+      uint32_t d[2][2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        bf16x4 c4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c4[e] = (__bf16)acc[bi][2 * p + h][e];
+        const auto two = __builtin_bit_cast(__attribute__((ext_vector_type(2))) uint32_t, c4);
+        d[h][0] = two[0];
+        d[h][1] = two[1];
+      }
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        const auto sw = __builtin_amdgcn_permlane16_swap(d[0][w], d[1][w], false, false);
+        d[0][w] = sw[0];
+        d[1][w] = sw[1];
+      }
+      chunk[p] = u32x4{d[0][0], d[0][1], d[1][0], d[1][1]};
+    }
+    const int row0 = row_base + 16 * bi;
+    if constexpr (TN == 4) {
+      // Whole 128-byte lines per store instruction: lanes r and r + 8 trade one chunk (a rotation by 8 inside
+      // the 16-lane row), after which the first instruction writes rows 0..7 of the block (lanes r < 8 the
+      // left 64 bytes, lanes r >= 8 the right 64 bytes) and the second one rows 8..15.
+      const bool low = er < 8;
+      u32x4 give, got, s0, s1;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) give[e] = low ? chunk[1][e] : chunk[0][e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) got[e] = __builtin_amdgcn_mov_dpp(give[e], 0x128 /* row_ror:8 */, 0xf, 0xf, false);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0[e] = low ? chunk[0][e] : got[e];
+        s1[e] = low ? got[e] : chunk[1][e];
+      }
+      const int col = ecol + (low ? 0 : 32);
+      const int row = row0 + (er & 7);
+      // C is written once and not read again by this kernel: streaming (non-temporal) stores
+      if (row < M && col < N) __builtin_nontemporal_store(s0, reinterpret_cast<u32x4*>(C + (size_t)row * N + col));
+      if (row + 8 < M && col < N) __builtin_nontemporal_store(s1, reinterpret_cast<u32x4*>(C + (size_t)(row + 8) * N + col));
+    } else {
+      const int row = row0 + er;
+      if (row < M && ecol < N) __builtin_nontemporal_store(chunk[0], reinterpret_cast<u32x4*>(C + (size_t)row * N + ecol));
+    }
+  }
+}
+
 // What the timing instantiation of the kernel records per workgroup (64-bit words): the shader clock
 // counter and the constant 100 MHz counter at kernel entry, at the start and at the end of the K
 // loop and after the last store was issued, then XCC_ID, HW_ID, the number of K steps, tile row,
@@ -451,63 +524,7 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, const 
     aim_at(npm * BM, npn * BN);
     open_tile();
   }
-  // Lane (r = lane % 16, g = lane / 16) holds, for every block (bi, bj), C[16 bi + r][16 bj + 4 g + 0..3]:
-  // 8 bytes once converted.  v_permlane16_swap exchanges the odd 16-lane rows of one register with the
-  // even rows of another; applied to the registers of blocks bj = 2p and 2p + 1 it leaves every lane with
-  // 16 contiguous bytes: lanes g = 0, 2 hold columns 0..7, 8..15 of block 2p, lanes g = 1, 3 those of block
-  // 2p + 1, so the four lanes of a row cover 64 contiguous bytes.
-  const int er = lane & 15, eg = lane >> 4;
-  const int ecol = n0 + wn * (TN * 16) + ((eg & 1) ? 16 + 4 * (eg - 1) : 4 * eg);     // + 32 p
-  static_assert(TN == 2 || TN == 4, "the register epilogue pairs up column blocks");
-#pragma unroll
-  for (int bi = 0; bi < TM; ++bi) {
-    u32x4 chunk[TN / 2];
-#pragma unroll
-    for (int p = 0; p < TN / 2; ++p) {
-      uint32_t d[2][2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        bf16x4 c4;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c4[e] = (__bf16)acc[bi][2 * p + h][e];
-        const auto two = __builtin_bit_cast(__attribute__((ext_vector_type(2))) uint32_t, c4);
-        d[h][0] = two[0];
-        d[h][1] = two[1];
-      }
-#pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        const auto sw = __builtin_amdgcn_permlane16_swap(d[0][w], d[1][w], false, false);
-        d[0][w] = sw[0];
-        d[1][w] = sw[1];
-      }
-      chunk[p] = u32x4{d[0][0], d[0][1], d[1][0], d[1][1]};
-    }
-    const int row0 = m0 + wm * (TM * 16) + 16 * bi;
-    if constexpr (TN == 4) {
-      // Whole 128-byte lines per store instruction: lanes r and r + 8 trade one chunk (a rotation by 8 inside
-      // the 16-lane row), after which the first instruction writes rows 0..7 of the block (lanes r < 8 the
-      // left 64 bytes, lanes r >= 8 the right 64 bytes) and the second one rows 8..15.
-      const bool low = er < 8;
-      u32x4 give, got, s0, s1;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) give[e] = low ? chunk[1][e] : chunk[0][e];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) got[e] = __builtin_amdgcn_mov_dpp(give[e], 0x128 /* row_ror:8 */, 0xf, 0xf, false);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s0[e] = low ? chunk[0][e] : got[e];
-        s1[e] = low ? got[e] : chunk[1][e];
-      }
-      const int col = ecol + (low ? 0 : 32);
-      const int row = row0 + (er & 7);
-      // C is written once and not read again by this kernel: streaming (non-temporal) stores
-      if (row < M && col < N) __builtin_nontemporal_store(s0, reinterpret_cast<u32x4*>(C + (size_t)row * N + col));
-      if (row + 8 < M && col < N) __builtin_nontemporal_store(s1, reinterpret_cast<u32x4*>(C + (size_t)(row + 8) * N + col));
-    } else {
-      const int row = row0 + er;
-      if (row < M && ecol < N) __builtin_nontemporal_store(chunk[0], reinterpret_cast<u32x4*>(C + (size_t)row * N + ecol));
-    }
-  }
+  store_wave_tile<TM, TN>(acc, C, M, N, m0 + wm * (TM * 16), n0 + wn * (TN * 16), lane);
   take_stamp(3);
   if constexpr (PROBE) {
     if (tid == 0) {

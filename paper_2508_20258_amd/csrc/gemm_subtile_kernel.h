@@ -1,0 +1,270 @@
+// Tiled bf16 GEMM for gfx950 for products that the large tiles of gemm_kernel.h leave the chip idle or
+// waiting on: few rows, few columns, small grids.  Same operands, layouts, fragments and K order as there (one chain
+// of v_mfma_f32_16x16x32_bf16 per element, k ascending), hence the same bits; what differs is how much of C a
+// workgroup owns and how the K loop is fed.
+//
+// What bounds these products is latency, not a rate: a 256 x 256 or 128 x 128 tile leaves 64 to 250 of 256 CUs
+// without work, and with three K steps of look-ahead (0.3 us) a tile that has its CU to itself waits for most
+// of its operands.  Hence
+//   * sub-tiles: a tile of the plan is cut into workgroups of 32x32 to 128x128 elements of C, which all sit on the XCD the
+//     map gives the tile (they share its operand panels in that L2);
+//   * a ring of 5 to 8 stages, 64 of K each, fetched global -> LDS four to seven stages ahead;
+//   * one barrier per stage, and two sets of fragments: the reads of one half of a stage (32 of K) are issued
+//     between the MFMAs of the other half, the barrier falls between the two.  Measured against reading a whole
+//     stage, then multiplying it: 128x128 at 2048^3 21.7 -> 18.8 us, 64x64 at 1024^3 6.3 -> 6.2 us;
+//   * every slot address a compile-time constant (the loop is unrolled over the ring, base pointers advance by additions):
+//     with slots computed at run time the scalar instructions of a stage alone took 200 ns, a third more than the whole of a
+//     32x32 stage now (512^3 4.6 -> 3.9 us, 8x4096x4096 17.4 -> 11.9 us).
+// Measured (kernel time, operands not in cache; 128x128 or 128x256 tiles of gemm_kernel.h -> sub-tiles, the shape the rule
+// in swz.hip takes):
+//   512^3            8.1 ->  4.0 us (32x32)      1024^3          12.6 ->  6.2 us (64x64)
+//   1536^3          17.0 -> 13.2 us (128x128)    2048^3          21.9 -> 19.0 us (128x128)
+//   8x4096x4096     32.2 -> 11.9 us (32x32)      32x8192x8192    66.5 -> 40.4 us (32x32; reading B takes 22 at 6.3 TB/s)
+//   256x2048x2048   19.0 ->  9.0 us (32x64)      1024x2048x4096  33.2 -> 23.1 us (128x64)
+//   128x32768x2048  40.6 -> 29.4 us (128x128)    64x65536x4096  118.3 -> 96.8 us (64x128)
+//
+// LDS of a stage: A, BM rows x 64 of K (128 bytes, chunk c of row r in slot c ^ ((r >> 1) & 7)), then B, 64 rows x
+// BN columns (chunk c of row k in slot c ^ sub_b_key(k)); both conflict-free for the fragment reads.
+// Rows >= M and columns >= N are fetched from clamped addresses, chunks with k >= K from a block of zeros.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "gemm_kernel.h"
+#include "pid_decode.h"
+
+namespace swz {
+
+constexpr int kStageK = 64;    // K extent of a ring stage: two MFMA steps, whole 128-byte lines of A
+
+template <int BM_, int BN_, int WM_, int WN_, int STAGES_>
+struct SubShape {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, STAGES = STAGES_;
+  static constexpr int NW = WM * WN, NT = NW * 64;
+  static constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+  static constexpr int A_BYTES = BM * kStageK * 2, B_BYTES = kStageK * BN * 2;
+  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
+  static constexpr int B_ROW_CHUNKS = BN / 8;
+  static constexpr int A_LOADS = A_BYTES / (NT * 16), B_LOADS = B_BYTES / (NT * 16);
+  static constexpr int LOADS = A_LOADS + B_LOADS;               // per thread and stage
+  static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
+  static_assert(BM % (WM * 16) == 0 && BN % (WN * 16) == 0, "wave tiling");
+  static_assert(A_BYTES % (NT * 16) == 0 && B_BYTES % (NT * 16) == 0, "load tiling");
+  static_assert((STAGES - 1) * LOADS < 64, "loads in flight per wave: the counter has six bits");
+  static_assert(LDS_BYTES <= 160 * 1024 && STAGES >= 3, "LDS per workgroup");
+};
+
+// XOR key of row k of a B stage (applied to 16-byte chunk indices, whole 32-byte pairs): the 8 rows a half-wave
+// of transposing reads touches (k mod 16 in 0..3 and 8..11) land in 8 different 32-byte bank groups.
+template <int BN>
+__device__ __forceinline__ int sub_b_key(int k) {
+  if constexpr (BN >= 128) return b_key(k);
+  else if constexpr (BN == 64) return (((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1;
+  else return ((k >> 3) & 1) << 1;
+}
+
+template <class S>
+__device__ __forceinline__ void gemm_subtile(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
+                                             uint16_t* __restrict__ C, int M, int N, int K, int m0, int n0,
+                                             unsigned char* smem) {
+  constexpr int BM = S::BM, BN = S::BN, TM = S::TM, TN = S::TN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wm = wave / S::WN, wn = wave % S::WN;
+
+  uint32_t a_off[S::A_LOADS], b_off[S::B_LOADS];
+#pragma unroll
+  for (int i = 0; i < S::A_LOADS; ++i) {
+    const int q = (wave * S::A_LOADS + i) * 64 + lane;
+    const int row = q >> 3, c = a_slot(row, q & 7);
+    const int r = (m0 + row < M) ? row : (M - 1 - m0);
+    a_off[i] = (uint32_t)r * (uint32_t)K * 2u + (uint32_t)c * 16u;
+  }
+#pragma unroll
+  for (int i = 0; i < S::B_LOADS; ++i) {
+    const int q = (wave * S::B_LOADS + i) * 64 + lane;
+    const int krow = q / S::B_ROW_CHUNKS, c = (q % S::B_ROW_CHUNKS) ^ sub_b_key<BN>(krow);
+    const int col = (n0 + c * 8 < N) ? c * 8 : (N - 8 - n0);
+    b_off[i] = (uint32_t)krow * (uint32_t)N * 2u + (uint32_t)(col * 2);
+  }
+  const unsigned char* a_tile = reinterpret_cast<const unsigned char*>(A + (size_t)m0 * K);
+  const unsigned char* b_tile = reinterpret_cast<const unsigned char*>(B + n0);
+  const unsigned char* zero = reinterpret_cast<const unsigned char*>(&kZeroChunk);
+  const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  const size_t b_stage = (size_t)kStageK * N * 2;
+
+  const uint32_t a_dst = smem_addr + (uint32_t)wave * (S::A_LOADS * 1024);
+  const uint32_t b_dst = smem_addr + S::A_BYTES + (uint32_t)wave * (S::B_LOADS * 1024);
+  const unsigned char *a_next = a_tile, *b_next = b_tile;      // where the next stage to fetch starts
+  auto load_full = [&](uint32_t slot_off) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < S::B_LOADS; ++i) load_to_lds_base_off(b_next, b_off[i], b_dst + slot_off + i * 1024);
+#pragma unroll
+    for (int i = 0; i < S::A_LOADS; ++i) load_to_lds_base_off(a_next, a_off[i], a_dst + slot_off + i * 1024);
+    a_next += kStageK * 2;
+    b_next += b_stage;
+  };
+  auto load_tail = [&](int k_left, uint32_t slot_off) __attribute__((always_inline)) {     // k_left < kStageK of K are left
+#pragma unroll
+    for (int i = 0; i < S::B_LOADS; ++i) {
+      const int krow = ((wave * S::B_LOADS + i) * 64 + lane) / S::B_ROW_CHUNKS;
+      load_to_lds(krow < k_left ? b_next + b_off[i] : zero, b_dst + slot_off + i * 1024);
+    }
+#pragma unroll
+    for (int i = 0; i < S::A_LOADS; ++i) {
+      const int q = (wave * S::A_LOADS + i) * 64 + lane;
+      load_to_lds(a_slot(q >> 3, q & 7) * 8 < k_left ? a_next + a_off[i] : zero, a_dst + slot_off + i * 1024);
+    }
+  };
+  auto load_any = [&](int t, uint32_t slot_off) __attribute__((always_inline)) {
+    if ((t + 1) * kStageK <= K) load_full(slot_off);
+    else load_tail(K - t * kStageK, slot_off);
+  };
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  typedef __attribute__((address_space(3))) const bf16x8* lds_a_ptr;
+  typedef __attribute__((address_space(3))) s16x4* lds_b_ptr;
+  const int a_row0 = wm * (TM * 16) + (lane & 15);
+  const int b_krow0 = 8 * (lane >> 4) + ((lane & 15) >> 2);
+  uint32_t a_rd[2], b_rd[TN];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) a_rd[h] = smem_addr + (uint32_t)a_lds_off(a_row0, (lane >> 4) + 4 * h);
+#pragma unroll
+  for (int bj = 0; bj < TN; ++bj) {
+    const int col = wn * (TN * 16) + 4 * (lane & 3) + 16 * bj;
+    b_rd[bj] = smem_addr + (uint32_t)(S::A_BYTES + b_krow0 * (BN * 2) + (((col >> 3) ^ sub_b_key<BN>(b_krow0)) << 4) + (col & 7) * 2);
+  }
+  // Two sets of fragments, one per half of a stage: while the MFMAs of one half run, the other half's fragments
+  // are on their way.
+  bf16x8 af[2][TM];
+  s16x4 bq[2][TN][2];
+  auto read_half = [&](auto half, uint32_t base) __attribute__((always_inline)) {          // base: byte offset of the stage's slot
+    constexpr int H = decltype(half)::value;
+#pragma unroll
+    for (int bj = 0; bj < TN; ++bj)
+#pragma unroll
+      for (int hi = 0; hi < 2; ++hi)
+        bq[H][bj][hi] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_b_ptr)(uintptr_t)(b_rd[bj] + base + (uint32_t)((32 * H + 4 * hi) * BN * 2)));
+#pragma unroll
+    for (int bi = 0; bi < TM; ++bi) af[H][bi] = *(lds_a_ptr)(uintptr_t)(a_rd[H] + base + (uint32_t)bi * 2048u);
+  };
+  auto multiply_half = [&](auto half) __attribute__((always_inline)) {
+    constexpr int H = decltype(half)::value;
+#pragma unroll
+    for (int bi = 0; bi < TM; ++bi)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int bj = (bi & 1) ? TN - 1 - j : j;
+        const bf16x8 b = __builtin_bit_cast(bf16x8, __builtin_shufflevector(bq[H][bj][0], bq[H][bj][1], 0, 1, 2, 3, 4, 5, 6, 7));
+        acc[bi][bj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, af[H][bi], acc[bi][bj], 0, 0, 0);
+      }
+  };
+  auto interleave = [&]() __attribute__((always_inline)) {
+    constexpr int NM = TM * TN, NR = TM + 2 * TN, PER = (NR + NM - 1) / NM;
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);        // one MFMA
+      if (i * PER < NR) __builtin_amdgcn_sched_group_barrier(0x100, PER, 0);   // then the reads that go with it
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr std::integral_constant<int, 0> kLow{};
+  constexpr std::integral_constant<int, 1> kHigh{};
+
+  const int T = (K + kStageK - 1) / kStageK, full = K / kStageK;
+  constexpr int AHEAD = S::STAGES - 1;                           // stages fetched ahead of the one being multiplied
+  for_each_index([&](auto i) __attribute__((always_inline)) {
+    if (decltype(i)::value < T) load_any(decltype(i)::value, decltype(i)::value * S::STAGE_BYTES);
+  }, std::make_integer_sequence<int, AHEAD>{});
+  auto publish = [&](auto newer) __attribute__((always_inline)) {          // newer: stages issued after the one waited for
+    wait_vmcnt<decltype(newer)::value * S::LOADS>();
+    __builtin_amdgcn_sched_barrier(0);
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for_each_index([&](auto i) __attribute__((always_inline)) {    // stage 0 has landed; min(T, AHEAD) were issued
+    constexpr int NEWER = AHEAD - 1 - decltype(i)::value;
+    if (NEWER == 0 ? T == 1 : NEWER == AHEAD - 1 ? T > NEWER : T == NEWER + 1) wait_vmcnt<NEWER * S::LOADS>();
+  }, std::make_integer_sequence<int, AHEAD>{});
+  __builtin_amdgcn_sched_barrier(0);
+  block_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  read_half(kLow, 0);
+  int t = 0;
+  // whole turns of the ring: every slot is a compile-time constant
+  for (; t + S::STAGES + AHEAD <= full; t += S::STAGES)
+    for_each_index([&](auto pos) __attribute__((always_inline)) {
+      constexpr int P = decltype(pos)::value;
+      read_half(kHigh, P * S::STAGE_BYTES);
+      multiply_half(kLow);
+      interleave();
+      publish(std::integral_constant<int, AHEAD - 2>{});
+      load_full(((P + AHEAD) % S::STAGES) * S::STAGE_BYTES);
+      __builtin_amdgcn_sched_barrier(0);
+      read_half(kLow, ((P + 1) % S::STAGES) * S::STAGE_BYTES);
+      multiply_half(kHigh);
+      interleave();
+    }, std::make_integer_sequence<int, S::STAGES>{});
+  uint32_t off = 0, off_ld = AHEAD * S::STAGE_BYTES;
+  auto next_slot = [](uint32_t o) __attribute__((always_inline)) { return o == AHEAD * S::STAGE_BYTES ? 0u : o + S::STAGE_BYTES; };
+  for (; t + AHEAD < T; ++t) {
+    read_half(kHigh, off);
+    multiply_half(kLow);
+    interleave();
+    publish(std::integral_constant<int, AHEAD - 2>{});
+    load_any(t + AHEAD, off_ld);
+    __builtin_amdgcn_sched_barrier(0);
+    off = next_slot(off);
+    off_ld = next_slot(off_ld);
+    read_half(kLow, off);
+    multiply_half(kHigh);
+    interleave();
+  }
+  // the last stages: nothing left to fetch, one stage fewer in flight each time
+  for_each_index([&](auto i) __attribute__((always_inline)) {
+    constexpr int LEFT = AHEAD - 1 - decltype(i)::value;         // stages after this one
+    if (LEFT < T) {
+      read_half(kHigh, off);
+      multiply_half(kLow);
+      interleave();
+      if constexpr (LEFT > 0) {
+        publish(std::integral_constant<int, LEFT - 1>{});
+        off = next_slot(off);
+        read_half(kLow, off);
+      }
+      multiply_half(kHigh);
+      if constexpr (LEFT > 0) interleave();
+    }
+  }, std::make_integer_sequence<int, AHEAD>{});
+  store_wave_tile<TM, TN>(acc, C, M, N, m0 + wm * (TM * 16), n0 + wn * (TN * 16), lane);
+}
+
+// A tile (bm x bn, as the plan names it) is computed by sub_m * sub_n workgroups of S::BM x S::BN each.  The map
+// is that of the tiles: hardware ids are dealt round-robin to the XCDs, so the sub-tiles of the tile that
+// the map gives to hardware id v are handed to ids that are v modulo `deal` (= the XCD count, or the tile count if
+// that is smaller) and run on the XCD the map means.  Ids past the last tile and sub-tiles outside C leave at once.
+template <class S>
+__global__ __launch_bounds__(S::NT) void gemm_bf16_subtile_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
+                                                                  uint16_t* __restrict__ C, int M, int N, int K, int grid_m,
+                                                                  int grid_n, int num_xcd, int group_m, int mode, int bm, int bn,
+                                                                  int sub_m, int sub_n, int deal) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int subs = sub_m * sub_n;
+  const int i = (int)blockIdx.x / deal, x = (int)blockIdx.x - i * deal;
+  const int turn = i / subs, sub = i - turn * subs;
+  const int v = turn * deal + x;
+  if (v >= grid_m * grid_n) return;                              // uniform, like the exit below
+  int pm, pn;
+  swz_decode_tile(v, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
+  const int m0 = pm * bm + (sub % sub_m) * S::BM, n0 = pn * bn + (sub / sub_m) * S::BN;
+  if (m0 >= M || n0 >= N) return;
+  gemm_subtile<S>(A, B, C, M, N, K, m0, n0, smem);
+}
+
+}  // namespace swz

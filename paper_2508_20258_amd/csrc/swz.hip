@@ -13,6 +13,7 @@
 #include "../../include/swz.h"
 #include "aux_kernels.h"
 #include "gemm_kernel.h"
+#include "gemm_subtile_kernel.h"
 #include "mfma_peak_kernel.h"
 #include "pid_decode.h"
 #include "rowwise_kernel.h"
@@ -30,6 +31,8 @@ struct DeviceFacts {
 };
 DeviceFacts g_facts[kMaxDevices];
 std::atomic<bool> g_attr_set[kMaxDevices][4][4][2];
+constexpr int kSubShapes = 6;
+std::atomic<bool> g_sub_attr_set[kMaxDevices][kSubShapes];
 std::mutex g_mu;
 
 // SWZ_NUM_XCD in the environment (read once per process): the XCD count to assume instead of the
@@ -145,6 +148,73 @@ int launch_gemm_probe(const void* A, const void* B, void* C, int M, int N, int K
     case SWZ_MODE_XCD_GROUPM: return go(swz::gemm_bf16_probe_kernel<S, kModeXcdGroupM>);
     default: return go(swz::gemm_bf16_probe_kernel<S, kModeGroupM>);
   }
+}
+
+// The sub-tile shapes, and what a stage (64 of K) of one workgroup costs in ns on a chip whose every CU has one
+// (measured: the slope of kernel time over K).  The fixed part of a round (launch or hand-over, the first
+// operands, the stores) is about kRoundNs whatever the shape.
+using Sub32x32 = swz::SubShape<32, 32, 2, 2, 8>;
+using Sub32x64 = swz::SubShape<32, 64, 2, 2, 6>;
+using Sub64x64 = swz::SubShape<64, 64, 2, 2, 5>;
+using Sub128x64 = swz::SubShape<128, 64, 4, 2, 6>;
+using Sub64x128 = swz::SubShape<64, 128, 2, 4, 6>;
+using Sub128x128 = swz::SubShape<128, 128, 2, 4, 5>;
+struct SubCost { int bm, bn, stage_ns; };
+constexpr SubCost kSubCost[kSubShapes] = {{32, 32, 140}, {32, 64, 160}, {64, 64, 195}, {128, 64, 310}, {64, 128, 310}, {128, 128, 520}};
+constexpr int64_t kRoundNs = 2500;
+
+// Which sub-tile shape (index into kSubCost) computes this product fastest, or -1 where the plan's tile as one
+// workgroup does.  The estimate is  rounds x (kRoundNs + stages x cost), rounds = workgroups that touch C over CUs; it
+// orders the shapes as measured on 60 products with M from 1 to 2048.  One 128x128, 128x256 and 256x256 tile of
+// gemm_kernel.h costs 600, 840 and 1350 ns a stage (two 128x128 ones share a CU: 920 the pair).  Ties go to the larger
+// tile: it moves fewer bytes.  A sub-tile has to be 5 % better than the tile, the spread of the estimate near a tie.
+int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, int cus) {
+  const int64_t stages = (K + swz::kStageK - 1) / swz::kStageK;
+  auto rounds = [&](int64_t bm, int64_t bn, int64_t per_round) {
+    return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + per_round - 1) / per_round;
+  };
+  auto estimate = [&](int64_t n, int64_t ns) { return n * (kRoundNs + stages * ns); };
+  int64_t best;
+  if (r.bm == 128 && r.bn == 128) {
+    best = rounds(128, 128, cus) == 1 ? estimate(1, 600) : estimate(rounds(128, 128, 2 * cus), 920);
+  } else {
+    best = estimate(rounds(r.bm, r.bn, cus), r.bm == r.bn ? 1350 : 840);
+  }
+  best -= best / 20;
+  int choice = -1;
+  for (int s = kSubShapes - 1; s >= 0; --s) {
+    const int64_t e = estimate(rounds(kSubCost[s].bm, kSubCost[s].bn, cus), kSubCost[s].stage_ns);
+    if (e < best) {
+      best = e;
+      choice = s;
+    }
+  }
+  return choice;
+}
+
+template <class S>
+int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, const swz_params& r, int grid_m, int grid_n,
+                   int group_m, int mode, hipStream_t stream, int shape) {
+  auto kernel = swz::gemm_bf16_subtile_kernel<S>;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SWZ_ERR_HIP;
+  std::atomic<bool>& ready = g_sub_attr_set[dev][shape];
+  if (!ready.load(std::memory_order_acquire)) {       // first launch of this kernel on this device only
+    std::lock_guard<std::mutex> lock(g_mu);
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            S::LDS_BYTES) != hipSuccess)
+      return SWZ_ERR_HIP;
+    ready.store(true, std::memory_order_release);
+  }
+  // a grid of one tile row (column) has no use for sub-tiles below (right of) C
+  const int sub_m = grid_m == 1 ? (M + S::BM - 1) / S::BM : r.bm / S::BM;
+  const int sub_n = grid_n == 1 ? (N + S::BN - 1) / S::BN : r.bn / S::BN;
+  const int total = grid_m * grid_n;
+  const int deal = r.num_xcd < total ? r.num_xcd : total;
+  const int64_t blocks = ((int64_t)total + deal - 1) / deal * deal * sub_m * sub_n;
+  return launch(kernel, dim3((unsigned)blocks), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
+                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, grid_m, grid_n, r.num_xcd, group_m, mode,
+                r.bm, r.bn, sub_m, sub_n, deal);
 }
 
 int resolve_plan(int64_t M, int64_t N, int64_t K, const swz_params* p, swz_params* r, int* grid_m, int* grid_n) {
@@ -489,6 +559,24 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
   int grid_m = 0, grid_n = 0, group_m = 0;
   const int st = check_gemm(A, B, C, M, N, K, dtype, mode, params, &r, &grid_m, &grid_n, &group_m);
   if (st != SWZ_OK) return st;
+  // Only where the caller left the tile to the library: a tile that was asked for is one workgroup.  Bounds: 32-bit
+  // source offsets over 64 rows of B, and a grid well inside the 32-bit range whatever the shape.
+  const bool free_tile = params == nullptr || (params->bm == 0 && params->bn == 0);
+  if (free_tile && !r.persistent && N < ((int64_t)1 << 24) && (int64_t)grid_m * grid_n < ((int64_t)1 << 16)) {
+    DeviceFacts f;
+    const int qs = query_device(&f);
+    if (qs != SWZ_OK) return qs;
+    const int m = (int)M, n = (int)N, k = (int)K;
+    switch (choose_subtile(M, N, K, r, f.cus > 0 ? f.cus : 256)) {
+      case 0: return launch_subtile<Sub32x32>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 0);
+      case 1: return launch_subtile<Sub32x64>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 1);
+      case 2: return launch_subtile<Sub64x64>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 2);
+      case 3: return launch_subtile<Sub128x64>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 3);
+      case 4: return launch_subtile<Sub64x128>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 4);
+      case 5: return launch_subtile<Sub128x128>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 5);
+      default: break;
+    }
+  }
   if (r.bm == 128 && r.bn == 128)
     return launch_gemm<Shape128>(A, B, C, (int)M, (int)N, (int)K, grid_m, grid_n, r.num_xcd, group_m, mode, r.num_wg, stream, 0);
   if (r.bm == 128)

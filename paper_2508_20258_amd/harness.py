@@ -79,7 +79,7 @@ def kernel_hash() -> str:
     """SHA-256 of the GEMM kernel sources: recorded counters are only valid for the kernel they were taken on."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("gemm_kernel.h", "pid_decode.h"):
+    for name in ("gemm_kernel.h", "gemm_subtile_kernel.h", "pid_decode.h"):
         with open(os.path.join(HERE, "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()

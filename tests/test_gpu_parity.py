@@ -623,3 +623,35 @@ def test_mfma_peak_kernel_runs_and_checks_its_buffer(swz):
     assert swz.lib.swz_mfma_peak(out.data_ptr(), out.numel() - 1, 10, 1, None, s) == -1     # buffer too small
     assert swz.lib.swz_mfma_peak(out.data_ptr(), out.numel(), 0, 1, None, s) == -1
     assert swz.lib.swz_mfma_peak(None, out.numel(), 10, 1, None, s) == -1
+
+
+# ---------------------------------------------------------------------------- default tiles cut into sub-tiles
+
+# M, N and the sub-tile shape the library takes there on 256 compute units; edges of every shape, one row, one column block
+SUBTILE_SHAPES = [(1, 8), (33, 40), (100, 520), (512, 512),                  # 32x32
+                  (300, 1032), (129, 3000),                                  # 32x64
+                  (1000, 1000), (449, 1992),                                 # 64x64
+                  (1280, 1600), (1217, 1544),                                # 128x64 / 64x128
+                  (300, 5000), (1100, 1504),                                 # 64x128
+                  (1537, 1400), (40, 33000), (70, 66000)]                    # 128x128; grids of 128x256 and 256x256 tiles
+
+
+@pytest.mark.parametrize("M,N", SUBTILE_SHAPES)
+def test_subtiles_give_the_bits_of_whole_tiles(swz, M, N):
+    # K: less than a stage of 64, partial stages, fewer stages than any ring, whole rings of 5, 6 and 8 and the hand-overs
+    for n, K in enumerate([8, 64, 72, 200, 320, 384, 456, 512, 704, 1032, 1344]):
+        if M * N * K > 1 << 30 and n % 3:
+            continue
+        g = torch.Generator(device="cuda").manual_seed(M + K)
+        a = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+        b = torch.randn((K, N), device="cuda", generator=g).to(torch.bfloat16)
+        want = swz.gemm(a, b, mode=0, bm=256, bn=256)
+        for mode, params in [(0, {}), (2, {}), (5, dict(num_xcd=3)), (6, dict(group_m=3)), (1, dict(num_xcd=1000)), (2, dict(num_xcd=1))]:
+            c = torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+            swz.gemm(a, b, c[:M], mode=mode, **params)
+            torch.cuda.synchronize()
+            assert torch.equal(c[:M].view(torch.int16), want.view(torch.int16)), (M, N, K, mode, params)
+            assert torch.isnan(c[M]).all()
+    if M <= 512 and N <= 1000:
+        ref = gemm_ref.gemm(to_bits(a), to_bits(b))
+        assert_within_tolerance(to_bits(c[:M]), ref, f"{M}x{N}x{K}")
