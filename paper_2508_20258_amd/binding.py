@@ -266,7 +266,7 @@ def _row_args(x, out):
 
 
 def softmax(x, out=None, chunks: int = 1, mode: int = MODE_XCD, stream=None, **params):
-    """Row softmax of a bf16 matrix on the GPU through swz_softmax; `chunks` workgroups per row."""
+    """Row softmax of a bf16 matrix on the GPU through swz_softmax; `chunks`: workgroups a row may be spread over."""
     out = _row_args(x, out)
     _same_current_device(stream, x, out)
     p = _params(**params)

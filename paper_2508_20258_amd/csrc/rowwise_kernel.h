@@ -2,37 +2,58 @@
 // Results and Appendix "Case Study: Other Swizzling Pattern Examples": the swizzle found for
 // both kernels puts all column chunks of one row on one XCD).
 //
-// Decomposition (the one the paper's remap is about): a row of N elements is cut into `chunks`
-// column chunks and one workgroup produces one chunk.  A chunk needs the statistics of its whole
-// row (maximum and sum of exponentials; mean and variance), so every workgroup reads the whole
-// row and then re-reads and writes its own chunk; nothing is exchanged between workgroups.  The
-// redundant row reads are what the mapping acts on: the grid is M x chunks, hardware id w is
-// decoded exactly like a GEMM tile id (row = logical id div chunks), and under the XCD
-// renumbering the workgroups of one row run back to back on one XCD and find the row in its L2.
-// With chunks = 1 a workgroup owns a whole row and the mapping is irrelevant; that is the form
-// to use whenever M alone fills the chip.  In that form a row of up to 256*8*KEEP elements
-// (KEEP <= 16 vectors per thread) stays in registers between the two phases, so HBM is read once;
-// and rows of at most 2048 elements are handled one per wave, four rows per workgroup, with no
-// LDS and no barrier (the grid is then ceil(M/4) x 1 groups of four consecutive rows).
+// Both are bound by HBM: 4*M*N bytes, x read once and y written once, which needs the row to stay on the
+// chip between its statistics and its stores.
 //
-// All arithmetic is fp32 on values widened exactly from bf16; results are rounded once to bf16
-// (nearest even).  The statistics are computed over the same thread partition of the row in
-// every workgroup of a launch, so the output bits never depend on the mode, and with 256 threads
-// per row (N > 2048, or chunks > 1) not on `chunks` either.
+//   Rows of up to 98304 elements.  TPR threads hold a row in KEEP 16-byte vectors each, in registers: 16 to 64 lanes of a
+//   wave for short rows (up to 16 rows per 256-thread workgroup, no LDS, no barrier), a workgroup of 256, 512 or 1024
+//   threads for longer ones.  The grid is one-dimensional over groups of consecutive rows.
+//   Longer rows.  A row is cut into segments of 32768 elements; row_stats_kernel computes the statistics of one segment
+//   per workgroup, row_emit_kernel merges them and produces one column chunk per workgroup, reading x a second
+//   time.  Between the launches a segment's statistics (8 bytes) wait in `out` itself: every chunk gets its own copy of all of
+//   them at its start, so that a workgroup reads only what it overwrites, after its own barrier.  No scratch memory, nothing
+//   exchanged inside a launch.  Grids rows x segments and rows x chunks, both decoded by swz_decode_tile: under the
+//   XCD renumbering a row's workgroups run back to back on one XCD.
+//
+// The decomposition of the paper, in which the workgroup of every column chunk reads the whole row for its statistics, is bound
+// by those reads and the arithmetic on them even where the remap has the L2 serve 82 % of them: 8 chunks of
+// 1024 x 65536 took 125 us (softmax) and 118 us (layer normalisation), the row in the registers of one workgroup takes 55 and 57.
+//
+// At 6 TB/s a CU has about 11 vector instructions per element, and a row's latencies stand in series: load, maximum or mean, sum, store.
+// So the maximum is taken first, on the raw values, and each exponential computed once and kept (an online maximum costs a
+// second one and a rescale); mean and deviations are two passes over registers (a merge of (count, mean, M2) per vector costs a
+// division); lanes are reduced with DPP and permlane exchanges (a shuffle through LDS takes about 60 ns a step); gamma and
+// beta are requested ahead of the statistics where there are registers for them.  Measured, operands not in cache, online and merging
+// kernels with late gamma and beta -> these (us; copy16_kernel on 128 MiB in and out: 43):
+//     layernorm 8192 x 8192    66 -> 55      softmax 8192 x 8192    55 -> 49      layernorm 32768 x 16384  388 -> 366
+//     softmax 32768 x 16384   382 -> 354     softmax 131072 x 128   49 -> 13      layernorm 300 x 2048     4.9 -> 3.5
+//     softmax 64 x 1048576    300 -> 70      softmax 1 x 1048576   220 -> 9       softmax 16 x 131072       29 -> 9
+//
+// All arithmetic is fp32 on values widened exactly from bf16; results are rounded once to bf16 (nearest even).  How a row is
+// accumulated follows from N alone: the bits depend neither on the mode nor on `chunks` nor on M.
 #pragma once
 
 #include <float.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "pid_decode.h"
 
 namespace swz {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t rw_u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t rw_u32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 rw_bf16x2;
 
-constexpr int kRowThreads = 256;
+constexpr int kSegThreads = 512;               // threads that share a segment of a row of more than 32768 elements
+constexpr int kSegKeep = 8;                    // 16-byte vectors each of them takes, at most
+constexpr int kSegVecs = kSegThreads * kSegKeep;
+constexpr int kMaxSegs = (1 << 24) / (kSegVecs * 8);
+constexpr int kEmitThreads = 256;              // a column chunk of a longer row: at most 8 vectors a thread, at least half
+constexpr int kEmitKeep = 8;                   // of that, so its first 4096 bytes can hold the statistics of all 512 segments
+constexpr int kMaxWaves = 16;
 constexpr float kLog2e = 1.4426950408889634f;
 
 __device__ __forceinline__ void rw_unpack(const rw_u32x4& v, float (&x)[8]) {
@@ -55,203 +76,335 @@ __device__ __forceinline__ rw_u32x4 rw_pack(const float (&y)[8]) {
   return v;
 }
 
+__device__ __forceinline__ float rw_sum8(const float (&x)[8]) {
+  return ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+}
+
 __device__ __forceinline__ float rw_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// (m, s): running maximum (in the log2 domain) and sum of 2^(t - m).  Identity: (-FLT_MAX, 0).
-__device__ __forceinline__ void soft_merge(float& m, float& s, float m2, float s2) {
-  const float mn = fmaxf(m, m2);
-  s = s * rw_exp2(m - mn) + s2 * rw_exp2(m2 - mn);
-  m = mn;
-}
+struct RwMax { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+struct RwSum { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
 
-__device__ __forceinline__ void soft_update(float& m, float& s, const rw_u32x4& v) {
-  float t[8];
-  rw_unpack(v, t);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) t[e] *= kLog2e;
-  const float vmax = fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])), fmaxf(fmaxf(t[4], t[5]), fmaxf(t[6], t[7])));
-  if (vmax > m) {                                          // rare once the running maximum has settled
-    s *= rw_exp2(m - vmax);
-    m = vmax;
+// op over groups of LANES (16, 32 or 64) lanes; every lane gets the result.  After the two quad steps the
+// lanes of a quad agree, so mirroring 8 (then 16) lanes pairs every quad (every 8) with the other one.
+template <int LANES, class Op>
+__device__ __forceinline__ float rw_reduce_lanes(float x, Op op) {
+  auto dpp = [](float v, auto ctrl) __attribute__((always_inline)) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  x = op(x, dpp(x, std::integral_constant<int, 0xB1>{}));        // quad_perm [1,0,3,2]
+  x = op(x, dpp(x, std::integral_constant<int, 0x4E>{}));        // quad_perm [2,3,0,1]
+  x = op(x, dpp(x, std::integral_constant<int, 0x141>{}));       // row_half_mirror
+  x = op(x, dpp(x, std::integral_constant<int, 0x140>{}));       // row_mirror
+  if constexpr (LANES >= 32) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = op(__uint_as_float(s[0]), __uint_as_float(s[1]));
   }
-  float add = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) add += rw_exp2(t[e] - m);
-  s += add;
-}
-
-// (n, mean, m2): count, mean and sum of squared deviations; merged with the pairwise update of
-// Chan, Golub and LeVeque, which is stable whatever the mean.  Identity: (0, 0, 0).
-__device__ __forceinline__ void moments_merge(float& n, float& mean, float& m2, float n2, float mean2, float m22) {
-  const float nn = n + n2;
-  const float inv = nn > 0.f ? 1.0f / nn : 0.f;
-  const float d = mean2 - mean;
-  mean += d * (n2 * inv);
-  m2 += m22 + d * d * (n * n2 * inv);
-  n = nn;
-}
-
-__device__ __forceinline__ void moments_update(float& n, float& mean, float& m2, const rw_u32x4& v) {
-  float x[8];
-  rw_unpack(v, x);
-  const float vmean = (((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]))) * 0.125f;
-  float vm2 = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) vm2 += (x[e] - vmean) * (x[e] - vmean);
-  moments_merge(n, mean, m2, 8.f, vmean, vm2);
-}
-
-// Applies `update` to every 16-byte vector of the row, vectors dealt to threads round-robin,
-// four loads in flight per thread.
-template <typename F>
-__device__ __forceinline__ void for_each_row_vector(const rw_u32x4* __restrict__ rowp, int nv, int tid, F update) {
-  int v = tid;
-  for (; v + 3 * kRowThreads < nv; v += 4 * kRowThreads) {
-    const rw_u32x4 a = rowp[v], b = rowp[v + kRowThreads], c = rowp[v + 2 * kRowThreads], d = rowp[v + 3 * kRowThreads];
-    update(a);
-    update(b);
-    update(c);
-    update(d);
+  if constexpr (LANES >= 64) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = op(__uint_as_float(s[0]), __uint_as_float(s[1]));
   }
-  for (; v < nv; v += kRowThreads) update(rowp[v]);
+  return x;
 }
 
-// Where a workgroup finds its work.  TPR = threads per row: 256 (one row or row chunk per
-// workgroup) or 64 (one row per wave, chunks == 1).  KEEP > 0 (chunks == 1 only): the row is held
-// in KEEP vector registers per thread, N <= TPR*8*KEEP.
-template <int MODE, int TPR>
+// op over the threads that share a row or segment: LANES <= 64 lanes of a wave, or this thread's group of LANES / 64
+// waves; `slots` is LDS for one float per wave of the workgroup, not written again before the next barrier.
+template <int LANES, class Op>
+__device__ __forceinline__ float rw_reduce_group(float x, Op op, float* slots) {
+  if constexpr (LANES <= 64) {
+    return rw_reduce_lanes<LANES>(x, op);
+  } else {
+    constexpr int W = LANES / 64;
+    x = rw_reduce_lanes<64>(x, op);
+    const int wave = (int)threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) slots[wave] = x;
+    __syncthreads();
+    float g[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) g[w] = slots[(wave & ~(W - 1)) + w];
+#pragma unroll
+    for (int n = W; n > 1; n /= 2)
+#pragma unroll
+      for (int w = 0; w < n / 2; ++w) g[w] = op(g[2 * w], g[2 * w + 1]);
+    return g[0];
+  }
+}
+
+// exp(x - m) is computed as exp2(x * log2(e) - m'), m' = m * log2(e), kept finite for a row or segment of -inf only
+// (all its exponentials are then 0).
+__device__ __forceinline__ float soft_scaled_max(float m) { return fmaxf(m * kLog2e, -FLT_MAX); }
+
+// Of KEEP vectors a thread holds: maximum, sum of exponentials, sum, sum of squared deviations.
+template <int KEEP>
+__device__ __forceinline__ float held_max(const rw_u32x4* held) {
+  float m = -FLT_MAX;
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    float x[8];
+    rw_unpack(held[i], x);                                       // vectors past the row's end hold -inf
+    m = fmaxf(m, fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7]))));
+  }
+  return m;
+}
+
+__device__ __forceinline__ void soft_exps(const rw_u32x4& v, float scaled_max, float (&p)[8]) {
+  rw_unpack(v, p);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) p[e] = rw_exp2(__builtin_fmaf(p[e], kLog2e, -scaled_max));
+}
+
+template <int KEEP>
+__device__ __forceinline__ float held_exp_sum(const rw_u32x4* held, float scaled_max) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    float p[8];
+    soft_exps(held[i], scaled_max, p);
+    s += rw_sum8(p);
+  }
+  return s;
+}
+
+// vectors first, first + stride, ... below nv are real, the others hold -inf
+template <int KEEP>
+__device__ __forceinline__ float held_sum(const rw_u32x4* held, int first, int stride, int nv) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i)
+    if (first + i * stride < nv) {
+      float x[8];
+      rw_unpack(held[i], x);
+      s += rw_sum8(x);
+    }
+  return s;
+}
+
+template <int KEEP>
+__device__ __forceinline__ float held_dev(const rw_u32x4* held, int first, int stride, int nv, float mean) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i)
+    if (first + i * stride < nv) {
+      float x[8];
+      rw_unpack(held[i], x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = (x[e] - mean) * (x[e] - mean);
+      s += rw_sum8(x);
+    }
+  return s;
+}
+
+constexpr uint32_t kNegInfPair = 0xFF80FF80u;  // two bfloat16 -inf
+
+template <int KEEP, bool STREAM = true>
+__device__ __forceinline__ void load_vectors(const rw_u32x4* __restrict__ p, int first, int stride, int nv, rw_u32x4* held) {
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    held[i] = rw_u32x4{kNegInfPair, kNegInfPair, kNegInfPair, kNegInfPair};
+    if (first + i * stride < nv) {
+      if constexpr (STREAM) held[i] = __builtin_nontemporal_load(p + first + i * stride);
+      else held[i] = p[first + i * stride];
+    }
+  }
+}
+
+// Elements of segment s of a row of N.
+__device__ __forceinline__ int seg_elems(int s, int N) {
+  const int left = N - s * (kSegVecs * 8);
+  return left < 0 ? 0 : left < kSegVecs * 8 ? left : kSegVecs * 8;
+}
+
+// Which row a workgroup of TPR-thread groups works on: TPR <= 64, groups of lanes; above, the whole workgroup.
+template <int TPR>
 struct RowJob {
-  int row, nv, v0, v1, tid;
-  bool live;
-  __device__ __forceinline__ RowJob(int M, int N, int chunks, int chunk_vecs, int num_xcd, int group_m) {
-    constexpr int ROWS = kRowThreads / TPR;
+  static constexpr int THREADS = TPR < 256 ? 256 : TPR;
+  int row, tid;
+  bool live;                                   // uniform per group of TPR threads; TPR >= 256: per workgroup
+  __device__ __forceinline__ RowJob(int M, int num_xcd, int group_m, int mode) {
+    constexpr int ROWS = THREADS / TPR;
     int group, chunk;
-    swz_decode_tile((int)blockIdx.x, (M + ROWS - 1) / ROWS, chunks, num_xcd, group_m, MODE, &group, &chunk);
+    swz_decode_tile((int)blockIdx.x, (M + ROWS - 1) / ROWS, 1, num_xcd, group_m, mode, &group, &chunk);
     row = group * ROWS + (int)threadIdx.x / TPR;
     tid = (int)threadIdx.x % TPR;
-    nv = N >> 3;
-    v0 = chunk * chunk_vecs;
-    v1 = v0 + chunk_vecs < nv ? v0 + chunk_vecs : nv;
-    live = row < M && v0 < nv;                             // uniform per workgroup when TPR == 256, per wave when TPR == 64
+    live = row < M;
   }
 };
 
-template <int MODE, int KEEP, int TPR>
-__global__ __launch_bounds__(kRowThreads) void softmax_rows_kernel(const uint16_t* __restrict__ in,
-                                                                   uint16_t* __restrict__ out, int M, int N, int chunks,
-                                                                   int chunk_vecs, int num_xcd, int group_m) {
-  static_assert(TPR == kRowThreads || (TPR == 64 && KEEP > 0), "a wave-sized row group keeps its row in registers");
-  const RowJob<MODE, TPR> job(M, N, chunks, chunk_vecs, num_xcd, group_m);
-  if (!job.live) return;                                   // an empty trailing chunk or row: nothing to produce
-  const int nv = job.nv, tid = job.tid;
-  const rw_u32x4* rowp = reinterpret_cast<const rw_u32x4*>(in + (size_t)job.row * N);
-
-  float m = -FLT_MAX, s = 0.f;
-  rw_u32x4 held[KEEP > 0 ? KEEP : 1];
-  if constexpr (KEEP > 0) {
+template <int KEEP, int TPR>
+__global__ __launch_bounds__(RowJob<TPR>::THREADS) void softmax_rows_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
+                                                                           int M, int N, int num_xcd, int group_m, int mode) {
+  __shared__ float slots[2][kMaxWaves];
+  const RowJob<TPR> job(M, num_xcd, group_m, mode);
+  if (!job.live) return;
+  const int nv = N >> 3, tid = job.tid;
+  rw_u32x4 held[KEEP];
+  load_vectors<KEEP>(reinterpret_cast<const rw_u32x4*>(in + (size_t)job.row * N), tid, TPR, nv, held);
+  const float ms = soft_scaled_max(rw_reduce_group<TPR>(held_max<KEEP>(held), RwMax{}, slots[0]));
+  constexpr bool KEEP_EXPS = KEEP <= 8;                          // the exponentials stay in registers where there is room
+  float p[KEEP_EXPS ? KEEP : 1][8], s = 0.f;
 #pragma unroll
-    for (int i = 0; i < KEEP; ++i)
-      if (tid + i * TPR < nv) held[i] = rowp[tid + i * TPR];
-#pragma unroll
-    for (int i = 0; i < KEEP; ++i)                          // same vectors, same order as the streaming form
-      if (tid + i * TPR < nv) soft_update(m, s, held[i]);
-  } else {
-    for_each_row_vector(rowp, nv, tid, [&](const rw_u32x4& v) __attribute__((always_inline)) { soft_update(m, s, v); });
+  for (int i = 0; i < KEEP; ++i) {
+    float(&q)[8] = p[KEEP_EXPS ? i : 0];
+    soft_exps(held[i], ms, q);
+    s += rw_sum8(q);
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) soft_merge(m, s, __shfl_xor(m, off, 64), __shfl_xor(s, off, 64));
-  if constexpr (TPR == kRowThreads) {
-    __shared__ float red[2 * (kRowThreads / 64)];
-    if ((tid & 63) == 0) {
-      red[2 * (tid >> 6)] = m;
-      red[2 * (tid >> 6) + 1] = s;
-    }
-    __syncthreads();
-    m = red[0];
-    s = red[1];
-#pragma unroll
-    for (int w = 1; w < kRowThreads / 64; ++w) soft_merge(m, s, red[2 * w], red[2 * w + 1]);
-  }
-  const float inv = 1.0f / s;
-
+  const float inv = 1.0f / rw_reduce_group<TPR>(s, RwSum{}, slots[1]);
   rw_u32x4* outp = reinterpret_cast<rw_u32x4*>(out + (size_t)job.row * N);
-  auto emit = [&](const rw_u32x4& xv, int v) __attribute__((always_inline)) {
-    float t[8], y[8];
-    rw_unpack(xv, t);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = rw_exp2(t[e] * kLog2e - m) * inv;
-    __builtin_nontemporal_store(rw_pack(y), outp + v);
-  };
-  if constexpr (KEEP > 0) {
+  for (int i = 0; i < KEEP; ++i)
+    if (tid + i * TPR < nv) {
+      float(&q)[8] = p[KEEP_EXPS ? i : 0];
+      if constexpr (!KEEP_EXPS) soft_exps(held[i], ms, q);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) q[e] *= inv;
+      __builtin_nontemporal_store(rw_pack(q), outp + tid + i * TPR);
+    }
+}
+
+__device__ __forceinline__ rw_u32x4 ln_vector(const rw_u32x4& xv, const rw_u32x4& gv, const rw_u32x4& bv, float mean, float rstd) {
+  float x[8], g[8], b[8];
+  rw_unpack(xv, x);
+  rw_unpack(gv, g);
+  rw_unpack(bv, b);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = (x[e] - mean) * rstd * g[e] + b[e];
+  return rw_pack(x);
+}
+
+template <int KEEP, int TPR>
+__global__ __launch_bounds__(RowJob<TPR>::THREADS) void layernorm_rows_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma,
+                                                                             const uint16_t* __restrict__ beta, uint16_t* __restrict__ out,
+                                                                             int M, int N, float eps, int num_xcd, int group_m, int mode) {
+  __shared__ float slots[2][kMaxWaves];
+  const RowJob<TPR> job(M, num_xcd, group_m, mode);
+  if (!job.live) return;
+  const int nv = N >> 3, tid = job.tid;
+  const rw_u32x4 *gp = reinterpret_cast<const rw_u32x4*>(gamma), *bp = reinterpret_cast<const rw_u32x4*>(beta);
+  constexpr bool EARLY = KEEP <= 8 && TPR <= 256;               // 4000 x 30000 with 512 threads: early 116 us, late 93
+  rw_u32x4 held[KEEP], gv[EARLY ? KEEP : 1], bv[EARLY ? KEEP : 1];
+  load_vectors<KEEP>(reinterpret_cast<const rw_u32x4*>(in + (size_t)job.row * N), tid, TPR, nv, held);
+  if constexpr (EARLY) {                                         // behind the row, ahead of its statistics
 #pragma unroll
     for (int i = 0; i < KEEP; ++i)
-      if (tid + i * TPR < nv) emit(held[i], tid + i * TPR);
+      if (tid + i * TPR < nv) {
+        gv[i] = gp[tid + i * TPR];
+        bv[i] = bp[tid + i * TPR];
+      }
+  }
+  const float mean = rw_reduce_group<TPR>(held_sum<KEEP>(held, tid, TPR, nv), RwSum{}, slots[0]) / (float)N;
+  const float dev = rw_reduce_group<TPR>(held_dev<KEEP>(held, tid, TPR, nv, mean), RwSum{}, slots[1]);
+  const float rstd = 1.0f / sqrtf(dev / (float)N + eps);
+  rw_u32x4* outp = reinterpret_cast<rw_u32x4*>(out + (size_t)job.row * N);
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i)
+    if (tid + i * TPR < nv) {
+      const int v = tid + i * TPR;
+      if constexpr (EARLY) __builtin_nontemporal_store(ln_vector(held[i], gv[i], bv[i], mean, rstd), outp + v);
+      else __builtin_nontemporal_store(ln_vector(held[i], gp[v], bp[v], mean, rstd), outp + v);
+    }
+}
+
+// ---- rows longer than a workgroup holds: two launches ----
+
+// First vector of chunk c of a row of nv vectors cut into `chunks` chunks (chunk c ends where c + 1 begins).
+__host__ __device__ __forceinline__ int chunk_first(int c, int chunks, int nv) { return (int)((int64_t)c * nv / chunks); }
+
+// Statistics of segment `seg` of row `row`, written into slot seg of every chunk of that row of `out`.
+template <bool SOFTMAX>
+__global__ __launch_bounds__(kSegThreads) void row_stats_kernel(const uint16_t* __restrict__ in, uint16_t* out, int M, int N, int segs,
+                                                                int chunks, int num_xcd, int group_m, int mode) {
+  __shared__ float slots[2][kMaxWaves];
+  int row, seg;
+  swz_decode_tile((int)blockIdx.x, M, segs, num_xcd, group_m, mode, &row, &seg);
+  const int nv = N >> 3, first = seg * kSegVecs + (int)threadIdx.x;
+  rw_u32x4 held[kSegKeep];
+  load_vectors<kSegKeep, false>(reinterpret_cast<const rw_u32x4*>(in + (size_t)row * N), first, kSegThreads, nv, held);
+  float a, b;
+  if constexpr (SOFTMAX) {
+    a = rw_reduce_group<kSegThreads>(held_max<kSegKeep>(held), RwMax{}, slots[0]);
+    b = rw_reduce_group<kSegThreads>(held_exp_sum<kSegKeep>(held, soft_scaled_max(a)), RwSum{}, slots[1]);
   } else {
-    for (int v = job.v0 + tid; v < job.v1; v += kRowThreads) emit(rowp[v], v);
+    a = rw_reduce_group<kSegThreads>(held_sum<kSegKeep>(held, first, kSegThreads, nv), RwSum{}, slots[0]) / (float)seg_elems(seg, N);
+    b = rw_reduce_group<kSegThreads>(held_dev<kSegKeep>(held, first, kSegThreads, nv, a), RwSum{}, slots[1]);
+  }
+  for (int c = (int)threadIdx.x; c < chunks; c += kSegThreads) {
+    rw_u32x4* chunk = reinterpret_cast<rw_u32x4*>(out + (size_t)row * N) + chunk_first(c, chunks, nv);
+    reinterpret_cast<rw_u32x2*>(chunk)[seg] = rw_u32x2{__float_as_uint(a), __float_as_uint(b)};
   }
 }
 
-template <int MODE, int KEEP, int TPR>
-__global__ __launch_bounds__(kRowThreads) void layernorm_rows_kernel(const uint16_t* __restrict__ in,
-                                                                     const uint16_t* __restrict__ gamma,
-                                                                     const uint16_t* __restrict__ beta,
-                                                                     uint16_t* __restrict__ out, int M, int N, float eps,
-                                                                     int chunks, int chunk_vecs, int num_xcd, int group_m) {
-  static_assert(TPR == kRowThreads || (TPR == 64 && KEEP > 0), "a wave-sized row group keeps its row in registers");
-  const RowJob<MODE, TPR> job(M, N, chunks, chunk_vecs, num_xcd, group_m);
-  if (!job.live) return;
-  const int nv = job.nv, tid = job.tid;
-  const rw_u32x4* rowp = reinterpret_cast<const rw_u32x4*>(in + (size_t)job.row * N);
-
-  float n = 0.f, mean = 0.f, m2 = 0.f;
-  rw_u32x4 held[KEEP > 0 ? KEEP : 1];
-  if constexpr (KEEP > 0) {
+template <bool SOFTMAX>
+__global__ __launch_bounds__(kEmitThreads) void row_emit_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma,
+                                                                const uint16_t* __restrict__ beta, uint16_t* out, int M, int N, float eps,
+                                                                int segs, int chunks, int num_xcd, int group_m, int mode) {
+  __shared__ float slots[2][kMaxWaves];
+  int row, chunk;
+  // from the last row backwards: what the other kernel read last is the likeliest to be in a cache still
+  swz_decode_tile((int)(gridDim.x - 1 - blockIdx.x), M, chunks, num_xcd, group_m, mode, &row, &chunk);
+  const int nv = N >> 3, v0 = chunk_first(chunk, chunks, nv), v1 = chunk_first(chunk + 1, chunks, nv);
+  const int first = v0 + (int)threadIdx.x;
+  rw_u32x4* outp = reinterpret_cast<rw_u32x4*>(out + (size_t)row * N);
+  rw_u32x4 held[kEmitKeep];
+  load_vectors<kEmitKeep>(reinterpret_cast<const rw_u32x4*>(in + (size_t)row * N), first, kEmitThreads, v1, held);
+  const rw_u32x4 *gp = reinterpret_cast<const rw_u32x4*>(gamma), *bp = reinterpret_cast<const rw_u32x4*>(beta);
+  rw_u32x4 gv[SOFTMAX ? 1 : kEmitKeep], bv[SOFTMAX ? 1 : kEmitKeep];
+  const rw_u32x2* stats = reinterpret_cast<const rw_u32x2*>(outp + v0);
+  constexpr int PER = kMaxSegs / kEmitThreads;
+  float sa[PER], sb[PER], a, b = 0.f;
 #pragma unroll
-    for (int i = 0; i < KEEP; ++i)
-      if (tid + i * TPR < nv) held[i] = rowp[tid + i * TPR];
-#pragma unroll
-    for (int i = 0; i < KEEP; ++i)
-      if (tid + i * TPR < nv) moments_update(n, mean, m2, held[i]);
-  } else {
-    for_each_row_vector(rowp, nv, tid, [&](const rw_u32x4& v) __attribute__((always_inline)) { moments_update(n, mean, m2, v); });
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1)
-    moments_merge(n, mean, m2, __shfl_xor(n, off, 64), __shfl_xor(mean, off, 64), __shfl_xor(m2, off, 64));
-  if constexpr (TPR == kRowThreads) {
-    __shared__ float red[3 * (kRowThreads / 64)];
-    if ((tid & 63) == 0) {
-      red[3 * (tid >> 6)] = n;
-      red[3 * (tid >> 6) + 1] = mean;
-      red[3 * (tid >> 6) + 2] = m2;
+  for (int i = 0; i < PER; ++i) {
+    const int s = (int)threadIdx.x + i * kEmitThreads;
+    sa[i] = SOFTMAX ? -FLT_MAX : 0.f;
+    sb[i] = 0.f;
+    if (s < segs) {
+      const rw_u32x2 w = stats[s];
+      sa[i] = __uint_as_float(w[0]);
+      sb[i] = __uint_as_float(w[1]);
     }
-    __syncthreads();
-    n = red[0];
-    mean = red[1];
-    m2 = red[2];
-#pragma unroll
-    for (int w = 1; w < kRowThreads / 64; ++w) moments_merge(n, mean, m2, red[3 * w], red[3 * w + 1], red[3 * w + 2]);
   }
-  const float rstd = 1.0f / sqrtf(m2 / n + eps);
-
-  const rw_u32x4* gp = reinterpret_cast<const rw_u32x4*>(gamma);
-  const rw_u32x4* bp = reinterpret_cast<const rw_u32x4*>(beta);
-  rw_u32x4* outp = reinterpret_cast<rw_u32x4*>(out + (size_t)job.row * N);
-  auto emit = [&](const rw_u32x4& xv, int v) __attribute__((always_inline)) {
-    float x[8], g[8], b[8], y[8];
-    rw_unpack(xv, x);
-    rw_unpack(gp[v], g);
-    rw_unpack(bp[v], b);
+  if constexpr (!SOFTMAX) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = (x[e] - mean) * rstd * g[e] + b[e];
-    __builtin_nontemporal_store(rw_pack(y), outp + v);
-  };
-  if constexpr (KEEP > 0) {
+    for (int i = 0; i < kEmitKeep; ++i)
+      if (first + i * kEmitThreads < v1) {
+        gv[i] = gp[first + i * kEmitThreads];
+        bv[i] = bp[first + i * kEmitThreads];
+      }
+  }
+  // The barriers inside the reductions separate these reads from the stores below: every thread has read the
+  // statistics before any of the chunk is overwritten.
+  if constexpr (SOFTMAX) {
+    a = -FLT_MAX;
 #pragma unroll
-    for (int i = 0; i < KEEP; ++i)
-      if (tid + i * TPR < nv) emit(held[i], tid + i * TPR);
+    for (int i = 0; i < PER; ++i) a = fmaxf(a, sa[i]);
+    a = rw_reduce_group<kEmitThreads>(a, RwMax{}, slots[0]);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) b += sb[i] * rw_exp2(soft_scaled_max(sa[i]) - soft_scaled_max(a));
   } else {
-    for (int v = job.v0 + tid; v < job.v1; v += kRowThreads) emit(rowp[v], v);
+    auto count = [&](int i) __attribute__((always_inline)) { return seg_elems((int)threadIdx.x + i * kEmitThreads, N); };
+    a = 0.f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) a += sa[i] * ((float)count(i) / (float)N);
+    a = rw_reduce_group<kEmitThreads>(a, RwSum{}, slots[0]);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) b += sb[i] + (sa[i] - a) * (sa[i] - a) * (float)count(i);
+  }
+  b = rw_reduce_group<kEmitThreads>(b, RwSum{}, slots[1]);
+  const float scale = SOFTMAX ? 1.0f / b : 1.0f / sqrtf(b / (float)N + eps);
+  const float scaled_max = soft_scaled_max(a);
+#pragma unroll
+  for (int i = 0; i < kEmitKeep; ++i) {
+    const int v = first + i * kEmitThreads;
+    if (v < v1) {
+      if constexpr (SOFTMAX) {
+        float y[8];
+        soft_exps(held[i], scaled_max, y);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] *= scale;
+        __builtin_nontemporal_store(rw_pack(y), outp + v);
+      } else {
+        __builtin_nontemporal_store(ln_vector(held[i], gv[i], bv[i], a, scale), outp + v);
+      }
+    }
   }
 }
 

@@ -304,14 +304,27 @@ int launch_transpose(const void* in, void* out, int M, int N, int gm, int gn, in
     return launch_transpose_s<TILE, true>(in, out, M, N, gm, gn, num_xcd, group_m, mode, stream);
   return launch_transpose_s<TILE, false>(in, out, M, N, gm, gn, num_xcd, group_m, mode, stream);
 }
-// How the two row-wise entry points launch: threads per row (256, or 64 = one row per wave when a
-// single workgroup per row is asked for and the row has at most 2048 elements), 16-byte vectors a
-// thread keeps in registers (0 = the row is streamed twice), the grid and the mapping parameters.
+// Threads per row and 16-byte vectors each of them holds, for rows of up to max_vecs vectors: the fastest of the pairs
+// measured (16 to 1024 threads x 1 to 16 vectors, M from 1 to 131072).  Few lanes for short rows (131072 x 128: 14 us with 16
+// lanes, 35 with 64), enough threads to leave each one 2 to 8 vectors for longer ones.  The two kernels part between 4096 and 16384
+// elements: softmax is faster with more threads (8192 x 8192: 50 us with 512, 52 with 256; 32768 x 16384: 356 us with 1024, 377
+// with 256), layer normalisation, which also holds gamma and beta, with fewer (32768 x 16384: 370 us with 256, 394 with 512).
+struct RowShape { int max_vecs, keep, tpr; };
+constexpr int kRowShapes = 16;
+constexpr RowShape kSoftmaxShapes[kRowShapes] = {
+    {16, 1, 16},    {32, 1, 32},    {64, 1, 64},    {128, 2, 64},   {224, 4, 64},   {256, 1, 256},  {512, 2, 256},   {1024, 2, 512},
+    {1536, 4, 512}, {2048, 2, 1024}, {4096, 8, 512}, {5120, 5, 1024}, {6144, 6, 1024}, {8192, 8, 1024}, {10240, 10, 1024}, {12288, 12, 1024}};
+constexpr RowShape kLayernormShapes[kRowShapes] = {
+    {16, 1, 16},    {32, 1, 32},    {64, 1, 64},    {128, 2, 64},   {224, 4, 64},   {256, 1, 256},  {512, 2, 256},   {1024, 4, 256},
+    {1536, 8, 256}, {2048, 8, 256}, {4096, 8, 512}, {5120, 5, 1024}, {6144, 6, 1024}, {8192, 8, 1024}, {10240, 10, 1024}, {12288, 12, 1024}};
+
+// How the two row-wise entry points launch: index into the kernel's table of shapes (-1: longer than a
+// workgroup holds, two launches, segs x chunks per row), mapping parameters.
 struct RowPlan {
-  int tpr, keep, grid_m, chunk_vecs, num_xcd, group_m;
+  int shape, grid_m, num_xcd, group_m, segs, chunks;
 };
 
-int resolve_rows(int64_t M, int64_t N, int chunks, int mode, const swz_params* params, RowPlan* plan) {
+int resolve_rows(int64_t M, int64_t N, int chunks, int mode, const swz_params* params, const RowShape* shapes, RowPlan* plan) {
   if (M < 1 || N < 1 || chunks < 1 || !valid_mode(mode)) return SWZ_ERR_INVALID_ARG;
   if (swz_mode_skewed(mode)) return SWZ_ERR_UNSUPPORTED;   // a skew would pull the chunks of a row apart again
   const int64_t lim = (int64_t)1 << 31;
@@ -333,33 +346,45 @@ int resolve_rows(int64_t M, int64_t N, int chunks, int mode, const swz_params* p
     plan->num_xcd = f.num_xcd;
     if (plan->num_xcd == 0) return SWZ_ERR_UNSUPPORTED;
   }
-  plan->chunk_vecs = (int)((nv + chunks - 1) / chunks);
-  plan->tpr = (chunks == 1 && nv <= 4 * 64) ? 64 : swz::kRowThreads;
-  const int64_t per_thread = (nv + plan->tpr - 1) / plan->tpr;
-  plan->keep = chunks != 1 ? 0 : per_thread <= 4 ? 4 : per_thread <= 16 ? 16 : 0;
-  const int rows_per_wg = swz::kRowThreads / plan->tpr;
-  plan->grid_m = (int)((M + rows_per_wg - 1) / rows_per_wg);
-  return check_map_args(plan->grid_m, chunks, plan->num_xcd, &plan->group_m, mode);
+  plan->segs = plan->chunks = 1;
+  plan->grid_m = (int)M;
+  plan->shape = 0;
+  while (plan->shape < kRowShapes && nv > shapes[plan->shape].max_vecs) ++plan->shape;
+  if (plan->shape == kRowShapes) {
+    plan->shape = -1;
+    plan->segs = (int)((nv + swz::kSegVecs - 1) / swz::kSegVecs);
+    plan->chunks = (int)((nv + swz::kEmitThreads * swz::kEmitKeep - 1) / (swz::kEmitThreads * swz::kEmitKeep));
+  } else if (shapes[plan->shape].tpr < 256) {
+    const int rows_per_wg = 256 / shapes[plan->shape].tpr;
+    plan->grid_m = (int)((M + rows_per_wg - 1) / rows_per_wg);
+  }
+  return check_map_args(plan->grid_m, plan->chunks, plan->num_xcd, &plan->group_m, mode);
 }
 
-#define SWZ_LAUNCH_BY_MODE(KERNEL, KEEP, TPR, ...)                                                                \
-  switch (mode) {                                                                                                 \
-    case SWZ_MODE_RR: return launch(KERNEL<kModeRR, KEEP, TPR>, grid, block, 0, stream, __VA_ARGS__);             \
-    case SWZ_MODE_XCD: return launch(KERNEL<kModeXcd, KEEP, TPR>, grid, block, 0, stream, __VA_ARGS__);           \
-    case SWZ_MODE_XCD_GROUPM: return launch(KERNEL<kModeXcdGroupM, KEEP, TPR>, grid, block, 0, stream, __VA_ARGS__); \
-    case SWZ_MODE_GROUPM: return launch(KERNEL<kModeGroupM, KEEP, TPR>, grid, block, 0, stream, __VA_ARGS__);     \
-    default: return SWZ_ERR_INVALID_ARG;                                                                          \
+// KERNEL<KEEP, TPR> of the chosen shape.
+#define SWZ_ROWS_CASE(S, KERNEL, SHAPES, ...)                                                                        \
+  case S:                                                                                                            \
+    return launch(KERNEL<SHAPES[S].keep, SHAPES[S].tpr>, dim3((unsigned)plan.grid_m),                                \
+                  dim3((unsigned)(SHAPES[S].tpr < 256 ? 256 : SHAPES[S].tpr)), 0, stream, __VA_ARGS__);
+#define SWZ_ROWS_CASES(A, B, C, D, ...) \
+  SWZ_ROWS_CASE(A, __VA_ARGS__) SWZ_ROWS_CASE(B, __VA_ARGS__) SWZ_ROWS_CASE(C, __VA_ARGS__) SWZ_ROWS_CASE(D, __VA_ARGS__)
+#define SWZ_LAUNCH_ROWS(...)                                                                                                 \
+  switch (plan.shape) {                                                                                                      \
+    SWZ_ROWS_CASES(0, 1, 2, 3, __VA_ARGS__) SWZ_ROWS_CASES(4, 5, 6, 7, __VA_ARGS__) SWZ_ROWS_CASES(8, 9, 10, 11, __VA_ARGS__) \
+    SWZ_ROWS_CASES(12, 13, 14, 15, __VA_ARGS__)                                                                              \
+    default: break;                                                                                                          \
   }
-#define SWZ_LAUNCH_BY_PLAN(KERNEL, ...)                                          \
-  if (plan.tpr == 64) {                                                          \
-    SWZ_LAUNCH_BY_MODE(KERNEL, 4, 64, __VA_ARGS__)                               \
-  } else if (plan.keep == 4) {                                                   \
-    SWZ_LAUNCH_BY_MODE(KERNEL, 4, 256, __VA_ARGS__)                              \
-  } else if (plan.keep == 16) {                                                  \
-    SWZ_LAUNCH_BY_MODE(KERNEL, 16, 256, __VA_ARGS__)                             \
-  } else {                                                                       \
-    SWZ_LAUNCH_BY_MODE(KERNEL, 0, 256, __VA_ARGS__)                              \
-  }
+static_assert(kRowShapes == 16, "the cases above");
+
+template <bool SOFTMAX>
+int launch_long_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* beta, uint16_t* out, int M, int N, float eps,
+                     const RowPlan& plan, int mode, hipStream_t stream) {
+  const int st = launch(swz::row_stats_kernel<SOFTMAX>, dim3((unsigned)((int64_t)M * plan.segs)), dim3(swz::kSegThreads), 0, stream, in, out, M,
+                        N, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, mode);
+  if (st != SWZ_OK) return st;
+  return launch(swz::row_emit_kernel<SOFTMAX>, dim3((unsigned)((int64_t)M * plan.chunks)), dim3(swz::kEmitThreads), 0, stream, in, gamma, beta,
+                out, M, N, eps, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, mode);
+}
 }  // namespace
 
 extern "C" {
@@ -483,27 +508,30 @@ int swz_softmax(const void* in, void* out, int64_t M, int64_t N, int chunks, int
                 hipStream_t stream) {
   if (in == nullptr || out == nullptr) return SWZ_ERR_INVALID_ARG;
   RowPlan plan;
-  const int st = resolve_rows(M, N, chunks, mode, params, &plan);
+  const int st = resolve_rows(M, N, chunks, mode, params, kSoftmaxShapes, &plan);
   if (st != SWZ_OK) return st;
   if ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) return SWZ_ERR_UNSUPPORTED;
-  const dim3 grid((unsigned)((int64_t)plan.grid_m * chunks)), block(swz::kRowThreads);
-  SWZ_LAUNCH_BY_PLAN(swz::softmax_rows_kernel, static_cast<const uint16_t*>(in), static_cast<uint16_t*>(out), (int)M,
-                     (int)N, chunks, plan.chunk_vecs, plan.num_xcd, plan.group_m)
+  auto* x = static_cast<const uint16_t*>(in);
+  auto* y = static_cast<uint16_t*>(out);
+  SWZ_LAUNCH_ROWS(swz::softmax_rows_kernel, kSoftmaxShapes, x, y, (int)M, (int)N, plan.num_xcd, plan.group_m, mode)
+  return launch_long_rows<true>(x, nullptr, nullptr, y, (int)M, (int)N, 0.f, plan, mode, stream);
 }
 
 int swz_layernorm(const void* in, const void* gamma, const void* beta, void* out, int64_t M, int64_t N, float eps,
                   int chunks, int mode, const swz_params* params, hipStream_t stream) {
   if (in == nullptr || gamma == nullptr || beta == nullptr || out == nullptr || !(eps >= 0.f)) return SWZ_ERR_INVALID_ARG;
   RowPlan plan;
-  const int st = resolve_rows(M, N, chunks, mode, params, &plan);
+  const int st = resolve_rows(M, N, chunks, mode, params, kLayernormShapes, &plan);
   if (st != SWZ_OK) return st;
   if ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(gamma) |
        reinterpret_cast<uintptr_t>(beta)) & 15)
     return SWZ_ERR_UNSUPPORTED;
-  const dim3 grid((unsigned)((int64_t)plan.grid_m * chunks)), block(swz::kRowThreads);
-  SWZ_LAUNCH_BY_PLAN(swz::layernorm_rows_kernel, static_cast<const uint16_t*>(in), static_cast<const uint16_t*>(gamma),
-                     static_cast<const uint16_t*>(beta), static_cast<uint16_t*>(out), (int)M, (int)N, eps, chunks,
-                     plan.chunk_vecs, plan.num_xcd, plan.group_m)
+  auto* x = static_cast<const uint16_t*>(in);
+  auto* g = static_cast<const uint16_t*>(gamma);
+  auto* b = static_cast<const uint16_t*>(beta);
+  auto* y = static_cast<uint16_t*>(out);
+  SWZ_LAUNCH_ROWS(swz::layernorm_rows_kernel, kLayernormShapes, x, g, b, y, (int)M, (int)N, eps, plan.num_xcd, plan.group_m, mode)
+  return launch_long_rows<false>(x, g, b, y, (int)M, (int)N, eps, plan, mode, stream);
 }
 
 int swz_mfma_peak(float* out, int64_t out_floats, int iters, int random_operands, int* workgroups, hipStream_t stream) {

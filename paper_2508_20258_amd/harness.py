@@ -487,7 +487,7 @@ def cmd_profile_rows(args):
              "Roofline: HBM, 8 TB/s; algorithmic bytes 4*M*N per launch (read x once, write y once): 256 MiB, 2 GiB for 32768 x 16384.",
              "Launches repeat over the same data; 256 MiB is partly held by the 256 MB memory-side cache between launches, 2 GiB is not.",
              f"The library's plain copy kernel, 1 GiB in + 1 GiB out, same session: {copy_us:.2f} us = {copy_gbs:.0f} GB/s ({100 * copy_gbs / 8000:.1f} % of 8 TB/s).",
-             f"us = kernel duration in the kernel trace, average over the last {args.launches} launches.  chunks = workgroups per row; each reads the whole row.",
+             f"us = kernel duration in the kernel trace, average over the last {args.launches} launches.  chunks = workgroups a row may be spread over; these rows are held by one each.",
              "", f"{'op':9s} {'M x N':>14s} {'chunks':>6s} {'mode':5s} {'us':>8s} {'GB/s':>6s} {'% of 8 TB/s':>11s} {'L2 hit %':>8s} {'fetch MiB':>10s} {'write MiB':>10s}"]
     for op, m, n, c, mode in cases:
         t = f"{out}/{op}_{m}x{n}_c{c}_{mode}"

@@ -150,3 +150,44 @@ def test_rowwise_error_paths(swz):
     assert L.swz_layernorm(xp, gp, gp, yp, 16, 1 << 25, 1e-5, 1, 0, None, s) == -2
     torch.cuda.synchronize()
     assert (y == 2.0).all()
+
+
+# Every way a row is held: the last N of each shape and the first of the next (16 to 64 lanes, 256 to 1024 threads), and the two
+# launches above 98304 elements (ragged segments and chunks; M chosen so that the last group of rows is ragged too)
+ROW_EDGES = [(33, 8), (33, 128), (17, 136), (17, 256), (9, 264), (9, 512), (9, 520), (5, 1024), (5, 1032), (6, 1792), (3, 1800),
+             (3, 4096), (3, 4104), (2, 8200), (2, 12288), (2, 12296), (2, 16384), (2, 16392), (3, 32776), (2, 40960), (2, 40968),
+             (2, 49160), (2, 65536), (2, 65544), (1, 81920), (2, 81928), (2, 98304), (3, 98312), (2, 131080), (1, 1 << 20), (1, 3145736)]
+
+
+@pytest.mark.parametrize("M,N", ROW_EDGES)
+def test_every_row_shape_matches_oracle(swz, M, N):
+    x = si.matrix_bf16(900 + M, 0, M, N, "normal", 3.0)
+    g, b = si.matrix_bf16(900 + M, 1, 1, N, "uniform", 2.0)[0], si.matrix_bf16(900 + M, 2, 1, N, "uniform")[0]
+    xs = x.copy()
+    xs[0, 1::3] = NEG_INF                           # masked entries; in the last row everything but its end, so that
+    xs[M - 1, :N - 5] = NEG_INF                     # whole vectors, lanes and segments hold nothing else
+    xd, xsd, gd, bd = to_dev(x), to_dev(xs), to_dev(g), to_dev(b)
+    chunks = min(8, N // 8)
+    out = torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    got = run_all_modes(lambda o, mode: swz.softmax(xsd, o, chunks=chunks, mode=mode), M, N)
+    swz.softmax(xsd, out[:M], chunks=1, mode=1, num_xcd=3)
+    assert np.array_equal(to_bits(out[:M]), got) and torch.isnan(out[M]).all()
+    ref = rw.softmax(xs)
+    assert (np.abs(si.bf16_bits_to_f64(got) - ref) <= rw.softmax_bound(ref)).all()
+    got = run_all_modes(lambda o, mode: swz.layernorm(xd, gd, bd, o, eps=1e-5, chunks=chunks, mode=mode), M, N)
+    swz.layernorm(xd, gd, bd, out[:M], eps=1e-5, chunks=1, mode=1, num_xcd=3)
+    assert np.array_equal(to_bits(out[:M]), got) and torch.isnan(out[M]).all()
+    ref = rw.layernorm(x, g, b, 1e-5)
+    assert (np.abs(si.bf16_bits_to_f64(got) - ref) <= rw.layernorm_bound(x, g, b, 1e-5)).all()
+
+
+@pytest.mark.parametrize("N", [64, 200, 1000, 5000, 40000, 200000])
+def test_softmax_of_infinities_nan_and_extreme_rows(swz, N):
+    x = torch.randn((5, N), device="cuda").to(torch.bfloat16)
+    x[0] = float("-inf")                            # no finite entry: NaN
+    x[1, N // 2] = float("nan")
+    x[2, N - 1] = float("inf")
+    x[3] = -3.0e38                                  # equal entries whose scaled value overflows
+    y = swz.softmax(x).float()
+    assert torch.isnan(y[:4]).all()
+    assert abs(y[4].double().sum().item() - 1.0) < 4e-3     # the row between them is untouched: half an ulp a value
