@@ -165,6 +165,8 @@ int swz_gemm_plan(int64_t M, int64_t N, int64_t K, const swz_params* params, swz
  *             neighbouring tiles: the case where the mapping decides the L2 hit rate).
  *   Once input plus output exceed the 256 MB memory-side cache the stores of tiles 64 and 128 are
  *   streaming stores (the faster choice there, the slower one below it).
+ *   Where rows of `out` do not start on 128-byte lines, a workgroup of a tile 64 writes the whole lines nearest to
+ *   its tile (from 16 MiB moved); the id -> tile map stays that of swz_pid_map.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null, M/N < 1, unknown mode), UNSUPPORTED (elem_bytes not 2 or 4, tile not 32/64/128
  * (not 64 for 4-byte elements), M or N not a multiple of 8 (4 for 4-byte elements), misaligned pointer),

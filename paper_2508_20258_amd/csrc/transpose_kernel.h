@@ -195,4 +195,68 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
   }
 }
 
+// The same transpose where rows of `out` do not start on 128-byte lines (M * sizeof(T) no multiple of 128, or `out` itself
+// off a line).  A 64-wide tile of the other kernels then writes two part lines per row, which reach memory in two
+// pieces.  Here the 64 columns a workgroup
+// writes of row n of `out` are shifted left by s(n), the elements by which the row overhangs a line, so that it writes whole lines: row n
+// gets columns [64 pm - s(n), 64 pm - s(n) + 64), the last tile of the row everything up to M (one line more at
+// most).  The tile of `in` grows by the E - 1 rows above it (E elements fill a line), which the neighbouring tile
+// row reads too: they come out of the L2.  s(n) differs from row to row, so a lane gathers its 16 bytes element by element, four rows or eight
+// rows of the tile at a column: the transposing LDS read takes the same rows for 4 columns.
+// A wave instruction stores 8 rows x 8 chunks = 8 whole lines: lane l takes row l / 8, chunk l % 8.
+// LDS: 16-byte chunk c of tile row r in slot c ^ key(r); key steps with the chunk of rows a lane gathers, so that the 8
+// chunks of one column lie in different banks whatever their shift.  The stores are streaming ones at every size: nothing
+// is left to merge in the L2.
+// Bound by HBM.  Measured, matrices not in cache, tiles on line-blind boundaries -> these (us; GB/s of the matrix read and written):
+//     two bytes   10000 x 7000  102 -> 74 (3780)    10000 x 7040  94 -> 62 (4540)    8200 x 8208   110 -> 67 (4020)
+//     four bytes   5800 x 5804   82 -> 59 (4560)     5800 x 5824  80 -> 58 (4660)   15764 x 8092   363 -> 212 (4810)
+// against 60 us where both pitches are whole lines (10048 x 7040) and no shift is needed.
+template <class T>
+__global__ __launch_bounds__(256) void transpose_lines_kernel(const T* __restrict__ in, T* __restrict__ out, int M, int N, int grid_m,
+                                                              int grid_n, int num_xcd, int group_m, int mode) {
+  constexpr int TILE = 64, CH = 16 / (int)sizeof(T), E = 128 / (int)sizeof(T);       // elements per chunk, per line
+  constexpr int SLOTS = TILE / CH, ROWS = TILE + E, ROW_BYTES = TILE * (int)sizeof(T), LINES = TILE / E;
+  __shared__ __attribute__((aligned(16))) unsigned char tile[ROWS * ROW_BYTES];
+  int pm, pn;
+  swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
+  const int m0 = pm * TILE - E, n0 = pn * TILE;                  // first row of `in` in the tile, first column
+  const int tid = threadIdx.x;
+  auto key = [](int r) { return sizeof(T) == 2 ? (r >> 3) & 7 : ((r >> 2) & 7) << 1; };
+#pragma unroll
+  for (int i = 0; i < ROWS * SLOTS / 256; ++i) {
+    const int q = tid + 256 * i, r = q / SLOTS, c = q % SLOTS;
+    const int m = m0 + r, n = n0 + c * CH;
+    t_u32x4 v = {0u, 0u, 0u, 0u};
+    if (m >= 0 && m < M && n < N) v = *reinterpret_cast<const t_u32x4*>(in + (size_t)m * N + n);
+    *reinterpret_cast<t_u32x4*>(tile + r * ROW_BYTES + ((c ^ key(r)) << 4)) = v;
+  }
+  __syncthreads();
+  const int lane = tid & 63, wave = tid >> 6;
+  const int jj = lane >> 3, rg = lane & 7;
+  const uint32_t base = (uint32_t)(reinterpret_cast<uintptr_t>(out) / sizeof(T));
+  const int lines = pm == grid_m - 1 ? LINES + 1 : LINES;        // uniform
+#pragma unroll
+  for (int jb = wave; jb < TILE / 8; jb += 4) {
+    const int col = 8 * jb + jj, n = n0 + col;                   // tile column = row of out
+    const int shift = (int)((base + (uint32_t)n * (uint32_t)M) % (uint32_t)E);       // E divides 2^32
+    for (int h = 0; h < lines; ++h) {
+      const int row = E - shift + h * E + CH * rg;               // tile row of this lane's first element
+      const int m = m0 + row;
+      if (n < N && m >= 0 && m < M) {                            // M % CH == 0: the chunk is in or out as a whole
+        T e[CH];
+#pragma unroll
+        for (int k = 0; k < CH; ++k)
+          e[k] = *reinterpret_cast<const T*>(tile + (row + k) * ROW_BYTES + (((col / CH) ^ key(row + k)) << 4) + (col % CH) * (int)sizeof(T));
+        t_u32x4 v;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          if constexpr (sizeof(T) == 2) v[w] = (uint32_t)e[2 * w] | ((uint32_t)e[2 * w + 1] << 16);
+          else v[w] = (uint32_t)e[w];
+        }
+        __builtin_nontemporal_store(v, reinterpret_cast<t_u32x4*>(out + (size_t)n * M + m));
+      }
+    }
+  }
+}
+
 }  // namespace swz

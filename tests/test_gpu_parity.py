@@ -655,3 +655,28 @@ def test_subtiles_give_the_bits_of_whole_tiles(swz, M, N):
     if M <= 512 and N <= 1000:
         ref = gemm_ref.gemm(to_bits(a), to_bits(b))
         assert_within_tolerance(to_bits(c[:M]), ref, f"{M}x{N}x{K}")
+
+
+# ---------------------------------------------------------------------------- transposes into rows that start inside a line
+
+@pytest.mark.parametrize("elem_bytes,M,N,offset", [
+    # at least 16 MiB moved; one tile row and several, last tiles of every width, rows shorter than a line
+    (2, 8, 600000, 0), (2, 56, 90008, 0), (2, 72, 60000, 0), (2, 120, 40000, 0), (2, 136, 40064, 0), (2, 2040, 2064, 0),
+    (2, 4104, 1032, 0), (2, 64, 70000, 8), (2, 2048, 2048, 56), (2, 2056, 2048, 24),
+    (4, 4, 600000, 0), (4, 28, 90004, 0), (4, 36, 60000, 0), (4, 60, 40000, 0), (4, 68, 40064, 0), (4, 1500, 1504, 0),
+    (4, 2044, 1028, 0), (4, 64, 40000, 4), (4, 1536, 1536, 28), (4, 1540, 1536, 12)])
+def test_transpose_into_part_lines_is_bit_exact(swz, elem_bytes, M, N, offset):
+    assert 2 * elem_bytes * M * N >= 16 << 20
+    dtype = torch.int16 if elem_bytes == 2 else torch.int32
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    x = torch.randint(-(1 << 15), 1 << 15, (M, N), device="cuda", generator=g).to(dtype)
+    if elem_bytes == 4:
+        x = x * 65537 + 77
+    want = x.t().contiguous()
+    for mode in (6, 0, 1, 2, 3, 4, 5, 7):
+        buf = torch.full((N * M + 128,), -7, dtype=dtype, device="cuda")       # what surrounds `out` must not change
+        out = buf[offset:offset + N * M].view(N, M)
+        swz.transpose(x, out, mode=mode, num_xcd=3 if mode == 7 else 0)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), mode
+        assert (buf[:offset] == -7).all() and (buf[offset + N * M:] == -7).all()
