@@ -128,8 +128,9 @@ int swz_pid_map_persistent_device(int grid_m, int grid_n, int num_xcd, int group
  *   Defaults: num_xcd detected, group_m = 4, tile 256x256x64; when the 256x256 tile grid would have at
  *   most half as many tiles as the device has compute units, 128x256x64, and at most a quarter, 128x128x64
  *   (the chip is then better filled by more and smaller tiles; the result bits do not depend on the tile shape).
- *   Small and narrow products go further: a tile the library chose may be computed by several workgroups (sub-tiles of
- *   32x32 to 128x128) that all run on the XCD the map gives the tile; plan, map and bits are those of the tile.
+ *   Small and narrow products, and the last, partial round of a large grid, go further: a tile the library chose may be
+ *   computed by several workgroups (sub-tiles of 32x32 to 128x256) on the XCD the map gives the tile; plan, map and bits are
+ *   those of the tile.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null pointer, M/N/K < 1, unknown mode), UNSUPPORTED (other dtype,
  * K or N not a multiple of 8, misaligned pointer), OVERFLOW (tile count >= 2^31 or a

@@ -267,4 +267,30 @@ __global__ __launch_bounds__(S::NT) void gemm_bf16_subtile_kernel(const uint16_t
   gemm_subtile<S>(A, B, C, M, N, K, m0, n0, smem);
 }
 
+// Whole tiles (S) for hardware ids below `whole`, a multiple of the compute units; the tiles of the last, partial round
+// in sub-tiles (P) behind them, dealt like those above, so that the round lasts as long as a sub-tile and not as long as a tile.
+// One launch: the first sub-tiles start where the first whole tiles end.
+template <class S, class P>
+__global__ __launch_bounds__(S::NT) void gemm_bf16_tail_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
+                                                               uint16_t* __restrict__ C, int M, int N, int K, int grid_m, int grid_n,
+                                                               int num_xcd, int group_m, int mode, int whole, int deal) {
+  static_assert(S::NT == P::NT && S::BM % P::BM == 0 && S::BN % P::BN == 0, "one block size, pieces that fill a tile");
+  constexpr int SUB_M = S::BM / P::BM, SUBS = SUB_M * (S::BN / P::BN);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int w = (int)blockIdx.x;
+  int pm, pn;
+  if (w < whole) {
+    swz_decode_tile(w, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
+    gemm_tile<S>(A, B, C, M, N, K, pm, pn, false, false, 0, 0, smem);
+  } else {
+    const int i = (w - whole) / deal, x = (w - whole) - i * deal, turn = i / SUBS, sub = i - turn * SUBS;
+    const int v = whole + turn * deal + x;
+    if (v >= grid_m * grid_n) return;                            // uniform, like the exit below
+    swz_decode_tile(v, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
+    const int m0 = pm * S::BM + (sub % SUB_M) * P::BM, n0 = pn * S::BN + (sub / SUB_M) * P::BN;
+    if (m0 >= M || n0 >= N) return;
+    gemm_subtile<P>(A, B, C, M, N, K, m0, n0, smem);
+  }
+}
+
 }  // namespace swz

@@ -31,8 +31,8 @@ struct DeviceFacts {
 };
 DeviceFacts g_facts[kMaxDevices];
 std::atomic<bool> g_attr_set[kMaxDevices][4][4][2];
-constexpr int kSubShapes = 6;
-std::atomic<bool> g_sub_attr_set[kMaxDevices][kSubShapes];
+constexpr int kSubShapes = 6, kTailShapes = 2;
+std::atomic<bool> g_sub_attr_set[kMaxDevices][kSubShapes + kTailShapes];
 std::mutex g_mu;
 
 // SWZ_NUM_XCD in the environment (read once per process): the XCD count to assume instead of the
@@ -166,7 +166,8 @@ constexpr int64_t kRoundNs = 2500;
 // Which sub-tile shape (index into kSubCost) computes this product fastest, or -1 where the plan's tile as one
 // workgroup does.  The estimate is  rounds x (kRoundNs + stages x cost), rounds = workgroups that touch C over CUs; it
 // orders the shapes as measured on 60 products with M from 1 to 2048.  One 128x128, 128x256 and 256x256 tile of
-// gemm_kernel.h costs 600, 840 and 1350 ns a stage (two 128x128 ones share a CU: 920 the pair).  Ties go to the larger
+// gemm_kernel.h costs 600, 840 and 1350 ns a stage (two 128x128 ones share a CU: 920 the pair; a partial last round of
+// 256x256 tiles costs what launch_tail makes of it).  Ties go to the larger
 // tile: it moves fewer bytes.  A sub-tile has to be 5 % better than the tile, the spread of the estimate near a tie.
 int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, int cus) {
   const int64_t stages = (K + swz::kStageK - 1) / swz::kStageK;
@@ -177,8 +178,11 @@ int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, int cus
   int64_t best;
   if (r.bm == 128 && r.bn == 128) {
     best = rounds(128, 128, cus) == 1 ? estimate(1, 600) : estimate(rounds(128, 128, 2 * cus), 920);
+  } else if (r.bm != r.bn) {
+    best = estimate(rounds(r.bm, r.bn, cus), 840);
   } else {
-    best = estimate(rounds(r.bm, r.bn, cus), r.bm == r.bn ? 1350 : 840);
+    const int64_t tiles = rounds(256, 256, 1), tail = tiles % cus;
+    best = estimate(tiles / cus, 1350) + (tail == 0 ? 0 : estimate(1, tiles < cus ? 1350 : 4 * tail <= cus ? 520 : 2 * tail <= cus ? 840 : 1350));
   }
   best -= best / 20;
   int choice = -1;
@@ -192,20 +196,25 @@ int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, int cus
   return choice;
 }
 
+// Once per kernel and device: a kernel that asks for more LDS than the default has to say so.
+int allow_lds(const void* kernel, int bytes, int slot) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SWZ_ERR_HIP;
+  std::atomic<bool>& ready = g_sub_attr_set[dev][slot];
+  if (!ready.load(std::memory_order_acquire)) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return SWZ_ERR_HIP;
+    ready.store(true, std::memory_order_release);
+  }
+  return SWZ_OK;
+}
+
 template <class S>
 int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, const swz_params& r, int grid_m, int grid_n,
                    int group_m, int mode, hipStream_t stream, int shape) {
   auto kernel = swz::gemm_bf16_subtile_kernel<S>;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SWZ_ERR_HIP;
-  std::atomic<bool>& ready = g_sub_attr_set[dev][shape];
-  if (!ready.load(std::memory_order_acquire)) {       // first launch of this kernel on this device only
-    std::lock_guard<std::mutex> lock(g_mu);
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            S::LDS_BYTES) != hipSuccess)
-      return SWZ_ERR_HIP;
-    ready.store(true, std::memory_order_release);
-  }
+  const int st = allow_lds(reinterpret_cast<const void*>(kernel), S::LDS_BYTES, shape);
+  if (st != SWZ_OK) return st;
   // a grid of one tile row (column) has no use for sub-tiles below (right of) C
   const int sub_m = grid_m == 1 ? (M + S::BM - 1) / S::BM : r.bm / S::BM;
   const int sub_n = grid_n == 1 ? (N + S::BN - 1) / S::BN : r.bn / S::BN;
@@ -215,6 +224,24 @@ int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, c
   return launch(kernel, dim3((unsigned)blocks), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
                 static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, grid_m, grid_n, r.num_xcd, group_m, mode,
                 r.bm, r.bn, sub_m, sub_n, deal);
+}
+
+// The last, partial round of a grid of 256x256 tiles in pieces P: `tail` tiles behind `whole` ones.
+using Whole256 = swz::GemmShape<256, 256, 2, 4>;
+using Piece128x128 = Sub128x128;
+using Piece128x256 = swz::SubShape<128, 256, 2, 4, 3>;
+template <class P>
+int launch_tail(const void* A, const void* B, void* C, int M, int N, int K, const swz_params& r, int grid_m, int grid_n, int group_m,
+                int mode, int whole, int tail, hipStream_t stream, int slot) {
+  auto kernel = swz::gemm_bf16_tail_kernel<Whole256, P>;
+  const int lds = Whole256::LDS_BYTES > P::LDS_BYTES ? Whole256::LDS_BYTES : P::LDS_BYTES;
+  const int st = allow_lds(reinterpret_cast<const void*>(kernel), lds, kSubShapes + slot);
+  if (st != SWZ_OK) return st;
+  const int deal = r.num_xcd < tail ? r.num_xcd : tail;
+  const int subs = (256 / P::BM) * (256 / P::BN);
+  const int64_t blocks = whole + ((int64_t)tail + deal - 1) / deal * deal * subs;
+  return launch(kernel, dim3((unsigned)blocks), dim3(Whole256::NT), lds, stream, static_cast<const uint16_t*>(A),
+                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, grid_m, grid_n, r.num_xcd, group_m, mode, whole, deal);
 }
 
 int resolve_plan(int64_t M, int64_t N, int64_t K, const swz_params* p, swz_params* r, int* grid_m, int* grid_n) {
@@ -615,6 +642,15 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
       case 4: return launch_subtile<Sub64x128>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 4);
       case 5: return launch_subtile<Sub128x128>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 5);
       default: break;
+    }
+    // A last round that fills at most half of the compute units is cut into halves or quarters of tiles, which then fit it:
+    // 1350 -> 840 or 520 ns a stage.  Measured, start -> here: 4352x4096x4096 (16 tiles left over) 154 -> 117 us, 6000x3000x3000 (32) 124 -> 101,
+    // 5120x4608x4096 (104) 162 -> 146, 10000x7000x4096 (96, fifth round) 442 -> 427.  Above half a round the pieces need a second
+    // round of their own: 5120x5120x5120 (144) stays at 198 us whole.
+    const int total = grid_m * grid_n, whole = f.cus > 0 ? total / f.cus * f.cus : total, tail = total - whole;
+    if (r.bm == 256 && r.bn == 256 && whole > 0 && tail > 0) {
+      if (4 * tail <= f.cus) return launch_tail<Piece128x128>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, whole, tail, stream, 0);
+      if (2 * tail <= f.cus) return launch_tail<Piece128x256>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, whole, tail, stream, 1);
     }
   }
   if (r.bm == 128 && r.bn == 128)

@@ -680,3 +680,20 @@ def test_transpose_into_part_lines_is_bit_exact(swz, elem_bytes, M, N, offset):
         torch.cuda.synchronize()
         assert torch.equal(out, want), mode
         assert (buf[:offset] == -7).all() and (buf[offset + N * M:] == -7).all()
+
+
+# 256x256 tiles beyond whole rounds of 256 compute units: up to 64 (quarters), up to 128 (halves), more (whole); ragged edges among
+# the pieces, pieces outside C, one tile left over
+@pytest.mark.parametrize("M,N", [(4352, 4096), (4200, 4104), (65793, 248), (5120, 4608), (4610, 5000), (4100, 6200), (8200, 8200)])
+def test_partial_last_round_in_pieces_gives_the_bits_of_whole_tiles(swz, M, N):
+    for K in (8, 200, 520):
+        g = torch.Generator(device="cuda").manual_seed(M + K)
+        a = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+        b = torch.randn((K, N), device="cuda", generator=g).to(torch.bfloat16)
+        want = swz.gemm(a, b, mode=0, bm=256, bn=256)
+        for mode, params in [(0, {}), (2, {}), (1, dict(num_xcd=3)), (6, dict(group_m=3)), (5, dict(num_xcd=1000))]:
+            c = torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+            swz.gemm(a, b, c[:M], mode=mode, **params)
+            torch.cuda.synchronize()
+            assert torch.equal(c[:M].view(torch.int16), want.view(torch.int16)), (M, N, K, mode, params)
+            assert torch.isnan(c[M]).all()
