@@ -171,3 +171,20 @@ def test_binding_refuses_tensors_of_another_device(monkeypatch):
     with pytest.raises(ValueError):
         swz.binding._same_current_device(there, here)
     swz.binding._same_current_device(here, here)
+
+
+def test_launch_stream_takes_the_fast_way_only_on_the_current_device(monkeypatch):
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 1000 + d, raising=False)
+    here, there = (types.SimpleNamespace(device=types.SimpleNamespace(index=i), get_device=lambda i=i: i) for i in (0, 1))
+    stream = types.SimpleNamespace(device=types.SimpleNamespace(index=0), cuda_stream=77)
+    away = types.SimpleNamespace(device=types.SimpleNamespace(index=1), cuda_stream=78)
+    assert swz.binding._launch_stream(None, here, here) == 1000
+    assert swz.binding._launch_stream(stream, here, here) == 77
+    for bad in ((None, here, there), (stream, there), (away, here)):
+        with pytest.raises(ValueError):
+            swz.binding._launch_stream(*bad)
