@@ -128,9 +128,10 @@ int swz_pid_map_persistent_device(int grid_m, int grid_n, int num_xcd, int group
  *   Defaults: num_xcd detected, group_m = 4, tile 256x256x64; when the 256x256 tile grid would have at
  *   most half as many tiles as the device has compute units, 128x256x64, and at most a quarter, 128x128x64
  *   (the chip is then better filled by more and smaller tiles; the result bits do not depend on the tile shape).
- *   Small and narrow products, and the last, partial round of a large grid, go further: a tile the library chose may be
- *   computed by several workgroups (sub-tiles of 32x32 to 128x256) on the XCD the map gives the tile; plan, map and bits are
- *   those of the tile.
+ *   Small and narrow products go further: where the library chose the tile it may compute C in sub-tiles of 32x32 to
+ *   128x128, one workgroup each, and then applies `mode`, num_xcd and the same band height to the grid of sub-tiles.  The
+ *   left-over tiles of a large grid's last, partial round may be computed by two or four workgroups each, on the XCD the
+ *   map gives the tile.  The bits are those of whole tiles.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null pointer, M/N/K < 1, unknown mode), UNSUPPORTED (other dtype,
  * K or N not a multiple of 8, misaligned pointer), OVERFLOW (tile count >= 2^31 or a
@@ -148,7 +149,8 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
 
 /* What swz_gemm_ex would launch for this problem: the resolved parameters and tile grid, i.e. the
  * arguments with which swz_pid_map reproduces the launch's map (the paper validates a remap by
- * its map being a bijection: Results, "broken remappings").
+ * its map being a bijection: Results, "broken remappings"); where swz_gemm computes C in sub-tiles, the map of the
+ * launch is that of a finer grid.
  * Pure host arithmetic apart from the device query that resolves num_xcd = 0.
  * Any output pointer may be null. */
 int swz_gemm_plan(int64_t M, int64_t N, int64_t K, const swz_params* params, swz_params* resolved,

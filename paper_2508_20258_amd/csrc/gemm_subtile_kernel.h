@@ -6,8 +6,7 @@
 // What bounds these products is latency, not a rate: a 256 x 256 or 128 x 128 tile leaves 64 to 250 of 256 CUs
 // without work, and with three K steps of look-ahead (0.3 us) a tile that has its CU to itself waits for most
 // of its operands.  Hence
-//   * sub-tiles: a tile of the plan is cut into workgroups of 32x32 to 128x128 elements of C, which all sit on the XCD the
-//     map gives the tile (they share its operand panels in that L2);
+//   * sub-tiles: workgroups of 32x32 to 128x128 elements of C, in a raster as fine as they are;
 //   * a ring of 5 to 8 stages, 64 of K each, fetched global -> LDS four to seven stages ahead;
 //   * one barrier per stage, and two sets of fragments: the reads of one half of a stage (32 of K) are issued
 //     between the MFMAs of the other half, the barrier falls between the two.  Measured against reading a whole
@@ -245,31 +244,27 @@ __device__ __forceinline__ void gemm_subtile(const uint16_t* __restrict__ A, con
   store_wave_tile<TM, TN>(acc, C, M, N, m0 + wm * (TM * 16), n0 + wn * (TN * 16), lane);
 }
 
-// A tile (bm x bn, as the plan names it) is computed by sub_m * sub_n workgroups of S::BM x S::BN each.  The map
-// is that of the tiles: hardware ids are dealt round-robin to the XCDs, so the sub-tiles of the tile that
-// the map gives to hardware id v are handed to ids that are v modulo `deal` (= the XCD count, or the tile count if
-// that is smaller) and run on the XCD the map means.  Ids past the last tile and sub-tiles outside C leave at once.
+// One workgroup per sub-tile.  The raster and the renumbering are those of a tile grid, over the grid of sub-tiles
+// (bands of as many rows of C): every XCD gets its share of them to within one.  Dealing whole tiles of the plan instead, with their
+// sub-tiles on one XCD, left some XCDs with more than 32 for their 32 CUs, and sub-tiles beyond C that leave at once
+// do not free the place they were dealt: 4352x416x6272 in 128x64 sub-tiles took 74 us that way.
 template <class S>
 __global__ __launch_bounds__(S::NT) void gemm_bf16_subtile_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                                   uint16_t* __restrict__ C, int M, int N, int K, int grid_m,
-                                                                  int grid_n, int num_xcd, int group_m, int mode, int bm, int bn,
-                                                                  int sub_m, int sub_n, int deal) {
+                                                                  int grid_n, int num_xcd, int group_m, int mode) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int subs = sub_m * sub_n;
-  const int i = (int)blockIdx.x / deal, x = (int)blockIdx.x - i * deal;
-  const int turn = i / subs, sub = i - turn * subs;
-  const int v = turn * deal + x;
-  if (v >= grid_m * grid_n) return;                              // uniform, like the exit below
   int pm, pn;
-  swz_decode_tile(v, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
-  const int m0 = pm * bm + (sub % sub_m) * S::BM, n0 = pn * bn + (sub / sub_m) * S::BN;
-  if (m0 >= M || n0 >= N) return;
-  gemm_subtile<S>(A, B, C, M, N, K, m0, n0, smem);
+  swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
+  gemm_subtile<S>(A, B, C, M, N, K, pm * S::BM, pn * S::BN, smem);
 }
 
 // Whole tiles (S) for hardware ids below `whole`, a multiple of the compute units; the tiles of the last, partial round
-// in sub-tiles (P) behind them, dealt like those above, so that the round lasts as long as a sub-tile and not as long as a tile.
-// One launch: the first sub-tiles start where the first whole tiles end.
+// in sub-tiles (P) behind them, so that the round lasts as long as a sub-tile and not as long as a tile.  One launch: the first
+// sub-tiles start where the first whole tiles end.  Hardware ids are dealt round-robin to the XCDs, so the sub-tiles of the
+// tile that the map gives to id v are handed to ids that are v modulo `deal` (the XCD count, or the number of left-over tiles if
+// that is smaller): they run on the XCD the map means and share the tile's operand panels in its L2.  At most half a round of tiles
+// is left over, in halves, or a quarter, in quarters, so no XCD gets more than it has CUs.  Ids past the last tile and
+// sub-tiles outside C leave at once.
 template <class S, class P>
 __global__ __launch_bounds__(S::NT) void gemm_bf16_tail_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                                uint16_t* __restrict__ C, int M, int N, int K, int grid_m, int grid_n,

@@ -210,20 +210,15 @@ int allow_lds(const void* kernel, int bytes, int slot) {
 }
 
 template <class S>
-int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, const swz_params& r, int grid_m, int grid_n,
-                   int group_m, int mode, hipStream_t stream, int shape) {
+int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, const swz_params& r, int group_m, int mode,
+                   hipStream_t stream, int shape) {
   auto kernel = swz::gemm_bf16_subtile_kernel<S>;
   const int st = allow_lds(reinterpret_cast<const void*>(kernel), S::LDS_BYTES, shape);
   if (st != SWZ_OK) return st;
-  // a grid of one tile row (column) has no use for sub-tiles below (right of) C
-  const int sub_m = grid_m == 1 ? (M + S::BM - 1) / S::BM : r.bm / S::BM;
-  const int sub_n = grid_n == 1 ? (N + S::BN - 1) / S::BN : r.bn / S::BN;
-  const int total = grid_m * grid_n;
-  const int deal = r.num_xcd < total ? r.num_xcd : total;
-  const int64_t blocks = ((int64_t)total + deal - 1) / deal * deal * sub_m * sub_n;
-  return launch(kernel, dim3((unsigned)blocks), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
-                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, grid_m, grid_n, r.num_xcd, group_m, mode,
-                r.bm, r.bn, sub_m, sub_n, deal);
+  const int gm = (M + S::BM - 1) / S::BM, gn = (N + S::BN - 1) / S::BN;
+  const int64_t band = (int64_t)group_m * (r.bm / S::BM);       // rows of sub-tiles as high as a band of tiles
+  return launch(kernel, dim3((unsigned)((int64_t)gm * gn)), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
+                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, gm, gn, r.num_xcd, (int)(band < gm ? band : gm), mode);
 }
 
 // The last, partial round of a grid of 256x256 tiles in pieces P: `tail` tiles behind `whole` ones.
@@ -635,12 +630,12 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
     if (qs != SWZ_OK) return qs;
     const int m = (int)M, n = (int)N, k = (int)K;
     switch (choose_subtile(M, N, K, r, f.cus > 0 ? f.cus : 256)) {
-      case 0: return launch_subtile<Sub32x32>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 0);
-      case 1: return launch_subtile<Sub32x64>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 1);
-      case 2: return launch_subtile<Sub64x64>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 2);
-      case 3: return launch_subtile<Sub128x64>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 3);
-      case 4: return launch_subtile<Sub64x128>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 4);
-      case 5: return launch_subtile<Sub128x128>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, stream, 5);
+      case 0: return launch_subtile<Sub32x32>(A, B, C, m, n, k, r, group_m, mode, stream, 0);
+      case 1: return launch_subtile<Sub32x64>(A, B, C, m, n, k, r, group_m, mode, stream, 1);
+      case 2: return launch_subtile<Sub64x64>(A, B, C, m, n, k, r, group_m, mode, stream, 2);
+      case 3: return launch_subtile<Sub128x64>(A, B, C, m, n, k, r, group_m, mode, stream, 3);
+      case 4: return launch_subtile<Sub64x128>(A, B, C, m, n, k, r, group_m, mode, stream, 4);
+      case 5: return launch_subtile<Sub128x128>(A, B, C, m, n, k, r, group_m, mode, stream, 5);
       default: break;
     }
     // A last round that fills at most half of the compute units is cut into halves or quarters of tiles, which then fit it:
