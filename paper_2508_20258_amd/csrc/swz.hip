@@ -31,7 +31,7 @@ struct DeviceFacts {
 };
 DeviceFacts g_facts[kMaxDevices];
 std::atomic<bool> g_attr_set[kMaxDevices][4][4][2];
-constexpr int kSubShapes = 6, kTailShapes = 2;
+constexpr int kSubShapes = 7, kTailShapes = 2;
 std::atomic<bool> g_sub_attr_set[kMaxDevices][kSubShapes + kTailShapes];
 std::mutex g_mu;
 
@@ -152,16 +152,18 @@ int launch_gemm_probe(const void* A, const void* B, void* C, int M, int N, int K
 
 // The sub-tile shapes, and what a stage (64 of K) of one workgroup costs in ns on a chip whose every CU has one
 // (measured: the slope of kernel time over K).  The fixed part of a round (launch or hand-over, the first
-// operands, the stores) is about kRoundNs whatever the shape.
+// operands, the stores) is about kRoundNs whatever the shape; a whole tile of gemm_kernel.h takes kWholeRoundNs, as it
+// also runs its look-ahead past the end of K.
 using Sub32x32 = swz::SubShape<32, 32, 2, 2, 8>;
 using Sub32x64 = swz::SubShape<32, 64, 2, 2, 6>;
 using Sub64x64 = swz::SubShape<64, 64, 2, 2, 5>;
 using Sub128x64 = swz::SubShape<128, 64, 4, 2, 6>;
 using Sub64x128 = swz::SubShape<64, 128, 2, 4, 6>;
 using Sub128x128 = swz::SubShape<128, 128, 2, 4, 5>;
+using Sub128x256 = swz::SubShape<128, 256, 2, 4, 3>;
 struct SubCost { int bm, bn, stage_ns; };
-constexpr SubCost kSubCost[kSubShapes] = {{32, 32, 140}, {32, 64, 160}, {64, 64, 195}, {128, 64, 310}, {64, 128, 310}, {128, 128, 520}};
-constexpr int64_t kRoundNs = 2500;
+constexpr SubCost kSubCost[kSubShapes] = {{32, 32, 140}, {32, 64, 160}, {64, 64, 195}, {128, 64, 310}, {64, 128, 310}, {128, 128, 520}, {128, 256, 950}};
+constexpr int64_t kRoundNs = 2500, kWholeRoundNs = 4000;
 
 // Which sub-tile shape (index into kSubCost) computes this product fastest, or -1 where the plan's tile as one
 // workgroup does.  The estimate is  rounds x (kRoundNs + stages x cost), rounds = workgroups that touch C over CUs; it
@@ -175,18 +177,20 @@ int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, int cus
     return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + per_round - 1) / per_round;
   };
   auto estimate = [&](int64_t n, int64_t ns) { return n * (kRoundNs + stages * ns); };
+  auto whole = [&](int64_t n, int64_t ns) { return n * (kWholeRoundNs + stages * ns); };
   int64_t best;
   if (r.bm == 128 && r.bn == 128) {
-    best = rounds(128, 128, cus) == 1 ? estimate(1, 600) : estimate(rounds(128, 128, 2 * cus), 920);
+    best = rounds(128, 128, cus) == 1 ? whole(1, 600) : whole(rounds(128, 128, 2 * cus), 920);
   } else if (r.bm != r.bn) {
-    best = estimate(rounds(r.bm, r.bn, cus), 840);
+    best = whole(rounds(r.bm, r.bn, cus), 840);
   } else {
     const int64_t tiles = rounds(256, 256, 1), tail = tiles % cus;
-    best = estimate(tiles / cus, 1350) + (tail == 0 ? 0 : estimate(1, tiles < cus ? 1350 : 4 * tail <= cus ? 520 : 2 * tail <= cus ? 840 : 1350));
+    best = whole(tiles / cus, 1350) + (tail == 0 ? 0 : whole(1, tiles < cus ? 1350 : 4 * tail <= cus ? 520 : 2 * tail <= cus ? 840 : 1350));
   }
   best -= best / 20;
   int choice = -1;
   for (int s = kSubShapes - 1; s >= 0; --s) {
+    if (kSubCost[s].bm > r.bm || kSubCost[s].bn > r.bn) continue;         // a sub-tile is no larger than the plan's tile
     const int64_t e = estimate(rounds(kSubCost[s].bm, kSubCost[s].bn, cus), kSubCost[s].stage_ns);
     if (e < best) {
       best = e;
@@ -224,7 +228,7 @@ int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, c
 // The last, partial round of a grid of 256x256 tiles in pieces P: `tail` tiles behind `whole` ones.
 using Whole256 = swz::GemmShape<256, 256, 2, 4>;
 using Piece128x128 = Sub128x128;
-using Piece128x256 = swz::SubShape<128, 256, 2, 4, 3>;
+using Piece128x256 = Sub128x256;
 template <class P>
 int launch_tail(const void* A, const void* B, void* C, int M, int N, int K, const swz_params& r, int grid_m, int grid_n, int group_m,
                 int mode, int whole, int tail, hipStream_t stream, int slot) {
@@ -636,6 +640,7 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
       case 3: return launch_subtile<Sub128x64>(A, B, C, m, n, k, r, group_m, mode, stream, 3);
       case 4: return launch_subtile<Sub64x128>(A, B, C, m, n, k, r, group_m, mode, stream, 4);
       case 5: return launch_subtile<Sub128x128>(A, B, C, m, n, k, r, group_m, mode, stream, 5);
+      case 6: return launch_subtile<Sub128x256>(A, B, C, m, n, k, r, group_m, mode, stream, 6);
       default: break;
     }
     // A last round that fills at most half of the compute units is cut into halves or quarters of tiles, which then fit it:
