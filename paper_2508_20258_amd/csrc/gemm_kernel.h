@@ -174,10 +174,14 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
   (f(std::integral_constant<int, Is>{}), ...);
 }
 
-// The TM x TN blocks of 16 x 16 a wave has accumulated -> bf16 (nearest even) -> C, first row row_base, first
-// column col_base; rows >= M and columns >= N are left out.
-template <int TM, int TN>
-__device__ __forceinline__ void store_wave_tile(const f32x4 (&acc)[TM][TN], uint16_t* __restrict__ C, int M, int N,
+template <bool STREAM, class V>
+__device__ __forceinline__ void store_c(V v, uint16_t* p) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
+  else *reinterpret_cast<V*>(p) = v;
+}
+
+template <bool STREAM, int TM, int TN>
+__device__ __forceinline__ void store_wave_tile_as(const f32x4 (&acc)[TM][TN], uint16_t* __restrict__ C, int M, int N,
                                                 int row_base, int col_base, int lane) {
   // Lane (r = lane % 16, g = lane / 16) holds, for every block (bi, bj), C[16 bi + r][16 bj + 4 g + 0..3]:
   // 8 bytes once converted.  v_permlane16_swap exchanges the odd 16-lane rows of one register with the
@@ -195,7 +199,7 @@ __device__ __forceinline__ void store_wave_tile(const f32x4 (&acc)[TM][TN], uint
 #pragma unroll
       for (int e = 0; e < 4; ++e) c4[e] = (__bf16)acc[bi][0][e];
       const int row = row_base + 16 * bi + er, col = col_base + 4 * eg;
-      if (row < M && col < N) __builtin_nontemporal_store(c4, reinterpret_cast<bf16x4*>(C + (size_t)row * N + col));
+      if (row < M && col < N) store_c<STREAM>(c4, C + (size_t)row * N + col);
       continue;
     }
     u32x4 chunk[TN > 1 ? TN / 2 : 1];
@@ -237,14 +241,28 @@ __device__ __forceinline__ void store_wave_tile(const f32x4 (&acc)[TM][TN], uint
       }
       const int col = ecol + (low ? 0 : 32);
       const int row = row0 + (er & 7);
-      // C is written once and not read again by this kernel: streaming (non-temporal) stores
-      if (row < M && col < N) __builtin_nontemporal_store(s0, reinterpret_cast<u32x4*>(C + (size_t)row * N + col));
-      if (row + 8 < M && col < N) __builtin_nontemporal_store(s1, reinterpret_cast<u32x4*>(C + (size_t)(row + 8) * N + col));
+      if (row < M && col < N) store_c<STREAM>(s0, C + (size_t)row * N + col);
+      if (row + 8 < M && col < N) store_c<STREAM>(s1, C + (size_t)(row + 8) * N + col);
     } else {
       const int row = row0 + er;
-      if (row < M && ecol < N) __builtin_nontemporal_store(chunk[0], reinterpret_cast<u32x4*>(C + (size_t)row * N + ecol));
+      if (row < M && ecol < N) store_c<STREAM>(chunk[0], C + (size_t)row * N + ecol);
     }
   }
+}
+
+// The TM x TN blocks of 16 x 16 a wave has accumulated -> bf16 (nearest even) -> C, first row row_base, first
+// column col_base; rows >= M and columns >= N are left out.
+// C is written once and not read again by this kernel: streaming (non-temporal) stores where rows of C start on whole or
+// half 128-byte lines (8192 x 8192 x 256: 55 us against 67 with ordinary ones, 12000 x 12000 x 1024: 255 against 259),
+// ordinary ones elsewhere, so that the parts of a half line meet in the L2 (9978 x 13976 x 320: 139 us against
+// 156 with streaming ones, 10000 x 7000 x 4096: 424 against 432).
+template <int TM, int TN>
+__device__ __forceinline__ void store_wave_tile(const f32x4 (&acc)[TM][TN], uint16_t* __restrict__ C, int M, int N,
+                                                int row_base, int col_base, int lane) {
+  if ((((uint32_t)N * 2u) | (uint32_t)reinterpret_cast<uintptr_t>(C)) & 63u)                  // uniform
+    store_wave_tile_as<false, TM, TN>(acc, C, M, N, row_base, col_base, lane);
+  else
+    store_wave_tile_as<true, TM, TN>(acc, C, M, N, row_base, col_base, lane);
 }
 
 // What the timing instantiation of the kernel records per workgroup (64-bit words): the shader clock
