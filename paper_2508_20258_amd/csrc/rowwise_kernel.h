@@ -30,7 +30,7 @@
 //     softmax 64 x 1048576    300 -> 70      softmax 1 x 1048576   220 -> 9       softmax 16 x 131072       29 -> 9
 //
 // All arithmetic is fp32 on values widened exactly from bf16; results are rounded once to bf16 (nearest even).  How a row is
-// accumulated follows from N alone: the bits depend neither on the mode nor on `chunks` nor on M.
+// accumulated follows from N alone (softmax: and from whether M reaches 2^22): the bits depend neither on the mode nor on `chunks`.
 #pragma once
 
 #include <float.h>

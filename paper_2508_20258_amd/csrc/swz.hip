@@ -546,12 +546,19 @@ int swz_softmax(const void* in, void* out, int64_t M, int64_t N, int chunks, int
                 hipStream_t stream) {
   if (in == nullptr || out == nullptr) return SWZ_ERR_INVALID_ARG;
   RowPlan plan;
-  const int st = resolve_rows(M, N, chunks, mode, params, kSoftmaxShapes, &plan);
+  // A launch has fewer than 2^32 threads: matrices of more rows than 1024 threads each allow take at most 256 a row (rows of
+  // more than 16384 elements, which the other table gives more, do not come in such numbers: 2^22 of them are 137 GB).
+  const bool few_threads = M >= (int64_t)1 << 22;
+  const int st = resolve_rows(M, N, chunks, mode, params, few_threads ? kLayernormShapes : kSoftmaxShapes, &plan);
   if (st != SWZ_OK) return st;
   if ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) return SWZ_ERR_UNSUPPORTED;
   auto* x = static_cast<const uint16_t*>(in);
   auto* y = static_cast<uint16_t*>(out);
-  SWZ_LAUNCH_ROWS(swz::softmax_rows_kernel, kSoftmaxShapes, x, y, (int)M, (int)N, plan.num_xcd, plan.group_m, mode)
+  if (few_threads) {
+    SWZ_LAUNCH_ROWS(swz::softmax_rows_kernel, kLayernormShapes, x, y, (int)M, (int)N, plan.num_xcd, plan.group_m, mode)
+  } else {
+    SWZ_LAUNCH_ROWS(swz::softmax_rows_kernel, kSoftmaxShapes, x, y, (int)M, (int)N, plan.num_xcd, plan.group_m, mode)
+  }
   return launch_long_rows<true>(x, nullptr, nullptr, y, (int)M, (int)N, 0.f, plan, mode, stream);
 }
 
