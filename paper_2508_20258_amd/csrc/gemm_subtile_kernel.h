@@ -3,19 +3,21 @@
 // of v_mfma_f32_16x16x32_bf16 per element, k ascending), hence the same bits; what differs is how much of C a
 // workgroup owns and how the K loop is fed.
 //
-// What bounds these products is latency, not a rate: a 256 x 256 or 128 x 128 tile leaves 64 to 250 of 256 CUs
-// without work, and with three K steps of look-ahead (0.3 us) a tile that has its CU to itself waits for most
-// of its operands.  Hence
-//   * sub-tiles: workgroups of 32x32 to 128x128 elements of C, in a raster as fine as they are;
-//   * a ring of 5 to 8 stages, 64 of K each, fetched global -> LDS four to seven stages ahead;
+// Whole tiles are bound by latency here: a 256 x 256 or 128 x 128 tile leaves 64 to 250 of 256 CUs without work, and with
+// three K steps of look-ahead (0.3 us) a tile that has its CU to itself waits for most of its operands.  Hence
+//   * sub-tiles: workgroups of 32x32 to 128x256 elements of C, in a raster as fine as they are;
+//   * a ring of 3 to 8 stages, 64 of K each, fetched global -> LDS as far ahead as the LDS allows (12 and 16 stages of the
+//     small shapes were no faster than 6 and 8, which leave room for a second workgroup on the CU);
 //   * one barrier per stage, and two sets of fragments: the reads of one half of a stage (32 of K) are issued
 //     between the MFMAs of the other half, the barrier falls between the two.  Measured against reading a whole
 //     stage, then multiplying it: 128x128 at 2048^3 21.7 -> 18.8 us, 64x64 at 1024^3 6.3 -> 6.2 us;
 //   * every slot address a compile-time constant (the loop is unrolled over the ring, base pointers advance by additions):
 //     with slots computed at run time the scalar instructions of a stage alone took 200 ns, a third more than the whole of a
 //     32x32 stage now (512^3 4.6 -> 3.9 us, 8x4096x4096 17.4 -> 11.9 us).
-// Measured (kernel time, operands not in cache; 128x128 or 128x256 tiles of gemm_kernel.h -> sub-tiles, the shape the rule
-// in swz.hip takes):
+// What bounds them now is the loads: without MFMAs and fragment reads 32x8192x8192 takes as long (40 us; without the loads 13),
+// 1024x1024x4096 in 64x64 sub-tiles 15.0 of 16.1 us (without the loads 10.2).  A full chip moves 22 TB/s from the L2s to LDS.
+// Measured (kernel time, operands not in cache; 128x128, 128x256 or 256x256 tiles of gemm_kernel.h -> sub-tiles, the
+// shape the rule in swz.hip takes):
 //   512^3            8.1 ->  4.0 us (32x32)      1024^3          12.6 ->  6.2 us (64x64)
 //   1536^3          17.0 -> 13.2 us (128x128)    2048^3          21.9 -> 19.0 us (128x128)
 //   8x4096x4096     32.2 -> 11.9 us (32x32)      32x8192x8192    66.5 -> 40.4 us (32x32; reading B takes 22 at 6.3 TB/s)
