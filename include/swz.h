@@ -183,8 +183,9 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
  * workgroups a row may be spread over; the library cuts a row only where that is faster: rows of up to 98304 elements are
  * held and written by one workgroup (short ones by 16 to 64 lanes, several rows a workgroup) whatever `chunks` says, longer
  * ones are cut into column chunks of at most 2048 16-byte vectors, in two launches (statistics of every 32768 elements,
- * then the chunks).  Hardware workgroup ids are decoded as swz_pid_map does: the grid is (groups of consecutive rows) x 1, or
- * M x pieces of a row (`mode`, params->group_m, params->num_xcd; other fields ignored).
+ * then the chunks).  The workgroups of long rows are decoded as swz_pid_map does for the grid M x pieces of a row (`mode`,
+ * params->group_m, params->num_xcd; other fields ignored); rows held whole share nothing, and the library takes them in the
+ * order it found faster.
  *   in, out : caller-owned DEVICE pointers, 16-byte aligned, must not overlap.  -inf entries are
  *             allowed (they get probability 0); a row of only -inf gives NaN.
  *   fp32 arithmetic, one rounding to bfloat16 (nearest even); the result bits depend neither on `mode` nor on `chunks`.

@@ -7,7 +7,7 @@
 //
 //   Rows of up to 98304 elements.  TPR threads hold a row in KEEP 16-byte vectors each, in registers: 16 to 64 lanes of a
 //   wave for short rows (up to 16 rows per 256-thread workgroup, no LDS, no barrier), a workgroup of 256, 512 or 1024
-//   threads for longer ones.  The grid is one-dimensional over groups of consecutive rows.
+//   threads for longer ones.  The grid is one-dimensional over groups of consecutive rows, taken in dispatch order.
 //   Longer rows.  A row is cut into segments of 32768 elements; row_stats_kernel computes the statistics of one segment
 //   per workgroup, row_emit_kernel merges them and produces one column chunk per workgroup, reading x a second
 //   time.  Between the launches a segment's statistics (8 bytes) wait in `out` itself: every chunk gets its own copy of all of
@@ -25,7 +25,7 @@
 // division); lanes are reduced with DPP and permlane exchanges (a shuffle through LDS takes about 60 ns a step); gamma and
 // beta are requested ahead of the statistics where there are registers for them.  Measured, operands not in cache, online and merging
 // kernels with late gamma and beta -> these (us; copy16_kernel on 128 MiB in and out: 43):
-//     layernorm 8192 x 8192    66 -> 55      softmax 8192 x 8192    55 -> 49      layernorm 32768 x 16384  388 -> 366
+//     layernorm 8192 x 8192    66 -> 50      softmax 8192 x 8192    55 -> 44      layernorm 32768 x 16384  388 -> 368
 //     softmax 32768 x 16384   382 -> 354     softmax 131072 x 128   49 -> 13      layernorm 300 x 2048     4.9 -> 3.5
 //     softmax 64 x 1048576    300 -> 70      softmax 1 x 1048576   220 -> 9       softmax 16 x 131072       29 -> 9
 //
@@ -214,16 +214,22 @@ __device__ __forceinline__ int seg_elems(int s, int N) {
   return left < 0 ? 0 : left < kSegVecs * 8 ? left : kSegVecs * 8;
 }
 
+constexpr int row_block(int tpr) { return tpr < 256 ? 256 : tpr; }
+
 // Which row a workgroup of TPR-thread groups works on: TPR <= 64, groups of lanes; above, the whole workgroup.
-template <int TPR>
+// Rows held whole share nothing, so no mapping helps the L2, and rows that run at the same time are best neighbours in memory: in
+// dispatch order 8192 x 8192 takes 44 us (softmax) and 50 us (layer normalisation), with every XCD on a run of rows of its own
+// 50 and 56; 65536 x 1024 44 and 45 against 48 and 51, 4000 x 30000 84 and 88 against 88 and 92.  The one shape that prefers the
+// runs, softmax with 1024 threads and two vectors each (32768 x 16384: 356 us against 364), is MAPPED.
+template <int TPR, bool MAPPED>
 struct RowJob {
-  static constexpr int THREADS = TPR < 256 ? 256 : TPR;
+  static constexpr int THREADS = row_block(TPR);
   int row, tid;
   bool live;                                   // uniform per group of TPR threads; TPR >= 256: per workgroup
   __device__ __forceinline__ RowJob(int M, int num_xcd, int group_m, int mode) {
     constexpr int ROWS = THREADS / TPR;
-    int group, chunk;
-    swz_decode_tile((int)blockIdx.x, (M + ROWS - 1) / ROWS, 1, num_xcd, group_m, mode, &group, &chunk);
+    int group = (int)blockIdx.x, chunk;
+    if constexpr (MAPPED) swz_decode_tile((int)blockIdx.x, (M + ROWS - 1) / ROWS, 1, num_xcd, group_m, mode, &group, &chunk);
     row = group * ROWS + (int)threadIdx.x / TPR;
     tid = (int)threadIdx.x % TPR;
     live = row < M;
@@ -231,10 +237,10 @@ struct RowJob {
 };
 
 template <int KEEP, int TPR>
-__global__ __launch_bounds__(RowJob<TPR>::THREADS) void softmax_rows_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
+__global__ __launch_bounds__(row_block(TPR)) void softmax_rows_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
                                                                            int M, int N, int num_xcd, int group_m, int mode) {
   __shared__ float slots[2][kMaxWaves];
-  const RowJob<TPR> job(M, num_xcd, group_m, mode);
+  const RowJob<TPR, TPR == 1024 && KEEP == 2> job(M, num_xcd, group_m, mode);
   if (!job.live) return;
   const int nv = N >> 3, tid = job.tid;
   rw_u32x4 held[KEEP];
@@ -272,11 +278,11 @@ __device__ __forceinline__ rw_u32x4 ln_vector(const rw_u32x4& xv, const rw_u32x4
 }
 
 template <int KEEP, int TPR>
-__global__ __launch_bounds__(RowJob<TPR>::THREADS) void layernorm_rows_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma,
+__global__ __launch_bounds__(row_block(TPR)) void layernorm_rows_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma,
                                                                              const uint16_t* __restrict__ beta, uint16_t* __restrict__ out,
                                                                              int M, int N, float eps, int num_xcd, int group_m, int mode) {
   __shared__ float slots[2][kMaxWaves];
-  const RowJob<TPR> job(M, num_xcd, group_m, mode);
+  const RowJob<TPR, false> job(M, num_xcd, group_m, mode);
   if (!job.live) return;
   const int nv = N >> 3, tid = job.tid;
   const rw_u32x4 *gp = reinterpret_cast<const rw_u32x4*>(gamma), *bp = reinterpret_cast<const rw_u32x4*>(beta);
