@@ -187,7 +187,8 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
  * params->group_m, params->num_xcd; other fields ignored); rows held whole share nothing, and the library takes them in the
  * order it found faster.
  *   in, out : caller-owned DEVICE pointers, 16-byte aligned, must not overlap.  -inf entries are
- *             allowed (they get probability 0); a row of only -inf gives NaN.
+ *             allowed (they get probability 0), finite ones may be of any size.  A row of only -inf, and
+ *             one with a NaN or +inf, gives NaN.
  *   fp32 arithmetic, one rounding to bfloat16 (nearest even); the result bits depend neither on `mode` nor on `chunks`.
  *   Between the two launches for long rows `out` holds intermediate values.
  * Asynchronous on `stream`; never allocates or synchronises.

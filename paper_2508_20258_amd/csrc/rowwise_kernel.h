@@ -130,9 +130,24 @@ __device__ __forceinline__ float rw_reduce_group(float x, Op op, float* slots) {
   }
 }
 
-// exp(x - m) is computed as exp2(x * log2(e) - m'), m' = m * log2(e), kept finite for a row or segment of -inf only
-// (all its exponentials are then 0).
-__device__ __forceinline__ float soft_scaled_max(float m) { return fmaxf(m * kLog2e, -FLT_MAX); }
+// exp(x - m), m the largest entry of the row or segment, is computed as exp2(x * scale - shift).  As a rule scale = log2(e) and
+// shift = m * log2(e), rounded: one fused multiply-add, and what the rounding of shift takes from every exponent, at most
+// 2^-4, leaves with the sum.  That rounding grows with |m| (m = 1e10: 2^328, and the sum is inf).  From 2^20 on the
+// bfloat16 numbers next to m are at least 2^12 away, so that only entries equal to m count, and scale = 1, shift = m has
+// them at exactly 0 and the others below every exponent, whatever m (-FLT_MAX, of entries that are all -inf, among them).
+constexpr float kSoftLarge = 1048576.f;
+__device__ __forceinline__ bool soft_large(float m) { return fabsf(m) >= kSoftLarge; }
+struct SoftScale {
+  float scale, shift;
+  __device__ __forceinline__ explicit SoftScale(float m) : scale(soft_large(m) ? 1.f : kLog2e), shift(soft_large(m) ? m : m * kLog2e) {}
+};
+
+// What the exponentials of a segment of maximum ms, summed against its own SoftScale, are worth in a row of maximum m >= ms.  Where m
+// is small and ms is not, the segment is 2^12 or more below m; its shift, kept from being fused into the difference
+// by the fmaxf, is then beside the point.
+__device__ __forceinline__ float soft_weight(float ms, float m) {
+  return rw_exp2(soft_large(m) ? ms - m : fmaxf(ms * kLog2e, -FLT_MAX) - SoftScale(m).shift);
+}
 
 // Of KEEP vectors a thread holds: maximum, sum of exponentials, sum, sum of squared deviations.
 template <int KEEP>
@@ -147,19 +162,19 @@ __device__ __forceinline__ float held_max(const rw_u32x4* held) {
   return m;
 }
 
-__device__ __forceinline__ void soft_exps(const rw_u32x4& v, float scaled_max, float (&p)[8]) {
+__device__ __forceinline__ void soft_exps(const rw_u32x4& v, const SoftScale& base, float (&p)[8]) {
   rw_unpack(v, p);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) p[e] = rw_exp2(__builtin_fmaf(p[e], kLog2e, -scaled_max));
+  for (int e = 0; e < 8; ++e) p[e] = rw_exp2(__builtin_fmaf(p[e], base.scale, -base.shift));
 }
 
 template <int KEEP>
-__device__ __forceinline__ float held_exp_sum(const rw_u32x4* held, float scaled_max) {
+__device__ __forceinline__ float held_exp_sum(const rw_u32x4* held, const SoftScale& base) {
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < KEEP; ++i) {
     float p[8];
-    soft_exps(held[i], scaled_max, p);
+    soft_exps(held[i], base, p);
     s += rw_sum8(p);
   }
   return s;
@@ -245,13 +260,13 @@ __global__ __launch_bounds__(row_block(TPR)) void softmax_rows_kernel(const uint
   const int nv = N >> 3, tid = job.tid;
   rw_u32x4 held[KEEP];
   load_vectors<KEEP>(reinterpret_cast<const rw_u32x4*>(in + (size_t)job.row * N), tid, TPR, nv, held);
-  const float ms = soft_scaled_max(rw_reduce_group<TPR>(held_max<KEEP>(held), RwMax{}, slots[0]));
+  const SoftScale base(rw_reduce_group<TPR>(held_max<KEEP>(held), RwMax{}, slots[0]));
   constexpr bool KEEP_EXPS = KEEP <= 8;                          // the exponentials stay in registers where there is room
   float p[KEEP_EXPS ? KEEP : 1][8], s = 0.f;
 #pragma unroll
   for (int i = 0; i < KEEP; ++i) {
     float(&q)[8] = p[KEEP_EXPS ? i : 0];
-    soft_exps(held[i], ms, q);
+    soft_exps(held[i], base, q);
     s += rw_sum8(q);
   }
   const float inv = 1.0f / rw_reduce_group<TPR>(s, RwSum{}, slots[1]);
@@ -260,7 +275,7 @@ __global__ __launch_bounds__(row_block(TPR)) void softmax_rows_kernel(const uint
   for (int i = 0; i < KEEP; ++i)
     if (tid + i * TPR < nv) {
       float(&q)[8] = p[KEEP_EXPS ? i : 0];
-      if constexpr (!KEEP_EXPS) soft_exps(held[i], ms, q);
+      if constexpr (!KEEP_EXPS) soft_exps(held[i], base, q);
 #pragma unroll
       for (int e = 0; e < 8; ++e) q[e] *= inv;
       __builtin_nontemporal_store(rw_pack(q), outp + tid + i * TPR);
@@ -328,7 +343,7 @@ __global__ __launch_bounds__(kSegThreads) void row_stats_kernel(const uint16_t* 
   float a, b;
   if constexpr (SOFTMAX) {
     a = rw_reduce_group<kSegThreads>(held_max<kSegKeep>(held), RwMax{}, slots[0]);
-    b = rw_reduce_group<kSegThreads>(held_exp_sum<kSegKeep>(held, soft_scaled_max(a)), RwSum{}, slots[1]);
+    b = rw_reduce_group<kSegThreads>(held_exp_sum<kSegKeep>(held, SoftScale(a)), RwSum{}, slots[1]);
   } else {
     a = rw_reduce_group<kSegThreads>(held_sum<kSegKeep>(held, first, kSegThreads, nv), RwSum{}, slots[0]) / (float)seg_elems(seg, N);
     b = rw_reduce_group<kSegThreads>(held_dev<kSegKeep>(held, first, kSegThreads, nv, a), RwSum{}, slots[1]);
@@ -384,7 +399,7 @@ __global__ __launch_bounds__(kEmitThreads) void row_emit_kernel(const uint16_t* 
     for (int i = 0; i < PER; ++i) a = fmaxf(a, sa[i]);
     a = rw_reduce_group<kEmitThreads>(a, RwMax{}, slots[0]);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) b += sb[i] * rw_exp2(soft_scaled_max(sa[i]) - soft_scaled_max(a));
+    for (int i = 0; i < PER; ++i) b += sb[i] * soft_weight(sa[i], a);
   } else {
     auto count = [&](int i) __attribute__((always_inline)) { return seg_elems((int)threadIdx.x + i * kEmitThreads, N); };
     a = 0.f;
@@ -396,14 +411,14 @@ __global__ __launch_bounds__(kEmitThreads) void row_emit_kernel(const uint16_t* 
   }
   b = rw_reduce_group<kEmitThreads>(b, RwSum{}, slots[1]);
   const float scale = SOFTMAX ? 1.0f / b : 1.0f / sqrtf(b / (float)N + eps);
-  const float scaled_max = soft_scaled_max(a);
+  const SoftScale base(a);
 #pragma unroll
   for (int i = 0; i < kEmitKeep; ++i) {
     const int v = first + i * kEmitThreads;
     if (v < v1) {
       if constexpr (SOFTMAX) {
         float y[8];
-        soft_exps(held[i], scaled_max, y);
+        soft_exps(held[i], base, y);
 #pragma unroll
         for (int e = 0; e < 8; ++e) y[e] *= scale;
         __builtin_nontemporal_store(rw_pack(y), outp + v);

@@ -187,7 +187,36 @@ def test_softmax_of_infinities_nan_and_extreme_rows(swz, N):
     x[0] = float("-inf")                            # no finite entry: NaN
     x[1, N // 2] = float("nan")
     x[2, N - 1] = float("inf")
-    x[3] = -3.0e38                                  # equal entries whose scaled value overflows
+    x[3] = -3.0e38                                  # equal finite entries, however large: 1 / N
     y = swz.softmax(x).float()
-    assert torch.isnan(y[:4]).all()
+    assert torch.isnan(y[:3]).all()
+    assert (y[3] == torch.tensor(1.0 / N, dtype=torch.float64).to(torch.bfloat16).item()).all()
     assert abs(y[4].double().sum().item() - 1.0) < 4e-3     # the row between them is untouched: half an ulp a value
+
+
+# One N per way a row is held: 16, 32, 64 lanes, a workgroup with one and with several vectors a thread, two launches
+FORMS = [64, 200, 1000, 1800, 5000, 12304, 40000, 98312, 200000]
+
+
+@pytest.mark.parametrize("N", FORMS)
+def test_softmax_of_rows_of_large_magnitude(swz, N):
+    # exp(x - max) of the largest entry is 1 whatever its size; 2^20 and 255 * 2^12 are neighbours among bfloat16 numbers
+    top = float(2 ** 20)
+    flat = [3e9, -1e10, 1e30, -1e30, 3e38, -3e38, float(torch.finfo(torch.bfloat16).min), top, -top, 1e6, -1e6, 12345.0]
+    rows = torch.empty((len(flat) + 6, N))
+    for i, v in enumerate(flat):
+        rows[i] = v                                         # equal entries: 1 / N
+    g = torch.Generator().manual_seed(N)
+    rows[len(flat):] = torch.randn((6, N), generator=g) * 3
+    rows[-6, N // 3] = 1e10                                 # one entry, and one of two, far above the others
+    rows[-5, N // 5], rows[-5, N - 1] = 1e30, 1e30
+    rows[-4, : N // 2] = -1e30                              # masks of large finite values
+    rows[-3, 1:] = float(torch.finfo(torch.bfloat16).min)
+    rows[-2, : N // 2], rows[-2, N // 2:] = top, top - 4096
+    rows[-1, : N // 2], rows[-1, N // 2:] = -top, 4096 - top
+    x = rows.to(torch.bfloat16)
+    got = run_all_modes(lambda out, mode: swz.softmax(x.cuda(), out, chunks=min(3, N // 8), mode=mode), x.shape[0], N)
+    ref = rw.softmax(to_bits(x))
+    err = np.abs(si.bf16_bits_to_f64(got) - ref)
+    bad = ~(err <= rw.softmax_bound(ref)).all(axis=1)
+    assert not bad.any(), f"rows {np.nonzero(bad)[0].tolist()} of N = {N}"
