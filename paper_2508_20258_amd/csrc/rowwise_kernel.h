@@ -402,10 +402,12 @@ __global__ __launch_bounds__(kEmitThreads) void row_emit_kernel(const uint16_t* 
     for (int i = 0; i < PER; ++i) b += sb[i] * soft_weight(sa[i], a);
   } else {
     auto count = [&](int i) __attribute__((always_inline)) { return seg_elems((int)threadIdx.x + i * kEmitThreads, N); };
+    // around the first segment's mean, so that equal means give that mean: the weights count / N are rounded and need not sum to 1
+    const float pivot = __uint_as_float(stats[0][0]);
     a = 0.f;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) a += sa[i] * ((float)count(i) / (float)N);
-    a = rw_reduce_group<kEmitThreads>(a, RwSum{}, slots[0]);
+    for (int i = 0; i < PER; ++i) a += (sa[i] - pivot) * ((float)count(i) / (float)N);
+    a = pivot + rw_reduce_group<kEmitThreads>(a, RwSum{}, slots[0]);
 #pragma unroll
     for (int i = 0; i < PER; ++i) b += sb[i] + (sa[i] - a) * (sa[i] - a) * (float)count(i);
   }

@@ -220,3 +220,16 @@ def test_softmax_of_rows_of_large_magnitude(swz, N):
     err = np.abs(si.bf16_bits_to_f64(got) - ref)
     bad = ~(err <= rw.softmax_bound(ref)).all(axis=1)
     assert not bad.any(), f"rows {np.nonzero(bad)[0].tolist()} of N = {N}"
+
+
+@pytest.mark.parametrize("N", FORMS + [16384, 65544, 98304, 131080, 250000, 500000, 1000000, 3145736])
+def test_layernorm_of_constant_rows_is_beta(swz, N):
+    # a sum of N equal bfloat16 numbers is exact (N is a multiple of 8 of at most 14 more bits, or cut into segments that are),
+    # so the mean is the number itself, the deviations are 0 and not one ulp of the mean times 1 / sqrt(eps)
+    values = [3.0, -0.37109375, 100.0, 1000.0, -10048.0, 1e6, 3e9, -1e15]
+    x = torch.tensor(values).to(torch.bfloat16)[:, None].expand(-1, N).contiguous().cuda()
+    g = torch.randn(N, device="cuda").to(torch.bfloat16)
+    b = torch.randn(N, device="cuda").to(torch.bfloat16)
+    y = swz.layernorm(x, g, b)
+    torch.cuda.synchronize()
+    assert torch.equal(y, b.expand_as(y))
