@@ -180,6 +180,11 @@ __device__ __forceinline__ float held_exp_sum(const rw_u32x4* held, const SoftSc
   return s;
 }
 
+// Sums of a row are kept in units of 2^17, more than its 98304 elements: a sum of eight that fp32 holds then never grows out of
+// it, and powers of two leave every rounding where it was.
+constexpr float kSumUnit = 131072.f;
+__device__ __forceinline__ float mean_of(float sum, int n) { return sum / ((float)n * (1.f / kSumUnit)); }
+
 // vectors first, first + stride, ... below nv are real, the others hold -inf
 template <int KEEP>
 __device__ __forceinline__ float held_sum(const rw_u32x4* held, int first, int stride, int nv) {
@@ -189,7 +194,7 @@ __device__ __forceinline__ float held_sum(const rw_u32x4* held, int first, int s
     if (first + i * stride < nv) {
       float x[8];
       rw_unpack(held[i], x);
-      s += rw_sum8(x);
+      s = __builtin_fmaf(rw_sum8(x), 1.f / kSumUnit, s);
     }
   return s;
 }
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(row_block(TPR)) void layernorm_rows_kernel(const ui
         bv[i] = bp[tid + i * TPR];
       }
   }
-  const float mean = rw_reduce_group<TPR>(held_sum<KEEP>(held, tid, TPR, nv), RwSum{}, slots[0]) / (float)N;
+  const float mean = mean_of(rw_reduce_group<TPR>(held_sum<KEEP>(held, tid, TPR, nv), RwSum{}, slots[0]), N);
   const float dev = rw_reduce_group<TPR>(held_dev<KEEP>(held, tid, TPR, nv, mean), RwSum{}, slots[1]);
   const float rstd = 1.0f / sqrtf(dev / (float)N + eps);
   rw_u32x4* outp = reinterpret_cast<rw_u32x4*>(out + (size_t)job.row * N);
@@ -345,7 +350,7 @@ __global__ __launch_bounds__(kSegThreads) void row_stats_kernel(const uint16_t* 
     a = rw_reduce_group<kSegThreads>(held_max<kSegKeep>(held), RwMax{}, slots[0]);
     b = rw_reduce_group<kSegThreads>(held_exp_sum<kSegKeep>(held, SoftScale(a)), RwSum{}, slots[1]);
   } else {
-    a = rw_reduce_group<kSegThreads>(held_sum<kSegKeep>(held, first, kSegThreads, nv), RwSum{}, slots[0]) / (float)seg_elems(seg, N);
+    a = mean_of(rw_reduce_group<kSegThreads>(held_sum<kSegKeep>(held, first, kSegThreads, nv), RwSum{}, slots[0]), seg_elems(seg, N));
     b = rw_reduce_group<kSegThreads>(held_dev<kSegKeep>(held, first, kSegThreads, nv, a), RwSum{}, slots[1]);
   }
   for (int c = (int)threadIdx.x; c < chunks; c += kSegThreads) {
@@ -406,10 +411,10 @@ __global__ __launch_bounds__(kEmitThreads) void row_emit_kernel(const uint16_t* 
     const float pivot = __uint_as_float(stats[0][0]);
     a = 0.f;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) a += (sa[i] - pivot) * ((float)count(i) / (float)N);
+    for (int i = 0; i < PER; ++i) a += count(i) > 0 ? (sa[i] - pivot) * ((float)count(i) / (float)N) : 0.f;
     a = pivot + rw_reduce_group<kEmitThreads>(a, RwSum{}, slots[0]);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) b += sb[i] + (sa[i] - a) * (sa[i] - a) * (float)count(i);
+    for (int i = 0; i < PER; ++i) b += count(i) > 0 ? sb[i] + (sa[i] - a) * (sa[i] - a) * (float)count(i) : 0.f;
   }
   b = rw_reduce_group<kEmitThreads>(b, RwSum{}, slots[1]);
   const float scale = SOFTMAX ? 1.0f / b : 1.0f / sqrtf(b / (float)N + eps);

@@ -233,3 +233,18 @@ def test_layernorm_of_constant_rows_is_beta(swz, N):
     y = swz.layernorm(x, g, b)
     torch.cuda.synchronize()
     assert torch.equal(y, b.expand_as(y))
+
+
+@pytest.mark.parametrize("N", FORMS)
+def test_layernorm_of_rows_whose_sum_is_beyond_fp32(swz, N):
+    # eight entries still have a sum in fp32, the row has not; y = beta where they are equal
+    values = torch.tensor([1e35, -1e37, 4e37, -4e37]).to(torch.bfloat16)
+    x = values[:, None].expand(-1, N).contiguous().cuda()
+    g = torch.randn(N, device="cuda").to(torch.bfloat16)
+    b = torch.randn(N, device="cuda").to(torch.bfloat16)
+    y = swz.layernorm(x, g, b)
+    x[0] = (1e35 * (1 + torch.rand(N, device="cuda"))).to(torch.bfloat16)       # squared deviations beyond fp32 too
+    z = swz.layernorm(x, g, b)
+    torch.cuda.synchronize()
+    assert torch.equal(y, b.expand_as(y))
+    assert torch.isfinite(z).all()
