@@ -28,7 +28,7 @@ typedef enum {
   SWZ_OK = 0,
   SWZ_ERR_INVALID_ARG = -1, /* null pointer, non-positive size, unknown mode                */
   SWZ_ERR_UNSUPPORTED = -2, /* valid request the library cannot serve (dtype, alignment, tile) */
-  SWZ_ERR_OVERFLOW = -3,    /* a count does not fit the 32-bit index arithmetic              */
+  SWZ_ERR_OVERFLOW = -3,    /* a count does not fit the 32-bit index arithmetic, or a launch would have 2^32 threads or more */
   SWZ_ERR_HIP = -4          /* the HIP runtime reported an error (launch, attribute query)   */
 } swz_status;
 
@@ -173,7 +173,7 @@ int swz_gemm_plan(int64_t M, int64_t N, int64_t K, const swz_params* params, swz
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null, M/N < 1, unknown mode), UNSUPPORTED (elem_bytes not 2 or 4, tile not 32/64/128
  * (not 64 for 4-byte elements), M or N not a multiple of 8 (4 for 4-byte elements), misaligned pointer),
- * OVERFLOW, HIP. */
+ * OVERFLOW (2^24 tiles or more), HIP. */
 int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_bytes, int tile, int mode,
                   const swz_params* params, hipStream_t stream);
 
@@ -190,7 +190,8 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
  *             allowed (they get probability 0), finite ones may be of any size.  A row of only -inf, and
  *             one with a NaN or +inf, gives NaN.
  *   fp32 arithmetic, one rounding to bfloat16 (nearest even); the result bits depend neither on `mode` nor on `chunks`.
- *   Between the two launches for long rows `out` holds intermediate values.
+ *   Between the two launches for long rows `out` holds intermediate values.  A launch has fewer than 2^32 threads: rows beyond
+ *   that (2^24 rows of 1800 elements or 2^28 of 8, for instance) go in further launches.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null, M/N/chunks < 1, chunks > N/8, unknown mode), UNSUPPORTED (N not a
  * multiple of 8 or above 2^24, misaligned pointer), OVERFLOW (M*chunks or a dimension >= 2^31), HIP. */

@@ -71,6 +71,10 @@ int query_device(DeviceFacts* out) {
   return SWZ_OK;
 }
 
+// A launch has fewer than 2^32 threads: the grid is handed to the device in threads, as a 32-bit number, and a larger one
+// comes back as "ok" with only the remainder modulo 2^32 run (2^24 + 1 workgroups of 256: one of them).
+constexpr int64_t kLaunchThreads = ((int64_t)1 << 32) - 1;
+
 // Launch through the call that returns the launch's own status: hipGetLastError() after a launch
 // would also report (and clear) an error some earlier, unrelated HIP call left behind.
 template <class... KArgs, size_t... Is>
@@ -83,6 +87,7 @@ int launch_impl(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hip
 template <class... KArgs, class... Args>
 int launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, Args... args) {
   static_assert(sizeof...(KArgs) == sizeof...(Args), "argument count");
+  if ((int64_t)grid.x * block.x > kLaunchThreads) return SWZ_ERR_OVERFLOW;
   std::tuple<KArgs...> vals{static_cast<KArgs>(args)...};
   return launch_impl(kernel, grid, block, lds, stream, vals, std::index_sequence_for<KArgs...>{});
 }
@@ -380,18 +385,47 @@ int resolve_rows(int64_t M, int64_t N, int chunks, int mode, const swz_params* p
     plan->shape = -1;
     plan->segs = (int)((nv + swz::kSegVecs - 1) / swz::kSegVecs);
     plan->chunks = (int)((nv + swz::kEmitThreads * swz::kEmitKeep - 1) / (swz::kEmitThreads * swz::kEmitKeep));
-  } else if (shapes[plan->shape].tpr < 256) {
-    const int rows_per_wg = 256 / shapes[plan->shape].tpr;
+  } else {
+    const int rows_per_wg = swz::row_block(shapes[plan->shape].tpr) / shapes[plan->shape].tpr;
     plan->grid_m = (int)((M + rows_per_wg - 1) / rows_per_wg);
   }
   return check_map_args(plan->grid_m, plan->chunks, plan->num_xcd, &plan->group_m, mode);
 }
 
-// KERNEL<KEEP, TPR> of the chosen shape.
-#define SWZ_ROWS_CASE(S, KERNEL, SHAPES, ...)                                                                        \
-  case S:                                                                                                            \
-    return launch(KERNEL<SHAPES[S].keep, SHAPES[S].tpr>, dim3((unsigned)plan.grid_m),                                \
-                  dim3((unsigned)(SHAPES[S].tpr < 256 ? 256 : SHAPES[S].tpr)), 0, stream, __VA_ARGS__);
+// launch(first row, rows, workgroups) over all rows: once, or in as few parts as a launch's threads allow.
+template <class F>
+int for_row_parts(const RowPlan& plan, int tpr, int64_t M, F&& launch_part) {
+  const int block = swz::row_block(tpr), rows_per_wg = block / tpr;
+  const int64_t part = kLaunchThreads / block;
+  for (int64_t g = 0; g < plan.grid_m; g += part) {
+    const int64_t groups = plan.grid_m - g < part ? plan.grid_m - g : part, row = g * rows_per_wg;
+    const int st = launch_part(row, (int)(M - row < groups * rows_per_wg ? M - row : groups * rows_per_wg), (int)groups);
+    if (st != SWZ_OK) return st;
+  }
+  return SWZ_OK;
+}
+
+template <int KEEP, int TPR>
+int launch_softmax_rows(const uint16_t* in, uint16_t* out, int64_t M, int N, const RowPlan& plan, int mode, hipStream_t stream) {
+  return for_row_parts(plan, TPR, M, [&](int64_t row, int rows, int groups) {
+    const int group_m = plan.group_m < groups ? plan.group_m : groups;
+    return launch(swz::softmax_rows_kernel<KEEP, TPR>, dim3((unsigned)groups), dim3(swz::row_block(TPR)), 0, stream, in + row * N,
+                  out + row * N, rows, N, plan.num_xcd, group_m, mode);
+  });
+}
+
+template <int KEEP, int TPR>
+int launch_layernorm_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* beta, uint16_t* out, int64_t M, int N, float eps,
+                          const RowPlan& plan, hipStream_t stream) {
+  return for_row_parts(plan, TPR, M, [&](int64_t row, int rows, int groups) {
+    return launch(swz::layernorm_rows_kernel<KEEP, TPR>, dim3((unsigned)groups), dim3(swz::row_block(TPR)), 0, stream, in + row * N,
+                  gamma, beta, out + row * N, rows, N, eps);
+  });
+}
+
+// FN<KEEP, TPR> of the chosen shape.
+#define SWZ_ROWS_CASE(S, FN, SHAPES, ...) \
+  case S: return FN<SHAPES[S].keep, SHAPES[S].tpr>(__VA_ARGS__);
 #define SWZ_ROWS_CASES(A, B, C, D, ...) \
   SWZ_ROWS_CASE(A, __VA_ARGS__) SWZ_ROWS_CASE(B, __VA_ARGS__) SWZ_ROWS_CASE(C, __VA_ARGS__) SWZ_ROWS_CASE(D, __VA_ARGS__)
 #define SWZ_LAUNCH_ROWS(...)                                                                                                 \
@@ -546,19 +580,12 @@ int swz_softmax(const void* in, void* out, int64_t M, int64_t N, int chunks, int
                 hipStream_t stream) {
   if (in == nullptr || out == nullptr) return SWZ_ERR_INVALID_ARG;
   RowPlan plan;
-  // A launch has fewer than 2^32 threads: matrices of more rows than 1024 threads each allow take at most 256 a row (rows of
-  // more than 16384 elements, which the other table gives more, do not come in such numbers: 2^22 of them are 137 GB).
-  const bool few_threads = M >= (int64_t)1 << 22;
-  const int st = resolve_rows(M, N, chunks, mode, params, few_threads ? kLayernormShapes : kSoftmaxShapes, &plan);
+  const int st = resolve_rows(M, N, chunks, mode, params, kSoftmaxShapes, &plan);
   if (st != SWZ_OK) return st;
   if ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) return SWZ_ERR_UNSUPPORTED;
   auto* x = static_cast<const uint16_t*>(in);
   auto* y = static_cast<uint16_t*>(out);
-  if (few_threads) {
-    SWZ_LAUNCH_ROWS(swz::softmax_rows_kernel, kLayernormShapes, x, y, (int)M, (int)N, plan.num_xcd, plan.group_m, mode)
-  } else {
-    SWZ_LAUNCH_ROWS(swz::softmax_rows_kernel, kSoftmaxShapes, x, y, (int)M, (int)N, plan.num_xcd, plan.group_m, mode)
-  }
+  SWZ_LAUNCH_ROWS(launch_softmax_rows, kSoftmaxShapes, x, y, M, (int)N, plan, mode, stream)
   return launch_long_rows<true>(x, nullptr, nullptr, y, (int)M, (int)N, 0.f, plan, mode, stream);
 }
 
@@ -575,7 +602,7 @@ int swz_layernorm(const void* in, const void* gamma, const void* beta, void* out
   auto* g = static_cast<const uint16_t*>(gamma);
   auto* b = static_cast<const uint16_t*>(beta);
   auto* y = static_cast<uint16_t*>(out);
-  SWZ_LAUNCH_ROWS(swz::layernorm_rows_kernel, kLayernormShapes, x, g, b, y, (int)M, (int)N, eps, plan.num_xcd, plan.group_m, mode)
+  SWZ_LAUNCH_ROWS(launch_layernorm_rows, kLayernormShapes, x, g, b, y, M, (int)N, eps, plan, stream)
   return launch_long_rows<false>(x, g, b, y, (int)M, (int)N, eps, plan, mode, stream);
 }
 

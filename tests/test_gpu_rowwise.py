@@ -248,3 +248,21 @@ def test_layernorm_of_rows_whose_sum_is_beyond_fp32(swz, N):
     torch.cuda.synchronize()
     assert torch.equal(y, b.expand_as(y))
     assert torch.isfinite(z).all()
+
+
+@pytest.mark.parametrize("op,M,N", [("softmax", (1 << 28) + 5, 8), ("layernorm", (1 << 28) + 5, 8), ("softmax", (1 << 24) + 3, 1800),
+                                    ("layernorm", (1 << 24) + 3, 1800), ("softmax", (1 << 23) + 3, 4104)])
+def test_more_rows_than_a_launch_has_threads_for(swz, op, M, N):
+    # rows x threads a row pass 2^32; every row repeats one of `block`, whose results a small launch gives
+    block = (torch.randn((4096, N), device="cuda") * 2).to(torch.bfloat16)
+    g, b = torch.randn((2, N), device="cuda").to(torch.bfloat16)
+    call = (lambda t: swz.softmax(t)) if op == "softmax" else (lambda t: swz.layernorm(t, g, b))
+    want = call(block)
+    y = call(block.repeat(-(-M // 4096), 1)[:M])
+    whole = y[:M // 4096 * 4096].view(-1, 4096, N)
+    step = max(1, (1 << 31) // (4096 * N))
+    for i in range(0, whole.shape[0], step):
+        assert (whole[i:i + step].view(torch.int16) == want.view(torch.int16)).all(), i
+    assert torch.equal(y[M // 4096 * 4096:], want[:M % 4096])
+    del y, whole
+    torch.cuda.empty_cache()                        # up to 140 GB

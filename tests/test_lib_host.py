@@ -69,6 +69,19 @@ def test_error_paths_leave_output_untouched():
         assert swz.status_string(s) and "unknown" not in swz.status_string(s)
 
 
+def test_launches_of_2_to_the_32_threads_are_refused():
+    # the device takes a grid in threads modulo 2^32: such a launch would run a remainder of it and report success
+    L = swz.lib
+    p = ctypes.byref(swz.SwzParams(0, 0, 0, 0, 8))
+    a, b = 0x1000, 0x2000                  # never dereferenced
+    for gm, gn in [(1 << 13, 1 << 13), (1 << 13, (1 << 13) + 1)]:
+        assert L.swz_pid_map_device(gm, gn, 8, 4, 0, a, None, None) == -3
+    assert L.swz_pid_map_persistent_device(4, 4, 8, 4, 0, (1 << 26) + 1, a, None, None) == -3
+    assert L.swz_transpose(a, b, 8, (1 << 30) + 8, 2, 64, 2, p, None) == -3
+    assert L.swz_transpose(a, b, 1 << 17, 1 << 17, 2, 32, 0, p, None) == -3
+    assert L.swz_transpose(a, b, 4, (1 << 30) + 4, 4, 64, 2, p, None) == -3
+
+
 def test_group_m_larger_than_grid_is_one_band():
     assert swz.pid_map(5, 7, 8, 1 << 30, 3).tolist() == opm.pid_map(5, 7, 8, 5, 3)
 
