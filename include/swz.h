@@ -129,9 +129,9 @@ int swz_pid_map_persistent_device(int grid_m, int grid_n, int num_xcd, int group
  *   most half as many tiles as the device has compute units, 128x256x64, and at most a quarter, 128x128x64
  *   (the chip is then better filled by more and smaller tiles; the result bits do not depend on the tile shape).
  *   Small and narrow products go further: where the library chose the tile it may compute C in sub-tiles of 32x32 to
- *   128x128, one workgroup each, and then applies `mode`, num_xcd and the same band height to the grid of sub-tiles.  The
+ *   128x256, one workgroup each, and then applies `mode`, num_xcd and the same band height to the grid of sub-tiles.  The
  *   left-over tiles of a large grid's last, partial round may be computed by two or four workgroups each, on the XCD the
- *   map gives the tile.  The bits are those of whole tiles.
+ *   map gives the tile unless fewer tiles than XCDs are left.  The bits are those of whole tiles.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null pointer, M/N/K < 1, unknown mode), UNSUPPORTED (other dtype,
  * K or N not a multiple of 8, misaligned pointer), OVERFLOW (tile count >= 2^31 or a
@@ -147,14 +147,24 @@ int swz_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_
 int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int dtype, int mode,
                 const swz_params* params, hipStream_t stream);
 
-/* What swz_gemm_ex would launch for this problem: the resolved parameters and tile grid, i.e. the
- * arguments with which swz_pid_map reproduces the launch's map (the paper validates a remap by
- * its map being a bijection: Results, "broken remappings"); where swz_gemm computes C in sub-tiles, the map of the
- * launch is that of a finer grid.
+/* The plan of swz_gemm_ex for this problem: the resolved parameters and the grid of tiles, which is what
+ * swz_gemm_probe launches, and swz_gemm_ex wherever it computes whole tiles.  Which block of C every workgroup of swz_gemm_ex
+ * computes, sub-tiles and pieces of tiles included, is what swz_gemm_launch_map says.
  * Pure host arithmetic apart from the device query that resolves num_xcd = 0.
  * Any output pointer may be null. */
 int swz_gemm_plan(int64_t M, int64_t N, int64_t K, const swz_params* params, swz_params* resolved,
                   int* grid_m, int* grid_n);
+
+/* The map of the launch swz_gemm_ex makes for this problem (the paper validates a remap by its map being a bijection: Results,
+ * "broken remappings").  Host arithmetic, no launch; the compute units are those of the current device, 256 without one.
+ *   workgroups : receives the number of workgroups of the launch.
+ *   out        : HOST buffer of out_words >= 4 * *workgroups int32, or null for the count alone; workgroup w (hardware id)
+ *                computes rows out[4w] .. + out[4w+2] and columns out[4w+1] .. + out[4w+3] of C, clipped to C, or nothing
+ *                (all four 0: an id that leaves at once).  The blocks cover C once.
+ * Errors: INVALID_ARG (null workgroups, unknown mode, too small a buffer, M/N/K < 1), and as swz_gemm_ex for sizes and
+ * parameters; UNSUPPORTED for the persistent launch (swz_pid_map_persistent). */
+int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_params* params, int32_t* out, int64_t out_words,
+                        int64_t* workgroups);
 
 /* out (N x M) = transpose of in (M x N), elements of 2 or 4 bytes moved verbatim, both row-major and dense
  * (the paper's transpose case study, its largest win from XCD swizzling: Results; Appendix "Case

@@ -24,7 +24,7 @@ MODES.update({name + "_skew": m + MODE_SKEW for name, m in list(MODES.items())})
 DTYPE_BF16 = 0
 
 EXPORTS = ("swz_status_string", "swz_device_info", "swz_pid_map", "swz_pid_map_device", "swz_gemm", "swz_gemm_ex",
-           "swz_gemm_plan", "swz_copy_bytes", "swz_pid_map_persistent", "swz_pid_map_persistent_device", "swz_transpose",
+           "swz_gemm_plan", "swz_gemm_launch_map", "swz_copy_bytes", "swz_pid_map_persistent", "swz_pid_map_persistent_device", "swz_transpose",
            "swz_softmax", "swz_layernorm", "swz_mfma_peak", "swz_gemm_probe")
 
 
@@ -72,6 +72,7 @@ def _load() -> ctypes.CDLL:
     L.swz_gemm.argtypes = [vp, vp, vp, i64, i64, i64, i, i, vp]
     L.swz_gemm_ex.argtypes = [vp, vp, vp, i64, i64, i64, i, i, pp, vp]
     L.swz_gemm_plan.argtypes = [i64, i64, i64, pp, pp, ip, ip]
+    L.swz_gemm_launch_map.argtypes = [i64, i64, i64, i, pp, vp, i64, ctypes.POINTER(i64)]
     L.swz_gemm_probe.argtypes = [vp, vp, vp, i64, i64, i64, i, i, pp, vp, i64, vp]
     L.swz_copy_bytes.argtypes = [vp, vp, i64, vp]
     L.swz_transpose.argtypes = [vp, vp, i64, i64, i, i, i, pp, vp]
@@ -174,6 +175,16 @@ def gemm_plan(M: int, N: int, K: int, **params) -> dict:
                              ctypes.byref(gn)), "swz_gemm_plan")
     return dict(bm=r.bm, bn=r.bn, bk=r.bk, group_m=r.group_m, num_xcd=r.num_xcd, persistent=r.persistent,
                 num_wg=r.num_wg, grid_m=gm.value, grid_n=gn.value)
+
+
+def gemm_launch_map(M: int, N: int, K: int, mode: int = MODE_XCD_GROUPM, **params) -> np.ndarray:
+    """The block of C every workgroup of gemm(...) computes: int32 array of (row, column, rows, columns), in the order of the
+    hardware ids; all 0 for one that leaves at once."""
+    p, n = _params_ref(params), ctypes.c_int64(0)
+    _check(lib.swz_gemm_launch_map(int(M), int(N), int(K), int(mode), p, None, 0, ctypes.byref(n)), "swz_gemm_launch_map")
+    out = np.full((n.value, 4), -1, dtype=np.int32)
+    _check(lib.swz_gemm_launch_map(int(M), int(N), int(K), int(mode), p, out.ctypes.data, out.size, ctypes.byref(n)), "swz_gemm_launch_map")
+    return out
 
 
 def gemm(a, b, c=None, mode: int = MODE_XCD_GROUPM, stream=None, **params):

@@ -17,7 +17,7 @@
 // What bounds them now is the loads: without MFMAs and fragment reads 32x8192x8192 takes as long (40 us; without the loads 13),
 // 1024x1024x4096 in 64x64 sub-tiles 15.0 of 16.1 us (without the loads 10.2).  A full chip moves 22 TB/s from the L2s to LDS.
 // Measured (kernel time, operands not in cache; 128x128, 128x256 or 256x256 tiles of gemm_kernel.h -> sub-tiles, the
-// shape the rule in swz.hip takes):
+// shape the rule in gemm_dispatch.h takes):
 //   512^3            8.1 ->  4.0 us (32x32)      1024^3          12.6 ->  6.2 us (64x64)
 //   1536^3          17.0 -> 13.2 us (128x128)    2048^3          21.9 -> 19.0 us (128x128)
 //   8x4096x4096     32.2 -> 11.9 us (32x32)      32x8192x8192    66.5 -> 40.4 us (32x32; reading B takes 22 at 6.3 TB/s)
@@ -32,12 +32,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_dispatch.h"
 #include "gemm_kernel.h"
 #include "pid_decode.h"
 
 namespace swz {
-
-constexpr int kStageK = 64;    // K extent of a ring stage: two MFMA steps, whole 128-byte lines of A
 
 template <int BM_, int BN_, int WM_, int WN_, int STAGES_>
 struct SubShape {
@@ -262,11 +261,11 @@ __global__ __launch_bounds__(S::NT) void gemm_bf16_subtile_kernel(const uint16_t
 
 // Whole tiles (S) for hardware ids below `whole`, a multiple of the compute units; the tiles of the last, partial round
 // in sub-tiles (P) behind them, so that the round lasts as long as a sub-tile and not as long as a tile.  One launch: the first
-// sub-tiles start where the first whole tiles end.  Hardware ids are dealt round-robin to the XCDs, so the sub-tiles of the
-// tile that the map gives to id v are handed to ids that are v modulo `deal` (the XCD count, or the number of left-over tiles if
-// that is smaller): they run on the XCD the map means and share the tile's operand panels in its L2.  At most half a round of tiles
-// is left over, in halves, or a quarter, in quarters, so no XCD gets more than it has CUs.  Ids past the last tile and
-// sub-tiles outside C leave at once.
+// sub-tiles start where the first whole tiles end.  Which id gets which piece: swz_tail_piece.  From as many left-over tiles as XCDs
+// on, a tile's pieces run on the XCD the map gives the tile and share its operand panels in its L2; fewer tiles are
+// spread (on one XCD each, with ids that leave at once between them: 2 x 131 tiles of K = 4096 120.9 us against 119.8, 7 x 37 114.3
+// against 114.6).  At most half a round of tiles is left over, in halves, or a quarter, in quarters, so no XCD gets more
+// than it has CUs.  Ids past the last tile and sub-tiles outside C leave at once.
 template <class S, class P>
 __global__ __launch_bounds__(S::NT) void gemm_bf16_tail_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                                uint16_t* __restrict__ C, int M, int N, int K, int grid_m, int grid_n,
@@ -280,9 +279,8 @@ __global__ __launch_bounds__(S::NT) void gemm_bf16_tail_kernel(const uint16_t* _
     swz_decode_tile(w, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
     gemm_tile<S>(A, B, C, M, N, K, pm, pn, false, false, 0, 0, smem);
   } else {
-    const int i = (w - whole) / deal, x = (w - whole) - i * deal, turn = i / SUBS, sub = i - turn * SUBS;
-    const int v = whole + turn * deal + x;
-    if (v >= grid_m * grid_n) return;                            // uniform, like the exit below
+    int v, sub;
+    if (!swz_tail_piece(w, whole, deal, SUBS, grid_m * grid_n, &v, &sub)) return;       // uniform, like the exit below
     swz_decode_tile(v, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
     const int m0 = pm * S::BM + (sub % SUB_M) * P::BM, n0 = pn * S::BN + (sub / SUB_M) * P::BN;
     if (m0 >= M || n0 >= N) return;

@@ -94,3 +94,15 @@ SWZ_HD int swz_persistent_logical(int w, int round, int num_wg, int total, int n
   const int64_t l = (int64_t)p + (int64_t)round * num_wg;
   return l < total ? (int)l : -1;
 }
+
+// Launches whose last tiles are computed in `subs` pieces each, by workgroups of their own behind the first `whole` ones (w >= whole):
+// the tile (hardware id v in the map's sense) and the piece that workgroup w computes, or false where it has none.  Ids are
+// handed out `deal` tiles at a time, a piece of each, so that all pieces of a tile sit on ids equal to v - whole modulo `deal`.
+// Where `deal` is the XCD count and divides `whole` they run on the XCD that the map gives the tile; with fewer
+// left-over tiles than XCDs (deal = their number) they spread over the XCDs as they come.  Requires total < 2^31.
+SWZ_HD bool swz_tail_piece(int w, int whole, int deal, int subs, int total, int* v, int* sub) {
+  const int i = (w - whole) / deal, x = (w - whole) - i * deal, turn = i / subs;
+  *sub = i - turn * subs;
+  *v = whole + turn * deal + x;
+  return *v < total;
+}

@@ -12,6 +12,7 @@
 
 #include "../../include/swz.h"
 #include "aux_kernels.h"
+#include "gemm_dispatch.h"
 #include "gemm_kernel.h"
 #include "gemm_subtile_kernel.h"
 #include "mfma_peak_kernel.h"
@@ -23,6 +24,7 @@ namespace {
 
 constexpr int kCusPerXcd = 32;   // gfx950: 8 XCDs x 32 CUs
 constexpr int kMaxDevices = 64;
+constexpr int kWholeCus = 256;   // compute units assumed where no device can be asked (a whole MI355X)
 constexpr int kDefaultBK = 64;  // K panel of a tile step; the kernel moves it as two 32-wide halves (ring of 4)
 
 struct DeviceFacts {
@@ -31,8 +33,7 @@ struct DeviceFacts {
 };
 DeviceFacts g_facts[kMaxDevices];
 std::atomic<bool> g_attr_set[kMaxDevices][4][4][2];
-constexpr int kSubShapes = 7, kTailShapes = 2;
-std::atomic<bool> g_sub_attr_set[kMaxDevices][kSubShapes + kTailShapes];
+std::atomic<bool> g_sub_attr_set[kMaxDevices][2 * swz::kSubTileCount];   // sub-tiles, then pieces of the last round
 std::mutex g_mu;
 
 // SWZ_NUM_XCD in the environment (read once per process): the XCD count to assume instead of the
@@ -155,56 +156,6 @@ int launch_gemm_probe(const void* A, const void* B, void* C, int M, int N, int K
   }
 }
 
-// The sub-tile shapes, and what a stage (64 of K) of one workgroup costs in ns on a chip whose every CU has one
-// (measured: the slope of kernel time over K).  The fixed part of a round (launch or hand-over, the first
-// operands, the stores) is about kRoundNs whatever the shape; a whole tile of gemm_kernel.h takes kWholeRoundNs, as it
-// also runs its look-ahead past the end of K.
-using Sub32x32 = swz::SubShape<32, 32, 2, 2, 8>;
-using Sub32x64 = swz::SubShape<32, 64, 2, 2, 6>;
-using Sub64x64 = swz::SubShape<64, 64, 2, 2, 5>;
-using Sub128x64 = swz::SubShape<128, 64, 4, 2, 6>;
-using Sub64x128 = swz::SubShape<64, 128, 2, 4, 6>;
-using Sub128x128 = swz::SubShape<128, 128, 2, 4, 5>;
-using Sub128x256 = swz::SubShape<128, 256, 2, 4, 3>;
-struct SubCost { int bm, bn, stage_ns; };
-constexpr SubCost kSubCost[kSubShapes] = {{32, 32, 140}, {32, 64, 160}, {64, 64, 195}, {128, 64, 310}, {64, 128, 310}, {128, 128, 520}, {128, 256, 950}};
-constexpr int64_t kRoundNs = 2500, kWholeRoundNs = 4000;
-
-// Which sub-tile shape (index into kSubCost) computes this product fastest, or -1 where the plan's tile as one
-// workgroup does.  The estimate is  rounds x (kRoundNs + stages x cost), rounds = workgroups that touch C over CUs; it
-// orders the shapes as measured on 60 products with M from 1 to 2048.  One 128x128, 128x256 and 256x256 tile of
-// gemm_kernel.h costs 600, 840 and 1350 ns a stage (two 128x128 ones share a CU: 920 the pair; a partial last round of
-// 256x256 tiles costs what launch_tail makes of it).  Ties go to the larger
-// tile: it moves fewer bytes.  A sub-tile has to be 5 % better than the tile, the spread of the estimate near a tie.
-int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, int cus) {
-  const int64_t stages = (K + swz::kStageK - 1) / swz::kStageK;
-  auto rounds = [&](int64_t bm, int64_t bn, int64_t per_round) {
-    return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + per_round - 1) / per_round;
-  };
-  auto estimate = [&](int64_t n, int64_t ns) { return n * (kRoundNs + stages * ns); };
-  auto whole = [&](int64_t n, int64_t ns) { return n * (kWholeRoundNs + stages * ns); };
-  int64_t best;
-  if (r.bm == 128 && r.bn == 128) {
-    best = rounds(128, 128, cus) == 1 ? whole(1, 600) : whole(rounds(128, 128, 2 * cus), 920);
-  } else if (r.bm != r.bn) {
-    best = whole(rounds(r.bm, r.bn, cus), 840);
-  } else {
-    const int64_t tiles = rounds(256, 256, 1), tail = tiles % cus;
-    best = whole(tiles / cus, 1350) + (tail == 0 ? 0 : whole(1, tiles < cus ? 1350 : 4 * tail <= cus ? 520 : 2 * tail <= cus ? 840 : 1350));
-  }
-  best -= best / 20;
-  int choice = -1;
-  for (int s = kSubShapes - 1; s >= 0; --s) {
-    if (kSubCost[s].bm > r.bm || kSubCost[s].bn > r.bn) continue;         // a sub-tile is no larger than the plan's tile
-    const int64_t e = estimate(rounds(kSubCost[s].bm, kSubCost[s].bn, cus), kSubCost[s].stage_ns);
-    if (e < best) {
-      best = e;
-      choice = s;
-    }
-  }
-  return choice;
-}
-
 // Once per kernel and device: a kernel that asks for more LDS than the default has to say so.
 int allow_lds(const void* kernel, int bytes, int slot) {
   int dev = 0;
@@ -218,34 +169,30 @@ int allow_lds(const void* kernel, int bytes, int slot) {
   return SWZ_OK;
 }
 
-template <class S>
-int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, const swz_params& r, int group_m, int mode,
-                   hipStream_t stream, int shape) {
+template <int I>
+using SubOf = swz::SubShape<swz::kSubTiles[I].bm, swz::kSubTiles[I].bn, swz::kSubTiles[I].wm, swz::kSubTiles[I].wn, swz::kSubTiles[I].stages>;
+
+// All of C in sub-tiles of shape I, or only the last, partial round of a grid of 256x256 tiles (pieces).
+template <int I>
+int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, const swz::GemmLaunch& l, int num_xcd, int mode, hipStream_t stream) {
+  using S = SubOf<I>;
   auto kernel = swz::gemm_bf16_subtile_kernel<S>;
-  const int st = allow_lds(reinterpret_cast<const void*>(kernel), S::LDS_BYTES, shape);
+  const int st = allow_lds(reinterpret_cast<const void*>(kernel), S::LDS_BYTES, I);
   if (st != SWZ_OK) return st;
-  const int gm = (M + S::BM - 1) / S::BM, gn = (N + S::BN - 1) / S::BN;
-  const int64_t band = (int64_t)group_m * (r.bm / S::BM);       // rows of sub-tiles as high as a band of tiles
-  return launch(kernel, dim3((unsigned)((int64_t)gm * gn)), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
-                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, gm, gn, r.num_xcd, (int)(band < gm ? band : gm), mode);
+  return launch(kernel, dim3((unsigned)l.blocks), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
+                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, l.grid_m, l.grid_n, num_xcd, l.group_m, mode);
 }
 
-// The last, partial round of a grid of 256x256 tiles in pieces P: `tail` tiles behind `whole` ones.
-using Whole256 = swz::GemmShape<256, 256, 2, 4>;
-using Piece128x128 = Sub128x128;
-using Piece128x256 = Sub128x256;
-template <class P>
-int launch_tail(const void* A, const void* B, void* C, int M, int N, int K, const swz_params& r, int grid_m, int grid_n, int group_m,
-                int mode, int whole, int tail, hipStream_t stream, int slot) {
-  auto kernel = swz::gemm_bf16_tail_kernel<Whole256, P>;
-  const int lds = Whole256::LDS_BYTES > P::LDS_BYTES ? Whole256::LDS_BYTES : P::LDS_BYTES;
-  const int st = allow_lds(reinterpret_cast<const void*>(kernel), lds, kSubShapes + slot);
+template <int I>
+int launch_pieces(const void* A, const void* B, void* C, int M, int N, int K, const swz::GemmLaunch& l, int num_xcd, int mode, hipStream_t stream) {
+  using Whole = swz::GemmShape<256, 256, 2, 4>;
+  using P = SubOf<I>;
+  auto kernel = swz::gemm_bf16_tail_kernel<Whole, P>;
+  const int lds = Whole::LDS_BYTES > P::LDS_BYTES ? Whole::LDS_BYTES : P::LDS_BYTES;
+  const int st = allow_lds(reinterpret_cast<const void*>(kernel), lds, swz::kSubTileCount + I);
   if (st != SWZ_OK) return st;
-  const int deal = r.num_xcd < tail ? r.num_xcd : tail;
-  const int subs = (256 / P::BM) * (256 / P::BN);
-  const int64_t blocks = whole + ((int64_t)tail + deal - 1) / deal * deal * subs;
-  return launch(kernel, dim3((unsigned)blocks), dim3(Whole256::NT), lds, stream, static_cast<const uint16_t*>(A),
-                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, grid_m, grid_n, r.num_xcd, group_m, mode, whole, deal);
+  return launch(kernel, dim3((unsigned)l.blocks), dim3(Whole::NT), lds, stream, static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B),
+                static_cast<uint16_t*>(C), M, N, K, l.grid_m, l.grid_n, num_xcd, l.group_m, mode, l.whole, l.deal);
 }
 
 int resolve_plan(int64_t M, int64_t N, int64_t K, const swz_params* p, swz_params* r, int* grid_m, int* grid_n) {
@@ -263,7 +210,7 @@ int resolve_plan(int64_t M, int64_t N, int64_t K, const swz_params* p, swz_param
     // faster; between a quarter and a half, 128x256 tiles are 1.25-1.3x faster (and 3-14 % ahead of 128x128);
     // above a half, 256x256 tiles win by 1.2-1.3x.  The device is only asked where its CU count decides.
     const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
-    int cus = 256;                                  // assumed where no device can be asked (a whole MI355X)
+    int cus = kWholeCus;
     if (t256 > 8 && t256 <= 152) {
       DeviceFacts f;
       if (query_device(&f) == SWZ_OK && f.cus > 0) cus = f.cus;
@@ -637,20 +584,51 @@ using Shape256 = swz::GemmShape<256, 256, 2, 4>;
 using Shape128x256 = swz::GemmShape<128, 256, 2, 4>;
 using Shape256x128 = swz::GemmShape<256, 128, 4, 2>;
 
-// Checks shared by the GEMM entry points; on success r, grid_m, grid_n and group_m describe the launch.
-static int check_gemm(const void* A, const void* B, const void* C, int64_t M, int64_t N, int64_t K, int dtype, int mode,
-                      const swz_params* params, swz_params* r, int* grid_m, int* grid_n, int* group_m) {
-  if (A == nullptr || B == nullptr || C == nullptr || !valid_mode(mode)) return SWZ_ERR_INVALID_ARG;
+// The sizes and parameters that the GEMM entry points take; on success r, grid_m, grid_n and group_m describe the plan's tiles.
+static int check_gemm_sizes(int64_t M, int64_t N, int64_t K, int dtype, int mode, const swz_params* params, swz_params* r, int* grid_m,
+                            int* grid_n, int* group_m) {
   int st = resolve_plan(M, N, K, params, r, grid_m, grid_n);
   if (st != SWZ_OK) return st;
   if (dtype != SWZ_DTYPE_BF16) return SWZ_ERR_UNSUPPORTED;
   if ((K % 8) != 0 || (N % 8) != 0) return SWZ_ERR_UNSUPPORTED;   // 16-byte vector loads along k and n
   // per-lane source offsets inside a tile step are 32-bit: (bm-1) rows of A, 31 rows of B
   if ((int64_t)r->bm * K * 2 >= ((int64_t)1 << 32) || (int64_t)32 * N * 2 >= ((int64_t)1 << 32)) return SWZ_ERR_OVERFLOW;
-  if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C)) & 15)
-    return SWZ_ERR_UNSUPPORTED;
   *group_m = r->group_m;
   return check_map_args(*grid_m, *grid_n, r->num_xcd, group_m, mode);
+}
+
+static int check_gemm(const void* A, const void* B, const void* C, int64_t M, int64_t N, int64_t K, int dtype, int mode,
+                      const swz_params* params, swz_params* r, int* grid_m, int* grid_n, int* group_m) {
+  if (A == nullptr || B == nullptr || C == nullptr || !valid_mode(mode)) return SWZ_ERR_INVALID_ARG;
+  const int st = check_gemm_sizes(M, N, K, dtype, mode, params, r, grid_m, grid_n, group_m);
+  if (st != SWZ_OK) return st;
+  if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C)) & 15)
+    return SWZ_ERR_UNSUPPORTED;
+  return SWZ_OK;
+}
+
+static bool tile_is_free(const swz_params* params) { return params == nullptr || (params->bm == 0 && params->bn == 0); }
+
+int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_params* params, int32_t* out, int64_t out_words, int64_t* workgroups) {
+  if (workgroups == nullptr || !valid_mode(mode)) return SWZ_ERR_INVALID_ARG;
+  swz_params r;
+  int grid_m = 0, grid_n = 0, group_m = 0;
+  const int st = check_gemm_sizes(M, N, K, SWZ_DTYPE_BF16, mode, params, &r, &grid_m, &grid_n, &group_m);
+  if (st != SWZ_OK) return st;
+  if (r.persistent) return SWZ_ERR_UNSUPPORTED;
+  DeviceFacts f;
+  const int cus = tile_is_free(params) && query_device(&f) == SWZ_OK && f.cus > 0 ? f.cus : kWholeCus;
+  const swz::GemmLaunch l = swz::gemm_launch(M, N, K, r, grid_m, grid_n, group_m, tile_is_free(params), cus);
+  if (out != nullptr && out_words < 4 * l.blocks) return SWZ_ERR_INVALID_ARG;
+  *workgroups = l.blocks;
+  for (int64_t w = 0; out != nullptr && w < l.blocks; ++w) {
+    const swz::GemmBlock b = swz::gemm_block(l, r.num_xcd, mode, M, N, (int)w);
+    out[4 * w] = b.row;
+    out[4 * w + 1] = b.col;
+    out[4 * w + 2] = b.rows;
+    out[4 * w + 3] = b.cols;
+  }
+  return SWZ_OK;
 }
 
 int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int dtype, int mode,
@@ -659,32 +637,24 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
   int grid_m = 0, grid_n = 0, group_m = 0;
   const int st = check_gemm(A, B, C, M, N, K, dtype, mode, params, &r, &grid_m, &grid_n, &group_m);
   if (st != SWZ_OK) return st;
-  // Only where the caller left the tile to the library: a tile that was asked for is one workgroup.  Bounds: 32-bit
-  // source offsets over 64 rows of B, and a grid well inside the 32-bit range whatever the shape.
-  const bool free_tile = params == nullptr || (params->bm == 0 && params->bn == 0);
-  if (free_tile && !r.persistent && N < ((int64_t)1 << 24) && (int64_t)grid_m * grid_n < ((int64_t)1 << 16)) {
+  if (tile_is_free(params) && !r.persistent) {
     DeviceFacts f;
     const int qs = query_device(&f);
     if (qs != SWZ_OK) return qs;
     const int m = (int)M, n = (int)N, k = (int)K;
-    switch (choose_subtile(M, N, K, r, f.cus > 0 ? f.cus : 256)) {
-      case 0: return launch_subtile<Sub32x32>(A, B, C, m, n, k, r, group_m, mode, stream, 0);
-      case 1: return launch_subtile<Sub32x64>(A, B, C, m, n, k, r, group_m, mode, stream, 1);
-      case 2: return launch_subtile<Sub64x64>(A, B, C, m, n, k, r, group_m, mode, stream, 2);
-      case 3: return launch_subtile<Sub128x64>(A, B, C, m, n, k, r, group_m, mode, stream, 3);
-      case 4: return launch_subtile<Sub64x128>(A, B, C, m, n, k, r, group_m, mode, stream, 4);
-      case 5: return launch_subtile<Sub128x128>(A, B, C, m, n, k, r, group_m, mode, stream, 5);
-      case 6: return launch_subtile<Sub128x256>(A, B, C, m, n, k, r, group_m, mode, stream, 6);
-      default: break;
-    }
-    // A last round that fills at most half of the compute units is cut into halves or quarters of tiles, which then fit it:
-    // 1350 -> 840 or 520 ns a stage.  Measured, start -> here: 4352x4096x4096 (16 tiles left over) 154 -> 117 us, 6000x3000x3000 (32) 124 -> 101,
-    // 5120x4608x4096 (104) 162 -> 146, 10000x7000x4096 (96, fifth round) 442 -> 427.  Above half a round the pieces need a second
-    // round of their own: 5120x5120x5120 (144) stays at 198 us whole.
-    const int total = grid_m * grid_n, whole = f.cus > 0 ? total / f.cus * f.cus : total, tail = total - whole;
-    if (r.bm == 256 && r.bn == 256 && whole > 0 && tail > 0) {
-      if (4 * tail <= f.cus) return launch_tail<Piece128x128>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, whole, tail, stream, 0);
-      if (2 * tail <= f.cus) return launch_tail<Piece128x256>(A, B, C, m, n, k, r, grid_m, grid_n, group_m, mode, whole, tail, stream, 1);
+    const swz::GemmLaunch l = swz::gemm_launch(M, N, K, r, grid_m, grid_n, group_m, true, f.cus > 0 ? f.cus : kWholeCus);
+    if (l.pieces)
+      return l.sub == swz::kQuarterPiece ? launch_pieces<swz::kQuarterPiece>(A, B, C, m, n, k, l, r.num_xcd, mode, stream)
+                                         : launch_pieces<swz::kHalfPiece>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+    switch (l.sub) {
+      case 0: return launch_subtile<0>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 1: return launch_subtile<1>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 2: return launch_subtile<2>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 3: return launch_subtile<3>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 4: return launch_subtile<4>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 5: return launch_subtile<5>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 6: return launch_subtile<6>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      default: break;                                   // whole tiles
     }
   }
   if (r.bm == 128 && r.bn == 128)

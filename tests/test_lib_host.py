@@ -19,7 +19,7 @@ def test_library_exports_every_declared_entry_point():
     assert declared == {"swz_status_string", "swz_device_info", "swz_pid_map", "swz_pid_map_device", "swz_gemm",
                         "swz_gemm_ex", "swz_gemm_plan", "swz_copy_bytes", "swz_pid_map_persistent",
                         "swz_pid_map_persistent_device", "swz_transpose", "swz_softmax", "swz_layernorm", "swz_mfma_peak",
-                        "swz_gemm_probe"}
+                        "swz_gemm_probe", "swz_gemm_launch_map"}
     raw = ctypes.CDLL(swz.binding.LIB_PATH)
     for name in declared:
         assert hasattr(raw, name), name
@@ -109,6 +109,58 @@ def test_plan_resolves_tiles_without_a_device_when_num_xcd_is_given():
     with pytest.raises(swz.SwzError) as e:
         swz.gemm_plan(1 << 31, 8, 8, num_xcd=8)
     assert e.value.status == -3
+
+
+def covers_once(blocks, M, N):
+    count = np.zeros((M, N // 8), dtype=np.int32)
+    for row, col, rows, cols in blocks[blocks[:, 2] > 0]:
+        assert 0 <= row and row + rows <= M and 0 <= col and col + cols <= N and col % 8 == cols % 8 == 0
+        count[row:row + rows, col // 8:(col + cols) // 8] += 1
+    return bool((count == 1).all())
+
+
+# sub-tiles of every shape, halves and quarters of the last round (with fewer left-over tiles than XCDs and more), whole tiles
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (100, 520, 64), (300, 1032, 64), (449, 1992, 512), (1217, 1544, 512), (300, 5000, 512), (1537, 1400, 512),
+                                   (40, 33000, 200), (70, 66000, 512), (4352, 4096, 512), (1800, 9472, 64), (5120, 4608, 512), (4610, 5000, 64),
+                                   (65793, 248, 64), (4096, 4096, 4096), (5120, 5120, 512)])
+def test_launch_map_covers_c_once(M, N, K):
+    for mode, params in [(0, dict(num_xcd=8)), (2, dict(num_xcd=8)), (1, dict(num_xcd=3)), (6, dict(num_xcd=8, group_m=3)), (5, dict(num_xcd=1000)),
+                         (2, dict(num_xcd=1)), (2, dict(num_xcd=8, bm=128, bn=256))]:
+        blocks = swz.gemm_launch_map(M, N, K, mode, **params)
+        assert covers_once(blocks, M, N), (mode, params)
+
+
+def test_launch_map_of_tiles_subtiles_and_pieces():
+    # whole tiles: the plan's grid under swz_pid_map; sub-tiles: the same of a finer grid with a band as high; pieces: on the XCD of their tile
+    def tiles(blocks, bm, bn, gn):
+        return (blocks[:, 0] // bm * gn + blocks[:, 1] // bn).tolist()
+
+    p = swz.gemm_plan(10000, 7000, 4096, num_xcd=8, bm=256, bn=256)
+    got = swz.gemm_launch_map(10000, 7000, 4096, 2, num_xcd=8, bm=256, bn=256)
+    assert tiles(got, 256, 256, p["grid_n"]) == opm.pid_map(p["grid_m"], p["grid_n"], 8, 4, 2)
+    got = swz.gemm_launch_map(512, 512, 512, 2, num_xcd=8)
+    assert len(got) == 256 and (got[:, 2:] == 32).all() and tiles(got, 32, 32, 16) == opm.pid_map(16, 16, 8, 16, 2)
+    got = swz.gemm_launch_map(10000, 7000, 4096, 2, num_xcd=8)
+    whole = opm.pid_map(40, 28, 8, 4, 2)
+    assert tiles(got[:1024], 256, 256, 28) == whole[:1024]
+    xcd_of_tile = {t: w % 8 for w, t in enumerate(whole)}
+    for w, (row, col, rows, cols) in enumerate(got[1024:].tolist(), 1024):
+        assert rows == 0 or (rows <= 128 and w % 8 == xcd_of_tile[row // 256 * 28 + col // 256])
+
+
+def test_launch_map_error_paths():
+    L, n = swz.lib, ctypes.c_int64(-7)
+    p, out = ctypes.byref(swz.SwzParams(0, 0, 0, 0, 8)), np.full(8, -7, dtype=np.int32)
+    ref = ctypes.byref(n)
+    assert L.swz_gemm_launch_map(64, 64, 64, 0, p, None, 0, None) == -1
+    assert L.swz_gemm_launch_map(64, 64, 64, 8, p, None, 0, ref) == -1
+    assert L.swz_gemm_launch_map(0, 64, 64, 0, p, None, 0, ref) == -1
+    assert L.swz_gemm_launch_map(64, 60, 64, 0, p, None, 0, ref) == -2
+    assert L.swz_gemm_launch_map(64, 64, 64, 0, p, out.ctypes.data, 8, ref) == -1         # four sub-tiles
+    assert L.swz_gemm_launch_map(1 << 31, 64, 64, 0, p, None, 0, ref) == -3
+    persistent = swz.SwzParams(0, 0, 0, 0, 8, 1, 256)
+    assert L.swz_gemm_launch_map(64, 64, 64, 0, ctypes.byref(persistent), None, 0, ref) == -2
+    assert n.value == -7 and (out == -7).all()
 
 
 def test_gemm_rejects_bad_arguments_before_touching_the_device():
