@@ -239,8 +239,8 @@ constexpr int row_block(int tpr) { return tpr < 256 ? 256 : tpr; }
 // Which row a workgroup of TPR-thread groups works on: TPR <= 64, groups of lanes; above, the whole workgroup.
 // Rows held whole share nothing, so no mapping helps the L2, and rows that run at the same time are best neighbours in memory: in
 // dispatch order 8192 x 8192 takes 44 us (softmax) and 50 us (layer normalisation), with every XCD on a run of rows of its own
-// 50 and 56; 65536 x 1024 44 and 45 against 48 and 51, 4000 x 30000 84 and 88 against 88 and 92.  The one shape that prefers the
-// runs, softmax with 1024 threads and two vectors each (32768 x 16384: 356 us against 364), is MAPPED.
+// 50 and 56; 65536 x 1024 44 and 45 against 48 and 51, 4000 x 30000 84 and 88 against 88 and 92.  The softmax shape of 1024 threads
+// with two vectors each is MAPPED: the host hands it the caller's mode where runs are not slower (soft_rows_mapped in swz.hip).
 template <int TPR, bool MAPPED>
 struct RowJob {
   static constexpr int THREADS = row_block(TPR);

@@ -352,8 +352,16 @@ int for_row_parts(const RowPlan& plan, int tpr, int64_t M, F&& launch_part) {
   return SWZ_OK;
 }
 
+// Whether softmax rows follow the caller's mode: from 16128 elements a row (to 16384, the end of the one shape that can) and 2^29
+// elements in all.  Time under the XCD renumbering over that in dispatch order, for 16128, 16376 and 16384 elements: 32768 rows 1.006, 0.979,
+// 0.994 (0.973 on another device), 40000 rows 1.007, 0.982, 0.989, 65536 rows 0.986, 0.980, 1.006.  Outside, dispatch order is
+// ahead: fewer rows (16384 elements x 24000, 16384, 4096 rows 1.007, 1.020, 1.126), shorter ones (12544 elements 1.10 to 1.28, 13312
+// 1.05 to 1.13, 15360 1.02 to 1.10, 16000 1.00 to 1.06; 14336 alone is at 0.96 to 0.99 from 32768 rows on).
+bool soft_rows_mapped(int64_t M, int64_t N) { return N >= 16128 && M * N >= ((int64_t)1 << 29); }
+
 template <int KEEP, int TPR>
 int launch_softmax_rows(const uint16_t* in, uint16_t* out, int64_t M, int N, const RowPlan& plan, int mode, hipStream_t stream) {
+  if (!soft_rows_mapped(M, N)) mode = SWZ_MODE_RR;
   return for_row_parts(plan, TPR, M, [&](int64_t row, int rows, int groups) {
     const int group_m = plan.group_m < groups ? plan.group_m : groups;
     return launch(swz::softmax_rows_kernel<KEEP, TPR>, dim3((unsigned)groups), dim3(swz::row_block(TPR)), 0, stream, in + row * N,
