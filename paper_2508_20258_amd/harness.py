@@ -61,7 +61,7 @@ def _inputs(workload):
                 a_bits, b_bits = z["a"], z["b"]
         except Exception:
             a_bits = b_bits = None
-    cfg = si.CONFIGS[workload]
+    cfg = si.ALL_CONFIGS[workload]
     if a_bits is None or a_bits.shape != (cfg["M"], cfg["K"]) or b_bits.shape != (cfg["K"], cfg["N"]):
         a_bits, b_bits = si.config_inputs(workload)
         try:
@@ -75,11 +75,15 @@ def _inputs(workload):
     return a, b
 
 
+HASHED_SOURCES = ("gemm_kernel.h", "gemm_subtile_kernel.h", "gemm_dispatch.h", "pid_decode.h")
+
+
 def kernel_hash() -> str:
-    """SHA-256 of the GEMM kernel sources: recorded counters are only valid for the kernel they were taken on."""
+    """SHA-256 of the GEMM kernel sources and of the rule that picks among the kernels: recorded counters are only valid for the
+    launch they were taken on."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("gemm_kernel.h", "gemm_subtile_kernel.h", "pid_decode.h"):
+    for name in HASHED_SOURCES:
         with open(os.path.join(HERE, "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
@@ -105,6 +109,23 @@ def panel_model(tile_of_wg, grid_n, num_xcd, slots):
 def co_resident_tiles_per_xcd(tile, compute_units, num_xcd):
     """Tiles one XCD works on at a time: a 256-wide tile fills a CU's LDS, two 128-wide ones fit."""
     return (compute_units // num_xcd) * (1 if tile >= 256 else 2)
+
+
+def covers_once(blocks, m, n):
+    """Whether the blocks (row, column, rows, columns) of a launch cover an m x n matrix once (rows and columns start on multiples of 32)."""
+    import numpy as np
+    count = np.zeros((-(-m // 32), -(-n // 32)), dtype=np.int32)
+    for row, col, rows, cols in blocks.tolist():
+        if row % 32 or col % 32 or row + rows > m or col + cols > n or (rows % 32 and row + rows < m) or (cols % 32 and col + cols < n):
+            return False
+        count[row // 32:-(-(row + rows) // 32), col // 32:-(-(col + cols) // 32)] += 1 if rows else 0
+    return bool((count == 1).all())
+
+
+def launched_kernel(name):
+    """(short name, whether it computes the plan's tiles one workgroup each) of a GEMM kernel's full name in a trace."""
+    short = name.split("(")[0].replace("void ", "").replace("swz::", "").strip()
+    return short, "subtile" not in short and "tail" not in short
 
 
 def warmup_launches(warmup_ms, flops):
@@ -144,9 +165,12 @@ def cmd_run(args):
         ref = torch.empty_like(c)
         swz.gemm(a, b, ref, mode=swz.MODE_RR, **{k: v for k, v in params.items() if k != "persistent"})
         torch.cuda.synchronize()
-        plan = swz.gemm_plan(a.shape[0], b.shape[1], a.shape[1], **params)
-        m = swz.pid_map(plan["grid_m"], plan["grid_n"], plan["num_xcd"], plan["group_m"], mode)
-        perm_ok = bool((np.sort(m) == np.arange(m.size)).all())
+        if args.persistent:
+            plan = swz.gemm_plan(a.shape[0], b.shape[1], a.shape[1], **params)
+            m = swz.pid_map_persistent(plan["grid_m"], plan["grid_n"], plan["num_xcd"], plan["group_m"], mode, plan["num_wg"])
+            perm_ok = bool((np.sort(m[m >= 0]) == np.arange(plan["grid_m"] * plan["grid_n"])).all())
+        else:
+            perm_ok = covers_once(swz.gemm_launch_map(a.shape[0], b.shape[1], a.shape[1], mode, **params), a.shape[0], b.shape[1])
         same = bool(torch.equal(c.view(torch.int16), ref.view(torch.int16)))
         print(f"check: bit_identical_to_rr={same} map_is_permutation={perm_ok} us_per_launch={us:.3f}", flush=True)
 
@@ -226,7 +250,7 @@ def cmd_rank(args):
     import paper_2508_20258_amd as swz
     env = dict(os.environ, TMPDIR=os.environ.get("TMPDIR", "/tmp"))
     root = os.path.dirname(HERE)
-    cfg = si.CONFIGS[args.workload]
+    cfg = si.ALL_CONFIGS[args.workload]
     M, N, K = cfg["M"], cfg["N"], cfg["K"]
     X = args.num_xcd
     me = [sys.executable, "-m", "paper_2508_20258_amd.harness", "run", "--workload", args.workload]
@@ -307,7 +331,7 @@ def profile_table(src, workload, warmup_ms, launches, num_xcd=8, compute_units=2
     import seeded_inputs as si
 
     import paper_2508_20258_amd as swz
-    cfg = si.CONFIGS[workload]
+    cfg = si.ALL_CONFIGS[workload]
     M, N, K = cfg["M"], cfg["N"], cfg["K"]
     bm = cfg["tile"][0]
     gm, gn = -(-M // bm), -(-N // bm)
@@ -317,7 +341,13 @@ def profile_table(src, workload, warmup_ms, launches, num_xcd=8, compute_units=2
     fs, ws = 1024 * 1024 / copy_f, 1024 * 1024 / copy_w
     H = "python3 -m paper_2508_20258_amd.harness"
     run = f"{H} run --workload {workload} --mode MODE"
-    lines = [f"rocprofv3 summary: swz gemm_bf16_kernel, workload {workload} (M={M} N={N} K={K}, tile {bm}x{bm}x64, grid {gm}x{gn}, {num_xcd} XCDs, group_m 4)",
+    kernels = {mode: launched_kernel(next(iter(summarize(f"{src}/{workload}_{mode}_kt", "gemm", launches)))) for mode in PROFILE_MODES}
+    grids = {mode: launched_workgroups(f"{src}/{workload}_{mode}_kt", "gemm") for mode in PROFILE_MODES}
+    by_kernel = {}
+    for mode in PROFILE_MODES:
+        by_kernel.setdefault((kernels[mode][0], grids[mode]), []).append(mode)
+    lines = [f"rocprofv3 summary: swz_gemm, workload {workload} (M={M} N={N} K={K}, {num_xcd} XCDs, plan: tile {bm}x{bm}x64, grid {gm}x{gn}, group_m 4)",
+             "Launched (kernel trace): " + "; ".join(f"{k}{f', {g} workgroups' if g else ''} ({', '.join(m)})" for (k, g), m in by_kernel.items()),
              "MI355X (gfx950), one GPU.  Written by (repository root, TMPDIR=/tmp):",
              f"  {H} profile --workload {workload} --out <dir>",
              "which runs, for MODE in rr, xcd, xcd_groupm:",
@@ -329,7 +359,7 @@ def profile_table(src, workload, warmup_ms, launches, num_xcd=8, compute_units=2
              f"Byte-counter calibration on the plain 1 GiB copy kernel: FETCH_SIZE read {copy_f:.0f} KiB, WRITE_SIZE read {copy_w:.0f} KiB for 1048576 KiB",
              f"  => scale FETCH_SIZE by {fs:.3f}, WRITE_SIZE by {ws:.3f}.  Algorithmic minimum HBM bytes 2(MK+KN+MN) = {2 * (M * K + K * N + M * N) / 2 ** 20:.1f} MiB.",
              "L2 hit = TCC_HIT/(TCC_HIT+TCC_MISS) over all TCC instances; per XCD = the instances of each DIMENSION_XCC.",
-             f"model = lock-step panel-count prediction on swz_pid_map's output, {co_resident_tiles_per_xcd(bm, compute_units, num_xcd)} co-resident tiles per XCD.",
+             f"model = lock-step panel-count prediction on swz_pid_map's output, {co_resident_tiles_per_xcd(bm, compute_units, num_xcd)} co-resident tiles per XCD; none where the launch is not one workgroup per tile of the plan.",
              f"us = average kernel duration in the kernel trace over the last {launches} dispatches (the timed launches; the warm-up launches before them, {warmup_ms:g} ms of GPU time, are not averaged);",
              "first us = the same over the first 10 dispatches of the run (device idle before: boost clocks); worst us = the slowest dispatch of the run (the power controller's",
              "throttling a few milliseconds in).  event us = the run's own event timing per timed launch (includes launch gaps).", ""]
@@ -361,9 +391,11 @@ def profile_table(src, workload, warmup_ms, launches, num_xcd=8, compute_units=2
         sq = _one(f"{t}_sq", "gemm")["counters"]
         util = 100 * sq["SQ_VALU_MFMA_BUSY_CYCLES"] / (sq["GRBM_GUI_ACTIVE"] / num_xcd * compute_units * 4)
         confl = 100 * sq["SQ_LDS_BANK_CONFLICT"] / sq["SQ_LDS_IDX_ACTIVE"]
-        tile_map = swz.pid_map(gm, gn, num_xcd, 4, swz.MODES[mode])
-        model = 100 * panel_model(tile_map, gn, num_xcd, co_resident_tiles_per_xcd(bm, compute_units, num_xcd))[0]
-        lines.append(f"{mode:11s} {us:9.2f} {cold:9.2f} {worst:9.2f} {ev:9.2f} {tf:8.1f} {tf / 25:6.1f} {hit:8.2f} {model:7.1f} {fkib / 1024:10.1f} {wkib / 1024:10.1f} "
+        model = None
+        if kernels[mode][1]:
+            tile_map = swz.pid_map(gm, gn, num_xcd, 4, swz.MODES[mode])
+            model = 100 * panel_model(tile_map, gn, num_xcd, co_resident_tiles_per_xcd(bm, compute_units, num_xcd))[0]
+        lines.append(f"{mode:11s} {us:9.2f} {cold:9.2f} {worst:9.2f} {ev:9.2f} {tf:8.1f} {tf / 25:6.1f} {hit:8.2f} {'-' if model is None else f'{model:.1f}':>7s} {fkib / 1024:10.1f} {wkib / 1024:10.1f} "
                      f"{util:9.1f} {confl:10.2f}  " + " ".join(f"{r:.1f}" for r in per))
         record[mode] = dict(kernel_us=us, l2_hit_pct=hit, l2_hit_pct_per_xcd=per, model_hit_pct=model, fetch_bytes=int(fkib * 1024),
                             write_bytes=int(wkib * 1024), mfma_util_pct=util,
@@ -372,6 +404,16 @@ def profile_table(src, workload, warmup_ms, launches, num_xcd=8, compute_units=2
     lines += ["", f"MfmaUtil = SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE per XCD x {compute_units * 4} SIMDs).  MFMA flops cross-check: "
               f"SQ_INSTS_VALU_MFMA_MOPS_BF16 x 512 = {issued / 1e9:.1f} GFLOP issued vs 2MNK = {flops / 1e9:.1f} GFLOP (edge tiles compute padding)."]
     return "\n".join(lines) + "\n", record
+
+
+def launched_workgroups(directory, kernel_filter):
+    """Workgroups of the last dispatch of the kernel in a trace; None where the trace has no grid columns."""
+    last, groups = -1, None
+    for path in glob.glob(os.path.join(directory, "**", "*kernel_trace.csv"), recursive=True):
+        for r in _rows(path):
+            if kernel_filter in r["Kernel_Name"] and r.get("Grid_Size_X") and int(r["Start_Timestamp"]) > last:
+                last, groups = int(r["Start_Timestamp"]), int(r["Grid_Size_X"]) // int(r["Workgroup_Size_X"])
+    return groups
 
 
 def summarize_spans(directory, kernel_filter):
@@ -406,12 +448,14 @@ def cmd_profile_transpose(args):
     out = os.path.abspath(args.out)
     os.makedirs(out, exist_ok=True)
     m, n = args.m, args.n
-    base = ["transpose", "--m", str(m), "--n", str(n)]
+    eb = args.elem_bytes
+    base = ["transpose", "--m", str(m), "--n", str(n)] + (["--elem-bytes", str(eb)] if eb != 2 else [])
+    moved = 2 * eb * m * n
     combos = [(t, mo) for t in args.tile for mo in args.mode]
     if not args.table_only:
         for c, tag in (("FETCH_SIZE", "copy_fetch"), ("WRITE_SIZE", "copy_write")):
             _rocprof(out, tag, "csv", ["--pmc", c], ["copy", "--mib", "1024", "--launches", "3"])
-        _rocprof(out, "copy_kt", "csv", ["--kernel-trace", "--stats"], ["copy", "--mib", str(4 * m * n >> 21), "--launches", str(args.launches + 1)])
+        _rocprof(out, "copy_kt", "csv", ["--kernel-trace", "--stats"], ["copy", "--mib", str(max(moved >> 21, 1)), "--launches", str(args.launches + 1)])
         for tile, mode in combos:
             prog = base + ["--tile", str(tile), "--mode", mode]
             t = f"t{tile}_{mode}"
@@ -422,23 +466,25 @@ def cmd_profile_transpose(args):
     fs = 1024 * 1024 / _one(f"{out}/copy_fetch", "copy")["counters"]["FETCH_SIZE"]
     ws = 1024 * 1024 / _one(f"{out}/copy_write", "copy")["counters"]["WRITE_SIZE"]
     copy_us = _one(f"{out}/copy_kt", "copy", args.launches)["warm_avg_ns"] / 1e3
-    copy_gbs = 4.0 * m * n / (copy_us * 1e-6) / 1e9
+    copy_gbs = 2.0 * (max(moved >> 21, 1) << 20) / (copy_us * 1e-6) / 1e9
     H = "python3 -m paper_2508_20258_amd.harness"
-    lines = [f"rocprofv3 summary: swz transpose16_kernel, {m} x {n} 16-bit elements ({2 * m * n >> 20} MiB in, {2 * m * n >> 20} MiB out), MI355X, one GPU.",
+    names = sorted({launched_kernel(k)[0].split("<")[0] for ti, mo in combos for k in summarize(f"{out}/t{ti}_{mo}_kt", "transpose")})
+    shape = " ".join(base[1:])
+    lines = [f"rocprofv3 summary: swz_transpose ({', '.join(names)}), {m} x {n} elements of {eb} bytes ({moved >> 21} MiB in, {moved >> 21} MiB out), MI355X, one GPU.",
              "Written by (repository root, TMPDIR=/tmp):",
-             f"  {H} profile-transpose --m {m} --n {n} --out <dir>",
+             f"  {H} profile-transpose {shape} --tile {' '.join(map(str, args.tile))} --mode {' '.join(args.mode)} --out <dir>",
              f"which runs, for TILE in {', '.join(map(str, args.tile))} and MODE in {', '.join(args.mode)}:",
-             f"  rocprofv3 --kernel-trace --stats --output-format csv -d <out> -- {H} transpose --m {m} --n {n} --tile TILE --mode MODE --launches {args.launches + 1}",
-             f"  rocprofv3 --pmc TCC_HIT TCC_MISS --output-format json -d <out> -- {H} transpose --m {m} --n {n} --tile TILE --mode MODE --launches 3",
+             f"  rocprofv3 --kernel-trace --stats --output-format csv -d <out> -- {H} transpose {shape} --tile TILE --mode MODE --launches {args.launches + 1}",
+             f"  rocprofv3 --pmc TCC_HIT TCC_MISS --output-format json -d <out> -- {H} transpose {shape} --tile TILE --mode MODE --launches 3",
              "  rocprofv3 --pmc FETCH_SIZE (then WRITE_SIZE) --output-format csv -d <out> -- the same",
-             f"  and the same passes on `{H} copy` (byte-counter calibration on 1 GiB: FETCH_SIZE x {fs:.3f}, WRITE_SIZE x {ws:.3f}; kernel trace on {4 * m * n >> 20} MiB moved).",
-             f"Roofline: HBM, 8 TB/s; algorithmic bytes 4*M*N = {4 * m * n >> 20} MiB per launch.  us = kernel duration in the kernel trace, average over the last {args.launches} launches.",
+             f"  and the same passes on `{H} copy` (byte-counter calibration on 1 GiB: FETCH_SIZE x {fs:.3f}, WRITE_SIZE x {ws:.3f}; kernel trace on {moved >> 20} MiB moved).",
+             f"Roofline: HBM, 8 TB/s; algorithmic bytes 2*M*N*{eb} = {moved >> 20} MiB per launch.  us = kernel duration in the kernel trace, average over the last {args.launches} launches.",
              f"The library's plain copy kernel on the same amount of data in the same session: {copy_us:.2f} us = {copy_gbs:.0f} GB/s ({100 * copy_gbs / 8000:.1f} % of 8 TB/s).",
              "", f"{'tile':>4s} {'mode':16s} {'us':>8s} {'GB/s':>6s} {'% of 8 TB/s':>11s} {'x copy':>7s} {'L2 hit %':>8s} {'fetch MiB':>10s} {'write MiB':>10s}"]
     for tile, mode in combos:
         t = f"{out}/t{tile}_{mode}"
         us = _one(t + "_kt", "transpose", args.launches)["warm_avg_ns"] / 1e3
-        gbs = 4.0 * m * n / (us * 1e-6) / 1e9
+        gbs = float(moved) / (us * 1e-6) / 1e9
         tj = next(iter(summarize_json(t + "_tcc", "transpose").values()))["counters"]
         hit = 100 * tj["TCC_HIT"]["total"] / (tj["TCC_HIT"]["total"] + tj["TCC_MISS"]["total"])
         f = _one(t + "_fetch", "transpose")["counters"]["FETCH_SIZE"] * fs / 1024
@@ -446,13 +492,19 @@ def cmd_profile_transpose(args):
         lines.append(f"{tile:4d} {mode:16s} {us:8.2f} {gbs:6.0f} {100 * gbs / 8000:11.1f} {gbs / copy_gbs:7.2f} {hit:8.2f} {f:10.1f} {w:10.1f}")
     text = "\n".join(lines) + "\n"
     print(text, flush=True)
-    with open(os.path.join(out, f"transpose_{m}x{n}.txt"), "w") as f:
+    with open(os.path.join(out, f"transpose_{m}x{n}_{eb}B.txt"), "w") as f:
         f.write(text)
 
 
-ROW_CASES = [  # (M, N, chunks, mode): chunked rows under both dispatch orders, one workgroup per row, one wave per row, beyond the cache
-    (1024, 65536, 8, "rr"), (1024, 65536, 8, "xcd"), (1024, 65536, 1, "rr"), (8192, 8192, 8, "rr"), (8192, 8192, 8, "xcd"),
-    (8192, 8192, 1, "rr"), (65536, 1024, 1, "rr"), (32768, 16384, 1, "rr")]
+ROW_CASES = [  # (M, N, chunks, mode).  Rows of up to 98304 elements are held by one workgroup whatever the chunks and, but for large
+    # softmax matrices of 16128 to 16384 columns, taken in dispatch order whatever the mode; longer ones take two launches under the caller's mode
+    (65536, 1024, 1, "rr"), (8192, 8192, 1, "rr"), (32768, 16384, 1, "rr"), (32768, 16384, 1, "xcd"), (1024, 65536, 8, "rr"),
+    (300, 100000, 1, "rr"), (300, 100000, 1, "xcd"), (64, 1048576, 4, "rr"), (64, 1048576, 4, "xcd")]
+
+
+def row_kernels(summary):
+    """The row-wise kernels of one call in a summary of dispatches or counters: one, or the two launches of long rows."""
+    return [d for k, d in sorted(summary.items()) if "rows_kernel" in k or "row_stats_kernel" in k or "row_emit_kernel" in k]
 
 
 def cmd_profile_rows(args):
@@ -476,7 +528,7 @@ def cmd_profile_rows(args):
     copy_us = _one(f"{out}/copy_kt", "copy", args.launches)["warm_avg_ns"] / 1e3
     copy_gbs = 2.0 * (1 << 30) / (copy_us * 1e-6) / 1e9
     H = "python3 -m paper_2508_20258_amd.harness"
-    lines = ["rocprofv3 summary: swz softmax_rows_kernel / layernorm_rows_kernel, bf16, MI355X, one GPU.",
+    lines = ["rocprofv3 summary: swz softmax_rows_kernel / layernorm_rows_kernel, and row_stats_kernel + row_emit_kernel for rows above 98304 elements, bf16, MI355X, one GPU.",
              "Written by (repository root, TMPDIR=/tmp):",
              f"  {H} profile-rows --out <dir>",
              "which runs, for OP in softmax, layernorm and (M, N, CHUNKS, MODE) as in the table:",
@@ -484,20 +536,20 @@ def cmd_profile_rows(args):
              f"  rocprofv3 --pmc TCC_HIT TCC_MISS --output-format json -d <out> -- {H} rows --op OP --m M --n N --chunks CHUNKS --mode MODE --launches 3",
              "  rocprofv3 --pmc FETCH_SIZE (then WRITE_SIZE) --output-format csv -d <out> -- the same",
              f"  and the same passes on `{H} copy --mib 1024` (byte-counter calibration: FETCH_SIZE x {fs:.3f}, WRITE_SIZE x {ws:.3f}).",
-             "Roofline: HBM, 8 TB/s; algorithmic bytes 4*M*N per launch (read x once, write y once): 256 MiB, 2 GiB for 32768 x 16384.",
-             "Launches repeat over the same data; 256 MiB is partly held by the 256 MB memory-side cache between launches, 2 GiB is not.",
+             "Roofline: HBM, 8 TB/s; algorithmic bytes 4*M*N per call (read x once, write y once).",
+             "Calls repeat over the same data; up to 256 MiB of it is partly held by the 256 MB memory-side cache between calls, the 2 GiB of 32768 x 16384 are not.",
              f"The library's plain copy kernel, 1 GiB in + 1 GiB out, same session: {copy_us:.2f} us = {copy_gbs:.0f} GB/s ({100 * copy_gbs / 8000:.1f} % of 8 TB/s).",
-             f"us = kernel duration in the kernel trace, average over the last {args.launches} launches.  chunks = workgroups a row may be spread over; these rows are held by one each.",
-             "", f"{'op':9s} {'M x N':>14s} {'chunks':>6s} {'mode':5s} {'us':>8s} {'GB/s':>6s} {'% of 8 TB/s':>11s} {'L2 hit %':>8s} {'fetch MiB':>10s} {'write MiB':>10s}"]
+             f"us = kernel duration in the kernel trace, average over the last {args.launches} launches of each of the call's kernels, added up; counters likewise.",
+             "", f"{'op':9s} {'M x N':>16s} {'chunks':>6s} {'mode':5s} {'launches':>8s} {'us':>8s} {'GB/s':>6s} {'% of 8 TB/s':>11s} {'L2 hit %':>8s} {'fetch MiB':>10s} {'write MiB':>10s}"]
     for op, m, n, c, mode in cases:
         t = f"{out}/{op}_{m}x{n}_c{c}_{mode}"
-        us = _one(t + "_kt", "rows_kernel", args.launches)["warm_avg_ns"] / 1e3
+        us = sum(d["warm_avg_ns"] for d in row_kernels(summarize(t + "_kt", None, args.launches))) / 1e3
         gbs = 4.0 * m * n / (us * 1e-6) / 1e9
-        tj = next(iter(summarize_json(t + "_tcc", "rows_kernel").values()))["counters"]
-        hit = 100 * tj["TCC_HIT"]["total"] / (tj["TCC_HIT"]["total"] + tj["TCC_MISS"]["total"])
-        f = _one(t + "_fetch", "rows_kernel")["counters"]["FETCH_SIZE"] * fs / 1024
-        w = _one(t + "_write", "rows_kernel")["counters"]["WRITE_SIZE"] * ws / 1024
-        lines.append(f"{op:9s} {m:>6d} x {n:<6d} {c:6d} {mode:5s} {us:8.2f} {gbs:6.0f} {100 * gbs / 8000:11.1f} {hit:8.2f} {f:10.1f} {w:10.1f}")
+        tcc = [d["counters"] for d in row_kernels(summarize_json(t + "_tcc"))]
+        h, ms = sum(x["TCC_HIT"]["total"] for x in tcc), sum(x["TCC_MISS"]["total"] for x in tcc)
+        f = sum(d["counters"]["FETCH_SIZE"] for d in row_kernels(summarize(t + "_fetch"))) * fs / 1024
+        w = sum(d["counters"]["WRITE_SIZE"] for d in row_kernels(summarize(t + "_write"))) * ws / 1024
+        lines.append(f"{op:9s} {m:>6d} x {n:<7d} {c:6d} {mode:5s} {len(tcc):8d} {us:8.2f} {gbs:6.0f} {100 * gbs / 8000:11.1f} {100 * h / (h + ms):8.2f} {f:10.1f} {w:10.1f}")
     text = "\n".join(lines) + "\n"
     print(text, flush=True)
     with open(os.path.join(out, "rowwise_softmax_layernorm.txt"), "w") as f:
@@ -847,6 +899,7 @@ def main(argv=None):
     pt = sub.add_parser("profile-transpose")
     pt.add_argument("--m", type=int, default=16384)
     pt.add_argument("--n", type=int, default=16384)
+    pt.add_argument("--elem-bytes", type=int, default=2, choices=[2, 4])
     pt.add_argument("--out", required=True)
     pt.add_argument("--tile", type=int, nargs="+", default=[64, 128, 32])
     pt.add_argument("--mode", nargs="+", default=["rr", "xcd", "xcd_groupm", "rr_skew", "xcd_skew", "xcd_groupm_skew"], choices=MODE_NAMES)

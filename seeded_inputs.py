@@ -91,10 +91,17 @@ CONFIGS = {
     "cfg5_ragged": dict(M=10000, N=7000, K=4096, seed=4, a=("uniform", 1.0), b=("uniform", 1.0), tile=(256, 256, 64)),
 }
 
+# Profiled beside them: products that the library cuts into sub-tiles.
+SUBTILE_CONFIGS = {
+    "few_rows_32": dict(M=32, N=8192, K=8192, seed=5, a=("normal", 1.0), b=("normal", 8192 ** -0.5), tile=(128, 128, 64)),
+    "square_2048": dict(M=2048, N=2048, K=2048, seed=6, a=("normal", 1.0), b=("normal", 2048 ** -0.5), tile=(128, 128, 64)),
+}
+ALL_CONFIGS = {**CONFIGS, **SUBTILE_CONFIGS}
+
 
 def config_inputs(name: str):
-    """(A_bits, B_bits) for one of CONFIGS."""
-    c = CONFIGS[name]
+    """(A_bits, B_bits) for one of ALL_CONFIGS."""
+    c = ALL_CONFIGS[name]
     a = matrix_bf16(c["seed"], 0, c["M"], c["K"], c["a"][0], c["a"][1])
     b = matrix_bf16(c["seed"], 1, c["K"], c["N"], c["b"][0], c["b"][1])
     return a, b

@@ -212,3 +212,33 @@ def test_profile_table_from_canned_rocprof_output(tmp_path):
     line = next(l for l in text.splitlines() if l.startswith("xcd_groupm"))
     assert line.split()[1] == "0.50" and line.split()[2] == "0.90" and line.split()[4] == "0.61"
     assert "scale FETCH_SIZE by 2.000, WRITE_SIZE by 1.000" in text
+
+
+def test_kernel_hash_covers_every_source_that_decides_a_gemm_launch():
+    csrc = os.path.join(os.path.dirname(harness.__file__), "csrc")
+    assert {f for f in os.listdir(csrc) if f.startswith("gemm")} | {"pid_decode.h"} == set(harness.HASHED_SOURCES)
+
+
+def test_covers_once_rejects_planted_maps():
+    import numpy as np
+
+    import paper_2508_20258_amd as swz
+    M, N = 300, 1032
+    good = swz.gemm_launch_map(M, N, 64, num_xcd=8)
+    assert harness.covers_once(good, M, N)
+    for i, col, value in [(5, 0, good[6, 0] + 32), (7, 2, 0), (0, 1, -32), (0, 3, good[0, 3] - 8), (3, 0, 16)]:
+        bad = good.copy()
+        bad[i, col] = value
+        assert not harness.covers_once(bad, M, N), (i, col, value)
+    assert not harness.covers_once(np.concatenate([good, good[:1]]), M, N) and not harness.covers_once(good[1:], M, N)
+
+
+def test_launched_kernel_and_its_grid_come_from_the_trace(tmp_path):
+    assert harness.launched_kernel("void swz::gemm_bf16_subtile_kernel<swz::SubShape<32, 32, 2, 2, 8> >(unsigned short const*, int)") == (
+        "gemm_bf16_subtile_kernel<SubShape<32, 32, 2, 2, 8> >", False)
+    assert not harness.launched_kernel("gemm_bf16_tail_kernel<A, B>(int)")[1] and harness.launched_kernel("gemm_bf16_kernel<A, 2>(int)")[1]
+    d = tmp_path / "run"
+    os.makedirs(d)
+    (d / "1_kernel_trace.csv").write_text('"Kernel_Name","Start_Timestamp","End_Timestamp","Workgroup_Size_X","Grid_Size_X"\n'
+                                          '"gemm<1>",2000,2500,256,65536\n"gemm<1>",1000,1500,256,512\n"copy",3000,3500,256,1024\n')
+    assert harness.launched_workgroups(str(d), "gemm") == 256
