@@ -189,13 +189,13 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
 
 /* Row softmax, y[i][j] = exp(x[i][j] - max_i) / sum_k exp(x[i][k] - max_i), over a row-major dense
  * M x N bfloat16 matrix (the paper's softmax kernel: Results; Appendix "Case Study: Other Swizzling
- * Pattern Examples", whose swizzle routes all column chunks of a row to one XCD).  `chunks` is the number of
- * workgroups a row may be spread over; the library cuts a row only where that is faster: rows of up to 98304 elements are
- * held and written by one workgroup (short ones by 16 to 64 lanes, several rows a workgroup) whatever `chunks` says, longer
- * ones are cut into column chunks of at most 2048 16-byte vectors, in two launches (statistics of every 32768 elements,
- * then the chunks).  The workgroups of long rows are decoded as swz_pid_map does for the grid M x pieces of a row (`mode`,
- * params->group_m, params->num_xcd; other fields ignored); rows held whole share nothing, and the library takes them in the
- * order it found faster.
+ * Pattern Examples", whose swizzle routes all column chunks of a row to one XCD).  `chunks`, the workgroups per row of the
+ * paper's decomposition, is checked and has no further effect: the library cuts rows by their length alone.  Rows of up to 98304
+ * elements are held and written by one workgroup (short ones by 16 to 64 lanes, several rows a workgroup), longer ones are
+ * cut into column chunks of at most 2048 16-byte vectors, in two launches (statistics of every 32768 elements, then the
+ * chunks).  The workgroups of long rows are decoded as swz_pid_map does for the grid M x pieces of a row (`mode`,
+ * params->group_m, params->num_xcd; other fields ignored).  Rows held whole share nothing and are taken in dispatch order;
+ * only softmax rows of 16128 to 16384 elements, 2^29 elements or more in all, follow `mode`.
  *   in, out : caller-owned DEVICE pointers, 16-byte aligned, must not overlap.  -inf entries are
  *             allowed (they get probability 0), finite ones may be of any size.  A row of only -inf, and
  *             one with a NaN or +inf, gives NaN.

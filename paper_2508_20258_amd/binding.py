@@ -292,7 +292,8 @@ def _row_args(x, out):
 
 
 def softmax(x, out=None, chunks: int = 1, mode: int = MODE_XCD, stream=None, **params):
-    """Row softmax of a bf16 matrix on the GPU through swz_softmax; `chunks`: workgroups a row may be spread over."""
+    """Row softmax of a bf16 matrix on the GPU through swz_softmax.  `chunks` (1 to columns / 8) is checked by the library, which
+    cuts rows by their length alone."""
     out = _row_args(x, out)
     h = _launch_stream(stream, x, out)
     M, N = x.shape
@@ -301,7 +302,7 @@ def softmax(x, out=None, chunks: int = 1, mode: int = MODE_XCD, stream=None, **p
 
 
 def layernorm(x, gamma, beta, out=None, eps: float = 1e-5, chunks: int = 1, mode: int = MODE_XCD, stream=None, **params):
-    """Layer normalisation of every row of a bf16 matrix on the GPU through swz_layernorm."""
+    """Layer normalisation of every row of a bf16 matrix on the GPU through swz_layernorm; `chunks` as for softmax."""
     out = _row_args(x, out)
     for t in (gamma, beta):
         assert t.is_cuda and t.is_contiguous() and t.dtype == x.dtype and t.numel() == x.shape[1]

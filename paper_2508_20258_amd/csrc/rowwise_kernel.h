@@ -26,7 +26,7 @@
 // beta are requested ahead of the statistics where there are registers for them.  Measured, operands not in cache, online and merging
 // kernels with late gamma and beta -> these (us; copy16_kernel on 128 MiB in and out: 43):
 //     layernorm 8192 x 8192    66 -> 50      softmax 8192 x 8192    55 -> 44      layernorm 32768 x 16384  388 -> 368
-//     softmax 32768 x 16384   382 -> 354     softmax 131072 x 128   49 -> 13      layernorm 300 x 2048     4.9 -> 3.5
+//     softmax 32768 x 16384   382 -> 354     softmax 131072 x 128   49 -> 13      layernorm 300 x 2048     4.9 -> 3.0
 //     softmax 64 x 1048576    300 -> 70      softmax 1 x 1048576   220 -> 9       softmax 16 x 131072       29 -> 9
 //
 // All arithmetic is fp32 on values widened exactly from bf16; results are rounded once to bf16 (nearest even).  How a row is
@@ -47,7 +47,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t rw_u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t rw_u32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 rw_bf16x2;
 
-constexpr int kSegThreads = 512;               // threads that share a segment of a row of more than 32768 elements
+constexpr int kSegThreads = 512;               // threads that share a segment (32768 elements) of a row of more than 98304
 constexpr int kSegKeep = 8;                    // 16-byte vectors each of them takes, at most
 constexpr int kSegVecs = kSegThreads * kSegKeep;
 constexpr int kMaxSegs = (1 << 24) / (kSegVecs * 8);

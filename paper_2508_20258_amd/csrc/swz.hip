@@ -354,7 +354,7 @@ int for_row_parts(const RowPlan& plan, int tpr, int64_t M, F&& launch_part) {
 
 // Whether softmax rows follow the caller's mode: from 16128 elements a row (to 16384, the end of the one shape that can) and 2^29
 // elements in all.  Time under the XCD renumbering over that in dispatch order, for 16128, 16376 and 16384 elements: 32768 rows 1.006, 0.979,
-// 0.994 (0.973 on another device), 40000 rows 1.007, 0.982, 0.989, 65536 rows 0.986, 0.980, 1.006.  Outside, dispatch order is
+// 0.994 (0.975 with three sets of buffers in turn), 40000 rows 1.007, 0.982, 0.989, 65536 rows 0.986, 0.980, 1.006.  Outside, dispatch order is
 // ahead: fewer rows (16384 elements x 24000, 16384, 4096 rows 1.007, 1.020, 1.126), shorter ones (12544 elements 1.10 to 1.28, 13312
 // 1.05 to 1.13, 15360 1.02 to 1.10, 16000 1.00 to 1.06; 14336 alone is at 0.96 to 0.99 from 32768 rows on).
 bool soft_rows_mapped(int64_t M, int64_t N) { return N >= 16128 && M * N >= ((int64_t)1 << 29); }

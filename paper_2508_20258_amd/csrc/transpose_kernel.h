@@ -200,9 +200,11 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
 // pieces.  Here the 64 columns a workgroup
 // writes of row n of `out` are shifted left by s(n), the elements by which the row overhangs a line, so that it writes whole lines: row n
 // gets columns [64 pm - s(n), 64 pm - s(n) + 64), the last tile of the row everything up to M (one line more at
-// most).  The tile of `in` grows by the E - 1 rows above it (E elements fill a line), which the neighbouring tile
-// row reads too: they come out of the L2.  s(n) differs from row to row, so a lane gathers its 16 bytes element by element, four rows or eight
-// rows of the tile at a column: the transposing LDS read takes the same rows for 4 columns.
+// most).  The tile of `in` grows by the E - 1 rows above it (E elements fill a line), which the neighbouring tile row reads too:
+// 1.5 times the input for four bytes, twice for two, in all.  1.28 and 1.37 times the input cross the fabric under the default mapping (FETCH_SIZE
+// at 5800 x 5804 x 4 B and 10000 x 7000 x 2 B; 1.13 and 1.12 without the skew), the L2 serves the rest.  s(n) differs from row
+// to row, so a lane gathers its 16 bytes element by element, four rows or eight rows of the tile at a column: the
+// transposing LDS read takes the same rows for 4 columns.
 // A wave instruction stores 8 rows x 8 chunks = 8 whole lines: lane l takes row l / 8, chunk l % 8.
 // LDS: 16-byte chunk c of tile row r in slot c ^ key(r); key steps with the chunk of rows a lane gathers, so that the 8
 // chunks of one column lie in different banks whatever their shift.  The stores are streaming ones at every size: nothing
