@@ -200,10 +200,10 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
  *             allowed (they get probability 0), finite ones may be of any size.  A row of only -inf, and
  *             one with a NaN or +inf, gives NaN.
  *   fp32 arithmetic, one rounding to bfloat16 (nearest even); the result bits depend neither on `mode` nor on `chunks`.
- *   Between the two launches for long rows `out` holds intermediate values.  A launch has fewer than 2^32 threads: rows beyond
+ *   Between the two launches for long rows `out` holds intermediate values; overlap with `in` is refused there.  A launch has fewer than 2^32 threads: rows beyond
  *   that (2^24 rows of 1800 elements or 2^28 of 8, for instance) go in further launches.
  * Asynchronous on `stream`; never allocates or synchronises.
- * Errors: INVALID_ARG (null, M/N/chunks < 1, chunks > N/8, unknown mode), UNSUPPORTED (N not a
+ * Errors: INVALID_ARG (null, M/N/chunks < 1, chunks > N/8, unknown mode, overlap where rows are long), UNSUPPORTED (N not a
  * multiple of 8 or above 2^24, misaligned pointer), OVERFLOW (M*chunks or a dimension >= 2^31), HIP. */
 int swz_softmax(const void* in, void* out, int64_t M, int64_t N, int chunks, int mode, const swz_params* params,
                 hipStream_t stream);

@@ -394,6 +394,9 @@ static_assert(kRowShapes == 16, "the cases above");
 template <bool SOFTMAX>
 int launch_long_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* beta, uint16_t* out, int M, int N, float eps,
                      const RowPlan& plan, int mode, hipStream_t stream) {
+  // `out` holds the statistics while `in` is read a second time
+  const uintptr_t i = reinterpret_cast<uintptr_t>(in), o = reinterpret_cast<uintptr_t>(out), bytes = (uintptr_t)M * (uintptr_t)N * 2;
+  if (i < o + bytes && o < i + bytes) return SWZ_ERR_INVALID_ARG;
   const int st = launch(swz::row_stats_kernel<SOFTMAX>, dim3((unsigned)((int64_t)M * plan.segs)), dim3(swz::kSegThreads), 0, stream, in, out, M,
                         N, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, mode);
   if (st != SWZ_OK) return st;

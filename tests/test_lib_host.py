@@ -82,6 +82,16 @@ def test_launches_of_2_to_the_32_threads_are_refused():
     assert L.swz_transpose(a, b, 4, (1 << 30) + 4, 4, 64, 2, p, None) == -3
 
 
+def test_long_rows_refuse_overlapping_buffers():
+    # rows above 98304 elements keep statistics in the output while the input is read again: in place they would come out wrong
+    L = swz.lib
+    p = ctypes.byref(swz.SwzParams(0, 0, 0, 0, 8))
+    x, M, N = 1 << 20, 3, 98312
+    for out in (x, x + 16, x + 2 * (M * N - 8), x - 16):
+        assert L.swz_softmax(x, out, M, N, 1, 1, p, None) == -1
+        assert L.swz_layernorm(x, x, x, out, M, N, 1e-5, 1, 1, p, None) == -1
+
+
 def test_group_m_larger_than_grid_is_one_band():
     assert swz.pid_map(5, 7, 8, 1 << 30, 3).tolist() == opm.pid_map(5, 7, 8, 5, 3)
 
