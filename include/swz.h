@@ -132,6 +132,8 @@ int swz_pid_map_persistent_device(int grid_m, int grid_n, int num_xcd, int group
  *   128x256, one workgroup each, and then applies `mode`, num_xcd and the same band height to the grid of sub-tiles.  The
  *   left-over tiles of a large grid's last, partial round may be computed by two or four workgroups each, on the XCD the
  *   map gives the tile unless fewer tiles than XCDs are left.  The bits are those of whole tiles.
+ *   For at most 192 rows and K >= 1024 the workgroups of compute units that have no sub-tile may read A and B ahead of the others, into
+ *   the L2 of their XCD; they compute and write nothing.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null pointer, M/N/K < 1, unknown mode), UNSUPPORTED (other dtype,
  * K or N not a multiple of 8, misaligned pointer), OVERFLOW (tile count >= 2^31 or a
@@ -160,7 +162,7 @@ int swz_gemm_plan(int64_t M, int64_t N, int64_t K, const swz_params* params, swz
  *   workgroups : receives the number of workgroups of the launch.
  *   out        : HOST buffer of out_words >= 4 * *workgroups int32, or null for the count alone; workgroup w (hardware id)
  *                computes rows out[4w] .. + out[4w+2] and columns out[4w+1] .. + out[4w+3] of C, clipped to C, or nothing
- *                (all four 0: an id that leaves at once).  The blocks cover C once.
+ *                (all four 0: an id that leaves at once, or that only reads ahead).  The blocks cover C once.
  * Errors: INVALID_ARG (null workgroups, unknown mode, too small a buffer, M/N/K < 1), and as swz_gemm_ex for sizes and
  * parameters; UNSUPPORTED for the persistent launch (swz_pid_map_persistent). */
 int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_params* params, int32_t* out, int64_t out_words,

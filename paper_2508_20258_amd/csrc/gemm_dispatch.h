@@ -2,6 +2,7 @@
 // shared by the launch (swz_gemm_ex) and by the entry point that reports it (swz_gemm_launch_map).
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 
 #include "../../include/swz.h"
@@ -15,11 +16,16 @@ constexpr int kStageK = 64;    // K extent of a ring stage of the sub-tile kerne
 // chip whose every CU has one (measured: the slope of kernel time over K).  The fixed part of a round (launch or hand-over, the
 // first operands, the stores) is about kRoundNs whatever the shape; a whole tile of gemm_kernel.h takes kWholeRoundNs, as it
 // also runs its look-ahead past the end of K.
-struct SubTile { int bm, bn, wm, wn, stages, stage_ns; };
-constexpr int kSubTileCount = 7;
-constexpr SubTile kSubTiles[kSubTileCount] = {{32, 32, 2, 2, 8, 140},   {32, 64, 2, 2, 6, 160},   {64, 64, 2, 2, 5, 195},  {128, 64, 4, 2, 6, 310},
-                                              {64, 128, 2, 4, 6, 310},  {128, 128, 2, 4, 5, 520}, {128, 256, 2, 4, 3, 950}};
+// fed_ns: what a stage costs where other workgroups fetch ahead (see feed_launch; 0: never).
+struct SubTile { int bm, bn, wm, wn, stages, stage_ns, fed_ns; };
+constexpr int kSubTileCount = 8;
+constexpr int kSoloSubTiles = 7;                       // shapes from here on run with feeders only
+constexpr SubTile kSubTiles[kSubTileCount] = {{32, 32, 2, 2, 8, 140, 90},    {32, 64, 2, 2, 6, 160, 120},  {64, 64, 2, 2, 5, 195, 150},
+                                              {128, 64, 4, 2, 6, 310, 0},    {64, 128, 2, 4, 6, 310, 0}, {128, 128, 2, 4, 5, 520, 0},
+                                              {128, 256, 2, 4, 3, 950, 0},   {64, 32, 2, 2, 8, 0, 130}};
 constexpr int kQuarterPiece = 5, kHalfPiece = 6;       // of a 256x256 tile
+// Bytes of B per XCD that are fetched ahead: an eighth of the L2 (32 x 2048 x 16384: 1/32 and 1/8 24 us, 1/4 27, 1/2 42)
+constexpr int kFeedLead = 1 << 19;
 constexpr int64_t kRoundNs = 2500, kWholeRoundNs = 4000;
 
 // Which sub-tile shape (index into kSubTiles) computes this product fastest, or -1 where the plan's tile as one
@@ -48,7 +54,7 @@ inline int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, 
   }
   best -= best / 20;
   int choice = -1;
-  for (int s = kSubTileCount - 1; s >= 0; --s) {
+  for (int s = kSoloSubTiles - 1; s >= 0; --s) {
     if (kSubTiles[s].bm > r.bm || kSubTiles[s].bn > r.bn) continue;         // a sub-tile is no larger than the plan's tile
     const int64_t e = estimate(rounds(kSubTiles[s].bm, kSubTiles[s].bn, cus), kSubTiles[s].stage_ns);
     if (e < best) {
@@ -66,13 +72,56 @@ struct GemmLaunch {
   int bm, bn, grid_m, grid_n, group_m;   // the grid the map is evaluated on (with `pieces` that of the 256x256 tiles)
   int whole, deal;                    // see swz_tail_piece
   int64_t blocks;                     // workgroups launched
+  int a_feeders, feed_ticks;          // workgroups per XCD that fetch A ahead, ticks of 10 ns per 1024 of K; 0: none fetches ahead
 };
+
+// Few rows and a long K: sub-tiles on at most 9/16 of the compute units, and the others fetch their operands ahead of them into the
+// L2 of their XCD (fetch_ahead in gemm_subtile_kernel.h says why).  false: not this product.
+//   K from 1024 on (2048 columns: K = 512 3.6 us without, 3.8 with; 1024 4.5, 4.5; 1536 5.6, 5.1), M up to 192 (229 x 792 x 16312 60.5, 62.6).
+//   More than 9/16 of the compute units with a sub-tile leave too few to fetch: 11008 columns in 172 sub-tiles 21.1 us without, 22.4 with.  The
+//   columns of an XCD's sub-tiles have to be a run, or every row of sub-tiles would fetch them again: one row, or bands that hold all rows.
+// Shape: the smallest ns a stage, the larger of the sub-tile's own cost, of B at 6.2 TB/s and of what the feeders of one XCD need at 2.4 ns a line.
+// A takes feeders of its own, so many that a line costs each 4 ns (with K = 8192 every row of A is in the same sets: 128 x 1024 x 8192 with one
+// 49 us, two 26, four 14).  Pace: where the sub-tiles are expected, a little slower, as lines that leave the L2 before
+// their use cost a sub-tile the 4 ns this is for (32 x 2048 x 16384 without a pace 44 us, with it 25).
+// Measured on 77 products with M up to 192, log-uniform (kernel time with over without): 0.37 to 1.02, on average 0.79.
+inline bool feed_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, int mode, int cus, GemmLaunch* l) {
+  if (M > 192 || K < 1024 || r.bm != 128 || r.num_xcd > cus) return false;
+  int64_t best = 0;
+  l->sub = -1;
+  for (int s = 0; s < kSubTileCount; ++s) {
+    const SubTile& t = kSubTiles[s];
+    const int64_t gm = (M + t.bm - 1) / t.bm, gn = (N + t.bn - 1) / t.bn;
+    const bool runs = gm == 1 || (swz_mode_renumbers(mode) && swz_mode_grouped(mode) && (int64_t)r.group_m * (r.bm / t.bm) >= gm);
+    if (t.fed_ns == 0 || !runs || 16 * gm * gn > 9 * cus) continue;
+    const int64_t stage = N * 2 % 128 == 0 ? t.fed_ns : t.fed_ns * 23 / 20;        // columns that start inside a line: more lines
+    const int64_t memory = kStageK * N * 2 / 6200, own = stage > memory ? stage : memory;
+    if (stage != t.fed_ns && memory > stage) continue;                             // 3 x 7824 x 3424 13.3 us without, 13.8 with
+    const int64_t a_feeders = (4 * M + own - 1) / own, idle = cus / r.num_xcd - (gm * gn + r.num_xcd - 1) / r.num_xcd;        // of one XCD
+    if (idle < 2 * a_feeders) continue;
+    const int64_t lines = (gn + r.num_xcd - 1) / r.num_xcd * t.bn / 64, feed = kStageK * lines * 12 / 5 / (idle - a_feeders);
+    const int64_t e = feed > own ? feed : own;
+    if (l->sub >= 0 && (e > best || (e == best && t.fed_ns > kSubTiles[l->sub].fed_ns))) continue;
+    const double both = (double)memory / (double)stage, pace = (double)stage * sqrt(sqrt(1.0 + both * both * both * both));
+    best = e;
+    l->sub = s;
+    l->bm = t.bm;
+    l->bn = t.bn;
+    l->grid_m = l->group_m = (int)gm;
+    l->grid_n = (int)gn;
+    l->blocks = cus;
+    l->a_feeders = (int)a_feeders;
+    l->feed_ticks = (int)((pace > (double)e ? pace : (double)e) * 1.6);
+  }
+  return l->sub >= 0;
+}
 
 // r: the resolved plan; cus: compute units.  `free_tile`: the caller left the tile to the library, otherwise a tile is one workgroup.
 // Bounds for anything else: 32-bit source offsets over 64 rows of B, and a grid well inside the 32-bit range whatever the shape.
-inline GemmLaunch gemm_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, int grid_m, int grid_n, int group_m, bool free_tile, int cus) {
-  GemmLaunch l = {-1, false, r.bm, r.bn, grid_m, grid_n, group_m, 0, 1, (int64_t)grid_m * grid_n};
+inline GemmLaunch gemm_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, int grid_m, int grid_n, int group_m, int mode, bool free_tile, int cus) {
+  GemmLaunch l = {-1, false, r.bm, r.bn, grid_m, grid_n, group_m, 0, 1, (int64_t)grid_m * grid_n, 0, 0};
   if (!free_tile || N >= ((int64_t)1 << 24) || l.blocks >= ((int64_t)1 << 16)) return l;
+  if (feed_launch(M, N, K, r, mode, cus, &l)) return l;
   l.sub = choose_subtile(M, N, K, r, cus);
   if (l.sub >= 0) {
     const SubTile& s = kSubTiles[l.sub];
@@ -106,6 +155,7 @@ struct GemmBlock { int32_t row, col, rows, cols; };
 inline GemmBlock gemm_block(const GemmLaunch& l, int num_xcd, int mode, int64_t M, int64_t N, int w) {
   int pm, pn;
   int64_t row, col, rows = l.bm, cols = l.bn;
+  if (!l.pieces && w >= l.grid_m * l.grid_n) return {0, 0, 0, 0};             // fetches ahead
   if (!l.pieces || w < l.whole) {
     swz_decode_tile(w, l.grid_m, l.grid_n, num_xcd, l.group_m, mode, &pm, &pn);
     row = (int64_t)pm * l.bm;

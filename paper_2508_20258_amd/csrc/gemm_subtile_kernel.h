@@ -245,6 +245,74 @@ __device__ __forceinline__ void gemm_subtile(const uint16_t* __restrict__ A, con
   store_wave_tile<TM, TN>(acc, C, M, N, m0 + wm * (TM * 16), n0 + wn * (TN * 16), lane);
 }
 
+// What a workgroup without a sub-tile does: it reads B, or A, in the order of K ahead of the workgroups of its XCD, into LDS that nobody
+// reads, so that their loads find the lines in the L2.  No result depends on it and nobody waits for it.
+// A CU that reads a column stripe gets one line of it from HBM every 3 to 4 ns, whatever the stripe's width, the loads in flight, their
+// order or the number of CUs that do so (plain reads of 8192 rows: 24.5 us, 33 where the pitch is a power of two), and a
+// sub-tile needs all K of them: a product of few rows took K x 4 ns however narrow B is.  From the L2 a line takes about 1 ns, and
+// the CUs without a sub-tile read rows in pieces as wide as their XCD's columns, at 2.3 ns a line each and 6 TB/s together.
+// K can not be cut instead: the order of the sums is part of the contract.  Measured (kernel time, operands not in cache, without -> with):
+//   32x8192x8192   40 -> 26 us (HBM: 21)     32x4096x16384  76 -> 31     64x4096x8192   36 -> 18      8x4096x4096  17 -> 9.0
+//   128x1024x8192  30 -> 13.5                16x2048x8192   32 -> 13.5   32x400x11776   41 -> 22     32x8256x8192  36 -> 31
+// In LDS of 90 KB a workgroup, one to a CU by force, the times are the same.
+template <class S>
+__device__ __forceinline__ void fetch_ahead(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, int M, int N, int K, int grid_m,
+                                            int grid_n, int num_xcd, int mode, int a_feeders, int feed_ticks, unsigned char* smem) {
+  constexpr int CHUNKS = S::BN / 8;                               // 16-byte chunks of a row of B per sub-tile
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int total = grid_m * grid_n, x = (int)blockIdx.x % num_xcd;
+  const int workers = x < total ? (total - 1 - x) / num_xcd + 1 : 0;      // of this XCD, like the feeders
+  const int mine = (int)blockIdx.x / num_xcd - workers, feeders = ((int)gridDim.x - 1 - x) / num_xcd + 1 - workers;
+  if (workers == 0) return;
+  // the columns of sub-tiles on this XCD: first, first + stride, ...
+  const bool run = swz_mode_renumbers(mode);
+  const int s0 = run ? swz_xcd_renumber(x, total, num_xcd) : x;
+  const int first = run ? s0 / grid_m : x, stride = run ? 1 : num_xcd;
+  const int cols = run ? (s0 + workers - 1) / grid_m - first + 1 : workers;
+  const uint32_t dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + (uint32_t)wave * 1024u;
+  const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+  const int lead = kFeedLead / (cols * S::BN * 2);
+  int loads = 0;
+  auto pace = [&](int k) __attribute__((always_inline)) {
+    wait_vmcnt<15>();
+    if ((loads++ & 7) != 0) return;
+    const uint64_t due = k > lead ? t0 + (uint64_t)(uint32_t)(k - lead) * (uint32_t)feed_ticks / 1024u : t0;
+    while (__builtin_amdgcn_s_memrealtime() < due) __builtin_amdgcn_s_sleep(4);
+  };
+  if (mine >= feeders - a_feeders) {                              // A: 256 of K of two rows a load
+    const int pairs = (M + 1) / 2, spans = (K + 255) / 256;
+    for (int f = (mine - (feeders - a_feeders)) * S::NW + wave; f < pairs * spans; f += a_feeders * S::NW) {
+      const int span = f / pairs;
+      int row = 2 * (f - span * pairs) + (lane >> 5), k = span * 256 + (lane & 31) * 8;
+      if (row >= M) row = M - 1;
+      if (k >= K) k = K - 8;
+      pace(span * 256);
+      load_to_lds(A + (size_t)row * K + k, dst);
+    }
+  } else {
+    // B: 64 chunks a load, row by row of the XCD's columns.  The loads of all waves together are whole rows, so that a wave's lanes keep their columns
+    // and a load is one addition: with the columns found anew for each the feeders brought 3.5 TB/s.
+    const int row_chunks = cols * CHUNKS;
+    int unit = cols;
+    for (int n = 64 / CHUNKS; n > 1 && unit % 2 == 0; n /= 2) unit /= 2;
+    const int waves = (feeders - a_feeders) * S::NW, team = waves - waves % unit, q = mine * S::NW + wave;
+    if (q >= team) return;
+    int k = q * 64 / row_chunks;
+    const int c0 = q * 64 - k * row_chunks, e = c0 + lane, lrow = e / row_chunks, c = e - lrow * row_chunks;
+    const int col = (first + c / CHUNKS * stride) * S::BN + c % CHUNKS * 8;
+    const uint32_t off = (uint32_t)lrow * (uint32_t)N * 2u + (uint32_t)(col < N ? col : N - 8) * 2u;
+    const int rows = (c0 + 63) / row_chunks + 1, step = team * 64 / row_chunks;
+    const unsigned char* src = reinterpret_cast<const unsigned char*>(B) + (size_t)k * N * 2;
+    const size_t src_step = (size_t)step * N * 2;
+    for (; k + rows <= K; k += step) {
+      pace(k);
+      load_to_lds_base_off(src, off, dst);
+      src += src_step;
+    }
+  }
+  wait_vmcnt<0>();
+}
+
 // One workgroup per sub-tile.  The raster and the renumbering are those of a tile grid, over the grid of sub-tiles
 // (bands of as many rows of C): every XCD gets its share of them to within one.  Dealing whole tiles of the plan instead, with their
 // sub-tiles on one XCD, left some XCDs with more than 32 for their 32 CUs, and sub-tiles beyond C that leave at once
@@ -252,8 +320,13 @@ __device__ __forceinline__ void gemm_subtile(const uint16_t* __restrict__ A, con
 template <class S>
 __global__ __launch_bounds__(S::NT) void gemm_bf16_subtile_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                                   uint16_t* __restrict__ C, int M, int N, int K, int grid_m,
-                                                                  int grid_n, int num_xcd, int group_m, int mode) {
+                                                                  int grid_n, int num_xcd, int group_m, int mode, int a_feeders,
+                                                                  int feed_ticks) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x >= grid_m * grid_n) {                       // uniform
+    fetch_ahead<S>(A, B, M, N, K, grid_m, grid_n, num_xcd, mode, a_feeders, feed_ticks, smem);
+    return;
+  }
   int pm, pn;
   swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
   gemm_subtile<S>(A, B, C, M, N, K, pm * S::BM, pn * S::BN, smem);

@@ -180,7 +180,8 @@ int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, c
   const int st = allow_lds(reinterpret_cast<const void*>(kernel), S::LDS_BYTES, I);
   if (st != SWZ_OK) return st;
   return launch(kernel, dim3((unsigned)l.blocks), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
-                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, l.grid_m, l.grid_n, num_xcd, l.group_m, mode);
+                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, l.grid_m, l.grid_n, num_xcd, l.group_m, mode,
+                l.a_feeders, l.feed_ticks);
 }
 
 template <int I>
@@ -629,7 +630,7 @@ int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_par
   if (r.persistent) return SWZ_ERR_UNSUPPORTED;
   DeviceFacts f;
   const int cus = tile_is_free(params) && query_device(&f) == SWZ_OK && f.cus > 0 ? f.cus : kWholeCus;
-  const swz::GemmLaunch l = swz::gemm_launch(M, N, K, r, grid_m, grid_n, group_m, tile_is_free(params), cus);
+  const swz::GemmLaunch l = swz::gemm_launch(M, N, K, r, grid_m, grid_n, group_m, mode, tile_is_free(params), cus);
   if (out != nullptr && out_words < 4 * l.blocks) return SWZ_ERR_INVALID_ARG;
   *workgroups = l.blocks;
   for (int64_t w = 0; out != nullptr && w < l.blocks; ++w) {
@@ -653,7 +654,7 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
     const int qs = query_device(&f);
     if (qs != SWZ_OK) return qs;
     const int m = (int)M, n = (int)N, k = (int)K;
-    const swz::GemmLaunch l = swz::gemm_launch(M, N, K, r, grid_m, grid_n, group_m, true, f.cus > 0 ? f.cus : kWholeCus);
+    const swz::GemmLaunch l = swz::gemm_launch(M, N, K, r, grid_m, grid_n, group_m, mode, true, f.cus > 0 ? f.cus : kWholeCus);
     if (l.pieces)
       return l.sub == swz::kQuarterPiece ? launch_pieces<swz::kQuarterPiece>(A, B, C, m, n, k, l, r.num_xcd, mode, stream)
                                          : launch_pieces<swz::kHalfPiece>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
@@ -665,6 +666,7 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
       case 4: return launch_subtile<4>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
       case 5: return launch_subtile<5>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
       case 6: return launch_subtile<6>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 7: return launch_subtile<7>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
       default: break;                                   // whole tiles
     }
   }

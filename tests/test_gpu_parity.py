@@ -699,3 +699,21 @@ def test_partial_last_round_in_pieces_gives_the_bits_of_whole_tiles(swz, M, N):
             torch.cuda.synchronize()
             assert torch.equal(c[:M].view(torch.int16), want.view(torch.int16)), (M, N, K, mode, params)
             assert torch.isnan(c[M]).all()
+
+
+# workgroups that fetch ahead: one sub-tile row and several, columns and rows that do not fill one, rows of B that start inside a line, XCDs without a
+# sub-tile, XCDs with different numbers of columns (T = 129, 17), K of no whole load; every byte a feeder reads lies inside A or B
+@pytest.mark.parametrize("M,N,K", [(1, 8, 1024), (32, 8192, 1056), (8, 4104, 1112), (33, 544, 2056), (64, 2056, 1024), (100, 1032, 1032), (192, 1000, 1544),
+                                   (129, 64, 8192), (5, 520, 16376)])
+def test_fed_subtiles_give_the_bits_of_whole_tiles(swz, M, N, K):
+    assert (swz.gemm_launch_map(M, N, K)[:, 2] == 0).any()
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+    b = torch.randn((K, N), device="cuda", generator=g).to(torch.bfloat16)
+    want = swz.gemm(a, b, mode=0, bm=256, bn=256)
+    for mode, params in [(2, {}), (0, {}), (1, dict(num_xcd=3)), (3, {}), (6, dict(group_m=1)), (2, dict(num_xcd=255)), (2, dict(num_xcd=1))]:
+        c = torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        swz.gemm(a, b, c[:M], mode=mode, **params)
+        torch.cuda.synchronize()
+        assert torch.equal(c[:M].view(torch.int16), want.view(torch.int16)), (M, N, K, mode, params)
+        assert torch.isnan(c[M]).all()
