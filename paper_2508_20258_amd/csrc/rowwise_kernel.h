@@ -199,18 +199,20 @@ __device__ __forceinline__ float held_sum(const rw_u32x4* held, int first, int s
   return s;
 }
 
+__device__ __forceinline__ float dev8(const rw_u32x4& v, float mean) {
+  float x[8];
+  rw_unpack(v, x);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = (x[e] - mean) * (x[e] - mean);
+  return rw_sum8(x);
+}
+
 template <int KEEP>
 __device__ __forceinline__ float held_dev(const rw_u32x4* held, int first, int stride, int nv, float mean) {
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < KEEP; ++i)
-    if (first + i * stride < nv) {
-      float x[8];
-      rw_unpack(held[i], x);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = (x[e] - mean) * (x[e] - mean);
-      s += rw_sum8(x);
-    }
+    if (first + i * stride < nv) s += dev8(held[i], mean);
   return s;
 }
 
@@ -328,6 +330,152 @@ __global__ __launch_bounds__(row_block(TPR)) void layernorm_rows_kernel(const ui
       if constexpr (EARLY) __builtin_nontemporal_store(ln_vector(held[i], gv[i], bv[i], mean, rstd), outp + v);
       else __builtin_nontemporal_store(ln_vector(held[i], gp[v], bp[v], mean, rstd), outp + v);
     }
+}
+
+// ---- the same rows, bit for bit, where there are more of them than compute units ----
+
+// A row as a buffer: what is loaded past its end is 0, what is stored there is dropped, and no access needs a branch.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_view(const uint16_t* p, int N, bool there = true) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, there ? N * 2 : 0, 0x00027000);
+}
+constexpr int kNonTemporal = 2;
+template <int STRIDE, int AUX>
+__device__ __forceinline__ rw_u32x4 view_load(__amdgpu_buffer_rsrc_t r, int i) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, threadIdx.x * 16u + (uint32_t)i * (STRIDE * 16u), 0, AUX);
+}
+template <int STRIDE>
+__device__ __forceinline__ void view_store(const rw_u32x4& v, __amdgpu_buffer_rsrc_t r, int i) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, threadIdx.x * 16u + (uint32_t)i * (STRIDE * 16u), 0, kNonTemporal);
+}
+// The next pass over v widens it again: its eight floats kept from the last pass would take twice its registers.
+__device__ __forceinline__ void anew(rw_u32x4& v) { asm volatile("" : "+v"(v)); }
+
+// Rows of more than 32768 elements.  With 1024 threads a row fills the registers of a compute unit and its load, its arithmetic and its stores
+// follow each other; 512 threads with twice the vectors, kept as they came, leave room for a second row beside it (128 registers a thread).  Thread
+// t holds the vectors of threads t and t + 512 of the other form and sums them apart, which gives the same sums.  Scheduling
+// barriers keep the compiler from widening several vectors at once.
+//     softmax    1024 x 65536  54 -> 47 us    300 x 65536  21 -> 16.5   1024 x 49152  42 -> 37    4096 x 65536  192 -> 183
+//     layernorm  4096 x 36000 122 -> 111      8000 x 32776 219 -> 198   1024 x 49152  43 -> 40.5
+// Not kept: the next row fetched into LDS meanwhile (55 us at 1024 x 65536: the waves wait to issue the loads and stores), 64 registers and 1024
+// threads (spills).
+constexpr int kWideThreads = 512;
+template <class Op>
+__device__ __forceinline__ float wide_reduce(float even, float odd, Op op, float* slots) {
+  even = rw_reduce_lanes<64>(even, op);
+  odd = rw_reduce_lanes<64>(odd, op);
+  const int wave = (int)threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    slots[wave] = even;
+    slots[wave + 8] = odd;
+  }
+  __syncthreads();
+  float g[kMaxWaves];
+#pragma unroll
+  for (int w = 0; w < kMaxWaves; ++w) g[w] = slots[w];
+#pragma unroll
+  for (int n = kMaxWaves; n > 1; n /= 2)
+#pragma unroll
+    for (int w = 0; w < n / 2; ++w) g[w] = op(g[2 * w], g[2 * w + 1]);
+  return g[0];
+}
+
+// KEEP vectors a thread, the first SURE of which are real in every row of this length.
+template <int KEEP, int SURE>
+__global__ __launch_bounds__(kWideThreads, 4) void softmax_wide_rows_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out, int N) {
+  __shared__ float slots[2][kMaxWaves];
+  const int nv = N >> 3;
+  const auto src = row_view(in + (size_t)blockIdx.x * N, N), dst = row_view(out + (size_t)blockIdx.x * N, N);
+  rw_u32x4 held[KEEP];
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) held[i] = view_load<kWideThreads, kNonTemporal>(src, i);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = SURE; i < KEEP; ++i)
+    if ((int)threadIdx.x + i * kWideThreads >= nv) held[i] = rw_u32x4{kNegInfPair, kNegInfPair, kNegInfPair, kNegInfPair};
+  float m = -FLT_MAX;
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    m = fmaxf(m, held_max<1>(held + i));
+    anew(held[i]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const SoftScale base(rw_reduce_group<kWideThreads>(m, RwMax{}, slots[0]));
+  constexpr int KEPT = KEEP <= 12 ? KEEP : (88 - 4 * KEEP) / 4;      // exponentials there are registers for; the others are computed twice
+  static_assert(KEPT > 0, "16 vectors at most");
+  float p[KEPT][8], s[2] = {0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    float q[8];
+    soft_exps(held[i], base, q);
+    s[i & 1] += rw_sum8(q);
+    if (i < KEPT) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p[i < KEPT ? i : 0][e] = q[e];
+    } else {
+      anew(held[i]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const float inv = 1.0f / wide_reduce(s[0], s[1], RwSum{}, slots[1]);
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    float q[8];
+    if (i >= KEPT) soft_exps(held[i], base, q);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) q[e] = (i < KEPT ? p[i < KEPT ? i : 0][e] : q[e]) * inv;
+    view_store<kWideThreads>(rw_pack(q), dst, i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+template <int KEEP, int SURE>
+__global__ __launch_bounds__(kWideThreads, 4) void layernorm_wide_rows_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma,
+                                                                              const uint16_t* __restrict__ beta, uint16_t* __restrict__ out, int N, float eps) {
+  __shared__ float slots[2][kMaxWaves];
+  const int nv = N >> 3;
+  const auto src = row_view(in + (size_t)blockIdx.x * N, N), dst = row_view(out + (size_t)blockIdx.x * N, N);
+  const auto gsrc = row_view(gamma, N), bsrc = row_view(beta, N);
+  rw_u32x4 held[KEEP];
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) held[i] = view_load<kWideThreads, kNonTemporal>(src, i);
+  __builtin_amdgcn_sched_barrier(0);
+  float s[2] = {0.f, 0.f}, d[2] = {0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {                               // zeros past the row's end
+    float x[8];
+    rw_unpack(held[i], x);
+    s[i & 1] = __builtin_fmaf(rw_sum8(x), 1.f / kSumUnit, s[i & 1]);
+    anew(held[i]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const float mean = mean_of(wide_reduce(s[0], s[1], RwSum{}, slots[0]), N);
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    const float q = dev8(held[i], mean);
+    d[i & 1] += i < SURE || (int)threadIdx.x + i * kWideThreads < nv ? q : 0.f;
+    anew(held[i]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  constexpr int AHEAD = KEEP <= 10 ? 6 : 5;                      // gamma and beta there are registers for
+  static_assert(KEEP <= 12, "registers");
+  rw_u32x4 gv[AHEAD], bv[AHEAD];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) {
+    gv[i] = view_load<kWideThreads, 0>(gsrc, i);
+    bv[i] = view_load<kWideThreads, 0>(bsrc, i);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const float rstd = 1.0f / sqrtf(wide_reduce(d[0], d[1], RwSum{}, slots[1]) / (float)N + eps);
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    const rw_u32x4 y = ln_vector(held[i], gv[i % AHEAD], bv[i % AHEAD], mean, rstd);
+    if (i + AHEAD < KEEP) {
+      gv[i % AHEAD] = view_load<kWideThreads, 0>(gsrc, i + AHEAD);
+      bv[i % AHEAD] = view_load<kWideThreads, 0>(bsrc, i + AHEAD);
+    }
+    view_store<kWideThreads>(y, dst, i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 // ---- rows longer than a workgroup holds: two launches ----

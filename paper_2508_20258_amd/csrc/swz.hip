@@ -300,7 +300,7 @@ constexpr RowShape kLayernormShapes[kRowShapes] = {
 // How the two row-wise entry points launch: index into the kernel's table of shapes (-1: longer than a
 // workgroup holds, two launches, segs x chunks per row), mapping parameters.
 struct RowPlan {
-  int shape, grid_m, num_xcd, group_m, segs, chunks;
+  int shape, grid_m, num_xcd, group_m, segs, chunks, cus;
 };
 
 int resolve_rows(int64_t M, int64_t N, int chunks, int mode, const swz_params* params, const RowShape* shapes, RowPlan* plan) {
@@ -318,10 +318,11 @@ int resolve_rows(int64_t M, int64_t N, int chunks, int mode, const swz_params* p
     if (params->group_m > 0) plan->group_m = params->group_m;
     plan->num_xcd = params->num_xcd;
   }
+  DeviceFacts f;
+  const int known = query_device(&f);
+  plan->cus = known == SWZ_OK && f.cus > 0 ? f.cus : kWholeCus;
   if (plan->num_xcd == 0) {
-    DeviceFacts f;
-    const int st = query_device(&f);
-    if (st != SWZ_OK) return st;
+    if (known != SWZ_OK) return known;
     plan->num_xcd = f.num_xcd;
     if (plan->num_xcd == 0) return SWZ_ERR_UNSUPPORTED;
   }
@@ -362,6 +363,12 @@ bool soft_rows_mapped(int64_t M, int64_t N) { return N >= 16128 && M * N >= ((in
 
 template <int KEEP, int TPR>
 int launch_softmax_rows(const uint16_t* in, uint16_t* out, int64_t M, int N, const RowPlan& plan, int mode, hipStream_t stream) {
+  // Rows of 40968 to 65536 elements: two to a compute unit.  With many rows the one-row form drifts into overlap by itself: 4096 x 65528 202 us with
+  // 1024 threads, 205 with 512 (2048 x 65536 101, 95; 4096 x 41000 132, 120); shorter rows fit twice in either form (4096 x 36000 100 us, 104).
+  if constexpr (TPR == 1024 && (KEEP == 6 || KEEP == 8)) {
+    if (M > plan.cus && M <= (KEEP == 6 ? 16 : 8) * plan.cus)
+      return launch(swz::softmax_wide_rows_kernel<2 * KEEP, KEEP == 6 ? 10 : 12>, dim3((unsigned)M), dim3(swz::kWideThreads), 0, stream, in, out, N);
+  }
   if (!soft_rows_mapped(M, N)) mode = SWZ_MODE_RR;
   return for_row_parts(plan, TPR, M, [&](int64_t row, int rows, int groups) {
     const int group_m = plan.group_m < groups ? plan.group_m : groups;
@@ -373,6 +380,14 @@ int launch_softmax_rows(const uint16_t* in, uint16_t* out, int64_t M, int N, con
 template <int KEEP, int TPR>
 int launch_layernorm_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* beta, uint16_t* out, int64_t M, int N, float eps,
                           const RowPlan& plan, hipStream_t stream) {
+  // Rows of 32776 to 49152 elements: two to a compute unit (from there to 65536 elements it is level: 1024 x 65536 55 us either way)
+  if constexpr (TPR == 1024 && (KEEP == 5 || KEEP == 6)) {
+    if (M > plan.cus)
+      return for_row_parts(plan, swz::kWideThreads, M, [&](int64_t row, int rows, int groups) {
+        return launch(swz::layernorm_wide_rows_kernel<2 * KEEP, 2 * KEEP - 2>, dim3((unsigned)groups), dim3(swz::kWideThreads), 0, stream, in + row * N,
+                      gamma, beta, out + row * N, N, eps);
+      });
+  }
   return for_row_parts(plan, TPR, M, [&](int64_t row, int rows, int groups) {
     return launch(swz::layernorm_rows_kernel<KEEP, TPR>, dim3((unsigned)groups), dim3(swz::row_block(TPR)), 0, stream, in + row * N,
                   gamma, beta, out + row * N, rows, N, eps);

@@ -266,3 +266,61 @@ def test_more_rows_than_a_launch_has_threads_for(swz, op, M, N):
     assert torch.equal(y[M // 4096 * 4096:], want[:M % 4096])
     del y, whole
     torch.cuda.empty_cache()                        # up to 140 GB
+
+
+# more rows than compute units: two long rows to a compute unit (softmax from 40968 to 65536 elements and up to 8 or 16 rows to each, layer normalisation from
+# 32776 to 49152), row after row (layer normalisation to 8192, one and two workgroups to each).  The bits are those of the same rows in calls with few.
+@pytest.mark.parametrize("op,M,N", [("softmax", 258, 40968), ("softmax", 300, 49152), ("softmax", 257, 49160), ("softmax", 261, 65536), ("softmax", 4096, 41000), ("softmax", 2049, 49160),
+                                    ("layernorm", 258, 32776), ("layernorm", 300, 40960), ("layernorm", 257, 40968), ("layernorm", 261, 49152),
+                                    ("layernorm", 513, 6000), ("layernorm", 1100, 8192), ("layernorm", 4800, 7008), ("layernorm", 1025, 3400),
+                                    ("layernorm", 1537, 4096), ("layernorm", 513, 8192)])
+def test_many_rows_give_the_bits_of_few(swz, op, M, N):
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    x = (torch.randn((M, N), device="cuda", generator=g) * 2 + 0.5).to(torch.bfloat16)
+    gamma, beta = (torch.randn((N,), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    if op == "softmax":
+        x[M // 2] = float("-inf")
+        x[M - 1, N - 1] = 3e38
+        x[0, 0] = float("nan")
+
+    def call(rows, out):
+        return swz.softmax(rows, out) if op == "softmax" else swz.layernorm(rows, gamma, beta, out)
+
+    buf = torch.full((M + 2, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    call(x, buf[1:M + 1])
+    torch.cuda.synchronize()
+    assert (buf[0] == 7).all() and (buf[M + 1] == 7).all()
+    for r in range(0, M, 250):
+        want = call(x[r:r + 250], torch.empty_like(x[r:r + 250]))
+        assert torch.equal(buf[1 + r:1 + r + len(want)].view(torch.int16), want.view(torch.int16)), r
+    inplace = x.clone()
+    call(inplace, inplace)
+    assert torch.equal(inplace.view(torch.int16), buf[1:M + 1].view(torch.int16))
+
+
+# the maximum of a row: rows of negative numbers only, zeros of both signs, infinities and NaNs of both signs, every place in a vector
+@pytest.mark.parametrize("N", [64, 264, 2048, 33000, 49152])
+def test_softmax_maximum_of_every_sign(swz, N):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    base = -(torch.rand((40, N), device="cuda", generator=g) * 60 + 1)
+    rows = base.clone()
+    for r in range(8):
+        rows[r, (N // 8 // 2) * 8 + r] = -0.5                       # the largest of a negative row
+        rows[8 + r, N - 8 + r] = -0.0
+        rows[16 + r, r] = 30.0
+        rows[24 + r, r] = float("-inf")
+    rows[32, 3], rows[33, 4] = float("inf"), float("nan")
+    rows[34] = float("-inf")
+    rows[35] = -0.0
+    rows[36, 1] = 0.0
+    rows[36, 2] = -0.0
+    x = rows.to(torch.bfloat16)
+    bits = x.view(torch.int16)
+    bits[37, 6] = -64                                               # 0xFFC0, a NaN with its sign set
+    bits[38, :] = -64
+    x = x.repeat(8, 1)                                              # more rows than compute units
+    y = swz.softmax(x).double().cpu()
+    want = torch.softmax(x.double(), dim=1).cpu()
+    assert torch.equal(torch.isnan(y), torch.isnan(want))
+    ok = ~torch.isnan(want)
+    assert ((y - want).abs()[ok] <= 2.0 ** -8 * want[ok] + 1e-30).all()
