@@ -478,6 +478,55 @@ __global__ __launch_bounds__(kWideThreads, 4) void layernorm_wide_rows_kernel(co
   }
 }
 
+// Layer normalisation of rows of up to 8192 elements: a workgroup takes row after row, gamma and beta stay in its registers (they were two thirds of
+// what came out of the L2) and the next row is on its way while one is normalised.  One or two workgroups a compute unit are enough.
+//     8192 x 8192  50 -> 45 us    12000 x 7200  70 -> 60    2100 x 8192  16.7 -> 14.9    60000 x 4096  175 -> 163    1100 x 8192  11.1 -> 9.0
+constexpr int kLoopThreads = 256;
+template <int KEEP>
+__global__ __launch_bounds__(kLoopThreads, 4) void layernorm_loop_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma,
+                                                                         const uint16_t* __restrict__ beta, uint16_t* __restrict__ out, int M, int N, float eps) {
+  __shared__ float slots[2][kMaxWaves];
+  const int nv = N >> 3, tid = (int)threadIdx.x, step = (int)gridDim.x;
+  rw_u32x4 next[KEEP], gv[KEEP], bv[KEEP];
+  auto load = [&](int row) __attribute__((always_inline)) {      // no traffic past the last row
+    const auto r = row_view(in + (size_t)(row < M ? row : 0) * N, N, row < M);
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) next[i] = view_load<kLoopThreads, kNonTemporal>(r, i);
+  };
+  int row = (int)blockIdx.x;
+  load(row);
+  const auto gsrc = row_view(gamma, N), bsrc = row_view(beta, N);
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    gv[i] = view_load<kLoopThreads, 0>(gsrc, i);
+    bv[i] = view_load<kLoopThreads, 0>(bsrc, i);
+  }
+  // all of it waited for here: a wait at the top of the loop would count as if no stores were behind the loads
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) asm volatile("" : "+v"(gv[i]), "+v"(bv[i]), "+v"(next[i]));
+  for (; row < M; row += step) {
+    rw_u32x4 held[KEEP];
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) held[i] = next[i];
+    load(row + step);
+    const float mean = mean_of(rw_reduce_group<kLoopThreads>(held_sum<KEEP>(held, 0, 0, 1), RwSum{}, slots[0]), N);
+    float d = 0.f;
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+      const float q = dev8(held[i], mean);
+      d += tid + i * kLoopThreads < nv ? q : 0.f;
+    }
+    const float rstd = 1.0f / sqrtf(rw_reduce_group<kLoopThreads>(d, RwSum{}, slots[1]) / (float)N + eps);
+    const auto dst = row_view(out + (size_t)row * N, N);
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+      anew(gv[i]);                                               // widened ahead of the loop they would take twice the registers
+      anew(bv[i]);
+      view_store<kLoopThreads>(ln_vector(held[i], gv[i], bv[i], mean, rstd), dst, i);
+    }
+  }
+}
+
 // ---- rows longer than a workgroup holds: two launches ----
 
 // First vector of chunk c of a row of nv vectors cut into `chunks` chunks (chunk c ends where c + 1 begins).

@@ -388,6 +388,16 @@ int launch_layernorm_rows(const uint16_t* in, const uint16_t* gamma, const uint1
                       gamma, beta, out + row * N, N, eps);
       });
   }
+  // Row after row where most of the KEEP x 256 vectors are real and every workgroup has a few.  One against two workgroups a compute unit: 5000 x 7200
+  // 27.2 us, 27.7; 12000 x 8192 64.9, 67.2; but 2100 x 8192 15.3, 14.9 and 12000 x 6400 55.5, 54.0.  Without the loop 800 x 3600 5.1 us,
+  // with it 5.2; 1100 x 3600 5.7, 5.7; 1100 x 4800 6.5, 6.9; 800 x 6400 6.7, 6.4.
+  if constexpr (TPR == swz::kLoopThreads && (KEEP == 2 || KEEP == 4)) {
+    if (KEEP == 4 ? N >= 6000 && M > 2 * plan.cus : N >= 3400 && M > 4 * plan.cus) {
+      const int64_t per_cu = N >= 7000 && M * N >= ((int64_t)1 << 25) ? 1 : 2;
+      return launch(swz::layernorm_loop_kernel<KEEP>, dim3((unsigned)(per_cu * plan.cus)), dim3(swz::kLoopThreads), 0, stream, in, gamma, beta, out, (int)M,
+                    N, eps);
+    }
+  }
   return for_row_parts(plan, TPR, M, [&](int64_t row, int rows, int groups) {
     return launch(swz::layernorm_rows_kernel<KEEP, TPR>, dim3((unsigned)groups), dim3(swz::row_block(TPR)), 0, stream, in + row * N,
                   gamma, beta, out + row * N, rows, N, eps);
