@@ -543,12 +543,14 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   // 2 B, 34 MiB moved, 11.5 against 9.9).
   const bool part_lines = ((M * elem_bytes) & 127) != 0 || (reinterpret_cast<uintptr_t>(out) & 127) != 0;
   if (tile == 64 && part_lines && M < ((int64_t)1 << 30) && 2 * M * N * elem_bytes >= ((int64_t)16 << 20)) {
-    const dim3 grid((unsigned)(gm * gn)), block(256);
+    const int rows = swz::lines_rows(elem_bytes), blocks_m = (int)((M + rows - 1) / rows);
+    const dim3 grid((unsigned)(blocks_m * gn)), block(swz::kLinesThreads);
+    if (group_m > blocks_m) group_m = blocks_m;
     if (elem_bytes == 2)
       return launch(swz::transpose_lines_kernel<uint16_t>, grid, block, 0, stream, static_cast<const uint16_t*>(in),
-                    static_cast<uint16_t*>(out), (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode);
+                    static_cast<uint16_t*>(out), (int)M, (int)N, blocks_m, (int)gn, num_xcd, group_m, mode);
     return launch(swz::transpose_lines_kernel<uint32_t>, grid, block, 0, stream, static_cast<const uint32_t*>(in),
-                  static_cast<uint32_t*>(out), (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode);
+                  static_cast<uint32_t*>(out), (int)M, (int)N, blocks_m, (int)gn, num_xcd, group_m, mode);
   }
   if (elem_bytes == 4) {
     if (M * N * 8 > kMemorySideCacheBytes)

@@ -197,36 +197,41 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
 
 // The same transpose where rows of `out` do not start on 128-byte lines (M * sizeof(T) no multiple of 128, or `out` itself
 // off a line).  A 64-wide tile of the other kernels then writes two part lines per row, which reach memory in two
-// pieces.  Here the 64 columns a workgroup
+// pieces.  Here a workgroup takes BM rows of `in` x 64 columns, and the BM elements it
 // writes of row n of `out` are shifted left by s(n), the elements by which the row overhangs a line, so that it writes whole lines: row n
-// gets columns [64 pm - s(n), 64 pm - s(n) + 64), the last tile of the row everything up to M (one line more at
-// most).  The tile of `in` grows by the E - 1 rows above it (E elements fill a line), which the neighbouring tile row reads too:
-// 1.5 times the input for four bytes, twice for two, in all.  1.28 and 1.37 times the input cross the fabric under the default mapping (FETCH_SIZE
-// at 5800 x 5804 x 4 B and 10000 x 7000 x 2 B; 1.13 and 1.12 without the skew), the L2 serves the rest.  s(n) differs from row
+// gets columns [BM pm - s(n), BM pm - s(n) + BM), the last block of the row everything up to M (one line more at
+// most).  Its block of `in` grows by the E - 1 rows above it (E elements fill a line), which the block above reads too: 128 rows and 31
+// more of four bytes, 256 and 63 of two, a quarter more than the input in all, part of which the L2 serves.  s(n) differs from row
 // to row, so a lane gathers its 16 bytes element by element, four rows or eight rows of the tile at a column: the
 // transposing LDS read takes the same rows for 4 columns.
 // A wave instruction stores 8 rows x 8 chunks = 8 whole lines: lane l takes row l / 8, chunk l % 8.
 // LDS: 16-byte chunk c of tile row r in slot c ^ key(r); key steps with the chunk of rows a lane gathers, so that the 8
 // chunks of one column lie in different banks whatever their shift.  The stores are streaming ones at every size: nothing
 // is left to merge in the L2.
-// Bound by HBM.  Measured, matrices not in cache, tiles on line-blind boundaries -> these (us; GB/s of the matrix read and written):
-//     two bytes   10000 x 7000  102 -> 74 (3780)    10000 x 7040  94 -> 62 (4540)    8200 x 8208   110 -> 67 (4020)
-//     four bytes   5800 x 5804   82 -> 59 (4560)     5800 x 5824  80 -> 58 (4660)   15764 x 8092   363 -> 212 (4810)
-// against 60 us where both pitches are whole lines (10048 x 7040) and no shift is needed.
+// Bound by HBM and the rows read twice.  Measured, matrices not in cache, 64 rows and 256 threads -> these (us; GB/s of the matrix read and written):
+//     two bytes   10000 x 7000  75 -> 60 (4670)    8200 x 8208  67 -> 57 (4720)    30000 x 1544   49 -> 41 (4560)    3000 x 3000  10.7 -> 9.0
+//     four bytes   5800 x 5804  60 -> 56 (4810)    200 x 20000  9.5 -> 8.6         15764 x 8092  214 -> 204 (5000)   2000 x 2004   8.1 -> 7.8
+// (tiles on line-blind boundaries 102, 110 and 82, 363 us; 60 us where both pitches are whole lines, 10048 x 7040.)  256 rows of four bytes leave a
+// compute unit two workgroups: 58 us at 5800 x 5804; with 256 threads 77.  128 columns: 60 us there, 61 at 10000 x 7000.
+constexpr int kLinesThreads = 512;
+__host__ __device__ constexpr int lines_rows(int elem_bytes) { return elem_bytes == 2 ? 256 : 128; }
+
 template <class T>
-__global__ __launch_bounds__(256) void transpose_lines_kernel(const T* __restrict__ in, T* __restrict__ out, int M, int N, int grid_m,
+__global__ __launch_bounds__(kLinesThreads) void transpose_lines_kernel(const T* __restrict__ in, T* __restrict__ out, int M, int N, int grid_m,
                                                               int grid_n, int num_xcd, int group_m, int mode) {
-  constexpr int TILE = 64, CH = 16 / (int)sizeof(T), E = 128 / (int)sizeof(T);       // elements per chunk, per line
-  constexpr int SLOTS = TILE / CH, ROWS = TILE + E, ROW_BYTES = TILE * (int)sizeof(T), LINES = TILE / E;
+  constexpr int TILE = 64, BM = lines_rows((int)sizeof(T)), NT = kLinesThreads;
+  constexpr int CH = 16 / (int)sizeof(T), E = 128 / (int)sizeof(T);                  // elements per chunk, per line
+  constexpr int SLOTS = TILE / CH, ROWS = BM + E, ROW_BYTES = TILE * (int)sizeof(T), LINES = BM / E;
   __shared__ __attribute__((aligned(16))) unsigned char tile[ROWS * ROW_BYTES];
   int pm, pn;
   swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
-  const int m0 = pm * TILE - E, n0 = pn * TILE;                  // first row of `in` in the tile, first column
+  const int m0 = pm * BM - E, n0 = pn * TILE;                    // first row of `in` in the tile, first column
   const int tid = threadIdx.x;
   auto key = [](int r) { return sizeof(T) == 2 ? (r >> 3) & 7 : ((r >> 2) & 7) << 1; };
+  static_assert(ROWS * SLOTS % NT == 0, "whole loads");
 #pragma unroll
-  for (int i = 0; i < ROWS * SLOTS / 256; ++i) {
-    const int q = tid + 256 * i, r = q / SLOTS, c = q % SLOTS;
+  for (int i = 0; i < ROWS * SLOTS / NT; ++i) {
+    const int q = tid + NT * i, r = q / SLOTS, c = q % SLOTS;
     const int m = m0 + r, n = n0 + c * CH;
     t_u32x4 v = {0u, 0u, 0u, 0u};
     if (m >= 0 && m < M && n < N) v = *reinterpret_cast<const t_u32x4*>(in + (size_t)m * N + n);
@@ -238,7 +243,7 @@ __global__ __launch_bounds__(256) void transpose_lines_kernel(const T* __restric
   const uint32_t base = (uint32_t)(reinterpret_cast<uintptr_t>(out) / sizeof(T));
   const int lines = pm == grid_m - 1 ? LINES + 1 : LINES;        // uniform
 #pragma unroll
-  for (int jb = wave; jb < TILE / 8; jb += 4) {
+  for (int jb = wave; jb < TILE / 8; jb += NT / 64) {
     const int col = 8 * jb + jj, n = n0 + col;                   // tile column = row of out
     const int shift = (int)((base + (uint32_t)n * (uint32_t)M) % (uint32_t)E);       // E divides 2^32
     for (int h = 0; h < lines; ++h) {

@@ -664,7 +664,9 @@ def test_subtiles_give_the_bits_of_whole_tiles(swz, M, N):
     (2, 8, 600000, 0), (2, 56, 90008, 0), (2, 72, 60000, 0), (2, 120, 40000, 0), (2, 136, 40064, 0), (2, 2040, 2064, 0),
     (2, 4104, 1032, 0), (2, 64, 70000, 8), (2, 2048, 2048, 56), (2, 2056, 2048, 24),
     (4, 4, 600000, 0), (4, 28, 90004, 0), (4, 36, 60000, 0), (4, 60, 40000, 0), (4, 68, 40064, 0), (4, 1500, 1504, 0),
-    (4, 2044, 1028, 0), (4, 64, 40000, 4), (4, 1536, 1536, 28), (4, 1540, 1536, 12)])
+    (4, 2044, 1028, 0), (4, 64, 40000, 4), (4, 1536, 1536, 28), (4, 1540, 1536, 12),
+    # blocks of 256 and 128 rows: one short of a block, one chunk more, a last block of less than the shift
+    (2, 248, 17000, 0), (2, 264, 16008, 0), (2, 312, 14000, 8), (2, 520, 8200, 40), (4, 124, 17004, 0), (4, 132, 16004, 0), (4, 156, 14000, 4), (4, 260, 8200, 20)])
 def test_transpose_into_part_lines_is_bit_exact(swz, elem_bytes, M, N, offset):
     assert 2 * elem_bytes * M * N >= 16 << 20
     dtype = torch.int16 if elem_bytes == 2 else torch.int32
