@@ -90,6 +90,24 @@ def _load() -> ctypes.CDLL:
 lib = _load()
 
 
+def _load_fast():
+    """_fastcall.so: the ordinary call of gemm, transpose, softmax and layernorm (plain CUDA tensors of the current device, an output, no stream
+    or parameters named).  Its functions return the status, or None for a call that is not ordinary."""
+    if torch is None:
+        return None
+    try:
+        from . import _fastcall as fast
+    except ImportError as e:
+        raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} is missing or does not load: build it with "
+                          "`python paper_2508_20258_amd/build.py`. There is no fallback path.") from e
+    fast.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.swz_gemm, lib.swz_transpose, lib.swz_softmax, lib.swz_layernorm)),
+              torch.nn.Parameter)
+    return fast
+
+
+_fast = _load_fast()
+
+
 def status_string(status: int) -> str:
     return lib.swz_status_string(int(status)).decode()
 
@@ -193,6 +211,11 @@ def gemm(a, b, c=None, mode: int = MODE_XCD_GROUPM, stream=None, **params):
     a (M x K), b (K x N): contiguous torch.bfloat16 CUDA tensors; c (M x N) is allocated if not given.
     Keyword params (bm, bn, bk, group_m, num_xcd, persistent, num_wg) select swz_gemm_ex.
     """
+    if stream is None and not params:
+        st = _fast.gemm(a, b, c, mode)
+        if st is not None:
+            _check(st, "swz_gemm")
+            return c
     assert a.is_cuda and b.is_cuda and a.dtype == torch.bfloat16 and b.dtype == torch.bfloat16
     assert a.is_contiguous() and b.is_contiguous() and a.dim() == 2 and b.dim() == 2 and a.shape[1] == b.shape[0]
     M, K = a.shape
@@ -272,6 +295,11 @@ def pid_map_persistent_device(grid_m: int, grid_n: int, num_xcd: int, group_m: i
 def transpose(x, out=None, tile: int = 64, mode: int = MODE_XCD_GROUPM + MODE_SKEW, stream=None, **params):
     """out (N x M) = x (M x N) transposed on the GPU through swz_transpose; tensors of 2-byte or 4-byte elements.
     The defaults (64-wide tiles, XCD renumbering + grouped raster + skew) are the fastest combination measured."""
+    if stream is None and not params:
+        st = _fast.transpose(x, out, tile, mode)
+        if st is not None:
+            _check(st, "swz_transpose")
+            return out
     assert x.is_cuda and x.is_contiguous() and x.dim() == 2 and x.element_size() in (2, 4)
     M, N = x.shape
     if out is None:
@@ -294,6 +322,11 @@ def _row_args(x, out):
 def softmax(x, out=None, chunks: int = 1, mode: int = MODE_XCD, stream=None, **params):
     """Row softmax of a bf16 matrix on the GPU through swz_softmax.  `chunks` (1 to columns / 8) is checked by the library, which
     cuts rows by their length alone."""
+    if stream is None and not params:
+        st = _fast.softmax(x, out, chunks, mode)
+        if st is not None:
+            _check(st, "swz_softmax")
+            return out
     out = _row_args(x, out)
     h = _launch_stream(stream, x, out)
     M, N = x.shape
@@ -303,6 +336,11 @@ def softmax(x, out=None, chunks: int = 1, mode: int = MODE_XCD, stream=None, **p
 
 def layernorm(x, gamma, beta, out=None, eps: float = 1e-5, chunks: int = 1, mode: int = MODE_XCD, stream=None, **params):
     """Layer normalisation of every row of a bf16 matrix on the GPU through swz_layernorm; `chunks` as for softmax."""
+    if stream is None and not params:
+        st = _fast.layernorm(x, gamma, beta, out, eps, chunks, mode)
+        if st is not None:
+            _check(st, "swz_layernorm")
+            return out
     out = _row_args(x, out)
     for t in (gamma, beta):
         assert t.is_cuda and t.is_contiguous() and t.dtype == x.dtype and t.numel() == x.shape[1]

@@ -719,3 +719,60 @@ def test_fed_subtiles_give_the_bits_of_whole_tiles(swz, M, N, K):
         torch.cuda.synchronize()
         assert torch.equal(c[:M].view(torch.int16), want.view(torch.int16)), (M, N, K, mode, params)
         assert torch.isnan(c[M]).all()
+
+
+def test_fast_call_and_general_path_agree(swz):
+    from paper_2508_20258_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(5)
+    a, b = (torch.randn((64, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    row = torch.randn((64,), device="cuda", generator=g).to(torch.bfloat16)
+    s = torch.cuda.current_stream()
+
+    def outs(**kw):
+        o = [torch.full_like(a, float("nan")) for _ in range(4)]
+        res = [swz.gemm(a, b, o[0], **kw), swz.transpose(a, o[1], **kw), swz.softmax(a, o[2], **kw), swz.layernorm(a, row, row, o[3], **kw)]
+        assert all(r is t for r, t in zip(res, o))
+        return o
+
+    fast, general = outs(), outs(stream=s)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(fast, general))
+    # weights kept as Parameters are ordinary; other subclasses, layouts, types, shapes and devices are not
+    out = torch.empty_like(a)
+    assert binding._fast.gemm(a, torch.nn.Parameter(b), out, 2) == 0
+    assert binding._fast.layernorm(a, torch.nn.Parameter(row), torch.nn.Parameter(row), out, 1e-5, 1, 1) == 0
+
+    class Sub(torch.Tensor):
+        pass
+
+    for bad in (b.t(), b.float(), b[:32], b.cpu(), b.as_subclass(Sub), b[None], b.to_sparse(), None):
+        assert binding._fast.gemm(a, bad, out, 2) is None
+    swz.gemm(a, b.as_subclass(Sub), out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, fast[0])
+    for call in (lambda: swz.gemm(a, b.t(), out), lambda: swz.gemm(a, b[:32], out), lambda: swz.gemm(a, b, out[:32]), lambda: swz.softmax(a, out.t()),
+                 lambda: swz.transpose(a, out[:32])):
+        with pytest.raises(AssertionError):
+            call()
+    # what the library refuses is refused the same way by both: misaligned, unknown mode
+    flat = torch.zeros(64 * 64 + 8, dtype=torch.bfloat16, device="cuda")
+    off = flat[1:1 + 64 * 64].view(64, 64)
+    for kw in ({}, {"stream": s}):
+        for call, status in ((lambda: swz.gemm(off, b, out, **kw), -2), (lambda: swz.gemm(a, b, out, mode=9, **kw), -1),
+                             (lambda: swz.softmax(a, out, chunks=9, **kw), -1), (lambda: swz.transpose(a, off, **kw), -2),
+                             (lambda: swz.layernorm(a, row, row, out, eps=-1.0, **kw), -1)):
+            with pytest.raises(swz.SwzError) as e:
+                call()
+            assert e.value.status == status
+    # on the stream that is current, under capture too
+    side = torch.cuda.Stream()
+    side.wait_stream(s)
+    graph, captured = torch.cuda.CUDAGraph(), torch.zeros_like(a)
+    with torch.cuda.graph(graph, stream=side):
+        swz.gemm(a, b, captured)
+    assert (captured == 0).all()
+    for _ in range(3):
+        captured.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(captured, fast[0])

@@ -278,3 +278,21 @@ def test_launch_map_of_fed_subtiles(M, N, K, fed):
             assert fed == (len(blocks) == 256 and not computes.all())
         if not computes.all():
             assert len(blocks) == 256 and computes[:computes.sum()].all() and 16 * computes.sum() <= 9 * 256
+
+
+def test_fast_call_leaves_what_is_not_ordinary_to_the_general_path():
+    # without a GPU (or with tensors elsewhere, other types, non-integers) the fast call answers None and the general path says what is wrong
+    torch = pytest.importorskip("torch")
+    from paper_2508_20258_amd import binding
+    x = torch.zeros((16, 16), dtype=torch.bfloat16)
+    row = torch.zeros((16,), dtype=torch.bfloat16)
+    fast = binding._fast
+    for args in [(x, x, x, 2), (x, x, None, 2), (x, x, x, 2.0), (x, x, x, 1 << 40), (x, x, x), (3, x, x, 2), (x.t(), x, x, 2)]:
+        assert fast.gemm(*args) is None
+    assert fast.transpose(x, x, 64, 6) is None and fast.softmax(x, x, 1, 1) is None and fast.softmax(x, x, None, 1) is None
+    assert fast.layernorm(x, row, row, x, 1e-5, 1, 1) is None and fast.layernorm(x, row, row, x, 0, 1, 1) is None and fast.layernorm() is None
+    for call in (lambda: swz.gemm(x, x, x), lambda: swz.transpose(x, x), lambda: swz.softmax(x, x), lambda: swz.layernorm(x, row, row, x)):
+        with pytest.raises(AssertionError):
+            call()
+    with pytest.raises(TypeError):
+        fast.bind(1, 2)
