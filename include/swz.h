@@ -132,7 +132,7 @@ int swz_pid_map_persistent_device(int grid_m, int grid_n, int num_xcd, int group
  *   128x256, one workgroup each, and then applies `mode`, num_xcd and the same band height to the grid of sub-tiles.  The
  *   left-over tiles of a large grid's last, partial round may be computed by two or four workgroups each, on the XCD the
  *   map gives the tile unless fewer tiles than XCDs are left.  The bits are those of whole tiles.
- *   For at most 192 rows and K >= 1024 the workgroups of compute units that have no sub-tile may read A and B ahead of the others, into
+ *   For at most 192 rows and K >= 2048 the workgroups of compute units that have no sub-tile may read A and B ahead of the others, into
  *   the L2 of their XCD; they compute and write nothing.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null pointer, M/N/K < 1, unknown mode), UNSUPPORTED (other dtype,

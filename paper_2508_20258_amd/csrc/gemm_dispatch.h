@@ -77,23 +77,24 @@ struct GemmLaunch {
 
 // Few rows and a long K: sub-tiles on at most 9/16 of the compute units, and the others fetch their operands ahead of them into the
 // L2 of their XCD (fetch_ahead in gemm_subtile_kernel.h says why).  false: not this product.
-//   K from 1024 on (2048 columns: K = 512 3.6 us without, 3.8 with; 1024 4.5, 4.5; 1536 5.6, 5.1), M up to 192 (229 x 792 x 16312 60.5, 62.6).
+//   K from 2048 on, M up to 128; from 4096 on up to 192 (229 x 792 x 16312 60.5 us without, 62.6 with).  Below, what is gained with B in HBM (32 x 8192 x 1024
+//   7.1, 6.5) is lost where it is in a cache already (4.3, 5.3; 192 x 1000 x 2048 6.3, 6.8; but 32 x 8192 x 8192 25.9, 25.1).
 //   More than 9/16 of the compute units with a sub-tile leave too few to fetch: 11008 columns in 172 sub-tiles 21.1 us without, 22.4 with.  The
 //   columns of an XCD's sub-tiles have to be a run, or every row of sub-tiles would fetch them again: one row, or bands that hold all rows.
 // Shape: the smallest ns a stage, the larger of the sub-tile's own cost, of B at 6.2 TB/s and of what the feeders of one XCD need at 2.4 ns a line.
 // A takes feeders of its own, so many that a line costs each 4 ns (with K = 8192 every row of A is in the same sets: 128 x 1024 x 8192 with one
 // 49 us, two 26, four 14).  Pace: where the sub-tiles are expected, a little slower, as lines that leave the L2 before
 // their use cost a sub-tile the 4 ns this is for (32 x 2048 x 16384 without a pace 44 us, with it 25).
-// Measured on 77 products with M up to 192, log-uniform (kernel time with over without): 0.37 to 1.02, on average 0.79.
+// Measured on 77 products with M up to 192 and K from 1024, log-uniform (kernel time with over without): 0.37 to 1.02, on average 0.79.
 inline bool feed_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, int mode, int cus, GemmLaunch* l) {
-  if (M > 192 || K < 1024 || r.bm != 128 || r.num_xcd > cus) return false;
+  if (M > 192 || K < (M <= 128 ? 2048 : 4096) || r.bm != 128 || r.num_xcd > cus) return false;
   int64_t best = 0;
   l->sub = -1;
   for (int s = 0; s < kSubTileCount; ++s) {
     const SubTile& t = kSubTiles[s];
     const int64_t gm = (M + t.bm - 1) / t.bm, gn = (N + t.bn - 1) / t.bn;
     const bool runs = gm == 1 || (swz_mode_renumbers(mode) && swz_mode_grouped(mode) && (int64_t)r.group_m * (r.bm / t.bm) >= gm);
-    if (t.fed_ns == 0 || !runs || 16 * gm * gn > 9 * cus) continue;
+    if (t.fed_ns == 0 || !runs || 16 * gm * gn > 9 * cus || (t.bm == 64 && M <= 32)) continue;
     const int64_t stage = N * 2 % 128 == 0 ? t.fed_ns : t.fed_ns * 23 / 20;        // columns that start inside a line: more lines
     const int64_t memory = kStageK * N * 2 / 6200, own = stage > memory ? stage : memory;
     if (stage != t.fed_ns && memory > stage) continue;                             // 3 x 7824 x 3424 13.3 us without, 13.8 with

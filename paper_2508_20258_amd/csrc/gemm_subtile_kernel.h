@@ -14,13 +14,14 @@
 //   * every slot address a compile-time constant (the loop is unrolled over the ring, base pointers advance by additions):
 //     with slots computed at run time the scalar instructions of a stage alone took 200 ns, a third more than the whole of a
 //     32x32 stage now (512^3 4.6 -> 3.9 us, 8x4096x4096 17.4 -> 11.9 us).
-// What bounds them now is the loads: without MFMAs and fragment reads 32x8192x8192 takes as long (40 us; without the loads 13),
-// 1024x1024x4096 in 64x64 sub-tiles 15.0 of 16.1 us (without the loads 10.2).  A full chip moves 22 TB/s from the L2s to LDS.
+// What bounds them now is the loads: 1024x1024x4096 in 64x64 sub-tiles takes 16.1 us, 15.0 of them without MFMAs and fragment reads (without the
+// loads 10.2).  A full chip moves 22 TB/s from the L2s to LDS; a product of few rows waits for its column stripes out of HBM, unless
+// other workgroups fetch them ahead (fetch_ahead).  One barrier per two stages instead of one was no faster (32x8192x8192 28.9 -> 35.9 us).
 // Measured (kernel time, operands not in cache; 128x128, 128x256 or 256x256 tiles of gemm_kernel.h -> sub-tiles, the
-// shape the rule in gemm_dispatch.h takes):
+// shape the rule in gemm_dispatch.h takes; fed: with feeders):
 //   512^3            8.1 ->  4.0 us (32x32)      1024^3          12.6 ->  6.2 us (64x64)
 //   1536^3          17.0 -> 13.2 us (128x128)    2048^3          21.9 -> 19.0 us (128x128)
-//   8x4096x4096     32.2 -> 11.9 us (32x32)      32x8192x8192    66.5 -> 40.4 us (32x32; reading B takes 22 at 6.3 TB/s)
+//   8x4096x4096     32.2 -> 11.9 -> 9.0 us (32x32, fed)          32x8192x8192    66.5 -> 40.4 -> 26 us (32x64, fed; reading B takes 21 at 6.3 TB/s)
 //   256x2048x2048   19.0 ->  9.0 us (32x64)      1024x2048x4096  33.2 -> 23.1 us (128x64)
 //   128x32768x2048  40.6 -> 29.4 us (128x128)    64x65536x4096  118.3 -> 96.8 us (64x128)
 //

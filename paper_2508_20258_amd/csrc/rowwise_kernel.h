@@ -7,7 +7,9 @@
 //
 //   Rows of up to 98304 elements.  TPR threads hold a row in KEEP 16-byte vectors each, in registers: 16 to 64 lanes of a
 //   wave for short rows (up to 16 rows per 256-thread workgroup, no LDS, no barrier), a workgroup of 256, 512 or 1024
-//   threads for longer ones.  The grid is one-dimensional over groups of consecutive rows, taken in dispatch order.
+//   threads for longer ones.  The grid is one-dimensional over groups of consecutive rows, taken in dispatch order.  Where there are more rows
+//   than compute units, two forms of the same sums take over for some lengths: two rows beside each other on a compute unit (the *_wide_rows
+//   kernels) and, for layer normalisation, a workgroup that takes row after row (layernorm_loop_rows_kernel).
 //   Longer rows.  A row is cut into segments of 32768 elements; row_stats_kernel computes the statistics of one segment
 //   per workgroup, row_emit_kernel merges them and produces one column chunk per workgroup, reading x a second
 //   time.  Between the launches a segment's statistics (8 bytes) wait in `out` itself: every chunk gets its own copy of all of
@@ -17,7 +19,7 @@
 //
 // The decomposition of the paper, in which the workgroup of every column chunk reads the whole row for its statistics, is bound
 // by those reads and the arithmetic on them even where the remap has the L2 serve 82 % of them: 8 chunks of
-// 1024 x 65536 took 125 us (softmax) and 118 us (layer normalisation), the row in the registers of one workgroup takes 55 and 57.
+// 1024 x 65536 took 125 us (softmax) and 118 us (layer normalisation), the row in the registers of one workgroup takes 47 and 55.
 //
 // At 6 TB/s a CU has about 11 vector instructions per element, and a row's latencies stand in series: load, maximum or mean, sum, store.
 // So the maximum is taken first, on the raw values, and each exponential computed once and kept (an online maximum costs a
@@ -25,7 +27,7 @@
 // division); lanes are reduced with DPP and permlane exchanges (a shuffle through LDS takes about 60 ns a step); gamma and
 // beta are requested ahead of the statistics where there are registers for them.  Measured, operands not in cache, online and merging
 // kernels with late gamma and beta -> these (us; copy16_kernel on 128 MiB in and out: 43):
-//     layernorm 8192 x 8192    66 -> 50      softmax 8192 x 8192    55 -> 44      layernorm 32768 x 16384  388 -> 368
+//     layernorm 8192 x 8192    66 -> 45      softmax 8192 x 8192    55 -> 44      layernorm 32768 x 16384  388 -> 368
 //     softmax 32768 x 16384   382 -> 354     softmax 131072 x 128   49 -> 13      layernorm 300 x 2048     4.9 -> 3.0
 //     softmax 64 x 1048576    300 -> 70      softmax 1 x 1048576   220 -> 9       softmax 16 x 131072       29 -> 9
 //
@@ -240,7 +242,7 @@ constexpr int row_block(int tpr) { return tpr < 256 ? 256 : tpr; }
 
 // Which row a workgroup of TPR-thread groups works on: TPR <= 64, groups of lanes; above, the whole workgroup.
 // Rows held whole share nothing, so no mapping helps the L2, and rows that run at the same time are best neighbours in memory: in
-// dispatch order 8192 x 8192 takes 44 us (softmax) and 50 us (layer normalisation), with every XCD on a run of rows of its own
+// dispatch order 8192 x 8192 takes 44 us (softmax; layer normalisation in this form 50), with every XCD on a run of rows of its own
 // 50 and 56; 65536 x 1024 44 and 45 against 48 and 51, 4000 x 30000 84 and 88 against 88 and 92.  The softmax shape of 1024 threads
 // with two vectors each is MAPPED: the host hands it the caller's mode where runs are not slower (soft_rows_mapped in swz.hip).
 template <int TPR, bool MAPPED>
@@ -483,7 +485,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void layernorm_wide_rows_kernel(co
 //     8192 x 8192  50 -> 45 us    12000 x 7200  70 -> 60    2100 x 8192  16.7 -> 14.9    60000 x 4096  175 -> 163    1100 x 8192  11.1 -> 9.0
 constexpr int kLoopThreads = 256;
 template <int KEEP>
-__global__ __launch_bounds__(kLoopThreads, 4) void layernorm_loop_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma,
+__global__ __launch_bounds__(kLoopThreads, 4) void layernorm_loop_rows_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ gamma,
                                                                          const uint16_t* __restrict__ beta, uint16_t* __restrict__ out, int M, int N, float eps) {
   __shared__ float slots[2][kMaxWaves];
   const int nv = N >> 3, tid = (int)threadIdx.x, step = (int)gridDim.x;

@@ -394,7 +394,7 @@ int launch_layernorm_rows(const uint16_t* in, const uint16_t* gamma, const uint1
   if constexpr (TPR == swz::kLoopThreads && (KEEP == 2 || KEEP == 4)) {
     if (KEEP == 4 ? N >= 6000 && M > 2 * plan.cus : N >= 3400 && M > 4 * plan.cus) {
       const int64_t per_cu = N >= 7000 && M * N >= ((int64_t)1 << 25) ? 1 : 2;
-      return launch(swz::layernorm_loop_kernel<KEEP>, dim3((unsigned)(per_cu * plan.cus)), dim3(swz::kLoopThreads), 0, stream, in, gamma, beta, out, (int)M,
+      return launch(swz::layernorm_loop_rows_kernel<KEEP>, dim3((unsigned)(per_cu * plan.cus)), dim3(swz::kLoopThreads), 0, stream, in, gamma, beta, out, (int)M,
                     N, eps);
     }
   }

@@ -705,7 +705,7 @@ def test_partial_last_round_in_pieces_gives_the_bits_of_whole_tiles(swz, M, N):
 
 # workgroups that fetch ahead: one sub-tile row and several, columns and rows that do not fill one, rows of B that start inside a line, XCDs without a
 # sub-tile, XCDs with different numbers of columns (T = 129, 17), K of no whole load; every byte a feeder reads lies inside A or B
-@pytest.mark.parametrize("M,N,K", [(1, 8, 1024), (32, 8192, 1056), (8, 4104, 1112), (33, 544, 2056), (64, 2056, 1024), (100, 1032, 1032), (192, 1000, 1544),
+@pytest.mark.parametrize("M,N,K", [(1, 8, 2048), (32, 8192, 2080), (8, 4104, 2136), (33, 544, 2056), (64, 2056, 2048), (100, 1032, 2056), (192, 1000, 4104),
                                    (129, 64, 8192), (5, 520, 16376)])
 def test_fed_subtiles_give_the_bits_of_whole_tiles(swz, M, N, K):
     assert (swz.gemm_launch_map(M, N, K)[:, 2] == 0).any()

@@ -266,8 +266,8 @@ def test_launch_stream_takes_the_fast_way_only_on_the_current_device(monkeypatch
 
 
 # few rows, long K: sub-tiles first, then workgroups that fetch ahead for them and compute nothing
-@pytest.mark.parametrize("M,N,K,fed", [(1, 8, 1024, True), (32, 8192, 8192, True), (33, 4104, 1032, True), (192, 1000, 2048, True), (192, 64, 1024, True),
-                                       (193, 1000, 2048, False), (32, 8192, 1016, False), (32, 16384, 8192, False)])
+@pytest.mark.parametrize("M,N,K,fed", [(1, 8, 2048, True), (32, 8192, 8192, True), (33, 4104, 2056, True), (128, 1000, 2048, True), (192, 64, 4096, True),
+                                       (193, 1000, 8192, False), (192, 1000, 4088, False), (32, 8192, 2040, False), (32, 16384, 8192, False)])
 def test_launch_map_of_fed_subtiles(M, N, K, fed):
     for mode, params in [(2, dict(num_xcd=8)), (0, dict(num_xcd=8)), (1, dict(num_xcd=3)), (3, dict(num_xcd=8, group_m=1)), (6, dict(num_xcd=8, group_m=1)),
                          (2, dict(num_xcd=1)), (2, dict(num_xcd=255)), (2, dict(num_xcd=1000))]:
