@@ -542,8 +542,10 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   // rows a tile reads cost more than its part lines (1000 x 1004 x 4 B 5.4 us against 5.6, 1000 x 1000 x 2 B 3.7 against 4.2; 3000 x 3000 x
   // 2 B, 34 MiB moved, 11.5 against 9.9).
   const bool part_lines = ((M * elem_bytes) & 127) != 0 || (reinterpret_cast<uintptr_t>(out) & 127) != 0;
-  if (tile == 64 && part_lines && M < ((int64_t)1 << 30) && 2 * M * N * elem_bytes >= ((int64_t)16 << 20)) {
-    const int rows = swz::lines_rows(elem_bytes), blocks_m = (int)((M + rows - 1) / rows);
+  const int rows = swz::lines_rows(elem_bytes), blocks_m = (int)((M + rows - 1) / rows);
+  // A block has twice the threads of a tile: where M fills no more blocks than tiles, a launch holds half as many columns of them.
+  const bool fits = (int64_t)blocks_m * gn * swz::kLinesThreads <= kLaunchThreads;
+  if (tile == 64 && part_lines && fits && M < ((int64_t)1 << 30) && 2 * M * N * elem_bytes >= ((int64_t)16 << 20)) {
     const dim3 grid((unsigned)(blocks_m * gn)), block(swz::kLinesThreads);
     if (group_m > blocks_m) group_m = blocks_m;
     if (elem_bytes == 2)

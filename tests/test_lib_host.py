@@ -82,6 +82,18 @@ def test_launches_of_2_to_the_32_threads_are_refused():
     assert L.swz_transpose(a, b, 4, (1 << 30) + 4, 4, 64, 2, p, None) == -3
 
 
+# fewer than 2^24 tiles of 64 x 64 are never too many, whatever blocks they are done in: 8 rows of `out` off their lines, one row of tiles (and
+# three, which are two blocks of four-byte elements)
+@pytest.mark.parametrize("M,N,elem_bytes", [(8, 1 << 29, 2), (8, 1 << 29, 4), (60, 1 << 29, 4), (164, 1 << 28, 4), (8, (1 << 30) - 64, 2), (4, (1 << 30) - 64, 4)])
+def test_transposes_of_fewer_than_2_to_the_24_tiles_are_not_refused(M, N, elem_bytes):
+    import torch
+    if torch.cuda.device_count() > 0:
+        pytest.skip("the pointers are not real: for a machine where the launch itself fails")
+    p = ctypes.byref(swz.SwzParams(0, 0, 0, 0, 8))
+    assert -(-M // 64) * -(-N // 64) < 1 << 24
+    assert swz.lib.swz_transpose(0x1000, 0x2000, M, N, elem_bytes, 64, 2, p, None) == -4          # no device
+
+
 def test_long_rows_refuse_overlapping_buffers():
     # rows above 98304 elements keep statistics in the output while the input is read again: in place they would come out wrong
     L = swz.lib
