@@ -180,9 +180,11 @@ int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_par
  *             neighbouring tiles: the case where the mapping decides the L2 hit rate).
  *   Once input plus output exceed the 256 MB memory-side cache the stores of tiles 64 and 128 are
  *   streaming stores (the faster choice there, the slower one below it).
- *   Where rows of `out` do not start on 128-byte lines, tile 64 (from 16 MiB moved) is done in blocks of 64 columns and 256 rows
- *   (elem_bytes 2) or 128 rows (4), a workgroup each, which writes the whole lines nearest to its block; the id -> block map is that of
- *   swz_pid_map for the grid of those blocks.
+ *   Where rows of `out` do not start on 128-byte lines, tile 64 (from 16 MiB moved) is done in blocks of 64 columns, a workgroup each, which
+ *   writes the whole lines nearest to its block; the id -> block map is that of swz_pid_map for the grid of those blocks, and group_m
+ *   counts them.  A block has 256 rows for elem_bytes 2 where M > 64, and M <= 448 or 30 MiB and more are moved, but not for 256 < M < 280; 128 rows for
+ *   elem_bytes 4 where M > 48, and M <= 256 or 44 MiB and more are moved, but not for 128 < M < 160; 64 rows otherwise, and wherever blocks of
+ *   those rows would be 2^23 or more.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null, M/N < 1, unknown mode), UNSUPPORTED (elem_bytes not 2 or 4, tile not 32/64/128
  * (not 64 for 4-byte elements), M or N not a multiple of 8 (4 for 4-byte elements), misaligned pointer),

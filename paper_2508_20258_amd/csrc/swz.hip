@@ -283,6 +283,33 @@ int launch_transpose(const void* in, void* out, int M, int N, int gm, int gn, in
     return launch_transpose_s<TILE, true>(in, out, M, N, gm, gn, num_xcd, group_m, mode, stream);
   return launch_transpose_s<TILE, false>(in, out, M, N, gm, gn, num_xcd, group_m, mode, stream);
 }
+
+// Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines, rather than 64 rows in 256 threads.  Time of the tall ones over
+// that of the others, matrices not in cache, 17 to 200 MiB moved:
+//   Few rows, one block either way, most of a tall one empty: two bytes 8 rows 1.61 to 1.76, 24 rows 1.22 to 1.41, 56 rows 1.10 to 1.16, but 72 rows
+//   0.80 to 0.91; four bytes 4 rows 1.42 to 1.53, 28 rows 1.00 to 1.13, 44 rows 0.89 to 1.14, but 52 and 60 rows 0.91 to 1.04, 68 rows 0.85 to 0.98.
+//   Just above one block, the second nearly empty: 264 rows of two bytes 0.96 to 1.09 (280 rows 0.92 to 1.03), 132 of four 0.98 to 1.07, 148
+//   0.96 to 1.11 (164 rows 0.92 to 1.02).
+//   Few blocks for the compute units: two bytes, 17, 24, 28 and 31 MiB, 440 rows 0.92, 0.88, 0.84, 0.87; 520 rows 1.10, 1.11, 1.07, 0.91; 1032 rows 1.10, 0.97,
+//   1.06, 0.93; 8200 rows 1.12, 1.08, 0.91, 0.91; from 33 MiB on 0.73 to 1.01.  Four bytes, 17, 24, 40 and 47 MiB, 252 rows 0.98, 0.89, 0.94, 0.93; 516
+//   rows 1.06, 0.97, 1.09, 0.83; 2052 rows 1.07, 1.02, 0.98, 0.89; from 50 MiB on 0.84 to 0.99.
+// A launch has to hold its threads too: with one row of blocks, or two instead of three, half and three quarters as many columns fit.
+bool tall_line_blocks(int64_t M, int64_t N, int elem_bytes) {
+  const int rows = swz::lines_rows(elem_bytes, true);
+  const int64_t blocks_m = (M + rows - 1) / rows, gn = (N + 63) / 64, moved = 2 * M * N * elem_bytes;
+  if (blocks_m * gn * swz::lines_threads(rows) > kLaunchThreads) return false;
+  if (elem_bytes == 2) return M > 64 && (M <= 256 || M >= 280) && (M <= 448 || moved >= ((int64_t)30 << 20));
+  return M > 48 && (M <= 128 || M >= 160) && (M <= 256 || moved >= ((int64_t)44 << 20));
+}
+
+template <class T, bool TALL>
+int launch_transpose_lines(const void* in, void* out, int M, int N, int gn, int num_xcd, int group_m, int mode, hipStream_t stream) {
+  constexpr int ROWS = swz::lines_rows((int)sizeof(T), TALL);
+  const int blocks_m = (M + ROWS - 1) / ROWS;
+  return launch(swz::transpose_lines_kernel<T, ROWS>, dim3((unsigned)(blocks_m * gn)), dim3(swz::lines_threads(ROWS)), 0, stream, static_cast<const T*>(in),
+                static_cast<T*>(out), M, N, blocks_m, gn, num_xcd, group_m < blocks_m ? group_m : blocks_m, mode);
+}
+
 // Threads per row and 16-byte vectors each of them holds, for rows of up to max_vecs vectors: the fastest of the pairs
 // measured (16 to 1024 threads x 1 to 16 vectors, M from 1 to 131072).  Few lanes for short rows (131072 x 128: 14 us with 16
 // lanes, 35 with 64), enough threads to leave each one 2 to 8 vectors for longer ones.  The two kernels part between 4096 and 16384
@@ -539,20 +566,16 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   const int st = check_map_args((int)gm, (int)gn, num_xcd, &group_m, mode);
   if (st != SWZ_OK) return st;
   // Rows of `out` that start inside a 128-byte line, and enough of them that the memory decides: below 16 MiB moved the extra
-  // rows a tile reads cost more than its part lines (1000 x 1004 x 4 B 5.4 us against 5.6, 1000 x 1000 x 2 B 3.7 against 4.2; 3000 x 3000 x
-  // 2 B, 34 MiB moved, 11.5 against 9.9).
+  // rows a block reads cost more than its part lines (blocks of 64 rows: 1000 x 1004 x 4 B 5.4 us against 5.6, 1000 x 1000 x 2 B 3.7 against 4.2; 3000 x
+  // 3000 x 2 B, 34 MiB moved, 11.5 against 9.9).
   const bool part_lines = ((M * elem_bytes) & 127) != 0 || (reinterpret_cast<uintptr_t>(out) & 127) != 0;
-  const int rows = swz::lines_rows(elem_bytes), blocks_m = (int)((M + rows - 1) / rows);
-  // A block has twice the threads of a tile: where M fills no more blocks than tiles, a launch holds half as many columns of them.
-  const bool fits = (int64_t)blocks_m * gn * swz::kLinesThreads <= kLaunchThreads;
-  if (tile == 64 && part_lines && fits && M < ((int64_t)1 << 30) && 2 * M * N * elem_bytes >= ((int64_t)16 << 20)) {
-    const dim3 grid((unsigned)(blocks_m * gn)), block(swz::kLinesThreads);
-    if (group_m > blocks_m) group_m = blocks_m;
+  if (tile == 64 && part_lines && M < ((int64_t)1 << 30) && 2 * M * N * elem_bytes >= ((int64_t)16 << 20)) {
+    const bool tall = tall_line_blocks(M, N, elem_bytes);
     if (elem_bytes == 2)
-      return launch(swz::transpose_lines_kernel<uint16_t>, grid, block, 0, stream, static_cast<const uint16_t*>(in),
-                    static_cast<uint16_t*>(out), (int)M, (int)N, blocks_m, (int)gn, num_xcd, group_m, mode);
-    return launch(swz::transpose_lines_kernel<uint32_t>, grid, block, 0, stream, static_cast<const uint32_t*>(in),
-                  static_cast<uint32_t*>(out), (int)M, (int)N, blocks_m, (int)gn, num_xcd, group_m, mode);
+      return tall ? launch_transpose_lines<uint16_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, stream)
+                  : launch_transpose_lines<uint16_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, stream);
+    return tall ? launch_transpose_lines<uint32_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, stream)
+                : launch_transpose_lines<uint32_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, stream);
   }
   if (elem_bytes == 4) {
     if (M * N * 8 > kMemorySideCacheBytes)

@@ -200,26 +200,28 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
 // pieces.  Here a workgroup takes BM rows of `in` x 64 columns, and the BM elements it
 // writes of row n of `out` are shifted left by s(n), the elements by which the row overhangs a line, so that it writes whole lines: row n
 // gets columns [BM pm - s(n), BM pm - s(n) + BM), the last block of the row everything up to M (one line more at
-// most).  Its block of `in` grows by the E - 1 rows above it (E elements fill a line), which the block above reads too: 128 rows and 31
-// more of four bytes, 256 and 63 of two, a quarter more than the input in all, part of which the L2 serves.  s(n) differs from row
+// most).  Its block of `in` grows by the E - 1 rows above it (E elements fill a line), which the block above reads too.  BM is 64 with 256
+// threads: 31 rows more of four bytes, 63 of two, half and all of the input once more; or 128 of four bytes and 256 of two with 512 threads, a
+// quarter more.  Part of that the L2 serves.  tall_line_blocks (swz.hip) says which: the tall blocks lose where M leaves most of one empty and where
+// there are too few of them.  s(n) differs from row
 // to row, so a lane gathers its 16 bytes element by element, four rows or eight rows of the tile at a column: the
 // transposing LDS read takes the same rows for 4 columns.
 // A wave instruction stores 8 rows x 8 chunks = 8 whole lines: lane l takes row l / 8, chunk l % 8.
 // LDS: 16-byte chunk c of tile row r in slot c ^ key(r); key steps with the chunk of rows a lane gathers, so that the 8
 // chunks of one column lie in different banks whatever their shift.  The stores are streaming ones at every size: nothing
 // is left to merge in the L2.
-// Bound by HBM and the rows read twice.  Measured, matrices not in cache, 64 rows and 256 threads -> these (us; GB/s of the matrix read and written):
+// Bound by HBM and the rows read twice.  Measured, matrices not in cache, 64 rows and 256 threads -> tall (us; GB/s of the matrix read and written):
 //     two bytes   10000 x 7000  75 -> 60 (4670)    8200 x 8208  67 -> 57 (4720)    30000 x 1544   49 -> 41 (4560)    3000 x 3000  10.7 -> 9.0
-//     four bytes   5800 x 5804  60 -> 56 (4810)    200 x 20000  9.5 -> 8.6         15764 x 8092  214 -> 204 (5000)   2000 x 2004   8.1 -> 7.8
+//     four bytes   5800 x 5804  60 -> 56 (4810)    200 x 20000  9.5 -> 8.6         15764 x 8092  214 -> 204 (5000)
 // (tiles on line-blind boundaries 102, 110 and 82, 363 us; 60 us where both pitches are whole lines, 10048 x 7040.)  256 rows of four bytes leave a
 // compute unit two workgroups: 58 us at 5800 x 5804; with 256 threads 77.  128 columns: 60 us there, 61 at 10000 x 7000.
-constexpr int kLinesThreads = 512;
-__host__ __device__ constexpr int lines_rows(int elem_bytes) { return elem_bytes == 2 ? 256 : 128; }
+__host__ __device__ constexpr int lines_rows(int elem_bytes, bool tall) { return !tall ? 64 : elem_bytes == 2 ? 256 : 128; }
+__host__ __device__ constexpr int lines_threads(int rows) { return rows == 64 ? 256 : 512; }
 
-template <class T>
-__global__ __launch_bounds__(kLinesThreads) void transpose_lines_kernel(const T* __restrict__ in, T* __restrict__ out, int M, int N, int grid_m,
-                                                              int grid_n, int num_xcd, int group_m, int mode) {
-  constexpr int TILE = 64, BM = lines_rows((int)sizeof(T)), NT = kLinesThreads;
+template <class T, int BM_>
+__global__ __launch_bounds__(lines_threads(BM_)) void transpose_lines_kernel(const T* __restrict__ in, T* __restrict__ out, int M, int N, int grid_m,
+                                                                                  int grid_n, int num_xcd, int group_m, int mode) {
+  constexpr int TILE = 64, BM = BM_, NT = lines_threads(BM_);
   constexpr int CH = 16 / (int)sizeof(T), E = 128 / (int)sizeof(T);                  // elements per chunk, per line
   constexpr int SLOTS = TILE / CH, ROWS = BM + E, ROW_BYTES = TILE * (int)sizeof(T), LINES = BM / E;
   __shared__ __attribute__((aligned(16))) unsigned char tile[ROWS * ROW_BYTES];

@@ -666,7 +666,10 @@ def test_subtiles_give_the_bits_of_whole_tiles(swz, M, N):
     (4, 4, 600000, 0), (4, 28, 90004, 0), (4, 36, 60000, 0), (4, 60, 40000, 0), (4, 68, 40064, 0), (4, 1500, 1504, 0),
     (4, 2044, 1028, 0), (4, 64, 40000, 4), (4, 1536, 1536, 28), (4, 1540, 1536, 12),
     # blocks of 256 and 128 rows: one short of a block, one chunk more, a last block of less than the shift
-    (2, 248, 17000, 0), (2, 264, 16008, 0), (2, 312, 14000, 8), (2, 520, 8200, 40), (4, 124, 17004, 0), (4, 132, 16004, 0), (4, 156, 14000, 4), (4, 260, 8200, 20)])
+    (2, 248, 17000, 0), (2, 264, 16008, 0), (2, 312, 14000, 8), (2, 520, 8200, 40), (4, 124, 17004, 0), (4, 132, 16004, 0), (4, 156, 14000, 4), (4, 260, 8200, 20),
+    # both heights of a block on each side of every line between them: M = 64, 280 and 448 with 16 to 30 MiB and above (two bytes), 48, 160 and 256 with 16 to 44 MiB
+    (2, 64, 70000, 16), (2, 280, 16008, 0), (2, 440, 10008, 0), (2, 456, 9608, 0), (2, 2056, 2056, 8), (2, 520, 15624, 40), (2, 3000, 2904, 0), (2, 4104, 4104, 0),
+    (4, 44, 50004, 0), (4, 52, 42004, 0), (4, 64, 40000, 8), (4, 164, 14004, 4), (4, 256, 9004, 4), (4, 260, 24000, 20), (4, 516, 4304, 0), (4, 2004, 2004, 0), (4, 3004, 2500, 12)])
 def test_transpose_into_part_lines_is_bit_exact(swz, elem_bytes, M, N, offset):
     assert 2 * elem_bytes * M * N >= 16 << 20
     dtype = torch.int16 if elem_bytes == 2 else torch.int32
