@@ -415,11 +415,13 @@ int launch_layernorm_rows(const uint16_t* in, const uint16_t* gamma, const uint1
                       gamma, beta, out + row * N, N, eps);
       });
   }
-  // Row after row where most of the KEEP x 256 vectors are real and every workgroup has a few.  One against two workgroups a compute unit: 5000 x 7200
-  // 27.2 us, 27.7; 12000 x 8192 64.9, 67.2; but 2100 x 8192 15.3, 14.9 and 12000 x 6400 55.5, 54.0.  Without the loop 800 x 3600 5.1 us,
-  // with it 5.2; 1100 x 3600 5.7, 5.7; 1100 x 4800 6.5, 6.9; 800 x 6400 6.7, 6.4.
+  // Row after row where most of the KEEP x 256 vectors are real and the workgroups have enough rows.  Time of the loop over that of a workgroup a row, operands
+  // not in cache: four vectors, from 2 rows a compute unit on 513 rows 0.90 to 0.99, 800 rows 0.83 to 0.97, 1540 rows 0.83 to 0.86 (of 6000 to 8192 elements;
+  // 4800 and less 1.06 at 1100 rows).  Two vectors: 4 to 5 rows a compute unit 0.94 to 1.02; from 5 on some workgroups have a third row and the others wait for
+  // them, 1290 rows 1.04 to 1.09; 1500 rows of 3400 and 3480 elements 1.05 to 1.08, of 3600 and more 0.93 to 0.98; 1600 rows 0.90 to 0.97, 2060 rows 0.88 to 0.96.
+  // One against two workgroups a compute unit: 5000 x 7200 27.2 us, 27.7; 12000 x 8192 64.9, 67.2; but 2100 x 8192 15.3, 14.9 and 12000 x 6400 55.5, 54.0.
   if constexpr (TPR == swz::kLoopThreads && (KEEP == 2 || KEEP == 4)) {
-    if (KEEP == 4 ? N >= 6000 && M > 2 * plan.cus : N >= 3400 && M > 4 * plan.cus) {
+    if (KEEP == 4 ? N >= 6000 && M > 2 * plan.cus : N >= 3400 && 2 * M > (N >= 3600 ? 11 : 12) * plan.cus) {
       const int64_t per_cu = N >= 7000 && M * N >= ((int64_t)1 << 25) ? 1 : 2;
       return launch(swz::layernorm_loop_rows_kernel<KEEP>, dim3((unsigned)(per_cu * plan.cus)), dim3(swz::kLoopThreads), 0, stream, in, gamma, beta, out, (int)M,
                     N, eps);

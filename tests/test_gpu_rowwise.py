@@ -273,7 +273,8 @@ def test_more_rows_than_a_launch_has_threads_for(swz, op, M, N):
 @pytest.mark.parametrize("op,M,N", [("softmax", 258, 40968), ("softmax", 300, 49152), ("softmax", 257, 49160), ("softmax", 261, 65536), ("softmax", 4096, 41000), ("softmax", 2049, 49160),
                                     ("layernorm", 258, 32776), ("layernorm", 300, 40960), ("layernorm", 257, 40968), ("layernorm", 261, 49152),
                                     ("layernorm", 513, 6000), ("layernorm", 1100, 8192), ("layernorm", 4800, 7008), ("layernorm", 1025, 3400),
-                                    ("layernorm", 1537, 4096), ("layernorm", 513, 8192)])
+                                    ("layernorm", 1537, 4096), ("layernorm", 513, 8192),
+                                    ("layernorm", 1409, 3600), ("layernorm", 1408, 3600), ("layernorm", 1537, 3592), ("layernorm", 1536, 3400)])
 def test_many_rows_give_the_bits_of_few(swz, op, M, N):
     g = torch.Generator(device="cuda").manual_seed(M + N)
     x = (torch.randn((M, N), device="cuda", generator=g) * 2 + 0.5).to(torch.bfloat16)
