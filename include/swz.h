@@ -133,7 +133,8 @@ int swz_pid_map_persistent_device(int grid_m, int grid_n, int num_xcd, int group
  *   left-over tiles of a large grid's last, partial round may be computed by two or four workgroups each, on the XCD the
  *   map gives the tile unless fewer tiles than XCDs are left.  The bits are those of whole tiles.
  *   For at most 192 rows and K >= 2048 the workgroups of compute units that have no sub-tile may read A and B ahead of the others, into
- *   the L2 of their XCD; they compute and write nothing.
+ *   the L2 of their XCD; they compute and write nothing.  The launch ends when they have ended too: about when the others do, later by up to the
+ *   time of a call where another stream holds most of the compute units and they start late.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null pointer, M/N/K < 1, unknown mode), UNSUPPORTED (other dtype,
  * K or N not a multiple of 8, misaligned pointer), OVERFLOW (tile count >= 2^31 or a

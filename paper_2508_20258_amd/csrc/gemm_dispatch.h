@@ -72,7 +72,7 @@ struct GemmLaunch {
   int bm, bn, grid_m, grid_n, group_m;   // the grid the map is evaluated on (with `pieces` that of the 256x256 tiles)
   int whole, deal;                    // see swz_tail_piece
   int64_t blocks;                     // workgroups launched
-  int a_feeders, feed_ticks;          // workgroups per XCD that fetch A ahead, ticks of 10 ns per 1024 of K; 0: none fetches ahead
+  int a_feeders, b_feeders, feed_ticks;   // workgroups per XCD that fetch A and B ahead, ticks of 10 ns per 1024 of K; 0: none fetches ahead
 };
 
 // Few rows and a long K: sub-tiles on at most 9/16 of the compute units, and the others fetch their operands ahead of them into the
@@ -85,7 +85,15 @@ struct GemmLaunch {
 // A takes feeders of its own, so many that a line costs each 4 ns (with K = 8192 every row of A is in the same sets: 128 x 1024 x 8192 with one
 // 49 us, two 26, four 14).  Pace: where the sub-tiles are expected, a little slower, as lines that leave the L2 before
 // their use cost a sub-tile the 4 ns this is for (32 x 2048 x 16384 without a pace 44 us, with it 25).
-// Measured on 77 products with M up to 192 and K from 1024, log-uniform (kernel time with over without): 0.37 to 1.02, on average 0.79.
+// How many: half as many again for B as that pace needs at 2.4 ns a line; the other workgroups leave at once.  The launch ends when the last of these ends, and one
+// that starts late, on a compute unit that another stream held, still takes its time.  With all of them at it: 16 x 2048 x 8192 13.5 us, 13.2 with as many as
+// needed; with 32, 64 and 224 compute units held by another kernel 19.7, 22.4, 82, now 13.5, 13.7, 64 (without feeders 33, 33, 50); 192 x 64 x 8192 13.5 and, 32
+// held, 19.6, now 12.7 and 12.8 (16); 160 x 1000 x 16384 45, now 34.5 (60).  With twice the need as with one and a half, with the need itself 15.0 at 16 x 2048 x 8192.
+// Held half of the chip: 32 x 8192 x 8192 68 us without feeders, 55 with; 64 x 4096 x 8192 55, 39; 8 x 4096 x 4096 17.4, 18.8; 32 x 4096 x 16384 73, 82; held 192
+// and more 0.66 to 1.28 times the time without, 192 x 64 x 8192 1.9.
+// Measured on 62 products the rule takes out of 77 with M up to 192 and K from 2048 (4096 above 128 rows), log-uniform, kernel time with over without: 0.32 to 0.99, on
+// average 0.63, with the operands out of HBM, as a program's weights come; repeated on operands that stay in a cache 0.62 to 1.25, on average 0.93 (the worst of 320
+// products with K from 2048: 1 x 8192 x 2048 5.2 us without, 6.8 with, 10.4 and 8.8 out of HBM; 128 x 2048 x 4096 8.5, 9.5, out of HBM 18.5 and 10.8).
 inline bool feed_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, int mode, int cus, GemmLaunch* l) {
   if (M > 192 || K < (M <= 128 ? 2048 : 4096) || r.bm != 128 || r.num_xcd > cus) return false;
   int64_t best = 0;
@@ -112,6 +120,9 @@ inline bool feed_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, in
     l->grid_n = (int)gn;
     l->blocks = cus;
     l->a_feeders = (int)a_feeders;
+    // whole lines: two sub-tiles of 32 columns share one
+    const int64_t need = (kStageK * ((gn + r.num_xcd - 1) / r.num_xcd * t.bn + 63) / 64 * 18 / 5 + own - 1) / own;
+    l->b_feeders = (int)(need < idle - a_feeders ? need : idle - a_feeders);
     l->feed_ticks = (int)((pace > (double)e ? pace : (double)e) * 1.6);
   }
   return l->sub >= 0;
@@ -120,7 +131,7 @@ inline bool feed_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, in
 // r: the resolved plan; cus: compute units.  `free_tile`: the caller left the tile to the library, otherwise a tile is one workgroup.
 // Bounds for anything else: 32-bit source offsets over 64 rows of B, and a grid well inside the 32-bit range whatever the shape.
 inline GemmLaunch gemm_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, int grid_m, int grid_n, int group_m, int mode, bool free_tile, int cus) {
-  GemmLaunch l = {-1, false, r.bm, r.bn, grid_m, grid_n, group_m, 0, 1, (int64_t)grid_m * grid_n, 0, 0};
+  GemmLaunch l = {-1, false, r.bm, r.bn, grid_m, grid_n, group_m, 0, 1, (int64_t)grid_m * grid_n, 0, 0, 0};
   if (!free_tile || N >= ((int64_t)1 << 24) || l.blocks >= ((int64_t)1 << 16)) return l;
   if (feed_launch(M, N, K, r, mode, cus, &l)) return l;
   l.sub = choose_subtile(M, N, K, r, cus);

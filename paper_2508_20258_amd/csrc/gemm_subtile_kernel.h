@@ -13,7 +13,7 @@
 //     stage, then multiplying it: 128x128 at 2048^3 21.7 -> 18.8 us, 64x64 at 1024^3 6.3 -> 6.2 us;
 //   * every slot address a compile-time constant (the loop is unrolled over the ring, base pointers advance by additions):
 //     with slots computed at run time the scalar instructions of a stage alone took 200 ns, a third more than the whole of a
-//     32x32 stage now (512^3 4.6 -> 3.9 us, 8x4096x4096 17.4 -> 11.9 us).
+//     32x32 stage now (512^3 4.6 -> 3.9 us).
 // What bounds them now is the loads: 1024x1024x4096 in 64x64 sub-tiles takes 16.1 us, 15.0 of them without MFMAs and fragment reads (without the
 // loads 10.2).  A full chip moves 22 TB/s from the L2s to LDS; a product of few rows waits for its column stripes out of HBM, unless
 // other workgroups fetch them ahead (fetch_ahead).  One barrier per two stages instead of one was no faster (32x8192x8192 28.9 -> 35.9 us).
@@ -21,7 +21,7 @@
 // shape the rule in gemm_dispatch.h takes; fed: with feeders):
 //   512^3            8.1 ->  4.0 us (32x32)      1024^3          12.6 ->  6.2 us (64x64)
 //   1536^3          17.0 -> 13.2 us (128x128)    2048^3          21.9 -> 19.0 us (128x128)
-//   8x4096x4096     32.2 -> 11.9 -> 9.0 us (32x32, fed)          32x8192x8192    66.5 -> 40.4 -> 26 us (32x64, fed; reading B takes 21 at 6.3 TB/s)
+//   8x4096x4096     32.2 -> 17 -> 9.0 us (32x32, fed)          32x8192x8192    66.5 -> 40.4 -> 26 us (32x64, fed; reading B takes 21 at 6.3 TB/s)
 //   256x2048x2048   19.0 ->  9.0 us (32x64)      1024x2048x4096  33.2 -> 23.1 us (128x64)
 //   128x32768x2048  40.6 -> 29.4 us (128x128)    64x65536x4096  118.3 -> 96.8 us (64x128)
 //
@@ -247,7 +247,8 @@ __device__ __forceinline__ void gemm_subtile(const uint16_t* __restrict__ A, con
 }
 
 // What a workgroup without a sub-tile does: it reads B, or A, in the order of K ahead of the workgroups of its XCD, into LDS that nobody
-// reads, so that their loads find the lines in the L2.  No result depends on it and nobody waits for it.
+// reads, so that their loads find the lines in the L2.  No result depends on it, but the launch ends when the last of these ends: they keep to the pace at which the
+// sub-tiles are expected from when they start, and no more of them run than that pace needs (feed_launch says what it costs where they start late).
 // A CU that reads a column stripe gets one line of it from HBM every 3 to 4 ns, whatever the stripe's width, the loads in flight, their
 // order or the number of CUs that do so (plain reads of 8192 rows: 24.5 us, 33 where the pitch is a power of two), and a
 // sub-tile needs all K of them: a product of few rows took K x 4 ns however narrow B is.  From the L2 a line takes about 1 ns, and
@@ -258,13 +259,14 @@ __device__ __forceinline__ void gemm_subtile(const uint16_t* __restrict__ A, con
 // In LDS of 90 KB a workgroup, one to a CU by force, the times are the same.
 template <class S>
 __device__ __forceinline__ void fetch_ahead(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, int M, int N, int K, int grid_m,
-                                            int grid_n, int num_xcd, int mode, int a_feeders, int feed_ticks, unsigned char* smem) {
+                                            int grid_n, int num_xcd, int mode, int a_feeders, int b_feeders, int feed_ticks, unsigned char* smem) {
   constexpr int CHUNKS = S::BN / 8;                               // 16-byte chunks of a row of B per sub-tile
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int total = grid_m * grid_n, x = (int)blockIdx.x % num_xcd;
   const int workers = x < total ? (total - 1 - x) / num_xcd + 1 : 0;      // of this XCD, like the feeders
-  const int mine = (int)blockIdx.x / num_xcd - workers, feeders = ((int)gridDim.x - 1 - x) / num_xcd + 1 - workers;
-  if (workers == 0) return;
+  const int mine = (int)blockIdx.x / num_xcd - workers, left = ((int)gridDim.x - 1 - x) / num_xcd + 1 - workers;
+  const int feeders = left < a_feeders + b_feeders ? left : a_feeders + b_feeders;
+  if (workers == 0 || mine >= feeders) return;
   // the columns of sub-tiles on this XCD: first, first + stride, ...
   const bool run = swz_mode_renumbers(mode);
   const int s0 = run ? swz_xcd_renumber(x, total, num_xcd) : x;
@@ -322,10 +324,10 @@ template <class S>
 __global__ __launch_bounds__(S::NT) void gemm_bf16_subtile_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                                   uint16_t* __restrict__ C, int M, int N, int K, int grid_m,
                                                                   int grid_n, int num_xcd, int group_m, int mode, int a_feeders,
-                                                                  int feed_ticks) {
+                                                                  int b_feeders, int feed_ticks) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if ((int)blockIdx.x >= grid_m * grid_n) {                       // uniform
-    fetch_ahead<S>(A, B, M, N, K, grid_m, grid_n, num_xcd, mode, a_feeders, feed_ticks, smem);
+    fetch_ahead<S>(A, B, M, N, K, grid_m, grid_n, num_xcd, mode, a_feeders, b_feeders, feed_ticks, smem);
     return;
   }
   int pm, pn;

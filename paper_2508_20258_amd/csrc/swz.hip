@@ -181,7 +181,7 @@ int launch_subtile(const void* A, const void* B, void* C, int M, int N, int K, c
   if (st != SWZ_OK) return st;
   return launch(kernel, dim3((unsigned)l.blocks), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
                 static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, l.grid_m, l.grid_n, num_xcd, l.group_m, mode,
-                l.a_feeders, l.feed_ticks);
+                l.a_feeders, l.b_feeders, l.feed_ticks);
 }
 
 template <int I>

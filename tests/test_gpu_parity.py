@@ -724,6 +724,38 @@ def test_fed_subtiles_give_the_bits_of_whole_tiles(swz, M, N, K):
         assert torch.isnan(c[M]).all()
 
 
+# what fetches ahead beside another stream's kernels, whose workgroups hold the compute units when it is to start, and in a graph's replays
+@pytest.mark.parametrize("M,N,K", [(16, 2048, 8192), (192, 64, 8192), (1, 8, 4096), (64, 4096, 4096)])
+def test_fed_subtiles_beside_another_stream_and_in_a_graph(swz, M, N, K):
+    assert (swz.gemm_launch_map(M, N, K)[:, 2] == 0).any()
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+    b = torch.randn((K, N), device="cuda", generator=g).to(torch.bfloat16)
+    x, y = (torch.randn((4096, 4096), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    want = swz.gemm(a, b, mode=0, bm=256, bn=256).view(torch.int16)
+    outs = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(12)]
+    other = torch.empty_like(x)
+    fed, busy = torch.cuda.Stream(), torch.cuda.Stream()
+    for s in (fed, busy):
+        s.wait_stream(torch.cuda.current_stream())
+    for c in outs:
+        with torch.cuda.stream(busy):
+            swz.gemm(x, y, other)
+        with torch.cuda.stream(fed):
+            swz.gemm(a, b, c)
+    torch.cuda.synchronize()
+    assert all(torch.equal(c.view(torch.int16), want) for c in outs)
+    graph, c = torch.cuda.CUDAGraph(), torch.empty_like(outs[0])
+    with torch.cuda.graph(graph, stream=fed):
+        swz.gemm(a, b, c)
+    for _ in range(3):
+        c.fill_(float("nan"))
+        graph.replay()
+        swz.gemm(a, b, outs[0])
+        torch.cuda.synchronize()
+        assert torch.equal(c.view(torch.int16), want) and torch.equal(outs[0].view(torch.int16), want)
+
+
 def test_fast_call_and_general_path_agree(swz):
     from paper_2508_20258_amd import binding
     g = torch.Generator(device="cuda").manual_seed(5)
