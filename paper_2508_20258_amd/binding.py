@@ -211,7 +211,7 @@ def gemm(a, b, c=None, mode: int = MODE_XCD_GROUPM, stream=None, **params):
     a (M x K), b (K x N): contiguous torch.bfloat16 CUDA tensors; c (M x N) is allocated if not given.
     Keyword params (bm, bn, bk, group_m, num_xcd, persistent, num_wg) select swz_gemm_ex.
     """
-    if stream is None and not params:
+    if c is not None and stream is None and not params:       # without an output it would be asked in vain, at 0.3 us
         st = _fast.gemm(a, b, c, mode)
         if st is not None:
             _check(st, "swz_gemm")
@@ -295,7 +295,7 @@ def pid_map_persistent_device(grid_m: int, grid_n: int, num_xcd: int, group_m: i
 def transpose(x, out=None, tile: int = 64, mode: int = MODE_XCD_GROUPM + MODE_SKEW, stream=None, **params):
     """out (N x M) = x (M x N) transposed on the GPU through swz_transpose; tensors of 2-byte or 4-byte elements.
     The defaults (64-wide tiles, XCD renumbering + grouped raster + skew) are the fastest combination measured."""
-    if stream is None and not params:
+    if out is not None and stream is None and not params:
         st = _fast.transpose(x, out, tile, mode)
         if st is not None:
             _check(st, "swz_transpose")
@@ -322,7 +322,7 @@ def _row_args(x, out):
 def softmax(x, out=None, chunks: int = 1, mode: int = MODE_XCD, stream=None, **params):
     """Row softmax of a bf16 matrix on the GPU through swz_softmax.  `chunks` (1 to columns / 8) is checked by the library, which
     cuts rows by their length alone."""
-    if stream is None and not params:
+    if out is not None and stream is None and not params:
         st = _fast.softmax(x, out, chunks, mode)
         if st is not None:
             _check(st, "swz_softmax")
@@ -336,7 +336,7 @@ def softmax(x, out=None, chunks: int = 1, mode: int = MODE_XCD, stream=None, **p
 
 def layernorm(x, gamma, beta, out=None, eps: float = 1e-5, chunks: int = 1, mode: int = MODE_XCD, stream=None, **params):
     """Layer normalisation of every row of a bf16 matrix on the GPU through swz_layernorm; `chunks` as for softmax."""
-    if stream is None and not params:
+    if out is not None and stream is None and not params:
         st = _fast.layernorm(x, gamma, beta, out, eps, chunks, mode)
         if st is not None:
             _check(st, "swz_layernorm")

@@ -308,3 +308,27 @@ def test_fast_call_leaves_what_is_not_ordinary_to_the_general_path():
             call()
     with pytest.raises(TypeError):
         fast.bind(1, 2)
+
+
+def test_calls_without_an_output_do_not_try_the_fast_call(monkeypatch):
+    # it would answer None to them: the general path makes the output
+    torch = pytest.importorskip("torch")
+    from paper_2508_20258_amd import binding
+    tried = []
+
+    class Recorder:
+        def __getattr__(self, name):
+            return lambda *args: tried.append(name)
+
+    monkeypatch.setattr(binding, "_fast", Recorder())
+    x = torch.zeros((16, 16), dtype=torch.bfloat16)
+    row = torch.zeros((16,), dtype=torch.bfloat16)
+    for call in (lambda **kw: swz.gemm(x, x, **kw), lambda **kw: swz.transpose(x, **kw), lambda **kw: swz.softmax(x, **kw), lambda **kw: swz.layernorm(x, row, row, **kw)):
+        for kw in ({}, {"stream": object()}, {"num_xcd": 8}):
+            with pytest.raises(AssertionError):
+                call(**kw)
+    assert not tried
+    for call in (lambda: swz.gemm(x, x, x), lambda: swz.transpose(x, x), lambda: swz.softmax(x, x), lambda: swz.layernorm(x, row, row, x)):
+        with pytest.raises(AssertionError):
+            call()
+    assert tried == ["gemm", "transpose", "softmax", "layernorm"]
