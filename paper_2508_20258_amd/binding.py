@@ -1,4 +1,5 @@
-"""ctypes binding for libswz: same names as the C entry points, argument marshalling only.
+"""Binding for libswz: same names as the C entry points, argument marshalling only.  ctypes, and for the ordinary call of gemm, transpose,
+softmax and layernorm a module of C++ (csrc/fastcall.cpp) that makes the same checks.
 
 torch is used for device memory (``tensor.data_ptr()``) and streams only.
 """
@@ -6,6 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import numpy as np
 
@@ -90,19 +92,30 @@ def _load() -> ctypes.CDLL:
 lib = _load()
 
 
+class _NoFast:
+    """In the place of _fastcall.so: nothing is an ordinary call."""
+    gemm = transpose = softmax = layernorm = staticmethod(lambda *args: None)
+
+
 def _load_fast():
     """_fastcall.so: the ordinary call of gemm, transpose, softmax and layernorm (plain CUDA tensors of the current device, an output, no stream
-    or parameters named).  Its functions return the status, or None for a call that is not ordinary."""
-    if torch is None:
-        return None
+    or parameters named).  Its functions return the status, or None for a call that is not ordinary; the general path, which calls the same
+    library, takes those.  Where it is missing or was built for another torch all calls do, 2 us slower, and a warning says so."""
+    if torch is None or torch.version.hip is None:
+        return _NoFast
     try:
         from . import _fastcall as fast
     except ImportError as e:
-        raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} is missing or does not load: build it with "
-                          "`python paper_2508_20258_amd/build.py`. There is no fallback path.") from e
-    fast.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.swz_gemm, lib.swz_transpose, lib.swz_softmax, lib.swz_layernorm)),
-              torch.nn.Parameter)
-    return fast
+        why = str(e)
+    else:
+        if fast.built_for == "swz built for torch " + torch.__version__:
+            fast.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.swz_gemm, lib.swz_transpose, lib.swz_softmax, lib.swz_layernorm)),
+                      torch.nn.Parameter)
+            return fast
+        why = f"{fast.built_for}, this is {torch.__version__}"
+    warnings.warn(f"{os.path.join(_HERE, '_fastcall.so')} is not used, calls take the slower general path ({why}): build it with "
+                  "`python paper_2508_20258_amd/build.py`", RuntimeWarning, stacklevel=2)
+    return _NoFast
 
 
 _fast = _load_fast()

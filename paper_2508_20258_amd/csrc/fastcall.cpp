@@ -153,4 +153,8 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, kMethods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit__fastcall() {
+  PyObject* m = PyModule_Create(&kModule);
+  if (m != nullptr && PyModule_AddStringConstant(m, "built_for", SWZ_TORCH_TAG) != 0) Py_CLEAR(m);       // binding.py uses it with that torch only
+  return m;
+}

@@ -332,3 +332,85 @@ def test_calls_without_an_output_do_not_try_the_fast_call(monkeypatch):
         with pytest.raises(AssertionError):
             call()
     assert tried == ["gemm", "transpose", "softmax", "layernorm"]
+
+
+def _build_module():
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("swz_build_under_test", os.path.join(ROOT, "paper_2508_20258_amd", "build.py"))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod
+
+
+def test_build_finds_the_hip_headers_where_hipcc_is_a_bare_name(monkeypatch):
+    mod = _build_module()
+    for hipcc in ("hipcc", "/opt/rocm/bin/hipcc", "no-such-hipcc"):
+        monkeypatch.setattr(mod, "HIPCC", hipcc)
+        monkeypatch.setenv("PATH", "/opt/rocm/bin:" + os.environ["PATH"])
+        assert os.path.exists(os.path.join(mod.rocm_include(), "hip", "hip_runtime.h")), hipcc
+
+
+def test_build_makes_the_library_where_the_fast_call_does_not_build(monkeypatch, tmp_path):
+    torch = pytest.importorskip("torch")
+    mod = _build_module()
+    monkeypatch.setattr(mod, "FAST", str(tmp_path / "_fastcall.so"))
+    (tmp_path / "_fastcall.so").write_bytes(b"of another torch")
+    made = []
+    monkeypatch.setattr(mod, "build_lib", lambda *a, **k: made.append(a) or mod.LIB)
+    for cxx in ("/nonexistent/g++", "false"):
+        monkeypatch.setenv("CXX", cxx)
+        with pytest.warns(RuntimeWarning, match="not built"):
+            assert mod.build() == mod.LIB
+        assert not os.path.exists(mod.FAST)                       # nothing stale is left to be loaded
+    assert len(made) == 2
+    monkeypatch.setattr(torch.version, "hip", None)               # a torch without ROCm: nothing to build, nothing to warn of
+    assert mod.build() == mod.LIB and mod.build_fastcall() is None
+
+
+def test_fast_call_is_built_again_for_another_torch_or_header(monkeypatch, tmp_path):
+    torch = pytest.importorskip("torch")
+    mod = _build_module()
+    assert mod.fastcall_is_current(torch)
+    header = tmp_path / "swz.h"
+    header.write_text("")
+    os.utime(header, (os.path.getmtime(mod.FAST) - 10,) * 2)
+    assert any(os.path.samefile(d, os.path.join(ROOT, "include", "swz.h")) for d in mod.FAST_DEPS)
+    monkeypatch.setattr(mod, "FAST_DEPS", [str(header)])
+    assert mod.fastcall_is_current(torch)
+    os.utime(header, (os.path.getmtime(mod.FAST) + 10,) * 2)
+    assert not mod.fastcall_is_current(torch)
+    os.utime(header, (os.path.getmtime(mod.FAST) - 10,) * 2)
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + ".1")
+    assert not mod.fastcall_is_current(torch)
+
+
+@pytest.mark.parametrize("how", ["missing", "another torch", "torch without ROCm"])
+def test_package_works_without_the_fast_call(how):
+    import subprocess
+    import sys
+    pytest.importorskip("torch")
+    code = f"""
+import sys, types, warnings
+import torch
+how = {how!r}
+if how == "missing":
+    sys.modules["paper_2508_20258_amd._fastcall"] = None
+elif how == "another torch":
+    sys.modules["paper_2508_20258_amd._fastcall"] = types.SimpleNamespace(built_for="swz built for torch 1.0")
+else:
+    torch.version.hip = None
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    import paper_2508_20258_amd as swz
+assert [x.category for x in w if "_fastcall" in str(x.message)] == ([] if how == "torch without ROCm" else [RuntimeWarning]), w
+assert swz.pid_map(4, 5, 4, 4, 1).tolist()[0] == 0 and swz.gemm_plan(512, 512, 512, num_xcd=8)["bm"] == 128
+x = torch.zeros((16, 16), dtype=torch.bfloat16)
+for call in (lambda: swz.gemm(x, x, x), lambda: swz.transpose(x, x), lambda: swz.softmax(x, x), lambda: swz.layernorm(x, x[0], x[0], x)):
+    try:
+        call()
+    except AssertionError:
+        continue
+    raise SystemExit("not the general path")
+"""
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
