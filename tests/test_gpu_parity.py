@@ -772,6 +772,19 @@ def test_fast_call_and_general_path_agree(swz):
     fast, general = outs(), outs(stream=s)
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(fast, general))
+    # each of the four is taken natively: None would send it down the general path, and that path would agree with itself
+    out = torch.full_like(a, float("nan"))
+    for i, call in enumerate((lambda: binding._fast.gemm(a, b, out, 2), lambda: binding._fast.transpose(a, out, 64, 6), lambda: binding._fast.softmax(a, out, 1, 1),
+                              lambda: binding._fast.layernorm(a, row, row, out, 1e-5, 1, 1))):
+        assert call() == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out, general[i]), i
+    for dtype, n in ((torch.int16, 72), (torch.int32, 68), (torch.float32, 68), (torch.float16, 72)):
+        x = torch.randint(-9999, 9999, (64, n), device="cuda", generator=g).to(dtype)
+        y = torch.zeros((n, 64), dtype=dtype, device="cuda")
+        assert binding._fast.transpose(x, y, 64, 6) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(y, x.t())
     # weights kept as Parameters are ordinary; other subclasses, layouts, types, shapes and devices are not
     out = torch.empty_like(a)
     assert binding._fast.gemm(a, torch.nn.Parameter(b), out, 2) == 0
