@@ -176,8 +176,8 @@ int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_par
  * swz_pid_map does for that grid (`mode`, params->group_m, params->num_xcd; other fields ignored).
  *   in, out : caller-owned DEVICE pointers, 16-byte aligned, must not overlap.
  *   elem_bytes : 2 (M and N multiples of 8) or 4 (M and N multiples of 4, tile 64 only).
- *   tile    : 64 (whole 128-byte lines; the fastest together with mode SWZ_MODE_XCD_GROUPM +
- *             SWZ_MODE_SKEW), 128 (row segments of 256 bytes) or 32 (half lines, shared between
+ *   tile    : 64 (whole 128-byte lines; the fastest, with mode SWZ_MODE_XCD_GROUPM, plus SWZ_MODE_SKEW
+ *             where the pitch of `out` is a multiple of a large power of two), 128 (row segments of 256 bytes) or 32 (half lines, shared between
  *             neighbouring tiles: the case where the mapping decides the L2 hit rate).
  *   Once input plus output exceed the 256 MB memory-side cache the stores of tiles 64 and 128 are
  *   streaming stores (the faster choice there, the slower one below it).

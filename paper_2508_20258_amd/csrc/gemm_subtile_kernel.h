@@ -14,9 +14,11 @@
 //   * every slot address a compile-time constant (the loop is unrolled over the ring, base pointers advance by additions):
 //     with slots computed at run time the scalar instructions of a stage alone took 200 ns, a third more than the whole of a
 //     32x32 stage now (512^3 4.6 -> 3.9 us).
-// What bounds them now is the loads: 1024x1024x4096 in 64x64 sub-tiles takes 16.1 us, 15.0 of them without MFMAs and fragment reads (without the
-// loads 10.2).  A full chip moves 22 TB/s from the L2s to LDS; a product of few rows waits for its column stripes out of HBM, unless
-// other workgroups fetch them ahead (fetch_ahead).  One barrier per two stages instead of one was no faster (32x8192x8192 28.9 -> 35.9 us).
+// What bounds them now is the loads.  In working copies, us a launch with the operands out of HBM and out of a cache: 2048^3 (128x128) 23.2 and 19.2; loads alone, without
+// MFMAs and fragment reads, 22.1 and 15.3; without MFMAs 22.2, 15.8; without fragment reads 22.3, 16.0; without loads 15.1, 14.9.  1024x1024x4096 (64x64) 22.6 and 15.2,
+// loads alone 22.3 and 14.4, without loads 9.8 and 9.3.  A stage of 128x128 takes 560 ns out of HBM and 454 out of a cache (the slope from K = 2048 to 8192 at
+// 2048 x 2048), loads alone 540 and 349: a full chip moves 15 and 19 TB/s, alone 15.5 and 24, from the L2s to LDS.  The LDS is not the bound out of HBM
+// (4 % without the fragment reads; 22 % of the clocks at 2048^3 by its counter).  A product of few rows waits for its column stripes out of HBM, unless other workgroups fetch them ahead (fetch_ahead).  One barrier per two stages instead of one was no faster (32x8192x8192 28.9 -> 35.9 us).
 // Measured (kernel time, operands not in cache; 128x128, 128x256 or 256x256 tiles of gemm_kernel.h -> sub-tiles, the
 // shape the rule in gemm_dispatch.h takes; fed: with feeders):
 //   512^3            8.1 ->  4.0 us (32x32)      1024^3          12.6 ->  6.2 us (64x64)

@@ -356,7 +356,7 @@ __device__ __forceinline__ void anew(rw_u32x4& v) { asm volatile("" : "+v"(v)); 
 // follow each other; 512 threads with twice the vectors, kept as they came, leave room for a second row beside it (128 registers a thread).  Thread
 // t holds the vectors of threads t and t + 512 of the other form and sums them apart, which gives the same sums.  Scheduling
 // barriers keep the compiler from widening several vectors at once.
-//     softmax    1024 x 65536  54 -> 47 us    300 x 65536  21 -> 16.5   1024 x 49152  42 -> 37    4096 x 65536  192 -> 183
+//     softmax    1024 x 65536  54 -> 47 us    300 x 65536  20 -> 15.7   1024 x 49152  42 -> 37    2048 x 65536  99.5 -> 93
 //     layernorm  4096 x 36000 122 -> 111      8000 x 32776 219 -> 198   1024 x 49152  43 -> 40.5
 // Not kept: the next row fetched into LDS meanwhile (55 us at 1024 x 65536: the waves wait to issue the loads and stores), 64 registers and 1024
 // threads (spills).
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void layernorm_wide_rows_kernel(co
   }
 }
 
-// Layer normalisation of rows of up to 8192 elements: a workgroup takes row after row, gamma and beta stay in its registers (they were two thirds of
+// Layer normalisation of rows of 3400 to 4096 and 6000 to 8192 elements, many of them: a workgroup takes row after row, gamma and beta stay in its registers (they were two thirds of
 // what came out of the L2) and the next row is on its way while one is normalised.  One or two workgroups a compute unit are enough.
 //     8192 x 8192  50 -> 45 us    12000 x 7200  70 -> 60    2100 x 8192  16.7 -> 14.9    60000 x 4096  175 -> 163    1100 x 8192  11.1 -> 9.0
 constexpr int kLoopThreads = 256;

@@ -19,7 +19,9 @@
 // the row pitch of `out` is a power of two that stripe lives in a few channels only.  The skewed
 // raster (pid_decode.h) makes tiles that run at the same time differ in their tile row as well as
 // in their tile column; measured at 16384 x 16384 it takes the 64-wide tile from 3.9 to 5.2 TB/s
-// (the 128-wide one from 4.3 to 4.7), and it costs 1-3 % where the pitch is no power of two.
+// (the 128-wide one from 4.3 to 4.7).  Where the pitch is no power of two it costs up to 7 % with the
+// matrices out of HBM (10048 x 7040 56.1 -> 59.2 us, 8192 x 8200 52.3 -> 55.8, 8200 x 8208 55.9 -> 56.9, 10000 x 7000
+// level; at 16384 x 16384 it takes 259 us to 175), and 9 % where they stay in the memory-side cache (10000 x 7000 46 -> 50 us).
 //
 // LDS layout: row r at byte r*(TILE*2), 16-byte chunk c in slot c ^ key(r) (same idea as the
 // GEMM's B panel; TILE*2/16 slots per row).

@@ -346,8 +346,13 @@ def profile_table(src, workload, warmup_ms, launches, num_xcd=8, compute_units=2
     by_kernel = {}
     for mode in PROFILE_MODES:
         by_kernel.setdefault((kernels[mode][0], grids[mode]), []).append(mode)
+    def launched(k, g, modes):
+        blocks = swz.gemm_launch_map(M, N, K, swz.MODES[modes[0]], num_xcd=num_xcd) if not launched_kernel(k)[1] else ()
+        idle = sum(int(b[2] == 0) for b in blocks) if g and len(blocks) == g else 0
+        return f"{k}{f', {g} workgroups' if g else ''}{f', {idle} of them without a block of C: they read A and B ahead or leave at once' if idle else ''} ({', '.join(modes)})"
+
     lines = [f"rocprofv3 summary: swz_gemm, workload {workload} (M={M} N={N} K={K}, {num_xcd} XCDs, plan: tile {bm}x{bm}x64, grid {gm}x{gn}, group_m 4)",
-             "Launched (kernel trace): " + "; ".join(f"{k}{f', {g} workgroups' if g else ''} ({', '.join(m)})" for (k, g), m in by_kernel.items()),
+             "Launched (kernel trace): " + "; ".join(launched(k, g, m) for (k, g), m in by_kernel.items()),
              "MI355X (gfx950), one GPU.  Written by (repository root, TMPDIR=/tmp):",
              f"  {H} profile --workload {workload} --out <dir>",
              "which runs, for MODE in rr, xcd, xcd_groupm:",
@@ -528,7 +533,7 @@ def cmd_profile_rows(args):
     copy_us = _one(f"{out}/copy_kt", "copy", args.launches)["warm_avg_ns"] / 1e3
     copy_gbs = 2.0 * (1 << 30) / (copy_us * 1e-6) / 1e9
     H = "python3 -m paper_2508_20258_amd.harness"
-    lines = ["rocprofv3 summary: swz softmax_rows_kernel / layernorm_rows_kernel, and row_stats_kernel + row_emit_kernel for rows above 98304 elements, bf16, MI355X, one GPU.",
+    lines = ["rocprofv3 summary: swz_softmax and swz_layernorm, bf16, by the kernels named in the last column (one launch, two for rows above 98304 elements), MI355X, one GPU.",
              "Written by (repository root, TMPDIR=/tmp):",
              f"  {H} profile-rows --out <dir>",
              "which runs, for OP in softmax, layernorm and (M, N, CHUNKS, MODE) as in the table:",
@@ -540,16 +545,18 @@ def cmd_profile_rows(args):
              "Calls repeat over the same data; up to 256 MiB of it is partly held by the 256 MB memory-side cache between calls, the 2 GiB of 32768 x 16384 are not.",
              f"The library's plain copy kernel, 1 GiB in + 1 GiB out, same session: {copy_us:.2f} us = {copy_gbs:.0f} GB/s ({100 * copy_gbs / 8000:.1f} % of 8 TB/s).",
              f"us = kernel duration in the kernel trace, average over the last {args.launches} launches of each of the call's kernels, added up; counters likewise.",
-             "", f"{'op':9s} {'M x N':>16s} {'chunks':>6s} {'mode':5s} {'launches':>8s} {'us':>8s} {'GB/s':>6s} {'% of 8 TB/s':>11s} {'L2 hit %':>8s} {'fetch MiB':>10s} {'write MiB':>10s}"]
+             "", f"{'op':9s} {'M x N':>16s} {'chunks':>6s} {'mode':5s} {'launches':>8s} {'us':>8s} {'GB/s':>6s} {'% of 8 TB/s':>11s} {'L2 hit %':>8s} {'fetch MiB':>10s} {'write MiB':>10s}  kernels"]
     for op, m, n, c, mode in cases:
         t = f"{out}/{op}_{m}x{n}_c{c}_{mode}"
-        us = sum(d["warm_avg_ns"] for d in row_kernels(summarize(t + "_kt", None, args.launches))) / 1e3
+        trace = summarize(t + "_kt", None, args.launches)
+        us = sum(d["warm_avg_ns"] for d in row_kernels(trace)) / 1e3
+        names = " + ".join(sorted((launched_kernel(k)[0] for k in trace if row_kernels({k: None})), reverse=True))
         gbs = 4.0 * m * n / (us * 1e-6) / 1e9
         tcc = [d["counters"] for d in row_kernels(summarize_json(t + "_tcc"))]
         h, ms = sum(x["TCC_HIT"]["total"] for x in tcc), sum(x["TCC_MISS"]["total"] for x in tcc)
         f = sum(d["counters"]["FETCH_SIZE"] for d in row_kernels(summarize(t + "_fetch"))) * fs / 1024
         w = sum(d["counters"]["WRITE_SIZE"] for d in row_kernels(summarize(t + "_write"))) * ws / 1024
-        lines.append(f"{op:9s} {m:>6d} x {n:<7d} {c:6d} {mode:5s} {len(tcc):8d} {us:8.2f} {gbs:6.0f} {100 * gbs / 8000:11.1f} {100 * h / (h + ms):8.2f} {f:10.1f} {w:10.1f}")
+        lines.append(f"{op:9s} {m:>6d} x {n:<7d} {c:6d} {mode:5s} {len(tcc):8d} {us:8.2f} {gbs:6.0f} {100 * gbs / 8000:11.1f} {100 * h / (h + ms):8.2f} {f:10.1f} {w:10.1f}  {names}")
     text = "\n".join(lines) + "\n"
     print(text, flush=True)
     with open(os.path.join(out, "rowwise_softmax_layernorm.txt"), "w") as f:
