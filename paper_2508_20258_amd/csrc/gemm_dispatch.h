@@ -75,7 +75,7 @@ struct GemmLaunch {
   int a_feeders, b_feeders, feed_ticks;   // workgroups per XCD that fetch A and B ahead, ticks of 10 ns per 1024 of K; 0: none fetches ahead
 };
 
-// Few rows and a long K: sub-tiles on at most 9/16 of the compute units, and the others fetch their operands ahead of them into the
+// Few rows and a long K: sub-tiles on at most 9/16 of the compute units, and others fetch their operands ahead of them into the
 // L2 of their XCD (fetch_ahead in gemm_subtile_kernel.h says why).  false: not this product.
 //   K from 2048 on, M up to 128; from 4096 on up to 192 (229 x 792 x 16312 60.5 us without, 62.6 with).  Below, what is gained with B in HBM (32 x 8192 x 1024
 //   7.1, 6.5) is lost where it is in a cache already (4.3, 5.3; 192 x 1000 x 2048 6.3, 6.8; but 32 x 8192 x 8192 25.9, 25.1).

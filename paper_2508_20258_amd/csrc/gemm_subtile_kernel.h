@@ -256,8 +256,8 @@ __device__ __forceinline__ void gemm_subtile(const uint16_t* __restrict__ A, con
 // sub-tile needs all K of them: a product of few rows took K x 4 ns however narrow B is.  From the L2 a line takes about 1 ns, and
 // the CUs without a sub-tile read rows in pieces as wide as their XCD's columns, at 2.3 ns a line each and 6 TB/s together.
 // K can not be cut instead: the order of the sums is part of the contract.  Measured (kernel time, operands not in cache, without -> with):
-//   32x8192x8192   40 -> 26 us (HBM: 21)     32x4096x16384  76 -> 31     64x4096x8192   36 -> 18      8x4096x4096  17 -> 9.0
-//   128x1024x8192  30 -> 13.5                16x2048x8192   32 -> 13.5   32x400x11776   41 -> 22     32x8256x8192  36 -> 31
+//   32x8192x8192   40 -> 26 us (HBM: 21)     32x4096x16384  76 -> 29     64x4096x8192   36 -> 18.7    8x4096x4096  17 -> 9.0
+//   128x1024x8192  31 -> 13.4                16x2048x8192   33 -> 13.2   160x1000x16384 60 -> 34.5    192x64x8192  16 -> 12.8
 // In LDS of 90 KB a workgroup, one to a CU by force, the times are the same.
 template <class S>
 __device__ __forceinline__ void fetch_ahead(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, int M, int N, int K, int grid_m,

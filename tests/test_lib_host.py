@@ -370,7 +370,6 @@ def test_build_makes_the_library_where_the_fast_call_does_not_build(monkeypatch,
 def test_fast_call_is_built_again_for_another_torch_or_header(monkeypatch, tmp_path):
     torch = pytest.importorskip("torch")
     mod = _build_module()
-    assert mod.fastcall_is_current(torch)
     header = tmp_path / "swz.h"
     header.write_text("")
     os.utime(header, (os.path.getmtime(mod.FAST) - 10,) * 2)
