@@ -90,7 +90,7 @@ int launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStrea
   static_assert(sizeof...(KArgs) == sizeof...(Args), "argument count");
   if ((int64_t)grid.x * block.x > kLaunchThreads) return SWZ_ERR_OVERFLOW;
   std::tuple<KArgs...> vals{static_cast<KArgs>(args)...};
-  return launch_impl(kernel, grid, block, lds, stream, vals, std::index_sequence_for<KArgs...>{});
+  return launch_impl(kernel, grid, block, 0, stream, vals, std::index_sequence_for<KArgs...>{});
 }
 
 bool valid_mode(int mode) { return mode >= 0 && mode < kModeCount; }
@@ -245,44 +245,50 @@ int resolve_plan(int64_t M, int64_t N, int64_t K, const swz_params* p, swz_param
 constexpr int64_t kMemorySideCacheBytes = (int64_t)256 << 20;   // gfx950: 256 MB behind the L2s, in front of HBM
 
 template <int TILE, bool STREAM>
-int launch_transpose_s(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode,
+int launch_transpose_s(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode, int sweep,
                        hipStream_t stream) {
   const dim3 grid((unsigned)(gm * gn)), block(256);
   auto* i = static_cast<const uint16_t*>(in);
   auto* o = static_cast<uint16_t*>(out);
   const int skew = swz_mode_skewed(mode) ? 1 : 0;
   switch (mode & 3) {
-    case SWZ_MODE_RR: return launch(swz::transpose16_kernel<TILE, kModeRR, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew);
-    case SWZ_MODE_XCD: return launch(swz::transpose16_kernel<TILE, kModeXcd, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew);
-    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose16_kernel<TILE, kModeXcdGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew);
-    default: return launch(swz::transpose16_kernel<TILE, kModeGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew);
+    case SWZ_MODE_RR: return launch(swz::transpose16_kernel<TILE, kModeRR, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD: return launch(swz::transpose16_kernel<TILE, kModeXcd, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose16_kernel<TILE, kModeXcdGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    default: return launch(swz::transpose16_kernel<TILE, kModeGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
   }
 }
 
 template <bool STREAM>
-int launch_transpose32(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode,
+int launch_transpose32(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode, int sweep,
                        hipStream_t stream) {
   const dim3 grid((unsigned)(gm * gn)), block(256);
   auto* i = static_cast<const uint32_t*>(in);
   auto* o = static_cast<uint32_t*>(out);
   const int skew = swz_mode_skewed(mode) ? 1 : 0;
   switch (mode & 3) {
-    case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew);
-    case SWZ_MODE_XCD: return launch(swz::transpose32_kernel<kModeXcd, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew);
-    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose32_kernel<kModeXcdGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew);
-    default: return launch(swz::transpose32_kernel<kModeGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew);
+    case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD: return launch(swz::transpose32_kernel<kModeXcd, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose32_kernel<kModeXcdGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    default: return launch(swz::transpose32_kernel<kModeGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
   }
 }
 
 template <int TILE>
-int launch_transpose(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode,
+int launch_transpose(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode, int sweep,
                      hipStream_t stream) {
   // streaming stores once input plus output no longer fit the memory-side cache (and only where a store
   // instruction covers whole lines: tiles of 64 and 128)
   if (TILE >= 64 && (int64_t)M * N * 4 > kMemorySideCacheBytes)
-    return launch_transpose_s<TILE, true>(in, out, M, N, gm, gn, num_xcd, group_m, mode, stream);
-  return launch_transpose_s<TILE, false>(in, out, M, N, gm, gn, num_xcd, group_m, mode, stream);
+    return launch_transpose_s<TILE, true>(in, out, M, N, gm, gn, num_xcd, group_m, mode, sweep, stream);
+  return launch_transpose_s<TILE, false>(in, out, M, N, gm, gn, num_xcd, group_m, mode, sweep, stream);
 }
+
+// Which transposes under the default mode, with the band height left to the library, take the sweep of tile_sweep.h.  Time of the sweep over that of the skewed raster: tiles
+// whose pitches are no powers of two 0.84 to 1.00 (8192 x 8192 x 2 B 0.89, 5824 x 5824 x 4 B 0.92), with a pitch of `out` of 32 KiB and more at 16 KiB steps and one of `in` at 8 KiB steps
+// 0.93 to 1.22 (8192 x 8192 x 4 B 1.12, 16384 x 8192 x 4 B 1.21).  Blocks into part lines, four bytes: 0.93 to 0.99, pitch of `in` a multiple of 8 KiB 0.98 to 1.04; two bytes level.
+bool sweep_tiles(int64_t M, int64_t N, int elem_bytes) { return !(M * elem_bytes % 16384 == 0 && M * elem_bytes >= 32768 && N * elem_bytes % 8192 == 0); }
+bool sweep_part_lines(int64_t N, int elem_bytes) { return elem_bytes == 4 && N * elem_bytes % 8192 != 0; }
 
 // Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines, rather than 64 rows in 256 threads.  Time of the tall ones over
 // that of the others, matrices not in cache, 17 to 200 MiB moved:
@@ -303,11 +309,12 @@ bool tall_line_blocks(int64_t M, int64_t N, int elem_bytes) {
 }
 
 template <class T, bool TALL>
-int launch_transpose_lines(const void* in, void* out, int M, int N, int gn, int num_xcd, int group_m, int mode, hipStream_t stream) {
+int launch_transpose_lines(const void* in, void* out, int M, int N, int gn, int num_xcd, int group_m, int mode, bool sweep, hipStream_t stream) {
   constexpr int ROWS = swz::lines_rows((int)sizeof(T), TALL);
   const int blocks_m = (M + ROWS - 1) / ROWS;
   return launch(swz::transpose_lines_kernel<T, ROWS>, dim3((unsigned)(blocks_m * gn)), dim3(swz::lines_threads(ROWS)), 0, stream, static_cast<const T*>(in),
-                static_cast<T*>(out), M, N, blocks_m, gn, num_xcd, group_m < blocks_m ? group_m : blocks_m, mode);
+                static_cast<T*>(out), M, N, blocks_m, gn, num_xcd, group_m < blocks_m ? group_m : blocks_m, mode,
+                sweep ? swz_sweep_rows(blocks_m, num_xcd, (int)sizeof(T)) : 0);
 }
 
 // Threads per row and 16-byte vectors each of them holds, for rows of up to max_vecs vectors: the fastest of the pairs
@@ -571,22 +578,25 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   // rows a block reads cost more than its part lines (blocks of 64 rows: 1000 x 1004 x 4 B 5.4 us against 5.6, 1000 x 1000 x 2 B 3.7 against 4.2; 3000 x
   // 3000 x 2 B, 34 MiB moved, 11.5 against 9.9).
   const bool part_lines = ((M * elem_bytes) & 127) != 0 || (reinterpret_cast<uintptr_t>(out) & 127) != 0;
+  const bool ours = tile == 64 && mode == (SWZ_MODE_XCD_GROUPM | SWZ_MODE_SKEW) && (params == nullptr || params->group_m == 0);
   if (tile == 64 && part_lines && M < ((int64_t)1 << 30) && 2 * M * N * elem_bytes >= ((int64_t)16 << 20)) {
+    const bool sweep = ours && sweep_part_lines(N, elem_bytes);
     const bool tall = tall_line_blocks(M, N, elem_bytes);
     if (elem_bytes == 2)
-      return tall ? launch_transpose_lines<uint16_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, stream)
-                  : launch_transpose_lines<uint16_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, stream);
-    return tall ? launch_transpose_lines<uint32_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, stream)
-                : launch_transpose_lines<uint32_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, stream);
+      return tall ? launch_transpose_lines<uint16_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream)
+                  : launch_transpose_lines<uint16_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream);
+    return tall ? launch_transpose_lines<uint32_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream)
+                : launch_transpose_lines<uint32_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream);
   }
+  const int sweep = ours && sweep_tiles(M, N, elem_bytes) ? swz_sweep_rows((int)gm, num_xcd, elem_bytes) : 0;
   if (elem_bytes == 4) {
     if (M * N * 8 > kMemorySideCacheBytes)
-      return launch_transpose32<true>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, stream);
-    return launch_transpose32<false>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, stream);
+      return launch_transpose32<true>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
+    return launch_transpose32<false>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
   }
-  if (tile == 128) return launch_transpose<128>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, stream);
-  return tile == 64 ? launch_transpose<64>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, stream)
-                    : launch_transpose<32>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, stream);
+  if (tile == 128) return launch_transpose<128>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
+  return tile == 64 ? launch_transpose<64>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream)
+                    : launch_transpose<32>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
 }
 
 int swz_softmax(const void* in, void* out, int64_t M, int64_t N, int chunks, int mode, const swz_params* params,

@@ -31,11 +31,18 @@
 #include <stdint.h>
 
 #include "pid_decode.h"
+#include "tile_sweep.h"
 
 namespace swz {
 
 typedef __attribute__((ext_vector_type(4))) short t_s16x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t t_u32x4;
+
+// Block (pm, pn) of this workgroup: by the mode, or, where sweep is not 0, in the sweep with so many tile rows to an XCD.
+__device__ __forceinline__ void tr_block(int grid_m, int grid_n, int num_xcd, int group_m, int mode, int sweep, int* pm, int* pn) {
+  if (sweep != 0) swz_sweep_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, sweep, pm, pn);       // uniform
+  else swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, mode, pm, pn);
+}
 
 template <int TILE>
 __device__ __forceinline__ int tr_key(int row) {
@@ -51,7 +58,7 @@ __device__ __forceinline__ int tr_key(int row) {
 template <int TILE, int MODE, bool STREAM>
 __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
                                                           int M, int N, int grid_m, int grid_n, int num_xcd,
-                                                          int group_m, int skew) {
+                                                          int group_m, int skew, int sweep) {
   constexpr int ROW_BYTES = TILE * 2;
   constexpr int SLOTS = ROW_BYTES / 16;                  // 16-byte chunks per tile row
   constexpr int CHUNKS = TILE * SLOTS;                   // chunks per tile
@@ -59,7 +66,7 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
   __shared__ __attribute__((aligned(16))) unsigned char tile[TILE * ROW_BYTES];
 
   int pm, pn;
-  swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, MODE | (skew ? kModeSkew : 0), &pm, &pn);
+  tr_block(grid_m, grid_n, num_xcd, group_m, MODE | (skew ? kModeSkew : 0), sweep, &pm, &pn);
   const int m0 = pm * TILE, n0 = pn * TILE;
   const int tid = threadIdx.x;
 
@@ -159,11 +166,11 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
 template <int MODE, bool STREAM>
 __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
                                                           int M, int N, int grid_m, int grid_n, int num_xcd,
-                                                          int group_m, int skew) {
+                                                          int group_m, int skew, int sweep) {
   constexpr int TILE = 64, SLOTS = TILE / 4, CHUNKS = TILE * SLOTS, ROW_BYTES = TILE * 4;
   __shared__ __attribute__((aligned(16))) unsigned char tile[TILE * ROW_BYTES];
   int pm, pn;
-  swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, MODE | (skew ? kModeSkew : 0), &pm, &pn);
+  tr_block(grid_m, grid_n, num_xcd, group_m, MODE | (skew ? kModeSkew : 0), sweep, &pm, &pn);
   const int m0 = pm * TILE, n0 = pn * TILE;
   const int tid = threadIdx.x;
   auto key = [](int r) { return ((r >> 2) & 7) << 1; };
@@ -222,13 +229,13 @@ __host__ __device__ constexpr int lines_threads(int rows) { return rows == 64 ? 
 
 template <class T, int BM_>
 __global__ __launch_bounds__(lines_threads(BM_)) void transpose_lines_kernel(const T* __restrict__ in, T* __restrict__ out, int M, int N, int grid_m,
-                                                                                  int grid_n, int num_xcd, int group_m, int mode) {
+                                                                                  int grid_n, int num_xcd, int group_m, int mode, int sweep) {
   constexpr int TILE = 64, BM = BM_, NT = lines_threads(BM_);
   constexpr int CH = 16 / (int)sizeof(T), E = 128 / (int)sizeof(T);                  // elements per chunk, per line
   constexpr int SLOTS = TILE / CH, ROWS = BM + E, ROW_BYTES = TILE * (int)sizeof(T), LINES = BM / E;
   __shared__ __attribute__((aligned(16))) unsigned char tile[ROWS * ROW_BYTES];
   int pm, pn;
-  swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, mode, &pm, &pn);
+  tr_block(grid_m, grid_n, num_xcd, group_m, mode, sweep, &pm, &pn);
   const int m0 = pm * BM - E, n0 = pn * TILE;                    // first row of `in` in the tile, first column
   const int tid = threadIdx.x;
   auto key = [](int r) { return sizeof(T) == 2 ? (r >> 3) & 7 : ((r >> 2) & 7) << 1; };

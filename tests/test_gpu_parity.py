@@ -687,6 +687,24 @@ def test_transpose_into_part_lines_is_bit_exact(swz, elem_bytes, M, N, offset):
         assert (buf[:offset] == -7).all() and (buf[offset + N * M:] == -7).all()
 
 
+# the default order: windows of the sweep without a rest and with one, too few rows for a window, pitches that keep the skewed raster
+@pytest.mark.parametrize("elem_bytes,M,N", [(2, 2048, 64), (2, 2056, 200), (2, 4104, 1032), (2, 520, 5000), (2, 4160, 2056), (2, 4096, 4096), (2, 16384, 2048), (2, 64, 40000), (2, 8192, 8256),
+                                            (4, 2048, 64), (4, 2116, 196), (4, 516, 2052), (4, 4100, 4100), (4, 8192, 2048), (4, 60, 30004), (4, 8256, 4160)])
+def test_default_order_of_a_transpose_is_bit_exact(swz, elem_bytes, M, N):
+    dtype = torch.int16 if elem_bytes == 2 else torch.int32
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    x = torch.randint(-(1 << 15), 1 << 15, (M, N), device="cuda", generator=g).to(dtype)
+    if elem_bytes == 4:
+        x = x * 65537 + 77
+    want = x.t().contiguous()
+    for params in ({}, dict(num_xcd=3), dict(num_xcd=1000), dict(group_m=3)):
+        buf = torch.full((N * M + 64,), -7, dtype=dtype, device="cuda")
+        swz.transpose(x, buf[:N * M].view(N, M), **params)
+        torch.cuda.synchronize()
+        assert torch.equal(buf[:N * M].view(N, M), want), params
+        assert (buf[N * M:] == -7).all()
+
+
 # 256x256 tiles beyond whole rounds of 256 compute units: up to 64 (quarters), up to 128 (halves), more (whole); ragged edges among
 # the pieces, pieces outside C, one tile left over
 @pytest.mark.parametrize("M,N", [(4352, 4096), (4200, 4104), (65793, 248), (5120, 4608), (4610, 5000), (4100, 6200), (8200, 8200)])
