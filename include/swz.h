@@ -179,15 +179,15 @@ int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_par
  *   tile    : 64 (whole 128-byte lines; the fastest, with mode SWZ_MODE_XCD_GROUPM + SWZ_MODE_SKEW), 128 (row segments of 256 bytes) or 32 (half lines, shared
  *             between neighbouring tiles: the case where the mapping decides the L2 hit rate).
  *   With tile 64, mode SWZ_MODE_XCD_GROUPM + SWZ_MODE_SKEW (6) and group_m left to the library (0) the order is the library's choice: the skewed raster
- *   that the mode names where the pitch of `out` is a multiple of 16 KiB, 32 KiB at least, and that of `in` of 8 KiB, else a sweep: all XCDs move
+ *   that the mode names where the pitches of `in` and `out` are both multiples of 16 KiB and one of them of 64 KiB, else a sweep: all XCDs move
  *   along the columns of a window of 4 * num_xcd tile rows together, every XCD in four neighbouring rows of its own (a bijection like the others; fewer rows in
  *   a low grid).  A group_m that is named always gets the raster that swz_pid_map describes.
  *   Once input plus output exceed the 256 MB memory-side cache the stores of tiles 64 and 128 are
  *   streaming stores (the faster choice there, the slower one below it).
  *   Where rows of `out` do not start on 128-byte lines, tile 64 (from 16 MiB moved) is done in blocks of 64 columns, a workgroup each, which
  *   writes the whole lines nearest to its block; the id -> block map is that of swz_pid_map (or the sweep: elem_bytes 4, pitch of `in` no multiple of 8 KiB) for the grid of those blocks, and group_m
- *   counts them.  A block has 256 rows for elem_bytes 2 where M > 64, and M <= 448 or 30 MiB and more are moved, but not for 256 < M < 280; 128 rows for
- *   elem_bytes 4 where M > 48, and M <= 256 or 44 MiB and more are moved, but not for 128 < M < 160; 64 rows otherwise, and wherever blocks of
+ *   counts them.  A block has 256 rows for elem_bytes 2 where M > 64, and M <= 1024 or 40 MiB and more are moved, but not for 256 < M < 280; 128 rows for
+ *   elem_bytes 4 where M > 48, but not for 128 < M < 160; 64 rows otherwise, and wherever blocks of
  *   those rows would be 2^23 or more.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null, M/N < 1, unknown mode), UNSUPPORTED (elem_bytes not 2 or 4, tile not 32/64/128

@@ -90,7 +90,7 @@ int launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStrea
   static_assert(sizeof...(KArgs) == sizeof...(Args), "argument count");
   if ((int64_t)grid.x * block.x > kLaunchThreads) return SWZ_ERR_OVERFLOW;
   std::tuple<KArgs...> vals{static_cast<KArgs>(args)...};
-  return launch_impl(kernel, grid, block, 0, stream, vals, std::index_sequence_for<KArgs...>{});
+  return launch_impl(kernel, grid, block, lds, stream, vals, std::index_sequence_for<KArgs...>{});
 }
 
 bool valid_mode(int mode) { return mode >= 0 && mode < kModeCount; }
@@ -244,18 +244,32 @@ int resolve_plan(int64_t M, int64_t N, int64_t K, const swz_params* p, swz_param
 
 constexpr int64_t kMemorySideCacheBytes = (int64_t)256 << 20;   // gfx950: 256 MB behind the L2s, in front of HBM
 
+// How many bytes the workgroups of a two-byte transpose have on their way at a time: both loads of a thread or one (paced), and LDS on top of the tile's 8 KB, which
+// holds five workgroups to a compute unit instead of eight.  Up to 32 MiB latency counts: both, eight (2176 x 2968 7.5 us, paced 7.7; 3200 x 1440 5.2, 6.0).  Above, the HBM serves
+// more bytes a second the fewer are asked for, 32 to 40 KB a compute unit: paced 3712 x 17656 57.6, both 61.9, both and five 58.4; 20416 x 1912 31.7, 34.4, 33.2; 12416 x 2704
+// 26.3, 29.6, 28.7.  At pitches of whole 4096 elements fewer workgroups are better than paced ones: 8192 x 8192 49.2, 50.8, 47.1; 16384 x 16384 179.4, 186.3, 176.3; 4096 x 4096
+// 15.4, 13.8, 14.3.  (Four bytes, all four loads: five workgroups to a compute unit 5824 x 5824 48.7 us, paced 50.4; from 256 MiB on three: 3648 x 9272 50.1, five 51.0, eight 51.5,
+// paced 54.1; 8192 x 8192 87.9, 90.7, 92.4, 90.0.)
+struct LoadPace { int paced, lds; };
+LoadPace load_pace(int tile, int M, int N) {
+  if (tile != 64 || (int64_t)M * N * 4 < ((int64_t)32 << 20)) return {0, 0};
+  if ((int64_t)M * 2 % 8192 == 0) return {0, 24576};
+  return {1, 0};
+}
+
 template <int TILE, bool STREAM>
 int launch_transpose_s(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode, int sweep,
                        hipStream_t stream) {
   const dim3 grid((unsigned)(gm * gn)), block(256);
   auto* i = static_cast<const uint16_t*>(in);
   auto* o = static_cast<uint16_t*>(out);
+  const LoadPace pace = load_pace(TILE, M, N);
   const int skew = swz_mode_skewed(mode) ? 1 : 0;
   switch (mode & 3) {
-    case SWZ_MODE_RR: return launch(swz::transpose16_kernel<TILE, kModeRR, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    case SWZ_MODE_XCD: return launch(swz::transpose16_kernel<TILE, kModeXcd, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose16_kernel<TILE, kModeXcdGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    default: return launch(swz::transpose16_kernel<TILE, kModeGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_RR: return launch(swz::transpose16_kernel<TILE, kModeRR, STREAM>, grid, block, pace.lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep, pace.paced);
+    case SWZ_MODE_XCD: return launch(swz::transpose16_kernel<TILE, kModeXcd, STREAM>, grid, block, pace.lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep, pace.paced);
+    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose16_kernel<TILE, kModeXcdGroupM, STREAM>, grid, block, pace.lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep, pace.paced);
+    default: return launch(swz::transpose16_kernel<TILE, kModeGroupM, STREAM>, grid, block, pace.lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep, pace.paced);
   }
 }
 
@@ -265,12 +279,13 @@ int launch_transpose32(const void* in, void* out, int M, int N, int gm, int gn, 
   const dim3 grid((unsigned)(gm * gn)), block(256);
   auto* i = static_cast<const uint32_t*>(in);
   auto* o = static_cast<uint32_t*>(out);
+  const size_t lds = STREAM ? 32768 : 12288;       // on top of the tile's 16 KB: three or five workgroups to a compute unit
   const int skew = swz_mode_skewed(mode) ? 1 : 0;
   switch (mode & 3) {
-    case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    case SWZ_MODE_XCD: return launch(swz::transpose32_kernel<kModeXcd, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose32_kernel<kModeXcdGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    default: return launch(swz::transpose32_kernel<kModeGroupM, STREAM>, grid, block, 0, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD: return launch(swz::transpose32_kernel<kModeXcd, STREAM>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose32_kernel<kModeXcdGroupM, STREAM>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    default: return launch(swz::transpose32_kernel<kModeGroupM, STREAM>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
   }
 }
 
@@ -284,28 +299,28 @@ int launch_transpose(const void* in, void* out, int M, int N, int gm, int gn, in
   return launch_transpose_s<TILE, false>(in, out, M, N, gm, gn, num_xcd, group_m, mode, sweep, stream);
 }
 
-// Which transposes under the default mode, with the band height left to the library, take the sweep of tile_sweep.h.  Time of the sweep over that of the skewed raster: tiles
-// whose pitches are no powers of two 0.84 to 1.00 (8192 x 8192 x 2 B 0.89, 5824 x 5824 x 4 B 0.92), with a pitch of `out` of 32 KiB and more at 16 KiB steps and one of `in` at 8 KiB steps
-// 0.93 to 1.22 (8192 x 8192 x 4 B 1.12, 16384 x 8192 x 4 B 1.21).  Blocks into part lines, four bytes: 0.93 to 0.99, pitch of `in` a multiple of 8 KiB 0.98 to 1.04; two bytes level.
-bool sweep_tiles(int64_t M, int64_t N, int elem_bytes) { return !(M * elem_bytes % 16384 == 0 && M * elem_bytes >= 32768 && N * elem_bytes % 8192 == 0); }
+// Which transposes under the default mode, with the band height left to the library, take the sweep of tile_sweep.h.  Time of the sweep over that of the skewed raster, loads and
+// occupancy as they are now.  Tiles: no pitch a power of two 0.84 to 1.00, on average 0.92 (40 sizes).  Both pitches multiples of 16 KiB: 8192 x 8192 x 4 B 0.99, 12288 x 8192
+// x 4 B 0.98, 16384 x 8192 x 2 B 0.94, but with one of 64 KiB 32768 x 8192 x 2 B 1.14, 16384 x 8192 x 4 B 1.13, 8192 x 16384 x 4 B 1.08, 16384 x 4096 x 4 B 1.01; 16384 x 16384
+// x 2 B (32 KiB) level.  Blocks into part lines, four bytes: 0.91 to 0.99, pitch of `in` a multiple of 8 KiB 0.98 to 1.04.
+bool sweep_tiles(int64_t M, int64_t N, int elem_bytes) { return (M | N) * elem_bytes % 16384 != 0 || (M * elem_bytes % 65536 != 0 && N * elem_bytes % 65536 != 0); }
 bool sweep_part_lines(int64_t N, int elem_bytes) { return elem_bytes == 4 && N * elem_bytes % 8192 != 0; }
 
-// Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines, rather than 64 rows in 256 threads.  Time of the tall ones over
-// that of the others, matrices not in cache, 17 to 200 MiB moved:
-//   Few rows, one block either way, most of a tall one empty: two bytes 8 rows 1.61 to 1.76, 24 rows 1.22 to 1.41, 56 rows 1.10 to 1.16, but 72 rows
-//   0.80 to 0.91; four bytes 4 rows 1.42 to 1.53, 28 rows 1.00 to 1.13, 44 rows 0.89 to 1.14, but 52 and 60 rows 0.91 to 1.04, 68 rows 0.85 to 0.98.
-//   Just above one block, the second nearly empty: 264 rows of two bytes 0.96 to 1.09 (280 rows 0.92 to 1.03), 132 of four 0.98 to 1.07, 148
-//   0.96 to 1.11 (164 rows 0.92 to 1.02).
-//   Few blocks for the compute units: two bytes, 17, 24, 28 and 31 MiB, 440 rows 0.92, 0.88, 0.84, 0.87; 520 rows 1.10, 1.11, 1.07, 0.91; 1032 rows 1.10, 0.97,
-//   1.06, 0.93; 8200 rows 1.12, 1.08, 0.91, 0.91; from 33 MiB on 0.73 to 1.01.  Four bytes, 17, 24, 40 and 47 MiB, 252 rows 0.98, 0.89, 0.94, 0.93; 516
-//   rows 1.06, 0.97, 1.09, 0.83; 2052 rows 1.07, 1.02, 0.98, 0.89; from 50 MiB on 0.84 to 0.99.
+// Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines, rather than 64 rows in 256 threads.  us with the tall ones and with the
+// others, operands in the memory-side cache (three sets of buffers in turn):
+//   Few rows, one block either way, most of a tall one empty: two bytes 72 rows 7.99, 8.08 (31 MiB moved) and 136 rows 4.69, 4.71, above 64 rows never behind by more
+//   than 5 %; four bytes 52 rows 9.88, 10.59 (47 MiB).
+//   Just above one block, the second nearly empty: four bytes 132 rows 4.47, 4.18 (17 MiB; out of HBM 7.49, 6.19), from 160 rows on level; two bytes out of HBM 264
+//   rows 8.39, 7.10, 280 rows 7.11, 7.35.
+//   Few blocks for the compute units, two bytes: above 1024 rows 1032 x 4312 5.49, 5.31; 8200 x 536 5.08, 4.50; 4104 x 1976 8.31, 7.23; from 40 MiB on 0.83 to 1.08.  Up to
+//   1024 rows 520 x 8568 4.66, 5.55; 776 x 8104 5.78, 6.94.  Four bytes 516 x 4312 4.21, 5.27, 2052 x 1912 6.34, 6.47, 1028 x 2160 4.53, 4.32.
 // A launch has to hold its threads too: with one row of blocks, or two instead of three, half and three quarters as many columns fit.
 bool tall_line_blocks(int64_t M, int64_t N, int elem_bytes) {
   const int rows = swz::lines_rows(elem_bytes, true);
   const int64_t blocks_m = (M + rows - 1) / rows, gn = (N + 63) / 64, moved = 2 * M * N * elem_bytes;
   if (blocks_m * gn * swz::lines_threads(rows) > kLaunchThreads) return false;
-  if (elem_bytes == 2) return M > 64 && (M <= 256 || M >= 280) && (M <= 448 || moved >= ((int64_t)30 << 20));
-  return M > 48 && (M <= 128 || M >= 160) && (M <= 256 || moved >= ((int64_t)44 << 20));
+  if (elem_bytes == 2) return M > 64 && (M <= 256 || M >= 280) && (M <= 1024 || moved >= ((int64_t)40 << 20));
+  return M > 48 && (M <= 128 || M >= 160);
 }
 
 template <class T, bool TALL>

@@ -19,9 +19,10 @@
 // the row pitch of `out` is a power of two that stripe lives in a few channels only.  The skewed
 // raster (pid_decode.h) makes tiles that run at the same time differ in their tile row as well as
 // in their tile column; measured at 16384 x 16384 it takes the 64-wide tile from 3.9 to 5.2 TB/s
-// (the 128-wide one from 4.3 to 4.7).  Where the pitch is no power of two it costs up to 7 % with the
-// matrices out of HBM (10048 x 7040 56.1 -> 59.2 us, 8192 x 8200 52.3 -> 55.8, 8200 x 8208 55.9 -> 56.9, 10000 x 7000
-// level; at 16384 x 16384 it takes 259 us to 175), and 9 % where they stay in the memory-side cache (10000 x 7000 46 -> 50 us).
+// (the 128-wide one from 4.3 to 4.7).  Where no such pitch asks for it, the tiles are swept (tile_sweep.h): us under the skewed raster -> swept, loads and occupancy as
+// they are now: two bytes 8192 x 8192 55 -> 47.5, 10048 x 7040 60 -> 52.7, 3712 x 17656 64 -> 58, 16384 x 8192 93 -> 87, 4096 x 32768 98 -> 87; four bytes 5824 x 5824
+// 54 -> 48.8, 5800 x 5804 55 -> 51.3.  What is left to a copy (5824 x 5824 x 4 43 us) is the memory's: workgroups that copy the same blocks to the same places without
+// transposing them take 48 to 54 us by the order of the blocks, 47 to 52 with both sides of a block in one piece of 16 KiB.
 //
 // LDS layout: row r at byte r*(TILE*2), 16-byte chunk c in slot c ^ key(r) (same idea as the
 // GEMM's B panel; TILE*2/16 slots per row).
@@ -44,6 +45,16 @@ __device__ __forceinline__ void tr_block(int grid_m, int grid_n, int num_xcd, in
   else swz_decode_tile((int)blockIdx.x, grid_m, grid_n, num_xcd, group_m, mode, pm, pn);
 }
 
+// Where the 16 bytes at row m, column n of `in` are, m and n brought inside it: no branch around a load.  With one, the compiler waits for every load
+// before it issues the next, and a block's two to five loads a thread took as many trips to memory (us one at a time -> together: 1024 x 1024 x 4 B 4.0 -> 2.7,
+// 2048 x 2048 x 2 B 5.4 -> 4.6, 300 x 600 x 4 B 2.6 -> 2.2).
+template <class T>
+__device__ __forceinline__ const t_u32x4* tr_source(const T* in, int m, int n, int M, int N) {
+  m = m < 0 ? 0 : m < M ? m : M - 1;
+  n = n < N ? n : N - 16 / (int)sizeof(T);
+  return reinterpret_cast<const t_u32x4*>(in + (size_t)m * N + n);
+}
+
 template <int TILE>
 __device__ __forceinline__ int tr_key(int row) {
   // the 16 lanes of a transposing read take 4 consecutive rows x 32 bytes (a chunk pair): give
@@ -58,7 +69,7 @@ __device__ __forceinline__ int tr_key(int row) {
 template <int TILE, int MODE, bool STREAM>
 __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
                                                           int M, int N, int grid_m, int grid_n, int num_xcd,
-                                                          int group_m, int skew, int sweep) {
+                                                          int group_m, int skew, int sweep, int paced) {
   constexpr int ROW_BYTES = TILE * 2;
   constexpr int SLOTS = ROW_BYTES / 16;                  // 16-byte chunks per tile row
   constexpr int CHUNKS = TILE * SLOTS;                   // chunks per tile
@@ -71,21 +82,23 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
   const int tid = threadIdx.x;
 
   // ---- in -> LDS: row-contiguous 16-byte chunks (columns are whole chunks: N % 8 == 0) ----
+  // Rows and columns outside `in` come from its edge (tr_source), their part of the tile is never stored.
+  t_u32x4 v[PER_THREAD];
 #pragma unroll
   for (int i = 0; i < PER_THREAD; ++i) {
     const int q = tid + 256 * i;
-    if (q < CHUNKS) {
-      const int r = q / SLOTS, c = q % SLOTS;
-      t_u32x4 v = {0u, 0u, 0u, 0u};
-      if (m0 + r < M && n0 + c * 8 < N) {
-        const t_u32x4* src = reinterpret_cast<const t_u32x4*>(in + (size_t)(m0 + r) * N + n0 + c * 8);
-        // whole-line tiles read every line exactly once: streaming loads; half-line tiles rely on the L2 keeping
-        // the line for the neighbouring tile
-        if constexpr (TILE >= 64) v = __builtin_nontemporal_load(src);
-        else v = *src;
-      }
-      *reinterpret_cast<t_u32x4*>(tile + r * ROW_BYTES + ((c ^ tr_key<TILE>(r)) << 4)) = v;
-    }
+    if (CHUNKS % 256 != 0 && q >= CHUNKS) continue;
+    const t_u32x4* src = tr_source(in, m0 + q / SLOTS, n0 + q % SLOTS * 8, M, N);
+    // whole-line tiles read every line exactly once: streaming loads; half-line tiles rely on the L2 keeping
+    // the line for the neighbouring tile
+    if constexpr (TILE >= 64) v[i] = __builtin_nontemporal_load(src);
+    else v[i] = *src;
+    if (PER_THREAD > 1 && paced != 0) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");        // uniform
+  }
+#pragma unroll
+  for (int i = 0; i < PER_THREAD; ++i) {
+    const int q = tid + 256 * i, r = q / SLOTS, c = q % SLOTS;
+    if (CHUNKS % 256 == 0 || q < CHUNKS) *reinterpret_cast<t_u32x4*>(tile + r * ROW_BYTES + ((c ^ tr_key<TILE>(r)) << 4)) = v[i];
   }
   __syncthreads();
 
@@ -174,14 +187,16 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
   const int m0 = pm * TILE, n0 = pn * TILE;
   const int tid = threadIdx.x;
   auto key = [](int r) { return ((r >> 2) & 7) << 1; };
+  t_u32x4 in_v[CHUNKS / 256];
 #pragma unroll
   for (int i = 0; i < CHUNKS / 256; ++i) {
     const int q = tid + 256 * i;
-    const int r = q / SLOTS, c = q % SLOTS;
-    t_u32x4 v = {0u, 0u, 0u, 0u};
-    if (m0 + r < M && n0 + c * 4 < N)               // N % 4 == 0: the 4 elements are in or out together
-      v = __builtin_nontemporal_load(reinterpret_cast<const t_u32x4*>(in + (size_t)(m0 + r) * N + n0 + c * 4));
-    *reinterpret_cast<t_u32x4*>(tile + r * ROW_BYTES + ((c ^ key(r)) << 4)) = v;
+    in_v[i] = __builtin_nontemporal_load(tr_source(in, m0 + q / SLOTS, n0 + q % SLOTS * 4, M, N));
+  }
+#pragma unroll
+  for (int i = 0; i < CHUNKS / 256; ++i) {
+    const int q = tid + 256 * i, r = q / SLOTS, c = q % SLOTS;
+    *reinterpret_cast<t_u32x4*>(tile + r * ROW_BYTES + ((c ^ key(r)) << 4)) = in_v[i];
   }
   __syncthreads();
   const int lane = tid & 63, wave = tid >> 6;
@@ -222,6 +237,8 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
 // Bound by HBM and the rows read twice.  Measured, matrices not in cache, 64 rows and 256 threads -> tall (us; GB/s of the matrix read and written):
 //     two bytes   10000 x 7000  75 -> 60 (4670)    8200 x 8208  67 -> 57 (4720)    30000 x 1544   49 -> 41 (4560)    3000 x 3000  10.7 -> 9.0
 //     four bytes   5800 x 5804  60 -> 56 (4810)    200 x 20000  9.5 -> 8.6         15764 x 8092  214 -> 204 (5000)
+// and with a block's loads on their way together, four-byte blocks swept: 10000 x 7000 60.5 -> 58, 5800 x 5804 56 -> 52 (5170), 15764 x 8092 209 -> 200, 5288 x 3128 x 2 B 15.1 -> 13.3.
+// Two-byte blocks are not swept: 10000 x 7000 57.5 -> 58.1, 8200 x 8200 up to 9 % slower, 5288 x 3128 13.3 -> 12.3.
 // (tiles on line-blind boundaries 102, 110 and 82, 363 us; 60 us where both pitches are whole lines, 10048 x 7040.)  256 rows of four bytes leave a
 // compute unit two workgroups: 58 us at 5800 x 5804; with 256 threads 77.  128 columns: 60 us there, 61 at 10000 x 7000.
 __host__ __device__ constexpr int lines_rows(int elem_bytes, bool tall) { return !tall ? 64 : elem_bytes == 2 ? 256 : 128; }
@@ -240,13 +257,17 @@ __global__ __launch_bounds__(lines_threads(BM_)) void transpose_lines_kernel(con
   const int tid = threadIdx.x;
   auto key = [](int r) { return sizeof(T) == 2 ? (r >> 3) & 7 : ((r >> 2) & 7) << 1; };
   static_assert(ROWS * SLOTS % NT == 0, "whole loads");
+  constexpr int LOADS = ROWS * SLOTS / NT;
+  t_u32x4 in_v[LOADS];
 #pragma unroll
-  for (int i = 0; i < ROWS * SLOTS / NT; ++i) {
+  for (int i = 0; i < LOADS; ++i) {
+    const int q = tid + NT * i;
+    in_v[i] = *tr_source(in, m0 + q / SLOTS, n0 + q % SLOTS * CH, M, N);
+  }
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) {
     const int q = tid + NT * i, r = q / SLOTS, c = q % SLOTS;
-    const int m = m0 + r, n = n0 + c * CH;
-    t_u32x4 v = {0u, 0u, 0u, 0u};
-    if (m >= 0 && m < M && n < N) v = *reinterpret_cast<const t_u32x4*>(in + (size_t)m * N + n);
-    *reinterpret_cast<t_u32x4*>(tile + r * ROW_BYTES + ((c ^ key(r)) << 4)) = v;
+    *reinterpret_cast<t_u32x4*>(tile + r * ROW_BYTES + ((c ^ key(r)) << 4)) = in_v[i];
   }
   __syncthreads();
   const int lane = tid & 63, wave = tid >> 6;
