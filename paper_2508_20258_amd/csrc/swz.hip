@@ -468,6 +468,14 @@ int launch_layernorm_rows(const uint16_t* in, const uint16_t* gamma, const uint1
   }
 static_assert(kRowShapes == 16, "the cases above");
 
+// The order of the second launch.  Softmax: the caller's mode.  Layer normalisation also reads gamma and beta, 4 N bytes a row.  In dispatch order chunk c of every row is on XCD c mod X where X
+// divides the chunks, and an XCD needs 4 N / X of those bytes for all rows, which its L2 keeps; with a row's chunks back to back on one XCD all of them cross the fabric again for every
+// row once they outgrow the 4 MB.  64 x 1048576 95 us with the rows of an XCD together, 67 in dispatch order (60 x 1000000 77, 66; 128 x 524288 69, 66; 16 x 131072 8.2, 7.9); where X
+// does not divide the chunks and gamma and beta fit, 100 x 600000 (37 chunks) 63 and 65, 90 x 700008 (43) 67 and 69: the caller's mode.
+int emit_mode(bool softmax, int N, const RowPlan& plan, int mode) {
+  return softmax || (plan.chunks % plan.num_xcd != 0 && (int64_t)N * 4 <= ((int64_t)3 << 20)) ? mode : (int)SWZ_MODE_RR;
+}
+
 template <bool SOFTMAX>
 int launch_long_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* beta, uint16_t* out, int M, int N, float eps,
                      const RowPlan& plan, int mode, hipStream_t stream) {
@@ -478,7 +486,7 @@ int launch_long_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* 
                         N, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, mode);
   if (st != SWZ_OK) return st;
   return launch(swz::row_emit_kernel<SOFTMAX>, dim3((unsigned)((int64_t)M * plan.chunks)), dim3(swz::kEmitThreads), 0, stream, in, gamma, beta,
-                out, M, N, eps, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, mode);
+                out, M, N, eps, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, emit_mode(SOFTMAX, N, plan, mode));
 }
 }  // namespace
 
