@@ -72,6 +72,7 @@ struct GemmLaunch {
   int bm, bn, grid_m, grid_n, group_m;   // the grid the map is evaluated on (with `pieces` that of the 256x256 tiles)
   int whole, deal;                    // see swz_tail_piece
   int64_t blocks;                     // workgroups launched
+  bool pair;                          // tiles of 128x256, two workgroups to a compute unit (gemm_pair_kernel.h)
   int a_feeders, b_feeders, feed_ticks;   // workgroups per XCD that fetch A and B ahead, ticks of 10 ns per 1024 of K; 0: none fetches ahead
 };
 
@@ -128,12 +129,34 @@ inline bool feed_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, in
   return l->sub >= 0;
 }
 
+// Whether tiles of 128x256, two to a compute unit (gemm_pair_kernel.h), compute it instead of 256x256 ones and what choose_subtile puts in their place.  Time of the
+// pair over that without, 110 products of K from 64 to 2048, log-uniform:
+//   More than half a round of 256x256 tiles: K up to 128 0.73 to 0.94, up to 352 0.80 to 0.98 (3976 x 2744 x 336 16.1 us, 14.9; 13930 x 9784 x 176 113, 105), then level and
+//   worse, as the tiles move half as many bytes again into LDS: 384 1.06, 504 to 576 1.00 to 1.13, 1024 1.05 to 1.12, 2048 1.20.
+//   One to one and a half rounds, which the finer tiles fill better: K = 400 0.89, 448 0.97, 544 0.90, 664 0.96; 1016 1.08.
+//   Half a round of tiles or less, where smaller sub-tiles are at work: 0.98 to 2.4.
+//   Fewer columns than half a tile: 100000 x 64 x 64 12.9 us, 8.8, x 304 18.3, 22.7; 65537 x 136 x 304 21.6, 19.2; few rows: 64 x 100000 x 304 16.3, 14.4.
+inline bool pair_wins(int64_t N, int64_t K, const swz_params& r, int64_t tiles, int cus) {
+  return r.bm == 256 && r.bn == 256 && 2 * tiles > cus && (N >= 128 || K <= 128) && (K <= 352 || (K <= 664 && tiles > cus && 2 * tiles <= 3 * cus));
+}
+
 // r: the resolved plan; cus: compute units.  `free_tile`: the caller left the tile to the library, otherwise a tile is one workgroup.
 // Bounds for anything else: 32-bit source offsets over 64 rows of B, and a grid well inside the 32-bit range whatever the shape.
 inline GemmLaunch gemm_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, int grid_m, int grid_n, int group_m, int mode, bool free_tile, int cus) {
-  GemmLaunch l = {-1, false, r.bm, r.bn, grid_m, grid_n, group_m, 0, 1, (int64_t)grid_m * grid_n, 0, 0, 0};
+  GemmLaunch l = {-1, false, r.bm, r.bn, grid_m, grid_n, group_m, 0, 1, (int64_t)grid_m * grid_n, false, 0, 0, 0};
   if (!free_tile || N >= ((int64_t)1 << 24) || l.blocks >= ((int64_t)1 << 16)) return l;
   if (feed_launch(M, N, K, r, mode, cus, &l)) return l;
+  if (pair_wins(N, K, r, l.blocks, cus)) {
+    l.pair = true;
+    l.bm = 128;
+    l.bn = 256;
+    l.grid_m = (int)((M + l.bm - 1) / l.bm);
+    l.grid_n = (int)((N + l.bn - 1) / l.bn);
+    l.blocks = (int64_t)l.grid_m * l.grid_n;
+    const int64_t band = (int64_t)group_m * (r.bm / l.bm);         // as high as a band of the plan's tiles
+    l.group_m = (int)(band < l.grid_m ? band : l.grid_m);
+    return l;
+  }
   l.sub = choose_subtile(M, N, K, r, cus);
   if (l.sub >= 0) {
     const SubTile& s = kSubTiles[l.sub];

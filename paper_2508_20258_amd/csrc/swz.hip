@@ -14,6 +14,7 @@
 #include "aux_kernels.h"
 #include "gemm_dispatch.h"
 #include "gemm_kernel.h"
+#include "gemm_pair_kernel.h"
 #include "gemm_subtile_kernel.h"
 #include "mfma_peak_kernel.h"
 #include "pid_decode.h"
@@ -33,7 +34,7 @@ struct DeviceFacts {
 };
 DeviceFacts g_facts[kMaxDevices];
 std::atomic<bool> g_attr_set[kMaxDevices][4][4][2];
-std::atomic<bool> g_sub_attr_set[kMaxDevices][2 * swz::kSubTileCount];   // sub-tiles, then pieces of the last round
+std::atomic<bool> g_sub_attr_set[kMaxDevices][2 * swz::kSubTileCount + 1];   // sub-tiles, then pieces of the last round, then the pair kernel
 std::mutex g_mu;
 
 // SWZ_NUM_XCD in the environment (read once per process): the XCD count to assume instead of the
@@ -194,6 +195,14 @@ int launch_pieces(const void* A, const void* B, void* C, int M, int N, int K, co
   if (st != SWZ_OK) return st;
   return launch(kernel, dim3((unsigned)l.blocks), dim3(Whole::NT), lds, stream, static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B),
                 static_cast<uint16_t*>(C), M, N, K, l.grid_m, l.grid_n, num_xcd, l.group_m, mode, l.whole, l.deal);
+}
+
+int launch_pair(const void* A, const void* B, void* C, int M, int N, int K, const swz::GemmLaunch& l, int num_xcd, int mode, hipStream_t stream) {
+  using S = swz::PairShape;
+  const int st = allow_lds(reinterpret_cast<const void*>(swz::gemm_bf16_pair_kernel), S::LDS_BYTES, 2 * swz::kSubTileCount);
+  if (st != SWZ_OK) return st;
+  return launch(swz::gemm_bf16_pair_kernel, dim3((unsigned)l.blocks), dim3(S::NT), S::LDS_BYTES, stream, static_cast<const uint16_t*>(A),
+                static_cast<const uint16_t*>(B), static_cast<uint16_t*>(C), M, N, K, l.grid_m, l.grid_n, num_xcd, l.group_m, mode);
 }
 
 int resolve_plan(int64_t M, int64_t N, int64_t K, const swz_params* p, swz_params* r, int* grid_m, int* grid_n) {
@@ -742,6 +751,7 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
     if (qs != SWZ_OK) return qs;
     const int m = (int)M, n = (int)N, k = (int)K;
     const swz::GemmLaunch l = swz::gemm_launch(M, N, K, r, grid_m, grid_n, group_m, mode, true, f.cus > 0 ? f.cus : kWholeCus);
+    if (l.pair) return launch_pair(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
     if (l.pieces)
       return l.sub == swz::kQuarterPiece ? launch_pieces<swz::kQuarterPiece>(A, B, C, m, n, k, l, r.num_xcd, mode, stream)
                                          : launch_pieces<swz::kHalfPiece>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);

@@ -75,7 +75,7 @@ def _inputs(workload):
     return a, b
 
 
-HASHED_SOURCES = ("gemm_kernel.h", "gemm_subtile_kernel.h", "gemm_dispatch.h", "pid_decode.h")
+HASHED_SOURCES = ("gemm_kernel.h", "gemm_subtile_kernel.h", "gemm_pair_kernel.h", "gemm_dispatch.h", "pid_decode.h")
 
 
 def kernel_hash() -> str:

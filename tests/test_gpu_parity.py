@@ -657,6 +657,25 @@ def test_subtiles_give_the_bits_of_whole_tiles(swz, M, N):
         assert_within_tolerance(to_bits(c[:M]), ref, f"{M}x{N}x{K}")
 
 
+# Tiles of 128x256, two to a compute unit: every K of one to four steps of 32 and their remainders, the ends of the rule, last tiles of one row and of one column
+# block, more rows than N and the other way round, rows of C on lines, on half lines and inside one
+@pytest.mark.parametrize("M,N,K", [(2817, 3080, 8), (2816, 3072, 32), (2944, 2824, 40), (129, 65800, 64), (65537, 136, 72), (3000, 3232, 96), (2817, 3080, 104),
+                                   (2816, 3328, 128), (5000, 1992, 200), (1300, 7176, 352), (4097, 4104, 512), (4224, 4104, 664)])
+def test_paired_tiles_give_the_bits_of_whole_tiles(swz, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+    b = torch.randn((K, N), device="cuda", generator=g).to(torch.bfloat16)
+    want = swz.gemm(a, b, mode=0, bm=256, bn=256)
+    for mode, params in [(0, {}), (1, {}), (2, {}), (5, dict(num_xcd=3)), (6, dict(group_m=3)), (2, dict(group_m=1000)), (2, dict(num_xcd=1))]:
+        blocks = swz.gemm_launch_map(M, N, K, mode, **params)
+        assert tuple(blocks[:, 2:].max(axis=0)) == (128, min(N, 256)), (mode, params)
+        c = torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        swz.gemm(a, b, c[:M], mode=mode, **params)
+        torch.cuda.synchronize()
+        assert torch.equal(c[:M].view(torch.int16), want.view(torch.int16)), (mode, params)
+        assert torch.isnan(c[M]).all()
+
+
 # ---------------------------------------------------------------------------- transposes into rows that start inside a line
 
 @pytest.mark.parametrize("elem_bytes,M,N,offset", [
@@ -712,7 +731,7 @@ def test_default_order_of_a_transpose_is_bit_exact(swz, elem_bytes, M, N):
 def test_partial_last_round_in_pieces_gives_the_bits_of_whole_tiles(swz, M, N):
     # quarters have rings of 5 stages of 64, 4 of them fetched ahead: from 576 on their loop makes whole turns
     quarters = (M + 255) // 256 * ((N + 255) // 256) % 256 <= 64
-    for K in (8, 200, 520, 576, 712, 1032) if quarters else (8, 200, 520):
+    for K in (8, 200, 520, 576, 712, 1032) if quarters else (8, 200, 520, 712):
         g = torch.Generator(device="cuda").manual_seed(M + K)
         a = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
         b = torch.randn((K, N), device="cuda", generator=g).to(torch.bfloat16)

@@ -144,7 +144,8 @@ def covers_once(blocks, M, N):
 # sub-tiles of every shape, halves and quarters of the last round (with fewer left-over tiles than XCDs and more), whole tiles
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (100, 520, 64), (300, 1032, 64), (449, 1992, 512), (1217, 1544, 512), (300, 5000, 512), (1537, 1400, 512),
                                    (40, 33000, 200), (70, 66000, 512), (4352, 4096, 512), (1800, 9472, 64), (5120, 4608, 512), (4610, 5000, 64),
-                                   (65793, 248, 64), (4096, 4096, 4096), (5120, 5120, 512)])
+                                   (65793, 248, 64), (4096, 4096, 4096), (5120, 5120, 512),
+                                   (1800, 9472, 704), (4610, 5000, 704), (65793, 248, 704), (4352, 4096, 704)])
 def test_launch_map_covers_c_once(M, N, K):
     for mode, params in [(0, dict(num_xcd=8)), (2, dict(num_xcd=8)), (1, dict(num_xcd=3)), (6, dict(num_xcd=8, group_m=3)), (5, dict(num_xcd=1000)),
                          (2, dict(num_xcd=1)), (2, dict(num_xcd=8, bm=128, bn=256))]:
