@@ -133,11 +133,15 @@ inline bool feed_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, in
 // pair over that without, 110 products of K from 64 to 2048, log-uniform:
 //   More than half a round of 256x256 tiles: K up to 128 0.73 to 0.94, up to 352 0.80 to 0.98 (3976 x 2744 x 336 16.1 us, 14.9; 13930 x 9784 x 176 113, 105), then level and
 //   worse, as the tiles move half as many bytes again into LDS: 384 1.06, 504 to 576 1.00 to 1.13, 1024 1.05 to 1.12, 2048 1.20.
-//   One to one and a half rounds, which the finer tiles fill better: K = 400 0.89, 448 0.97, 544 0.90, 664 0.96; 1016 1.08.
+//   One and a quarter to one and a half rounds, which the finer tiles fill better: K = 400 0.87 to 0.97, 448 0.94 to 1.00, 512 0.94 to 1.02, 640 0.99 to 1.09 (up to one and
+//   a quarter, whose last tiles go in quarters: K = 400 0.97 to 1.01, 512 1.03 to 1.08).
+//   Renumbered without bands, where B comes from the memory-side cache again and again: K up to 304 0.73 to 1.02, 8192 x 8192 x 344 1.03.
 //   Half a round of tiles or less, where smaller sub-tiles are at work: 0.98 to 2.4.
 //   Fewer columns than half a tile: 100000 x 64 x 64 12.9 us, 8.8, x 304 18.3, 22.7; 65537 x 136 x 304 21.6, 19.2; few rows: 64 x 100000 x 304 16.3, 14.4.
-inline bool pair_wins(int64_t N, int64_t K, const swz_params& r, int64_t tiles, int cus) {
-  return r.bm == 256 && r.bn == 256 && 2 * tiles > cus && (N >= 128 || K <= 128) && (K <= 352 || (K <= 664 && tiles > cus && 2 * tiles <= 3 * cus));
+inline bool pair_wins(int64_t N, int64_t K, const swz_params& r, int64_t tiles, int mode, int cus) {
+  if (r.bm != 256 || r.bn != 256 || 2 * tiles <= cus || (N < 128 && K > 128)) return false;
+  if (4 * tiles > 5 * cus && 2 * tiles <= 3 * cus) return K <= 448;
+  return K <= (swz_mode_renumbers(mode) && !swz_mode_grouped(mode) ? 304 : 352);
 }
 
 // r: the resolved plan; cus: compute units.  `free_tile`: the caller left the tile to the library, otherwise a tile is one workgroup.
@@ -146,7 +150,7 @@ inline GemmLaunch gemm_launch(int64_t M, int64_t N, int64_t K, const swz_params&
   GemmLaunch l = {-1, false, r.bm, r.bn, grid_m, grid_n, group_m, 0, 1, (int64_t)grid_m * grid_n, false, 0, 0, 0};
   if (!free_tile || N >= ((int64_t)1 << 24) || l.blocks >= ((int64_t)1 << 16)) return l;
   if (feed_launch(M, N, K, r, mode, cus, &l)) return l;
-  if (pair_wins(N, K, r, l.blocks, cus)) {
+  if (pair_wins(N, K, r, l.blocks, mode, cus)) {
     l.pair = true;
     l.bm = 128;
     l.bn = 256;
