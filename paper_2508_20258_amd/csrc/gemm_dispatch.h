@@ -16,13 +16,13 @@ constexpr int kStageK = 64;    // K extent of a ring stage of the sub-tile kerne
 // chip whose every CU has one (measured: the slope of kernel time over K).  The fixed part of a round (launch or hand-over, the
 // first operands, the stores) is about kRoundNs whatever the shape; a whole tile of gemm_kernel.h takes kWholeRoundNs, as it
 // also runs its look-ahead past the end of K.
-// fed_ns: what a stage costs where other workgroups fetch ahead (see feed_launch; 0: never).
+// stage_ns 0: only with feeders.  fed_ns: what a stage costs where other workgroups fetch ahead (see feed_launch; 0: never).
 struct SubTile { int bm, bn, wm, wn, stages, stage_ns, fed_ns; };
-constexpr int kSubTileCount = 8;
-constexpr int kSoloSubTiles = 7;                       // shapes from here on run with feeders only
+constexpr int kSubTileCount = 10;
 constexpr SubTile kSubTiles[kSubTileCount] = {{32, 32, 2, 2, 8, 140, 90},    {32, 64, 2, 2, 6, 160, 120},  {64, 64, 2, 2, 5, 195, 150},
                                               {128, 64, 4, 2, 6, 310, 0},    {64, 128, 2, 4, 6, 310, 0}, {128, 128, 2, 4, 5, 520, 0},
-                                              {128, 256, 2, 4, 3, 950, 0},   {64, 32, 2, 2, 8, 0, 130}};
+                                              {128, 256, 2, 4, 3, 950, 0},   {64, 32, 2, 2, 8, 0, 130},    {96, 128, 2, 2, 5, 440, 0},
+                                              {192, 128, 4, 2, 4, 715, 0}};
 constexpr int kQuarterPiece = 5, kHalfPiece = 6;       // of a 256x256 tile
 // Bytes of B per XCD that are fetched ahead: an eighth of the L2 (32 x 2048 x 16384: 1/32 and 1/8 24 us, 1/4 27, 1/2 42)
 constexpr int kFeedLead = 1 << 19;
@@ -33,6 +33,9 @@ constexpr int64_t kRoundNs = 2500, kWholeRoundNs = 4000;
 // 128x128, 128x256 and 256x256 tile of gemm_kernel.h costs 600, 840 and 1350 ns a stage (two 128x128 ones share a CU: 920 the
 // pair; a partial last round of 256x256 tiles costs what its pieces make of it, see gemm_launch).  Ties go to the larger
 // tile: it moves fewer bytes.  A sub-tile has to be 5 % better than the tile, the spread of the estimate near a tie.
+// 96 and 192 rows fill a round that the powers of two leave half empty or just outgrow: 9516x544x1056 20.2 -> 16.3 us (128x256 -> 192x128), 542x4128x14888 147 -> 123
+// (128x128 -> 96x128), 11034x368x2048 29.3 -> 22.9; over the 120 products drawn for which the choice changed 0.93 of the time, worst 1.06 (289x6792x168 5.0, 5.3).  Not kept:
+// 96x64 and 192x64, 0.95 to 1.32 of the time, as stripes of B half as wide come out of HBM at half the pace (13429x136x4744 55 -> 72); 160x128, no faster than 192x128.
 // Fitted on 60 products.  On 140 others, every shape timed (log-uniform sizes, N and K from 64 to 16384): 60 with M from 1 to
 // 16384 are on average as fast as with their best shape (worst 3.6 % behind), 80 with M from 128 to 16384 0.5 % behind (worst 13 %:
 // 1528x4880x536, 16.2 us in whole 128x256 tiles and 14.3 in sub-tiles of that size).
@@ -54,8 +57,9 @@ inline int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, 
   }
   best -= best / 20;
   int choice = -1;
-  for (int s = kSoloSubTiles - 1; s >= 0; --s) {
-    if (kSubTiles[s].bm > r.bm || kSubTiles[s].bn > r.bn) continue;         // a sub-tile is no larger than the plan's tile
+  for (int s = kSubTileCount - 1; s >= 0; --s) {
+    if (kSubTiles[s].stage_ns == 0 || kSubTiles[s].bn > r.bn || kSubTiles[s].bm > r.bm * 3 / 2) continue;      // those with feeders only; larger than the plan's tile
+    if (kSubTiles[s].bm > r.bm && K >= (1 << 23)) continue;                    // the 32-bit source offsets of bm rows are checked for the plan's tile
     const int64_t e = estimate(rounds(kSubTiles[s].bm, kSubTiles[s].bn, cus), kSubTiles[s].stage_ns);
     if (e < best) {
       best = e;
@@ -169,7 +173,7 @@ inline GemmLaunch gemm_launch(int64_t M, int64_t N, int64_t K, const swz_params&
     l.grid_m = (int)((M + s.bm - 1) / s.bm);
     l.grid_n = (int)((N + s.bn - 1) / s.bn);
     l.blocks = (int64_t)l.grid_m * l.grid_n;
-    const int64_t band = (int64_t)group_m * (r.bm / s.bm);       // rows of sub-tiles as high as a band of tiles
+    const int64_t band = r.bm < s.bm ? group_m : (int64_t)group_m * (r.bm / s.bm);   // rows of sub-tiles, as high as a band of tiles
     l.group_m = (int)(band < l.grid_m ? band : l.grid_m);
     return l;
   }

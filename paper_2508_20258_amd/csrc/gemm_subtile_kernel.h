@@ -26,6 +26,7 @@
 //   8x4096x4096     32.2 -> 17 -> 9.0 us (32x32, fed)          32x8192x8192    66.5 -> 40.4 -> 26 us (32x64, fed; reading B takes 21 at 6.3 TB/s)
 //   256x2048x2048   19.0 ->  9.0 us (32x64)      1024x2048x4096  33.2 -> 23.1 us (128x64)
 //   128x32768x2048  40.6 -> 29.4 us (128x128)    64x65536x4096  118.3 -> 96.8 us (64x128)
+//   4575x1112x576   13.1 -> 10.7 us (192x128)    940x2816x12696   136 -> 116 us (96x128)   [against the sub-tiles without these two shapes]
 //
 // LDS of a stage: A, BM rows x 64 of K (128 bytes, chunk c of row r in slot c ^ ((r >> 1) & 7)), then B, 64 rows x
 // BN columns (chunk c of row k in slot c ^ sub_b_key(k)); both conflict-free for the fragment reads.

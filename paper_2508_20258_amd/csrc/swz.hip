@@ -764,6 +764,8 @@ int swz_gemm_ex(const void* A, const void* B, void* C, int64_t M, int64_t N, int
       case 5: return launch_subtile<5>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
       case 6: return launch_subtile<6>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
       case 7: return launch_subtile<7>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 8: return launch_subtile<8>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
+      case 9: return launch_subtile<9>(A, B, C, m, n, k, l, r.num_xcd, mode, stream);
       default: break;                                   // whole tiles
     }
   }

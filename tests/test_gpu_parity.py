@@ -633,7 +633,8 @@ SUBTILE_SHAPES = [(1, 8), (33, 40), (100, 520), (512, 512),                  # 3
                   (1000, 1000), (449, 1992),                                 # 64x64
                   (1280, 1600), (1217, 1544),                                # 128x64 / 64x128
                   (300, 5000), (1100, 1504),                                 # 64x128
-                  (1537, 1400), (40, 33000), (70, 66000)]                    # 128x128; grids of 128x256 and 256x256 tiles
+                  (1537, 1400), (40, 33000), (70, 66000),                    # 128x128; grids of 128x256 and 256x256 tiles
+                  (577, 3848), (4359, 488), (1537, 2680), (572, 9424), (4575, 1112)]         # 96x128, 192x128: one row, one column block and all but one in the last
 
 
 @pytest.mark.parametrize("M,N", SUBTILE_SHAPES)

@@ -145,7 +145,8 @@ def covers_once(blocks, M, N):
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (100, 520, 64), (300, 1032, 64), (449, 1992, 512), (1217, 1544, 512), (300, 5000, 512), (1537, 1400, 512),
                                    (40, 33000, 200), (70, 66000, 512), (4352, 4096, 512), (1800, 9472, 64), (5120, 4608, 512), (4610, 5000, 64),
                                    (65793, 248, 64), (4096, 4096, 4096), (5120, 5120, 512),
-                                   (1800, 9472, 704), (4610, 5000, 704), (65793, 248, 704), (4352, 4096, 704)])
+                                   (1800, 9472, 704), (4610, 5000, 704), (65793, 248, 704), (4352, 4096, 704),
+                                   (577, 3848, 512), (1537, 2680, 512), (193, 12304, 512)])
 def test_launch_map_covers_c_once(M, N, K):
     for mode, params in [(0, dict(num_xcd=8)), (2, dict(num_xcd=8)), (1, dict(num_xcd=3)), (6, dict(num_xcd=8, group_m=3)), (5, dict(num_xcd=1000)),
                          (2, dict(num_xcd=1)), (2, dict(num_xcd=8, bm=128, bn=256))]:
@@ -414,3 +415,11 @@ for call in (lambda: swz.gemm(x, x, x), lambda: swz.transpose(x, x), lambda: swz
 """
     res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr
+
+
+def test_no_sub_tile_reads_beyond_its_source_offsets():
+    # (rows - 1) * K * 2 fits 32 bits for every block of a launch
+    for K in (1 << 22, (1 << 23) - 8, 1 << 23, 11184816, (1 << 24) - 8):
+        for M, N in [(1537, 2680), (4575, 1112), (193, 12304), (577, 3848)]:
+            rows = int(swz.gemm_launch_map(M, N, K, 2, num_xcd=8)[:, 2].max())
+            assert rows * K * 2 < 1 << 32, (M, N, K, rows)
