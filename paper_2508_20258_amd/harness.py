@@ -125,7 +125,7 @@ def covers_once(blocks, m, n):
 def launched_kernel(name):
     """(short name, whether it computes the plan's tiles one workgroup each) of a GEMM kernel's full name in a trace."""
     short = name.split("(")[0].replace("void ", "").replace("swz::", "").strip()
-    return short, "subtile" not in short and "tail" not in short
+    return short, short.split("<")[0] == "gemm_bf16_kernel"
 
 
 def warmup_launches(warmup_ms, flops):

@@ -237,6 +237,7 @@ def test_launched_kernel_and_its_grid_come_from_the_trace(tmp_path):
     assert harness.launched_kernel("void swz::gemm_bf16_subtile_kernel<swz::SubShape<32, 32, 2, 2, 8> >(unsigned short const*, int)") == (
         "gemm_bf16_subtile_kernel<SubShape<32, 32, 2, 2, 8> >", False)
     assert not harness.launched_kernel("gemm_bf16_tail_kernel<A, B>(int)")[1] and harness.launched_kernel("gemm_bf16_kernel<A, 2>(int)")[1]
+    assert harness.launched_kernel("swz::gemm_bf16_pair_kernel(unsigned short const*, int)") == ("gemm_bf16_pair_kernel", False)
     d = tmp_path / "run"
     os.makedirs(d)
     (d / "1_kernel_trace.csv").write_text('"Kernel_Name","Start_Timestamp","End_Timestamp","Workgroup_Size_X","Grid_Size_X"\n'
