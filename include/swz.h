@@ -219,7 +219,9 @@ int swz_softmax(const void* in, void* out, int64_t M, int64_t N, int chunks, int
 
 /* Layer normalisation of every row, y[i][j] = (x[i][j] - mean_i) / sqrt(var_i + eps) * gamma[j] + beta[j]
  * with the biased variance (the paper's layer normalisation kernel, same appendix: all column chunks
- * of a row on one XCD).  Same decomposition, grid, mapping, layout and error behaviour as swz_softmax.
+ * of a row on one XCD).  Same decomposition, grid, mapping, layout and error behaviour as swz_softmax, but for the order of the second
+ * launch for long rows: with params null, or group_m and num_xcd both 0, chunks are taken in dispatch order (as by SWZ_MODE_RR) where the
+ * XCDs divide the chunks of a row (ceil(N / 16384)) or gamma and beta together exceed 3 MiB.  A named group_m or num_xcd always gets `mode`.
  *   gamma, beta : DEVICE pointers to N bfloat16 each, 16-byte aligned.   eps >= 0.
  *   Mean and variance are accumulated in fp32, the variance from deviations from the mean. */
 int swz_layernorm(const void* in, const void* gamma, const void* beta, void* out, int64_t M, int64_t N, float eps,

@@ -15,7 +15,8 @@
 //   time.  Between the launches a segment's statistics (8 bytes) wait in `out` itself: every chunk gets its own copy of all of
 //   them at its start, so that a workgroup reads only what it overwrites, after its own barrier.  No scratch memory, nothing
 //   exchanged inside a launch.  Grids rows x segments and rows x chunks, both decoded by swz_decode_tile: under the
-//   XCD renumbering a row's workgroups run back to back on one XCD.
+//   XCD renumbering a row's workgroups run back to back on one XCD.  The second launch of a layer normalisation may take its
+//   chunks in dispatch order instead (row_dispatch.h).
 //
 // The decomposition of the paper, in which the workgroup of every column chunk reads the whole row for its statistics, is bound
 // by those reads and the arithmetic on them even where the remap has the L2 serve 82 % of them: 8 chunks of

@@ -18,6 +18,7 @@
 #include "gemm_subtile_kernel.h"
 #include "mfma_peak_kernel.h"
 #include "pid_decode.h"
+#include "row_dispatch.h"
 #include "rowwise_kernel.h"
 #include "transpose_kernel.h"
 
@@ -359,6 +360,7 @@ constexpr RowShape kLayernormShapes[kRowShapes] = {
 // workgroup holds, two launches, segs x chunks per row), mapping parameters.
 struct RowPlan {
   int shape, grid_m, num_xcd, group_m, segs, chunks, cus;
+  bool named;                         // the caller named num_xcd or group_m
 };
 
 int resolve_rows(int64_t M, int64_t N, int chunks, int mode, const swz_params* params, const RowShape* shapes, RowPlan* plan) {
@@ -376,6 +378,7 @@ int resolve_rows(int64_t M, int64_t N, int chunks, int mode, const swz_params* p
     if (params->group_m > 0) plan->group_m = params->group_m;
     plan->num_xcd = params->num_xcd;
   }
+  plan->named = params != nullptr && (params->group_m > 0 || params->num_xcd > 0);
   DeviceFacts f;
   const int known = query_device(&f);
   plan->cus = known == SWZ_OK && f.cus > 0 ? f.cus : kWholeCus;
@@ -477,14 +480,6 @@ int launch_layernorm_rows(const uint16_t* in, const uint16_t* gamma, const uint1
   }
 static_assert(kRowShapes == 16, "the cases above");
 
-// The order of the second launch.  Softmax: the caller's mode.  Layer normalisation also reads gamma and beta, 4 N bytes a row.  In dispatch order chunk c of every row is on XCD c mod X where X
-// divides the chunks, and an XCD needs 4 N / X of those bytes for all rows, which its L2 keeps; with a row's chunks back to back on one XCD all of them cross the fabric again for every
-// row once they outgrow the 4 MB.  64 x 1048576 95 us with the rows of an XCD together, 67 in dispatch order (60 x 1000000 77, 66; 128 x 524288 69, 66; 16 x 131072 8.2, 7.9); where X
-// does not divide the chunks and gamma and beta fit, 100 x 600000 (37 chunks) 63 and 65, 90 x 700008 (43) 67 and 69: the caller's mode.
-int emit_mode(bool softmax, int N, const RowPlan& plan, int mode) {
-  return softmax || (plan.chunks % plan.num_xcd != 0 && (int64_t)N * 4 <= ((int64_t)3 << 20)) ? mode : (int)SWZ_MODE_RR;
-}
-
 template <bool SOFTMAX>
 int launch_long_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* beta, uint16_t* out, int M, int N, float eps,
                      const RowPlan& plan, int mode, hipStream_t stream) {
@@ -494,8 +489,9 @@ int launch_long_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* 
   const int st = launch(swz::row_stats_kernel<SOFTMAX>, dim3((unsigned)((int64_t)M * plan.segs)), dim3(swz::kSegThreads), 0, stream, in, out, M,
                         N, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, mode);
   if (st != SWZ_OK) return st;
+  const int order = !SOFTMAX && swz::emit_in_dispatch_order(N, plan.chunks, plan.num_xcd, plan.named) ? (int)SWZ_MODE_RR : mode;
   return launch(swz::row_emit_kernel<SOFTMAX>, dim3((unsigned)((int64_t)M * plan.chunks)), dim3(swz::kEmitThreads), 0, stream, in, gamma, beta,
-                out, M, N, eps, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, emit_mode(SOFTMAX, N, plan, mode));
+                out, M, N, eps, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, order);
 }
 }  // namespace
 
