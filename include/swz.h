@@ -221,7 +221,8 @@ int swz_softmax(const void* in, void* out, int64_t M, int64_t N, int chunks, int
  * with the biased variance (the paper's layer normalisation kernel, same appendix: all column chunks
  * of a row on one XCD).  Same decomposition, grid, mapping, layout and error behaviour as swz_softmax, but for the order of the second
  * launch for long rows: with params null, or group_m and num_xcd both 0, chunks are taken in dispatch order (as by SWZ_MODE_RR) where the
- * XCDs divide the chunks of a row (ceil(N / 16384)) or gamma and beta together exceed 3 MiB.  A named group_m or num_xcd always gets `mode`.
+ * chunks of a row (C = ceil(N / 16384)) and the XCDs have a common divisor above 1 and gamma and beta together exceed 3 MiB, or the XCDs
+ * divide C and 64 C divides N or M * N < 2^25.  A named group_m or num_xcd always gets `mode`.
  *   gamma, beta : DEVICE pointers to N bfloat16 each, 16-byte aligned.   eps >= 0.
  *   Mean and variance are accumulated in fp32, the variance from deviations from the mean. */
 int swz_layernorm(const void* in, const void* gamma, const void* beta, void* out, int64_t M, int64_t N, float eps,

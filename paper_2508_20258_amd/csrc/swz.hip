@@ -489,7 +489,7 @@ int launch_long_rows(const uint16_t* in, const uint16_t* gamma, const uint16_t* 
   const int st = launch(swz::row_stats_kernel<SOFTMAX>, dim3((unsigned)((int64_t)M * plan.segs)), dim3(swz::kSegThreads), 0, stream, in, out, M,
                         N, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, mode);
   if (st != SWZ_OK) return st;
-  const int order = !SOFTMAX && swz::emit_in_dispatch_order(N, plan.chunks, plan.num_xcd, plan.named) ? (int)SWZ_MODE_RR : mode;
+  const int order = !SOFTMAX && swz::emit_in_dispatch_order(M, N, plan.chunks, plan.num_xcd, plan.named) ? (int)SWZ_MODE_RR : mode;
   return launch(swz::row_emit_kernel<SOFTMAX>, dim3((unsigned)((int64_t)M * plan.chunks)), dim3(swz::kEmitThreads), 0, stream, in, gamma, beta,
                 out, M, N, eps, plan.segs, plan.chunks, plan.num_xcd, plan.group_m, order);
 }
