@@ -31,14 +31,28 @@ constexpr int64_t kRoundNs = 2500, kWholeRoundNs = 4000;
 // Which sub-tile shape (index into kSubTiles) computes this product fastest, or -1 where the plan's tile as one
 // workgroup does.  The estimate is  rounds x (kRoundNs + stages x cost), rounds = workgroups that touch C over CUs.  One
 // 128x128, 128x256 and 256x256 tile of gemm_kernel.h costs 600, 840 and 1350 ns a stage (two 128x128 ones share a CU: 920 the
-// pair; a partial last round of 256x256 tiles costs what its pieces make of it, see gemm_launch).  Ties go to the larger
-// tile: it moves fewer bytes.  A sub-tile has to be 5 % better than the tile, the spread of the estimate near a tie.
+// pair; a partial last round of 256x256 tiles costs what its pieces make of it, see gemm_launch).  Ties go to the later
+// shape of the table.  A sub-tile has to be 5 % better than the tile, the spread of the estimate near a tie.
 // 96 and 192 rows fill a round that the powers of two leave half empty or just outgrow: 9516x544x1056 20.2 -> 16.3 us (128x256 -> 192x128), 542x4128x14888 147 -> 123
-// (128x128 -> 96x128), 11034x368x2048 29.3 -> 22.9; over the 120 products drawn for which the choice changed 0.93 of the time, worst 1.06 (289x6792x168 5.0, 5.3).  Not kept:
+// (128x128 -> 96x128), 11034x368x2048 29.3 -> 22.9; over the 120 products drawn for which the choice changed 0.93 of the time (see rows96_pay for those where it was more).  Not kept:
 // 96x64 and 192x64, 0.95 to 1.32 of the time, as stripes of B half as wide come out of HBM at half the pace (13429x136x4744 55 -> 72); 160x128, no faster than 192x128.
 // Fitted on 60 products.  On 140 others, every shape timed (log-uniform sizes, N and K from 64 to 16384): 60 with M from 1 to
 // 16384 are on average as fast as with their best shape (worst 3.6 % behind), 80 with M from 128 to 16384 0.5 % behind (worst 13 %:
 // 1528x4880x536, 16.2 us in whole 128x256 tiles and 14.3 in sub-tiles of that size).
+
+// Where 96 rows to a sub-tile may take the place of 128.  They have the fabric carry B once more for every further row of sub-tiles, half and a third as often again where 128 rows make two
+// and three of them.  us with 128x128 and with 96x128, first with operands out of HBM, then out of the memory-side cache:
+//   One stage of K, one round: nothing to gain.  203 x 9576 x 8 4.7, 5.0 and 3.8, 4.0; 289 x 6792 x 32 4.9, 5.1 and 3.9, 4.0; 440 x 5200 x 8 4.6, 4.9 and 4.0, 3.9.
+//   193 to 256 rows, where the third row of sub-tiles is less than half full or K short: 193 x 10400 x 520 9.9, 9.2 and 8.2, 8.5, x 2056 25.1, 23.3 and 18.9, 21.5, x 4104 46, 42 and
+//   33, 39; 224 x 10400 x 4104 46, 41 and 34, 37; 256 x 8200 x 264 8.2, 7.6 and 5.9, 6.2.  But 240 x 9000 x 520 11.2, 9.9 and 8.4, 8.2; 256 x 9000 x 2056 29.8, 24.8 and 20.5, 19.1.
+//   289 to 384 rows: 289 x 6792 x 168 6.4, 6.3 and 4.8, 5.0; 300 x 7504 x 264 7.9, 7.6 and 6.1, 6.3; from K = 328 on 300 x 6792 8.4, 8.0 and 6.7, 6.7, x 520 10.3, 9.6 and 8.4, 8.1.
+//   More rows, two stages: 480 x 4504 x 104 5.8, 5.5 and 4.4, 4.3.
+inline bool rows96_pay(int64_t M, int64_t K, bool one_round) {
+  if (one_round && K <= kStageK) return false;
+  if (M > 192 && M <= 256) return M >= 240 && K >= 512;
+  return M <= 288 || M > 384 || K >= 328;
+}
+
 inline int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, int cus) {
   const int64_t stages = (K + kStageK - 1) / kStageK;
   auto rounds = [&](int64_t bm, int64_t bn, int64_t per_round) {
@@ -60,8 +74,9 @@ inline int choose_subtile(int64_t M, int64_t N, int64_t K, const swz_params& r, 
   for (int s = kSubTileCount - 1; s >= 0; --s) {
     if (kSubTiles[s].stage_ns == 0 || kSubTiles[s].bn > r.bn || kSubTiles[s].bm > r.bm * 3 / 2) continue;      // those with feeders only; larger than the plan's tile
     if (kSubTiles[s].bm > r.bm && K >= (1 << 23)) continue;                    // the 32-bit source offsets of bm rows are checked for the plan's tile
-    const int64_t e = estimate(rounds(kSubTiles[s].bm, kSubTiles[s].bn, cus), kSubTiles[s].stage_ns);
+    const int64_t n = rounds(kSubTiles[s].bm, kSubTiles[s].bn, cus), e = estimate(n, kSubTiles[s].stage_ns);
     if (e < best) {
+      if (kSubTiles[s].bm == 96 && !rows96_pay(M, K, n == 1)) continue;
       best = e;
       choice = s;
     }

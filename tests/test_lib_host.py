@@ -423,3 +423,12 @@ def test_no_sub_tile_reads_beyond_its_source_offsets():
         for M, N in [(1537, 2680), (4575, 1112), (193, 12304), (577, 3848)]:
             rows = int(swz.gemm_launch_map(M, N, K, 2, num_xcd=8)[:, 2].max())
             assert rows * K * 2 < 1 << 32, (M, N, K, rows)
+
+
+# a third and a fourth row of sub-tiles, each of which reads all of B, and a K of one stage: 128 rows; else 96
+@pytest.mark.parametrize("M,N,K,rows", [(203, 9576, 264, 128), (193, 10400, 2056, 128), (239, 9000, 2056, 128), (240, 9000, 504, 128), (240, 9000, 520, 96),
+                                        (256, 9000, 2056, 96), (289, 6792, 168, 128), (300, 6792, 320, 128), (300, 6792, 328, 96), (384, 6792, 520, 96),
+                                        (440, 5200, 64, 128), (440, 5200, 72, 96), (170, 11504, 256, 96), (170, 11504, 64, 128), (274, 9008, 72, 96)])
+def test_sub_tiles_of_96_rows(M, N, K, rows):
+    blocks = swz.gemm_launch_map(M, N, K, 2, num_xcd=8)
+    assert tuple(blocks[:, 2:].max(axis=0)) == (rows, 128)
