@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libswz.so")
 SOURCES = ["swz.hip"]
-HEADERS = ["gemm_kernel.h", "gemm_subtile_kernel.h", "gemm_pair_kernel.h", "gemm_dispatch.h", "aux_kernels.h", "transpose_kernel.h", "tile_sweep.h", "rowwise_kernel.h", "row_dispatch.h", "mfma_peak_kernel.h", "pid_decode.h", os.path.join("..", "..", "include", "swz.h")]
+HEADERS = ["gemm_kernel.h", "gemm_subtile_kernel.h", "gemm_pair_kernel.h", "gemm_dispatch.h", "aux_kernels.h", "transpose_kernel.h", "transpose_dispatch.h", "tile_sweep.h", "rowwise_kernel.h", "row_dispatch.h", "mfma_peak_kernel.h", "pid_decode.h", os.path.join("..", "..", "include", "swz.h")]
 
 FAST_SOURCE = os.path.join(CSRC, "fastcall.cpp")
 FAST = os.path.join(HERE, "_fastcall.so")

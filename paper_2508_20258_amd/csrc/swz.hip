@@ -20,6 +20,7 @@
 #include "pid_decode.h"
 #include "row_dispatch.h"
 #include "rowwise_kernel.h"
+#include "transpose_dispatch.h"
 #include "transpose_kernel.h"
 
 namespace {
@@ -74,9 +75,7 @@ int query_device(DeviceFacts* out) {
   return SWZ_OK;
 }
 
-// A launch has fewer than 2^32 threads: the grid is handed to the device in threads, as a 32-bit number, and a larger one
-// comes back as "ok" with only the remainder modulo 2^32 run (2^24 + 1 workgroups of 256: one of them).
-constexpr int64_t kLaunchThreads = ((int64_t)1 << 32) - 1;
+using swz::kLaunchThreads;
 
 // Launch through the call that returns the launch's own status: hipGetLastError() after a launch
 // would also report (and clear) an error some earlier, unrelated HIP call left behind.
@@ -254,26 +253,13 @@ int resolve_plan(int64_t M, int64_t N, int64_t K, const swz_params* p, swz_param
 
 constexpr int64_t kMemorySideCacheBytes = (int64_t)256 << 20;   // gfx950: 256 MB behind the L2s, in front of HBM
 
-// How many bytes the workgroups of a two-byte transpose have on their way at a time: both loads of a thread or one (paced), and LDS on top of the tile's 8 KB, which
-// holds five workgroups to a compute unit instead of eight.  Up to 32 MiB latency counts: both, eight (2176 x 2968 7.5 us, paced 7.7; 3200 x 1440 5.2, 6.0).  Above, the HBM serves
-// more bytes a second the fewer are asked for, 32 to 40 KB a compute unit: paced 3712 x 17656 57.6, both 61.9, both and five 58.4; 20416 x 1912 31.7, 34.4, 33.2; 12416 x 2704
-// 26.3, 29.6, 28.7.  At pitches of whole 4096 elements fewer workgroups are better than paced ones: 8192 x 8192 49.2, 50.8, 47.1; 16384 x 16384 179.4, 186.3, 176.3; 4096 x 4096
-// 15.4, 13.8, 14.3.  (Four bytes, all four loads: five workgroups to a compute unit 5824 x 5824 48.7 us, paced 50.4; from 256 MiB on three: 3648 x 9272 50.1, five 51.0, eight 51.5,
-// paced 54.1; 8192 x 8192 87.9, 90.7, 92.4, 90.0.)
-struct LoadPace { int paced, lds; };
-LoadPace load_pace(int tile, int M, int N) {
-  if (tile != 64 || (int64_t)M * N * 4 < ((int64_t)32 << 20)) return {0, 0};
-  if ((int64_t)M * 2 % 8192 == 0) return {0, 24576};
-  return {1, 0};
-}
-
 template <int TILE, bool STREAM>
 int launch_transpose_s(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode, int sweep,
                        hipStream_t stream) {
   const dim3 grid((unsigned)(gm * gn)), block(256);
   auto* i = static_cast<const uint16_t*>(in);
   auto* o = static_cast<uint16_t*>(out);
-  const LoadPace pace = load_pace(TILE, M, N);
+  const swz::LoadPace pace = swz::load_pace(TILE, M, N, mode);
   const int skew = swz_mode_skewed(mode) ? 1 : 0;
   switch (mode & 3) {
     case SWZ_MODE_RR: return launch(swz::transpose16_kernel<TILE, kModeRR, STREAM>, grid, block, pace.lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep, pace.paced);
@@ -307,30 +293,6 @@ int launch_transpose(const void* in, void* out, int M, int N, int gm, int gn, in
   if (TILE >= 64 && (int64_t)M * N * 4 > kMemorySideCacheBytes)
     return launch_transpose_s<TILE, true>(in, out, M, N, gm, gn, num_xcd, group_m, mode, sweep, stream);
   return launch_transpose_s<TILE, false>(in, out, M, N, gm, gn, num_xcd, group_m, mode, sweep, stream);
-}
-
-// Which transposes under the default mode, with the band height left to the library, take the sweep of tile_sweep.h.  Time of the sweep over that of the skewed raster, loads and
-// occupancy as they are now.  Tiles: no pitch a power of two 0.84 to 1.00, on average 0.92 (40 sizes).  Both pitches multiples of 16 KiB: 8192 x 8192 x 4 B 0.99, 12288 x 8192
-// x 4 B 0.98, 16384 x 8192 x 2 B 0.94, but with one of 64 KiB 32768 x 8192 x 2 B 1.14, 16384 x 8192 x 4 B 1.13, 8192 x 16384 x 4 B 1.08, 16384 x 4096 x 4 B 1.01; 16384 x 16384
-// x 2 B (32 KiB) level.  Blocks into part lines, four bytes: 0.91 to 0.99, pitch of `in` a multiple of 8 KiB 0.98 to 1.04.
-bool sweep_tiles(int64_t M, int64_t N, int elem_bytes) { return (M | N) * elem_bytes % 16384 != 0 || (M * elem_bytes % 65536 != 0 && N * elem_bytes % 65536 != 0); }
-bool sweep_part_lines(int64_t N, int elem_bytes) { return elem_bytes == 4 && N * elem_bytes % 8192 != 0; }
-
-// Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines, rather than 64 rows in 256 threads.  us with the tall ones and with the
-// others, operands in the memory-side cache (three sets of buffers in turn):
-//   Few rows, one block either way, most of a tall one empty: two bytes 72 rows 7.99, 8.08 (31 MiB moved) and 136 rows 4.69, 4.71, above 64 rows never behind by more
-//   than 5 %; four bytes 52 rows 9.88, 10.59 (47 MiB).
-//   Just above one block, the second nearly empty: four bytes 132 rows 4.47, 4.18 (17 MiB; out of HBM 7.49, 6.19), from 160 rows on level; two bytes out of HBM 264
-//   rows 8.39, 7.10, 280 rows 7.11, 7.35.
-//   Few blocks for the compute units, two bytes: above 1024 rows 1032 x 4312 5.49, 5.31; 8200 x 536 5.08, 4.50; 4104 x 1976 8.31, 7.23; from 40 MiB on 0.83 to 1.08.  Up to
-//   1024 rows 520 x 8568 4.66, 5.55; 776 x 8104 5.78, 6.94.  Four bytes 516 x 4312 4.21, 5.27, 2052 x 1912 6.34, 6.47, 1028 x 2160 4.53, 4.32.
-// A launch has to hold its threads too: with one row of blocks, or two instead of three, half and three quarters as many columns fit.
-bool tall_line_blocks(int64_t M, int64_t N, int elem_bytes) {
-  const int rows = swz::lines_rows(elem_bytes, true);
-  const int64_t blocks_m = (M + rows - 1) / rows, gn = (N + 63) / 64, moved = 2 * M * N * elem_bytes;
-  if (blocks_m * gn * swz::lines_threads(rows) > kLaunchThreads) return false;
-  if (elem_bytes == 2) return M > 64 && (M <= 256 || M >= 280) && (M <= 1024 || moved >= ((int64_t)40 << 20));
-  return M > 48 && (M <= 128 || M >= 160);
 }
 
 template <class T, bool TALL>
@@ -608,15 +570,15 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   const bool part_lines = ((M * elem_bytes) & 127) != 0 || (reinterpret_cast<uintptr_t>(out) & 127) != 0;
   const bool ours = tile == 64 && mode == (SWZ_MODE_XCD_GROUPM | SWZ_MODE_SKEW) && (params == nullptr || params->group_m == 0);
   if (tile == 64 && part_lines && M < ((int64_t)1 << 30) && 2 * M * N * elem_bytes >= ((int64_t)16 << 20)) {
-    const bool sweep = ours && sweep_part_lines(N, elem_bytes);
-    const bool tall = tall_line_blocks(M, N, elem_bytes);
+    const bool sweep = ours && swz::sweep_part_lines(N, elem_bytes);
+    const bool tall = swz::tall_line_blocks(M, N, elem_bytes);
     if (elem_bytes == 2)
       return tall ? launch_transpose_lines<uint16_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream)
                   : launch_transpose_lines<uint16_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream);
     return tall ? launch_transpose_lines<uint32_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream)
                 : launch_transpose_lines<uint32_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream);
   }
-  const int sweep = ours && sweep_tiles(M, N, elem_bytes) ? swz_sweep_rows((int)gm, num_xcd, elem_bytes) : 0;
+  const int sweep = ours && swz::sweep_tiles(M, N, elem_bytes) ? swz_sweep_rows((int)gm, num_xcd, elem_bytes) : 0;
   if (elem_bytes == 4) {
     if (M * N * 8 > kMemorySideCacheBytes)
       return launch_transpose32<true>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);

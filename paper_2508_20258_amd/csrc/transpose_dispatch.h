@@ -1,0 +1,56 @@
+// How a transpose is launched: which order its tiles are taken in, how many bytes are asked for at a time, which blocks a transpose into part lines takes.
+// Host arithmetic only.
+#pragma once
+
+#include <stdint.h>
+
+#include "pid_decode.h"
+
+namespace swz {
+
+// A launch has fewer than 2^32 threads: the grid is handed to the device in threads, as a 32-bit number, and a larger one
+// comes back as "ok" with only the remainder modulo 2^32 run (2^24 + 1 workgroups of 256: one of them).
+constexpr int64_t kLaunchThreads = ((int64_t)1 << 32) - 1;
+
+// Rows and threads of a block of a transpose into part lines (transpose_lines_kernel)
+constexpr int lines_rows(int elem_bytes, bool tall) { return !tall ? 64 : elem_bytes == 2 ? 256 : 128; }
+constexpr int lines_threads(int rows) { return rows == 64 ? 256 : 512; }
+
+// How many bytes the workgroups of a two-byte transpose have on their way at a time: both loads of a thread or one (paced), and LDS on top of the tile's 8 KB, which
+// holds five workgroups to a compute unit instead of eight.  Up to 32 MiB latency counts: both, eight (2176 x 2968 7.5 us, paced 7.7; 3200 x 1440 5.2, 6.0).  Above, the HBM serves
+// more bytes a second the fewer are asked for, 32 to 40 KB a compute unit: paced 3712 x 17656 57.6, both 61.9, both and five 58.4; 20416 x 1912 31.7, 34.4, 33.2; 12416 x 2704
+// 26.3, 29.6, 28.7.  At pitches of whole 4096 elements fewer workgroups are better than paced ones: 8192 x 8192 49.2, 50.8, 47.1; 16384 x 16384 179.4, 186.3, 176.3; 4096 x 4096
+// 15.4, 13.8, 14.3.  (Four bytes, all four loads: five workgroups to a compute unit 5824 x 5824 48.7 us, paced 50.4; from 256 MiB on three: 3648 x 9272 50.1, five 51.0, eight 51.5,
+// paced 54.1; 8192 x 8192 87.9, 90.7, 92.4, 90.0.)
+struct LoadPace { int paced, lds; };
+inline LoadPace load_pace(int tile, int64_t M, int64_t N, int mode) {
+  if (tile != 64 || M * N * 4 < ((int64_t)32 << 20)) return {0, 0};
+  if (M * 2 % 8192 == 0) return {0, 24576};
+  return {1, 0};
+}
+
+// Which transposes under the default mode, with the band height left to the library, take the sweep of tile_sweep.h.  Time of the sweep over that of the skewed raster, loads and
+// occupancy as they are now.  Tiles: no pitch a power of two 0.84 to 1.00, on average 0.92 (40 sizes).  Both pitches multiples of 16 KiB: 8192 x 8192 x 4 B 0.99, 12288 x 8192
+// x 4 B 0.98, 16384 x 8192 x 2 B 0.94, but with one of 64 KiB 32768 x 8192 x 2 B 1.14, 16384 x 8192 x 4 B 1.13, 8192 x 16384 x 4 B 1.08, 16384 x 4096 x 4 B 1.01; 16384 x 16384
+// x 2 B (32 KiB) level.  Blocks into part lines, four bytes: 0.91 to 0.99, pitch of `in` a multiple of 8 KiB 0.98 to 1.04.
+inline bool sweep_tiles(int64_t M, int64_t N, int elem_bytes) { return (M | N) * elem_bytes % 16384 != 0 || (M * elem_bytes % 65536 != 0 && N * elem_bytes % 65536 != 0); }
+inline bool sweep_part_lines(int64_t N, int elem_bytes) { return elem_bytes == 4 && N * elem_bytes % 8192 != 0; }
+
+// Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines, rather than 64 rows in 256 threads.  us with the tall ones and with the
+// others, operands in the memory-side cache (three sets of buffers in turn):
+//   Few rows, one block either way, most of a tall one empty: two bytes 72 rows 7.99, 8.08 (31 MiB moved) and 136 rows 4.69, 4.71, above 64 rows never behind by more
+//   than 5 %; four bytes 52 rows 9.88, 10.59 (47 MiB).
+//   Just above one block, the second nearly empty: four bytes 132 rows 4.47, 4.18 (17 MiB; out of HBM 7.49, 6.19), from 160 rows on level; two bytes out of HBM 264
+//   rows 8.39, 7.10, 280 rows 7.11, 7.35.
+//   Few blocks for the compute units, two bytes: above 1024 rows 1032 x 4312 5.49, 5.31; 8200 x 536 5.08, 4.50; 4104 x 1976 8.31, 7.23; from 40 MiB on 0.83 to 1.08.  Up to
+//   1024 rows 520 x 8568 4.66, 5.55; 776 x 8104 5.78, 6.94.  Four bytes 516 x 4312 4.21, 5.27, 2052 x 1912 6.34, 6.47, 1028 x 2160 4.53, 4.32.
+// A launch has to hold its threads too: with one row of blocks, or two instead of three, half and three quarters as many columns fit.
+inline bool tall_line_blocks(int64_t M, int64_t N, int elem_bytes) {
+  const int rows = lines_rows(elem_bytes, true);
+  const int64_t blocks_m = (M + rows - 1) / rows, gn = (N + 63) / 64, moved = 2 * M * N * elem_bytes;
+  if (blocks_m * gn * lines_threads(rows) > kLaunchThreads) return false;
+  if (elem_bytes == 2) return M > 64 && (M <= 256 || M >= 280) && (M <= 1024 || moved >= ((int64_t)40 << 20));
+  return M > 48 && (M <= 128 || M >= 160);
+}
+
+}  // namespace swz

@@ -33,6 +33,7 @@
 
 #include "pid_decode.h"
 #include "tile_sweep.h"
+#include "transpose_dispatch.h"
 
 namespace swz {
 
@@ -241,8 +242,6 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
 // Two-byte blocks are not swept: 10000 x 7000 57.5 -> 58.1, 8200 x 8200 up to 9 % slower, 5288 x 3128 13.3 -> 12.3.
 // (tiles on line-blind boundaries 102, 110 and 82, 363 us; 60 us where both pitches are whole lines, 10048 x 7040.)  256 rows of four bytes leave a
 // compute unit two workgroups: 58 us at 5800 x 5804; with 256 threads 77.  128 columns: 60 us there, 61 at 10000 x 7000.
-__host__ __device__ constexpr int lines_rows(int elem_bytes, bool tall) { return !tall ? 64 : elem_bytes == 2 ? 256 : 128; }
-__host__ __device__ constexpr int lines_threads(int rows) { return rows == 64 ? 256 : 512; }
 
 template <class T, int BM_>
 __global__ __launch_bounds__(lines_threads(BM_)) void transpose_lines_kernel(const T* __restrict__ in, T* __restrict__ out, int M, int N, int grid_m,
