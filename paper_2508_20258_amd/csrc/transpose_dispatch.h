@@ -22,8 +22,17 @@ constexpr int lines_threads(int rows) { return rows == 64 ? 256 : 512; }
 // 26.3, 29.6, 28.7.  At pitches of whole 4096 elements fewer workgroups are better than paced ones: 8192 x 8192 49.2, 50.8, 47.1; 16384 x 16384 179.4, 186.3, 176.3; 4096 x 4096
 // 15.4, 13.8, 14.3.  (Four bytes, all four loads: five workgroups to a compute unit 5824 x 5824 48.7 us, paced 50.4; from 256 MiB on three: 3648 x 9272 50.1, five 51.0, eight 51.5,
 // paced 54.1; 8192 x 8192 87.9, 90.7, 92.4, 90.0.)
+// Tiles of 128, whose threads have eight loads each: all together, 1024 x 1024 4.0 us, paced 7.1 (out of the memory-side cache 3.2, 3.8), 8192 x 16384 97.5, 114, but paced without the skew
+// where both pitches alias: rows of `out` in multiples of 32 KiB and of `in` in 8, from 256 MiB on, 16384 x 16384 219, 267 together (16384 x 8192 123, 138; 16384 x 4096 62, 64; but
+// 16384 x 2048 31.9, 25.7 and 32768 x 2048 60, 56), and without the bands in multiples of 8 and 16 KiB, from 64 MiB on (4096 x 8192 29.7, 34.2; 8192 x 8192 58.9, 61.2; but 8192 x 4096
+// 29.5, 25.8).
 struct LoadPace { int paced, lds; };
 inline LoadPace load_pace(int tile, int64_t M, int64_t N, int mode) {
+  if (tile == 128) {
+    const bool far = M * 2 % 32768 == 0 && N * 2 % 8192 == 0 && M * N * 4 >= ((int64_t)256 << 20);
+    const bool unbanded = (mode & 3) == kModeXcd && M * 2 % 8192 == 0 && N * 2 % 16384 == 0 && M * N * 4 >= ((int64_t)64 << 20);
+    return {!swz_mode_skewed(mode) && (far || unbanded) ? 1 : 0, 0};
+  }
   if (tile != 64 || M * N * 4 < ((int64_t)32 << 20)) return {0, 0};
   if (M * 2 % 8192 == 0) return {0, 24576};
   return {1, 0};

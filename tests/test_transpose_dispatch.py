@@ -1,0 +1,33 @@
+"""The rules of a transpose's launch: order, loads on their way, blocks of part lines."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2508_20258_amd", "csrc")
+RR, XCD, XCD_GROUPM, SKEWED = 0, 1, 2, 6
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("transpose")
+    (d / "t.cpp").write_text('#include "transpose_dispatch.h"\nextern "C" {\n'
+                             "int paced(int tile, long long m, long long n, int mode) { return swz::load_pace(tile, m, n, mode).paced; }\n"
+                             "int lds(int tile, long long m, long long n, int mode) { return swz::load_pace(tile, m, n, mode).lds; }\n"
+                             "int sweep(long long m, long long n, int eb) { return swz::sweep_tiles(m, n, eb); }\n"
+                             "int tall(long long m, long long n, int eb) { return swz::tall_line_blocks(m, n, eb); }\n}\n")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", str(d / "t.cpp"), "-o", str(d / "t.so")], check=True)
+    lib = ctypes.CDLL(str(d / "t.so"))
+    for f in (lib.paced, lib.lds):
+        f.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    for f in (lib.sweep, lib.tall):
+        f.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    return lib
+
+
+@pytest.mark.parametrize("M,N,mode,paced", [(16384, 16384, XCD_GROUPM, 1), (16384, 16384, RR, 1), (16384, 16384, SKEWED, 0), (16384, 4096, XCD_GROUPM, 1),
+                                            (16384, 2048, XCD_GROUPM, 0), (16384, 4608, XCD_GROUPM, 0), (8192, 16384, XCD_GROUPM, 0), (4096, 8192, XCD, 1),
+                                            (4096, 8192, RR, 0), (8192, 4096, XCD, 0), (2048, 8192, XCD, 0), (10048, 7040, XCD_GROUPM, 0)])
+def test_loads_of_tiles_of_128(rules, M, N, mode, paced):
+    assert rules.paced(128, M, N, mode) == paced and rules.lds(128, M, N, mode) == 0
