@@ -17,10 +17,14 @@ constexpr int lines_rows(int elem_bytes, bool tall) { return !tall ? 64 : elem_b
 constexpr int lines_threads(int rows) { return rows == 64 ? 256 : 512; }
 
 // How many bytes the workgroups of a two-byte transpose have on their way at a time: both loads of a thread or one (paced), and LDS on top of the tile's 8 KB, which
-// holds five workgroups to a compute unit instead of eight.  Up to 32 MiB latency counts: both, eight (2176 x 2968 7.5 us, paced 7.7; 3200 x 1440 5.2, 6.0).  Above, the HBM serves
-// more bytes a second the fewer are asked for, 32 to 40 KB a compute unit: paced 3712 x 17656 57.6, both 61.9, both and five 58.4; 20416 x 1912 31.7, 34.4, 33.2; 12416 x 2704
-// 26.3, 29.6, 28.7.  At pitches of whole 4096 elements fewer workgroups are better than paced ones: 8192 x 8192 49.2, 50.8, 47.1; 16384 x 16384 179.4, 186.3, 176.3; 4096 x 4096
-// 15.4, 13.8, 14.3.  (Four bytes, all four loads: five workgroups to a compute unit 5824 x 5824 48.7 us, paced 50.4; from 256 MiB on three: 3648 x 9272 50.1, five 51.0, eight 51.5,
+// holds five workgroups to a compute unit instead of eight.  us under the default mode, paced / both / both and five.  Up to 32 MiB latency counts: both, eight (2176 x 2968 7.7 / 7.5;
+// 3200 x 1440 6.0 / 5.2), but round robin from 20 MiB on paced (2176 x 2968 8.6 / 9.1).  Above, the HBM serves more
+// bytes a second the fewer are asked for, 32 to 40 KB a compute unit: 3712 x 17656 57.6 / 61.9 / 58.4; 20416 x 1912 31.7 / 34.4 / 33.2; 12416 x 2704 26.3 / 29.6 / 28.7.
+//   Rows of `out` in whole multiples of 8 KiB: fewer workgroups are better than paced ones, 8192 x 8192 49.2 / 50.8 / 47.1; 16384 x 16384 179.4 / 186.3 / 176.3 (under the bands without
+//   the skew not in odd multiples of 16 KiB, 8192 x 8192 49.7 / 51.5 / 52.0, and round robin below 56 MiB, 4096 x 2560 10.8 / 11.7 / 11.3).
+//   Rows of `in` or `out` in such multiples, under the bands and below 80 MiB: both, eight, 4096 x 4096 15.4 / 13.8 / 14.3; 2048 x 4096 9.3 / 9.0 / 8.5; 4160 x 4096 16.6 / 15.6 / 16.2;
+//   4096 x 4160 16.2 / 15.4 / 16.5; 8192 x 2048 15.6 / 14.8 / 15.4; from there on level, 5120 x 4096 19.1 / 19.2 / 18.6.
+// (Four bytes, all four loads: five workgroups to a compute unit 5824 x 5824 48.7 us, paced 50.4; from 256 MiB on three: 3648 x 9272 50.1, five 51.0, eight 51.5,
 // paced 54.1; 8192 x 8192 87.9, 90.7, 92.4, 90.0.)
 // Tiles of 128, whose threads have eight loads each: all together, 1024 x 1024 4.0 us, paced 7.1 (out of the memory-side cache 3.2, 3.8), 8192 x 16384 97.5, 114, but paced without the skew
 // where both pitches alias: rows of `out` in multiples of 32 KiB and of `in` in 8, from 256 MiB on, 16384 x 16384 219, 267 together (16384 x 8192 123, 138; 16384 x 4096 62, 64; but
@@ -33,9 +37,12 @@ inline LoadPace load_pace(int tile, int64_t M, int64_t N, int mode) {
     const bool unbanded = (mode & 3) == kModeXcd && M * 2 % 8192 == 0 && N * 2 % 16384 == 0 && M * N * 4 >= ((int64_t)64 << 20);
     return {!swz_mode_skewed(mode) && (far || unbanded) ? 1 : 0, 0};
   }
-  if (tile != 64 || M * N * 4 < ((int64_t)32 << 20)) return {0, 0};
-  if (M * 2 % 8192 == 0) return {0, 24576};
-  return {1, 0};
+  const bool banded = swz_mode_grouped(mode), rr = (mode & 3) == kModeRR, out_8k = M * 2 % 8192 == 0;
+  const int64_t moved = M * N * 4;
+  if (tile != 64 || moved < (int64_t)(rr ? 20 : 32) << 20) return {0, 0};
+  if (banded && (out_8k || N * 2 % 8192 == 0) && moved < ((int64_t)80 << 20)) return {0, 0};
+  const bool few = out_8k && !(rr && moved < ((int64_t)56 << 20)) && !(banded && !swz_mode_skewed(mode) && M * 2 % 32768 == 16384);
+  return {few ? 0 : 1, few ? 24576 : 0};
 }
 
 // Which transposes under the default mode, with the band height left to the library, take the sweep of tile_sweep.h.  Time of the sweep over that of the skewed raster, loads and

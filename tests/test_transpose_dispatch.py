@@ -31,3 +31,13 @@ def rules(tmp_path_factory):
                                             (4096, 8192, RR, 0), (8192, 4096, XCD, 0), (2048, 8192, XCD, 0), (10048, 7040, XCD_GROUPM, 0)])
 def test_loads_of_tiles_of_128(rules, M, N, mode, paced):
     assert rules.paced(128, M, N, mode) == paced and rules.lds(128, M, N, mode) == 0
+
+
+@pytest.mark.parametrize("M,N,mode,paced,lds", [
+    (1024, 1024, SKEWED, 0, 0), (2944, 2848, SKEWED, 0, 0), (2944, 2856, SKEWED, 1, 0), (5056, 5000, SKEWED, 1, 0), (5056, 5000, XCD, 1, 0),
+    (4096, 4096, SKEWED, 0, 0), (2048, 4096, SKEWED, 0, 0), (4160, 4096, XCD_GROUPM, 0, 0), (4096, 4160, SKEWED, 0, 0), (5120, 4096, SKEWED, 1, 0),
+    (8192, 2560, SKEWED, 0, 24576), (8192, 8192, SKEWED, 0, 24576), (8192, 8192, XCD_GROUPM, 1, 0), (16384, 16384, XCD_GROUPM, 0, 24576), (4096, 4096, XCD, 0, 24576),
+    (4160, 4096, XCD, 1, 0), (2176, 2408, RR, 0, 0), (2176, 2416, RR, 1, 0), (4096, 2560, RR, 1, 0), (4096, 4096, RR, 0, 24576)])
+def test_loads_of_tiles_of_64(rules, M, N, mode, paced, lds):
+    assert (rules.paced(64, M, N, mode), rules.lds(64, M, N, mode)) == (paced, lds)
+    assert (rules.paced(32, M, N, mode), rules.lds(32, M, N, mode)) == (0, 0)
