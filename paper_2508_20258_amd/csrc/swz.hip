@@ -269,19 +269,19 @@ int launch_transpose_s(const void* in, void* out, int M, int N, int gm, int gn, 
   }
 }
 
-template <bool STREAM>
+template <bool STREAM, bool PACED>
 int launch_transpose32(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode, int sweep,
                        hipStream_t stream) {
   const dim3 grid((unsigned)(gm * gn)), block(256);
   auto* i = static_cast<const uint32_t*>(in);
   auto* o = static_cast<uint32_t*>(out);
-  const size_t lds = STREAM ? 32768 : 12288;       // on top of the tile's 16 KB: three or five workgroups to a compute unit
+  const size_t lds = STREAM ? 32768 : PACED ? 0 : 12288;       // on top of the tile's 16 KB: three, ten or five workgroups to a compute unit
   const int skew = swz_mode_skewed(mode) ? 1 : 0;
   switch (mode & 3) {
-    case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    case SWZ_MODE_XCD: return launch(swz::transpose32_kernel<kModeXcd, STREAM>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose32_kernel<kModeXcdGroupM, STREAM>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    default: return launch(swz::transpose32_kernel<kModeGroupM, STREAM>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM, PACED>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD: return launch(swz::transpose32_kernel<kModeXcd, STREAM, PACED>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose32_kernel<kModeXcdGroupM, STREAM, PACED>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    default: return launch(swz::transpose32_kernel<kModeGroupM, STREAM, PACED>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
   }
 }
 
@@ -581,8 +581,9 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   const int sweep = ours && swz::sweep_tiles(M, N, elem_bytes) ? swz_sweep_rows((int)gm, num_xcd, elem_bytes) : 0;
   if (elem_bytes == 4) {
     if (M * N * 8 > kMemorySideCacheBytes)
-      return launch_transpose32<true>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
-    return launch_transpose32<false>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
+      return launch_transpose32<true, false>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
+    if (swz::paced_tiles32(M, N)) return launch_transpose32<false, true>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
+    return launch_transpose32<false, false>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
   }
   if (tile == 128) return launch_transpose<128>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
   return tile == 64 ? launch_transpose<64>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream)

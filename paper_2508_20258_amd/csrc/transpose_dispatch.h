@@ -24,8 +24,6 @@ constexpr int lines_threads(int rows) { return rows == 64 ? 256 : 512; }
 //   the skew not in odd multiples of 16 KiB, 8192 x 8192 49.7 / 51.5 / 52.0, and round robin below 56 MiB, 4096 x 2560 10.8 / 11.7 / 11.3).
 //   Rows of `in` or `out` in such multiples, under the bands and below 68 MiB: both, eight, 4096 x 4096 15.4 / 13.8 / 14.3; 2048 x 4096 9.3 / 9.0 / 8.5; 4160 x 4096 16.6 / 15.6 / 16.2;
 //   4096 x 4160 16.2 / 15.4 / 16.5; 8192 x 2048 15.6 / 14.8 / 15.4; above not, 320 x 57344 15.5 / 16.2; 1600 x 12288 16.5 / 17.2.
-// (Four bytes, all four loads: five workgroups to a compute unit 5824 x 5824 48.7 us, paced 50.4; from 256 MiB on three: 3648 x 9272 50.1, five 51.0, eight 51.5,
-// paced 54.1; 8192 x 8192 87.9, 90.7, 92.4, 90.0.)
 // Tiles of 128, whose threads have eight loads each: all together, 1024 x 1024 4.0 us, paced 7.1 (out of the memory-side cache 3.2, 3.8), 8192 x 16384 97.5, 114, but paced without the skew
 // where both pitches alias: rows of `out` in multiples of 32 KiB and of `in` in 8, from 256 MiB on, 16384 x 16384 219, 267 together (16384 x 8192 123, 138; 16384 x 4096 62, 64; but
 // 16384 x 2048 31.9, 25.7 and 32768 x 2048 60, 56), and without the bands in multiples of 8 and 16 KiB, from 64 MiB on (4096 x 8192 29.7, 34.2; 8192 x 8192 58.9, 61.2; but 8192 x 4096
@@ -44,6 +42,13 @@ inline LoadPace load_pace(int tile, int64_t M, int64_t N, int mode) {
   const bool few = out_8k && !(rr && moved < ((int64_t)56 << 20)) && !(banded && !swz_mode_skewed(mode) && M * 2 % 32768 == 16384);
   return {few ? 0 : 1, few ? 24576 : 0};
 }
+
+// Four-byte tiles: all four loads of a thread on their way, and LDS for five workgroups to a compute unit: level with eight up to 64 MiB (1024 x 1024 3.9 us, 3.8; 2048 x 2048 7.8, 7.9;
+// 2048 x 4096 14.6, 14.4), ahead from there to 256 MiB (1024 x 16384 27.9, 30.1; 4128 x 4200 29.1, 29.9; 5600 x 5600 51.0, 50.5), then three: 3648 x 9272 50.1, five 51.0, eight 51.5, paced
+// 54.1; 8192 x 8192 87.9, 90.7, 92.4, 90.0.  But from 36 to 63 MiB one load at a time and as many workgroups as fit, paced / together and five, operands out of HBM and out of the memory-side
+// cache: 2048 x 3072 9.8 / 11.1 and 10.0 / 10.7; 2144 x 2300 8.6 / 9.3 and 8.2 / 8.8; 4096 x 1500 9.9 / 11.2 and 10.0 / 10.8; 2720 x 3000 13.6 / 14.8 and 13.2 / 13.8; below and above
+// not, 2048 x 2048 8.4 / 7.8; 4096 x 2048 14.5 / 14.6 and 15.1 / 13.7.
+inline bool paced_tiles32(int64_t M, int64_t N) { return M * N * 8 >= ((int64_t)36 << 20) && M * N * 8 < ((int64_t)63 << 20); }
 
 // Which transposes under the default mode, with the band height left to the library, take the sweep of tile_sweep.h.  Time of the sweep over that of the skewed raster, loads and
 // occupancy as they are now.  Tiles: no pitch a power of two 0.84 to 1.00, on average 0.92 (40 sizes).  Both pitches multiples of 16 KiB: 8192 x 8192 x 4 B 0.99, 12288 x 8192

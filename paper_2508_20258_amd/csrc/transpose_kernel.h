@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
 // 32 h + 4 (l%8) .. +3.  LDS layout: row r at byte r*256, 16-byte chunk c (4 columns) in slot
 // c ^ (((r >> 2) & 7) << 1): the 64 lanes of one read (8 row groups x 8 columns = 2 chunks) then hit 64
 // different banks.  Same mapping arguments, same streaming-store rule as the 16-bit kernel.
-template <int MODE, bool STREAM>
+template <int MODE, bool STREAM, bool PACED>
 __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
                                                           int M, int N, int grid_m, int grid_n, int num_xcd,
                                                           int group_m, int skew, int sweep) {
@@ -193,6 +193,7 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
   for (int i = 0; i < CHUNKS / 256; ++i) {
     const int q = tid + 256 * i;
     in_v[i] = __builtin_nontemporal_load(tr_source(in, m0 + q / SLOTS, n0 + q % SLOTS * 4, M, N));
+    if constexpr (PACED) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
   }
 #pragma unroll
   for (int i = 0; i < CHUNKS / 256; ++i) {

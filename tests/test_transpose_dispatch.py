@@ -15,12 +15,14 @@ def rules(tmp_path_factory):
     (d / "t.cpp").write_text('#include "transpose_dispatch.h"\nextern "C" {\n'
                              "int paced(int tile, long long m, long long n, int mode) { return swz::load_pace(tile, m, n, mode).paced; }\n"
                              "int lds(int tile, long long m, long long n, int mode) { return swz::load_pace(tile, m, n, mode).lds; }\n"
+                             "int paced32(long long m, long long n) { return swz::paced_tiles32(m, n); }\n"
                              "int sweep(long long m, long long n, int eb) { return swz::sweep_tiles(m, n, eb); }\n"
                              "int tall(long long m, long long n, int eb) { return swz::tall_line_blocks(m, n, eb); }\n}\n")
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", str(d / "t.cpp"), "-o", str(d / "t.so")], check=True)
     lib = ctypes.CDLL(str(d / "t.so"))
     for f in (lib.paced, lib.lds):
         f.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    lib.paced32.argtypes = [ctypes.c_longlong] * 2
     for f in (lib.sweep, lib.tall):
         f.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
     return lib
@@ -47,3 +49,8 @@ def test_loads_of_tiles_of_64(rules, M, N, mode, paced, lds):
                                                   (2048, 8192, 2, 0), (2048, 8200, 2, 1), (1536, 4096, 2, 0), (1472, 4096, 2, 1), (4288, 4096, 2, 0), (4352, 4096, 2, 1)])
 def test_which_tiles_are_swept(rules, M, N, elem_bytes, sweep):
     assert rules.sweep(M, N, elem_bytes) == sweep
+
+
+@pytest.mark.parametrize("M,N,paced", [(2048, 2300, 0), (2048, 2304, 1), (2048, 4028, 1), (2048, 4032, 0), (64, 64, 0), (8192, 8192, 0)])
+def test_loads_of_four_byte_tiles(rules, M, N, paced):
+    assert rules.paced32(M, N) == paced
