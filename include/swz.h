@@ -186,8 +186,8 @@ int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_par
  *   streaming stores (the faster choice there, the slower one below it).
  *   Where rows of `out` do not start on 128-byte lines, tile 64 (from 16 MiB moved) is done in blocks of 64 columns, a workgroup each, which
  *   writes the whole lines nearest to its block; the id -> block map is that of swz_pid_map (or the sweep: elem_bytes 4, pitch of `in` no multiple of 8 KiB) for the grid of those blocks, and group_m
- *   counts them.  A block has 256 rows for elem_bytes 2 where M > 64, and M <= 1024 or 40 MiB and more are moved, but not for 256 < M < 280; 128 rows for
- *   elem_bytes 4 where M > 48, but not for 128 < M < 160; 64 rows otherwise, and wherever blocks of
+ *   counts them.  A block has 256 rows for elem_bytes 2 where M > 64, and M <= 1024 or 22 MiB and more are moved, but not for 256 < M < 280 (320 from 128 MiB on);
+ *   128 rows for elem_bytes 4 where M > 48, but not for 128 < M < 188; 64 rows otherwise, and wherever blocks of
  *   those rows would be 2^23 or more.
  * Asynchronous on `stream`; never allocates or synchronises.
  * Errors: INVALID_ARG (null, M/N < 1, unknown mode), UNSUPPORTED (elem_bytes not 2 or 4, tile not 32/64/128

@@ -295,11 +295,11 @@ int launch_transpose(const void* in, void* out, int M, int N, int gm, int gn, in
   return launch_transpose_s<TILE, false>(in, out, M, N, gm, gn, num_xcd, group_m, mode, sweep, stream);
 }
 
-template <class T, bool TALL>
+template <class T, bool TALL, bool PACED>
 int launch_transpose_lines(const void* in, void* out, int M, int N, int gn, int num_xcd, int group_m, int mode, bool sweep, hipStream_t stream) {
   constexpr int ROWS = swz::lines_rows((int)sizeof(T), TALL);
   const int blocks_m = (M + ROWS - 1) / ROWS;
-  return launch(swz::transpose_lines_kernel<T, ROWS>, dim3((unsigned)(blocks_m * gn)), dim3(swz::lines_threads(ROWS)), 0, stream, static_cast<const T*>(in),
+  return launch(swz::transpose_lines_kernel<T, ROWS, PACED>, dim3((unsigned)(blocks_m * gn)), dim3(swz::lines_threads(ROWS)), 0, stream, static_cast<const T*>(in),
                 static_cast<T*>(out), M, N, blocks_m, gn, num_xcd, group_m < blocks_m ? group_m : blocks_m, mode,
                 sweep ? swz_sweep_rows(blocks_m, num_xcd, (int)sizeof(T)) : 0);
 }
@@ -571,12 +571,16 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   const bool ours = tile == 64 && mode == (SWZ_MODE_XCD_GROUPM | SWZ_MODE_SKEW) && (params == nullptr || params->group_m == 0);
   if (tile == 64 && part_lines && M < ((int64_t)1 << 30) && 2 * M * N * elem_bytes >= ((int64_t)16 << 20)) {
     const bool sweep = ours && swz::sweep_part_lines(N, elem_bytes);
-    const bool tall = swz::tall_line_blocks(M, N, elem_bytes);
-    if (elem_bytes == 2)
-      return tall ? launch_transpose_lines<uint16_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream)
-                  : launch_transpose_lines<uint16_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream);
-    return tall ? launch_transpose_lines<uint32_t, true>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream)
-                : launch_transpose_lines<uint32_t, false>(in, out, (int)M, (int)N, (int)gn, num_xcd, group_m, mode, sweep, stream);
+    const int m = (int)M, n = (int)N, g = (int)gn;
+    auto go = [&](auto elem) {
+      using T = decltype(elem);
+      switch (swz::line_blocks(M, N, elem_bytes)) {
+        case swz::kLinesTallPaced: return launch_transpose_lines<T, true, true>(in, out, m, n, g, num_xcd, group_m, mode, sweep, stream);
+        case swz::kLinesTall: return launch_transpose_lines<T, true, false>(in, out, m, n, g, num_xcd, group_m, mode, sweep, stream);
+        default: return launch_transpose_lines<T, false, false>(in, out, m, n, g, num_xcd, group_m, mode, sweep, stream);
+      }
+    };
+    return elem_bytes == 2 ? go(uint16_t{}) : go(uint32_t{});
   }
   const int sweep = ours && swz::sweep_tiles(M, N, elem_bytes) ? swz_sweep_rows((int)gm, num_xcd, elem_bytes) : 0;
   if (elem_bytes == 4) {

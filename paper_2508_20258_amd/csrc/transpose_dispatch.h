@@ -62,21 +62,30 @@ inline bool sweep_tiles(int64_t M, int64_t N, int elem_bytes) {
 }
 inline bool sweep_part_lines(int64_t N, int elem_bytes) { return elem_bytes == 4 && N * elem_bytes % 8192 != 0; }
 
-// Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines, rather than 64 rows in 256 threads.  us with the tall ones and with the
-// others, operands in the memory-side cache (three sets of buffers in turn):
-//   Few rows, one block either way, most of a tall one empty: two bytes 72 rows 7.99, 8.08 (31 MiB moved) and 136 rows 4.69, 4.71, above 64 rows never behind by more
-//   than 5 %; four bytes 52 rows 9.88, 10.59 (47 MiB).
-//   Just above one block, the second nearly empty: four bytes 132 rows 4.47, 4.18 (17 MiB; out of HBM 7.49, 6.19), from 160 rows on level; two bytes out of HBM 264
-//   rows 8.39, 7.10, 280 rows 7.11, 7.35.
-//   Few blocks for the compute units, two bytes: above 1024 rows 1032 x 4312 5.49, 5.31; 8200 x 536 5.08, 4.50; 4104 x 1976 8.31, 7.23; from 40 MiB on 0.83 to 1.08.  Up to
-//   1024 rows 520 x 8568 4.66, 5.55; 776 x 8104 5.78, 6.94.  Four bytes 516 x 4312 4.21, 5.27, 2052 x 1912 6.34, 6.47, 1028 x 2160 4.53, 4.32.
+// Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines (tall), rather than 64 rows in 256 threads, and whether a thread's loads are on their way one at a time
+// (paced) or together.  us, tall / 64 rows, operands out of HBM and, where it says otherwise, out of the memory-side cache (three sets of buffers in turn):
+//   Few rows, one block either way, most of a tall one empty: two bytes 56 rows 8.3 / 6.8 (17 MiB moved), 72 rows 7.2 / 7.7, 136 rows 51 / 54 (200 MiB); four bytes 44 rows 0.89 to 1.14
+//   of the time, 52 rows 9.9 / 10.6 (47 MiB).
+//   Just above one block, the second nearly empty: two bytes 264 rows 8.4 / 7.1, 280 rows 7.2 / 7.4 and 4.9 / 6.1 out of the cache, but from 128 MiB on 59.7 / 54.3 (304 x 172456); four
+//   bytes 132 rows 7.5 / 6.3, 164 rows 8.5 / 7.6, 180 rows 8.6 / 7.9, 196 rows 6.6 / 8.2.
+//   Few blocks for the compute units, two bytes above 1024 rows, below 22 MiB: 1032 x 4312 7.6 / 7.3 and 5.8 / 5.4, 8200 x 536 7.4 / 7.1 and 5.5 / 4.9; up to 1024 rows 520 x 8568 7.4 / 7.4
+//   and 4.9 / 5.8, 776 x 8104 8.1 / 9.1 and 5.7 / 7.1; four bytes 516 x 4316 6.6 / 6.5 and 4.4 / 5.5, 1028 x 2164 6.6 / 6.5 and 4.7 / 4.9.
+//   Paced / together, tall: two bytes 4104 x 1656 8.1 / 9.2 and 7.0 / 6.6, 2056 x 4840 10.6 / 11.7 and 9.5 / 9.8, 8200 x 1400 10.5 / 12.4 and 9.4 / 9.6, but 1032 x 13208 15.4 / 14.5
+//   and 12.6 / 10.9; four bytes 1028 x 4204 8.7 / 10.3 and 7.8 / 8.4, 2052 x 2424 9.6 / 11.1 and 8.6 / 8.5, 516 x 8380 8.6 / 10.2 and 7.5 / 7.3, but 516 x 13208 15.0 / 14.4 and
+//   13.9 / 11.6.  Outside the sizes below: together, out of the cache up to 21 % ahead of 64 rows paced, out of
+//   HBM level on average, but 8200 x 664 7.4 / 6.5, 776 x 8776 9.7 / 8.0, 392 x 22064 9.9 / 8.6.
 // A launch has to hold its threads too: with one row of blocks, or two instead of three, half and three quarters as many columns fit.
-inline bool tall_line_blocks(int64_t M, int64_t N, int elem_bytes) {
+enum LineBlocks : int { kLines = 0, kLinesTall = 1, kLinesTallPaced = 2 };
+inline LineBlocks line_blocks(int64_t M, int64_t N, int elem_bytes) {
   const int rows = lines_rows(elem_bytes, true);
-  const int64_t blocks_m = (M + rows - 1) / rows, gn = (N + 63) / 64, moved = 2 * M * N * elem_bytes;
-  if (blocks_m * gn * lines_threads(rows) > kLaunchThreads) return false;
-  if (elem_bytes == 2) return M > 64 && (M <= 256 || M >= 280) && (M <= 1024 || moved >= ((int64_t)40 << 20));
-  return M > 48 && (M <= 128 || M >= 160);
+  const int64_t blocks_m = (M + rows - 1) / rows, gn = (N + 63) / 64, mib = (2 * M * N * elem_bytes) >> 20;
+  if (blocks_m * gn * lines_threads(rows) > kLaunchThreads) return kLines;
+  if (elem_bytes == 2) {
+    if (M <= 64 || (M > 256 && M < (mib < 128 ? 280 : 320)) || (M > 1024 && mib < 22)) return kLines;
+    return M > 1024 && mib < (M > 3072 ? 50 : 40) ? kLinesTallPaced : kLinesTall;
+  }
+  if (M <= 48 || (M > 128 && M < 188)) return kLines;
+  return M > 256 && mib >= 31 && mib < (M > 1000 ? 56 : 40) ? kLinesTallPaced : kLinesTall;
 }
 
 }  // namespace swz

@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
 // (tiles on line-blind boundaries 102, 110 and 82, 363 us; 60 us where both pitches are whole lines, 10048 x 7040.)  256 rows of four bytes leave a
 // compute unit two workgroups: 58 us at 5800 x 5804; with 256 threads 77.  128 columns: 60 us there, 61 at 10000 x 7000.
 
-template <class T, int BM_>
+template <class T, int BM_, bool PACED>
 __global__ __launch_bounds__(lines_threads(BM_)) void transpose_lines_kernel(const T* __restrict__ in, T* __restrict__ out, int M, int N, int grid_m,
                                                                                   int grid_n, int num_xcd, int group_m, int mode, int sweep) {
   constexpr int TILE = 64, BM = BM_, NT = lines_threads(BM_);
@@ -263,6 +263,7 @@ __global__ __launch_bounds__(lines_threads(BM_)) void transpose_lines_kernel(con
   for (int i = 0; i < LOADS; ++i) {
     const int q = tid + NT * i;
     in_v[i] = *tr_source(in, m0 + q / SLOTS, n0 + q % SLOTS * CH, M, N);
+    if constexpr (PACED) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
   }
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {

@@ -17,13 +17,13 @@ def rules(tmp_path_factory):
                              "int lds(int tile, long long m, long long n, int mode) { return swz::load_pace(tile, m, n, mode).lds; }\n"
                              "int paced32(long long m, long long n) { return swz::paced_tiles32(m, n); }\n"
                              "int sweep(long long m, long long n, int eb) { return swz::sweep_tiles(m, n, eb); }\n"
-                             "int tall(long long m, long long n, int eb) { return swz::tall_line_blocks(m, n, eb); }\n}\n")
+                             "int lines(long long m, long long n, int eb) { return swz::line_blocks(m, n, eb); }\n}\n")
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", str(d / "t.cpp"), "-o", str(d / "t.so")], check=True)
     lib = ctypes.CDLL(str(d / "t.so"))
     for f in (lib.paced, lib.lds):
         f.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
     lib.paced32.argtypes = [ctypes.c_longlong] * 2
-    for f in (lib.sweep, lib.tall):
+    for f in (lib.sweep, lib.lines):
         f.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
     return lib
 
@@ -54,3 +54,17 @@ def test_which_tiles_are_swept(rules, M, N, elem_bytes, sweep):
 @pytest.mark.parametrize("M,N,paced", [(2048, 2300, 0), (2048, 2304, 1), (2048, 4028, 1), (2048, 4032, 0), (64, 64, 0), (8192, 8192, 0)])
 def test_loads_of_four_byte_tiles(rules, M, N, paced):
     assert rules.paced32(M, N) == paced
+
+
+SHORT, TALL, TALL_PACED = 0, 1, 2
+
+
+@pytest.mark.parametrize("M,N,elem_bytes,blocks", [
+    (64, 87376, 2, SHORT), (72, 87376, 2, TALL), (256, 40000, 2, TALL), (264, 40000, 2, SHORT), (272, 200000, 2, SHORT), (280, 40000, 2, TALL), (312, 200000, 2, SHORT),
+    (320, 200000, 2, TALL), (1024, 4456, 2, TALL), (1032, 5576, 2, SHORT), (1032, 5592, 2, TALL_PACED), (1032, 10152, 2, TALL_PACED), (1032, 10168, 2, TALL),
+    (3080, 4248, 2, TALL_PACED), (3080, 4256, 2, TALL), (8200, 600, 2, SHORT), (10000, 7000, 2, TALL), (8, 1 << 29, 2, SHORT),
+    (48, 60000, 4, SHORT), (52, 60000, 4, TALL), (128, 60000, 4, TALL), (132, 60000, 4, SHORT), (184, 60000, 4, SHORT), (188, 60000, 4, TALL),
+    (260, 16000, 4, TALL_PACED), (256, 16000, 4, TALL), (260, 15620, 4, TALL), (1000, 5240, 4, TALL_PACED), (1000, 5244, 4, TALL), (1004, 7308, 4, TALL_PACED),
+    (1004, 7316, 4, TALL), (5800, 5804, 4, TALL)])
+def test_blocks_into_part_lines(rules, M, N, elem_bytes, blocks):
+    assert rules.lines(M, N, elem_bytes) == blocks
