@@ -269,19 +269,19 @@ int launch_transpose_s(const void* in, void* out, int M, int N, int gm, int gn, 
   }
 }
 
-template <bool STREAM, bool PACED>
+template <bool STREAM, bool PACED, int LOADS>
 int launch_transpose32(const void* in, void* out, int M, int N, int gm, int gn, int num_xcd, int group_m, int mode, int sweep,
                        hipStream_t stream) {
   const dim3 grid((unsigned)(gm * gn)), block(256);
   auto* i = static_cast<const uint32_t*>(in);
   auto* o = static_cast<uint32_t*>(out);
-  const size_t lds = STREAM ? 32768 : PACED ? 0 : 12288;       // on top of the tile's 16 KB: three, ten or five workgroups to a compute unit
+  const size_t lds = STREAM ? 32768 : PACED || LOADS < 4 ? 0 : 12288;       // on top of the tile's 16 KB: three, eight or five workgroups to a compute unit
   const int skew = swz_mode_skewed(mode) ? 1 : 0;
   switch (mode & 3) {
-    case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM, PACED>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    case SWZ_MODE_XCD: return launch(swz::transpose32_kernel<kModeXcd, STREAM, PACED>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose32_kernel<kModeXcdGroupM, STREAM, PACED>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
-    default: return launch(swz::transpose32_kernel<kModeGroupM, STREAM, PACED>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM, PACED, LOADS>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD: return launch(swz::transpose32_kernel<kModeXcd, STREAM, PACED, LOADS>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    case SWZ_MODE_XCD_GROUPM: return launch(swz::transpose32_kernel<kModeXcdGroupM, STREAM, PACED, LOADS>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
+    default: return launch(swz::transpose32_kernel<kModeGroupM, STREAM, PACED, LOADS>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
   }
 }
 
@@ -584,10 +584,14 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   }
   const int sweep = ours && swz::sweep_tiles(M, N, elem_bytes) ? swz_sweep_rows((int)gm, num_xcd, elem_bytes) : 0;
   if (elem_bytes == 4) {
-    if (M * N * 8 > kMemorySideCacheBytes)
-      return launch_transpose32<true, false>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
-    if (swz::paced_tiles32(M, N)) return launch_transpose32<false, true>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
-    return launch_transpose32<false, false>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
+    const int m = (int)M, n = (int)N, tm = (int)gm, tn = (int)gn;
+    if (M * N * 8 > kMemorySideCacheBytes) return launch_transpose32<true, false, 4>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
+    // one row of tiles, a quarter or half of it real: no loads for the rest, and eight workgroups to a compute unit, as each has little on its way (us, all loads and five workgroups -> these:
+    // 4 x 521008 13.6 -> 10.0, 16 x 98304 4.6 -> 4.1, 24 x 86832 5.5 -> 4.7)
+    if (M <= 16) return launch_transpose32<false, false, 1>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
+    if (M <= 32) return launch_transpose32<false, false, 2>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
+    if (swz::paced_tiles32(M, N)) return launch_transpose32<false, true, 4>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
+    return launch_transpose32<false, false, 4>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
   }
   if (tile == 128) return launch_transpose<128>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream);
   return tile == 64 ? launch_transpose<64>(in, out, (int)M, (int)N, (int)gm, (int)gn, num_xcd, group_m, mode, sweep, stream)

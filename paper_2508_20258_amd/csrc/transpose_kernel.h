@@ -177,7 +177,8 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
 // 32 h + 4 (l%8) .. +3.  LDS layout: row r at byte r*256, 16-byte chunk c (4 columns) in slot
 // c ^ (((r >> 2) & 7) << 1): the 64 lanes of one read (8 row groups x 8 columns = 2 chunks) then hit 64
 // different banks.  Same mapping arguments, same streaming-store rule as the 16-bit kernel.
-template <int MODE, bool STREAM, bool PACED>
+// LOADS of the four that a thread has for a tile, 16 rows each: fewer where `in` has no more rows (one tile row).
+template <int MODE, bool STREAM, bool PACED, int LOADS>
 __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
                                                           int M, int N, int grid_m, int grid_n, int num_xcd,
                                                           int group_m, int skew, int sweep) {
@@ -188,15 +189,16 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
   const int m0 = pm * TILE, n0 = pn * TILE;
   const int tid = threadIdx.x;
   auto key = [](int r) { return ((r >> 2) & 7) << 1; };
-  t_u32x4 in_v[CHUNKS / 256];
+  static_assert(LOADS * 256 <= CHUNKS, "a tile");
+  t_u32x4 in_v[LOADS];
 #pragma unroll
-  for (int i = 0; i < CHUNKS / 256; ++i) {
+  for (int i = 0; i < LOADS; ++i) {
     const int q = tid + 256 * i;
     in_v[i] = __builtin_nontemporal_load(tr_source(in, m0 + q / SLOTS, n0 + q % SLOTS * 4, M, N));
     if constexpr (PACED) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
   }
 #pragma unroll
-  for (int i = 0; i < CHUNKS / 256; ++i) {
+  for (int i = 0; i < LOADS; ++i) {
     const int q = tid + 256 * i, r = q / SLOTS, c = q % SLOTS;
     *reinterpret_cast<t_u32x4*>(tile + r * ROW_BYTES + ((c ^ key(r)) << 4)) = in_v[i];
   }
