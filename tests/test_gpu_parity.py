@@ -627,22 +627,27 @@ def test_mfma_peak_kernel_runs_and_checks_its_buffer(swz):
 
 # ---------------------------------------------------------------------------- default tiles cut into sub-tiles
 
-# M, N and the sub-tile shape the library takes there on 256 compute units; edges of every shape, one row, one column block
+# M, N and the sub-tile shapes the library takes there on 256 compute units (test_gemm_dispatch.py asks the rule); edges of every shape, one row, one column block
 SUBTILE_SHAPES = [(1, 8), (33, 40), (100, 520), (512, 512),                  # 32x32
                   (300, 1032), (129, 3000),                                  # 32x64
                   (1000, 1000), (449, 1992),                                 # 64x64
-                  (1280, 1600), (1217, 1544),                                # 128x64 / 64x128
+                  (1280, 1600), (1217, 1544),                                # 128x64
                   (300, 5000), (1100, 1504),                                 # 64x128
-                  (1537, 1400), (40, 33000), (70, 66000),                    # 128x128; grids of 128x256 and 256x256 tiles
-                  (577, 3848), (4359, 488), (1537, 2680), (572, 9424), (4575, 1112)]         # 96x128, 192x128: one row, one column block and all but one in the last
+                  (1537, 1400), (40, 33000), (70, 66000),                    # 128x128 and 96x128; paired tiles, 128x256 and 64x128; paired tiles and 96x128
+                  (577, 3848), (4359, 488), (1537, 2680), (572, 9424), (4575, 1112),          # 96x128, 192x128: one row, one column block and all but one in the last
+                  (193, 12304), (1985, 2024),                                # 128x128
+                  (1929, 3848), (257, 19208)]                                # 128x256 and whole tiles of that size; paired tiles and 128x256
+# less than a stage of 64, partial stages, fewer stages than any ring, whole rings of 5, 6 and 8 and the hand-overs
+SUBTILE_KS = [8, 64, 72, 200, 320, 384, 456, 512, 704, 1032, 1344]
+
+
+def subtile_ks(M, N):
+    return [K for n, K in enumerate(SUBTILE_KS) if M * N * K <= 1 << 30 or n % 3 == 0]
 
 
 @pytest.mark.parametrize("M,N", SUBTILE_SHAPES)
 def test_subtiles_give_the_bits_of_whole_tiles(swz, M, N):
-    # K: less than a stage of 64, partial stages, fewer stages than any ring, whole rings of 5, 6 and 8 and the hand-overs
-    for n, K in enumerate([8, 64, 72, 200, 320, 384, 456, 512, 704, 1032, 1344]):
-        if M * N * K > 1 << 30 and n % 3:
-            continue
+    for K in subtile_ks(M, N):
         g = torch.Generator(device="cuda").manual_seed(M + K)
         a = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
         b = torch.randn((K, N), device="cuda", generator=g).to(torch.bfloat16)
@@ -687,9 +692,12 @@ def test_paired_tiles_give_the_bits_of_whole_tiles(swz, M, N, K):
     (4, 2044, 1028, 0), (4, 64, 40000, 4), (4, 1536, 1536, 28), (4, 1540, 1536, 12),
     # blocks of 256 and 128 rows: one short of a block, one chunk more, a last block of less than the shift
     (2, 248, 17000, 0), (2, 264, 16008, 0), (2, 312, 14000, 8), (2, 520, 8200, 40), (4, 124, 17004, 0), (4, 132, 16004, 0), (4, 156, 14000, 4), (4, 260, 8200, 20),
-    # both heights of a block on each side of every line between them: M = 64, 280 and 448 with 16 to 30 MiB and above (two bytes), 48, 160 and 256 with 16 to 44 MiB
     (2, 64, 70000, 16), (2, 280, 16008, 0), (2, 440, 10008, 0), (2, 456, 9608, 0), (2, 2056, 2056, 8), (2, 520, 15624, 40), (2, 3000, 2904, 0), (2, 4104, 4104, 0),
-    (4, 44, 50004, 0), (4, 52, 42004, 0), (4, 64, 40000, 8), (4, 164, 14004, 4), (4, 256, 9004, 4), (4, 260, 24000, 20), (4, 516, 4304, 0), (4, 2004, 2004, 0), (4, 3004, 2500, 12)])
+    (4, 44, 50004, 0), (4, 52, 42004, 0), (4, 64, 40000, 8), (4, 164, 14004, 4), (4, 256, 9004, 4), (4, 260, 24000, 20), (4, 516, 4304, 0), (4, 2004, 2004, 0), (4, 3004, 2500, 12),
+    # both heights of a block, and the tall ones with their loads together and one at a time, on each side of every line between them (test_transpose_dispatch.py has the
+    # rule): two bytes M = 1024, 22, 40 and 50 MiB, 272 and 320 rows from 128 MiB on; four bytes M = 188, 31, 40 and 56 MiB
+    (2, 1016, 5808, 0), (2, 1032, 5576, 0), (2, 1032, 5600, 8), (2, 1032, 10168, 0), (2, 3080, 4248, 0), (2, 3080, 4264, 24), (2, 272, 126008, 0), (2, 312, 110008, 0),
+    (2, 328, 104008, 0), (4, 184, 14004, 0), (4, 188, 14004, 0), (4, 260, 15624, 0), (4, 260, 15640, 4), (4, 1000, 5260, 0), (4, 1004, 7308, 12), (4, 1004, 7320, 0)])
 def test_transpose_into_part_lines_is_bit_exact(swz, elem_bytes, M, N, offset):
     assert 2 * elem_bytes * M * N >= 16 << 20
     dtype = torch.int16 if elem_bytes == 2 else torch.int32
@@ -710,9 +718,9 @@ def test_transpose_into_part_lines_is_bit_exact(swz, elem_bytes, M, N, offset):
 # the default order: windows of the sweep without a rest and with one, too few rows for a window, pitches that keep the skewed raster; loads one at a time and all at once,
 # with more and less than 32 MiB (two bytes) and 256 MiB moved, and (four bytes) with 36 to 63; one row of
 # four-byte tiles, a quarter, half and all of it real
-@pytest.mark.parametrize("elem_bytes,M,N", [(2, 2048, 64), (2, 2056, 200), (2, 4104, 1032), (2, 520, 5000), (2, 4160, 2056), (2, 4096, 4096), (2, 16384, 2048), (2, 64, 40000), (2, 8192, 8256),
+@pytest.mark.parametrize("elem_bytes,M,N", [(2, 2048, 64), (2, 2056, 200), (2, 4104, 1032), (2, 520, 5000), (2, 4160, 2056), (2, 4096, 4096), (2, 16384, 2048), (2, 64, 40000), (2, 8192, 8256), (2, 2112, 4096), (2, 1472, 8192),
                                             (4, 2048, 64), (4, 2116, 196), (4, 516, 2052), (4, 4100, 4100), (4, 8192, 2048), (4, 60, 30004), (4, 8256, 4160), (4, 2080, 2500), (4, 2048, 2304), (4, 32, 196604),
-                                            (4, 4, 4100), (4, 16, 8200), (4, 20, 4100), (4, 32, 1028), (4, 36, 4100)])
+                                            (4, 4, 4100), (4, 16, 8200), (4, 20, 4100), (4, 32, 1028), (4, 36, 4100), (4, 4096, 16384)])
 def test_default_order_of_a_transpose_is_bit_exact(swz, elem_bytes, M, N):
     dtype = torch.int16 if elem_bytes == 2 else torch.int32
     g = torch.Generator(device="cuda").manual_seed(M + N)
@@ -729,12 +737,19 @@ def test_default_order_of_a_transpose_is_bit_exact(swz, elem_bytes, M, N):
 
 
 # 256x256 tiles beyond whole rounds of 256 compute units: up to 64 (quarters), up to 128 (halves), more (whole); ragged edges among
-# the pieces, pieces outside C, one tile left over
-@pytest.mark.parametrize("M,N", [(4352, 4096), (4200, 4104), (65793, 248), (5120, 4608), (4610, 5000), (4100, 6200), (8200, 8200)])
-def test_partial_last_round_in_pieces_gives_the_bits_of_whole_tiles(swz, M, N):
+# the pieces, pieces outside C, one tile left over.  K of 8 and 200 go to paired tiles, from 456 on every shape is cut this way.
+PIECE_SHAPES = [(4352, 4096), (4200, 4104), (65793, 248), (5120, 4608), (4610, 5000), (4100, 6200), (8200, 8200)]
+
+
+def piece_ks(M, N):
     # quarters have rings of 5 stages of 64, 4 of them fetched ahead: from 576 on their loop makes whole turns
     quarters = (M + 255) // 256 * ((N + 255) // 256) % 256 <= 64
-    for K in (8, 200, 520, 576, 712, 1032) if quarters else (8, 200, 520, 712):
+    return (8, 200, 360, 456, 520, 576, 712, 1032) if quarters else (8, 200, 360, 456, 520, 712)
+
+
+@pytest.mark.parametrize("M,N", PIECE_SHAPES)
+def test_partial_last_round_in_pieces_gives_the_bits_of_whole_tiles(swz, M, N):
+    for K in piece_ks(M, N):
         g = torch.Generator(device="cuda").manual_seed(M + K)
         a = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
         b = torch.randn((K, N), device="cuda", generator=g).to(torch.bfloat16)
