@@ -139,6 +139,9 @@ def other_kernels(swz, torch):
         for mode in ("rr", "xcd_groupm", "xcd_groupm_skew"):
             us = time_calls(torch, lambda: swz.transpose(x, y, tile=tile, mode=swz.MODES[mode]))
             res[f"transpose_{m}x{n}_tile{tile}_{mode}"] = entry(us, m, n, copy_gbs)
+    # with tile 64 and no band height named that last mode is the order of the library's choice (swept here); a named one is the raster itself
+    us = time_calls(torch, lambda: swz.transpose(x, y, mode=swz.MODES["xcd_groupm_skew"], group_m=4))
+    res[f"transpose_{m}x{n}_tile64_xcd_groupm_skew_group_m4"] = entry(us, m, n, copy_gbs)
     del x, y
     # 32768 x 16384: 1 GiB in, 1 GiB out, beyond what the 256 MB memory-side cache can hold between launches; the smaller
     # cases are partly served from it.  Rows of up to 98304 elements are held whole, by one workgroup, in an order of the library's
@@ -154,6 +157,9 @@ def other_kernels(swz, torch):
             if mode == "xcd" or n > 98304:
                 us = time_calls(torch, lambda: swz.layernorm(x, g, b, y, eps=1e-5, chunks=chunks, mode=swz.MODES[mode]))
                 res[f"layernorm_{m}x{n}_chunks{chunks}_{mode}"] = entry(us, m, n)
+            if mode == "xcd" and n > 98304:        # the second launch above is in dispatch order, here under the mode
+                us = time_calls(torch, lambda: swz.layernorm(x, g, b, y, eps=1e-5, chunks=chunks, mode=swz.MODES[mode], group_m=4))
+                res[f"layernorm_{m}x{n}_chunks{chunks}_{mode}_group_m4"] = entry(us, m, n)
         del x, y
     return res
 

@@ -431,6 +431,20 @@ def summarize_spans(directory, kernel_filter):
     return out
 
 
+def mode_and_group(text):
+    """(mode, group_m) of MODE or MODE@G; group_m 0, the library's choice, where none is named."""
+    name, at, group = text.partition("@")
+    if name not in MODE_NAMES or (at and not (group.isdigit() and int(group) > 0)):
+        raise ValueError(f"not a mapping mode: {text}")
+    return name, int(group) if at else 0
+
+
+def mapping_args(text):
+    """The arguments of `transpose` and `rows` for MODE or MODE@G."""
+    name, group = mode_and_group(text)
+    return ["--mode", name] + (["--group-m", str(group)] if group else [])
+
+
 def _rocprof(out, tag, fmt, prof_args, prog_args, limit=180):
     """One rocprofv3 run of `python -m paper_2508_20258_amd.harness <prog_args>` into <out>/<tag> (log beside it)."""
     import shutil
@@ -462,7 +476,7 @@ def cmd_profile_transpose(args):
             _rocprof(out, tag, "csv", ["--pmc", c], ["copy", "--mib", "1024", "--launches", "3"])
         _rocprof(out, "copy_kt", "csv", ["--kernel-trace", "--stats"], ["copy", "--mib", str(max(moved >> 21, 1)), "--launches", str(args.launches + 1)])
         for tile, mode in combos:
-            prog = base + ["--tile", str(tile), "--mode", mode]
+            prog = base + ["--tile", str(tile), *mapping_args(mode)]
             t = f"t{tile}_{mode}"
             _rocprof(out, t + "_kt", "csv", ["--kernel-trace", "--stats"], prog + ["--launches", str(args.launches + 1)])
             _rocprof(out, t + "_tcc", "json", ["--pmc", "TCC_HIT", "TCC_MISS"], prog + ["--launches", "3"])
@@ -484,8 +498,10 @@ def cmd_profile_transpose(args):
              "  rocprofv3 --pmc FETCH_SIZE (then WRITE_SIZE) --output-format csv -d <out> -- the same",
              f"  and the same passes on `{H} copy` (byte-counter calibration on 1 GiB: FETCH_SIZE x {fs:.3f}, WRITE_SIZE x {ws:.3f}; kernel trace on {moved >> 20} MiB moved).",
              f"Roofline: HBM, 8 TB/s; algorithmic bytes 2*M*N*{eb} = {moved >> 20} MiB per launch.  us = kernel duration in the kernel trace, average over the last {args.launches} launches.",
+             "MODE@G names group_m=G (--mode MODE --group-m G).  xcd_groupm_skew with tile 64 and no group_m named is the order of the library's choice, the sweep of tile_sweep.h but for some",
+             "pitches (sweep_tiles and sweep_part_lines in transpose_dispatch.h); xcd_groupm_skew@4 is the skewed raster of that name.  The other rows are the rasters they name, bands of 4.",
              f"The library's plain copy kernel on the same amount of data in the same session: {copy_us:.2f} us = {copy_gbs:.0f} GB/s ({100 * copy_gbs / 8000:.1f} % of 8 TB/s).",
-             "", f"{'tile':>4s} {'mode':16s} {'us':>8s} {'GB/s':>6s} {'% of 8 TB/s':>11s} {'x copy':>7s} {'L2 hit %':>8s} {'fetch MiB':>10s} {'write MiB':>10s}"]
+             "", f"{'tile':>4s} {'mode':17s} {'us':>8s} {'GB/s':>6s} {'% of 8 TB/s':>11s} {'x copy':>7s} {'L2 hit %':>8s} {'fetch MiB':>10s} {'write MiB':>10s}"]
     for tile, mode in combos:
         t = f"{out}/t{tile}_{mode}"
         us = _one(t + "_kt", "transpose", args.launches)["warm_avg_ns"] / 1e3
@@ -494,7 +510,7 @@ def cmd_profile_transpose(args):
         hit = 100 * tj["TCC_HIT"]["total"] / (tj["TCC_HIT"]["total"] + tj["TCC_MISS"]["total"])
         f = _one(t + "_fetch", "transpose")["counters"]["FETCH_SIZE"] * fs / 1024
         w = _one(t + "_write", "transpose")["counters"]["WRITE_SIZE"] * ws / 1024
-        lines.append(f"{tile:4d} {mode:16s} {us:8.2f} {gbs:6.0f} {100 * gbs / 8000:11.1f} {gbs / copy_gbs:7.2f} {hit:8.2f} {f:10.1f} {w:10.1f}")
+        lines.append(f"{tile:4d} {mode:17s} {us:8.2f} {gbs:6.0f} {100 * gbs / 8000:11.1f} {gbs / copy_gbs:7.2f} {hit:8.2f} {f:10.1f} {w:10.1f}")
     text = "\n".join(lines) + "\n"
     print(text, flush=True)
     with open(os.path.join(out, f"transpose_{m}x{n}_{eb}B.txt"), "w") as f:
@@ -502,9 +518,11 @@ def cmd_profile_transpose(args):
 
 
 ROW_CASES = [  # (M, N, chunks, mode).  Rows of up to 98304 elements are held by one workgroup whatever the chunks and, but for large
-    # softmax matrices of 16128 to 16384 columns, taken in dispatch order whatever the mode; longer ones take two launches under the caller's mode
+    # softmax matrices of 16128 to 16384 columns, taken in dispatch order whatever the mode; longer ones take two launches under the caller's mode,
+    # the second of a layer normalisation in dispatch order where nothing but the mode is named (row_dispatch.h); xcd@4 names group_m=4
     (65536, 1024, 1, "rr"), (8192, 8192, 1, "rr"), (32768, 16384, 1, "rr"), (32768, 16384, 1, "xcd"), (1024, 65536, 8, "rr"),
-    (300, 100000, 1, "rr"), (300, 100000, 1, "xcd"), (64, 1048576, 4, "rr"), (64, 1048576, 4, "xcd")]
+    (300, 100000, 1, "rr"), (300, 100000, 1, "xcd"), (64, 1048576, 4, "rr"), (64, 1048576, 4, "xcd"),
+    (64, 1048576, 4, "xcd@4")]
 
 
 def row_kernels(summary):
@@ -522,7 +540,7 @@ def cmd_profile_rows(args):
             _rocprof(out, tag, "csv", ["--pmc", c], ["copy", "--mib", "1024", "--launches", "3"])
         _rocprof(out, "copy_kt", "csv", ["--kernel-trace", "--stats"], ["copy", "--mib", "1024", "--launches", str(args.launches + 1)])
         for op, m, n, c, mode in cases:
-            prog = ["rows", "--op", op, "--m", str(m), "--n", str(n), "--chunks", str(c), "--mode", mode]
+            prog = ["rows", "--op", op, "--m", str(m), "--n", str(n), "--chunks", str(c), *mapping_args(mode)]
             t = f"{op}_{m}x{n}_c{c}_{mode}"
             _rocprof(out, t + "_kt", "csv", ["--kernel-trace", "--stats"], prog + ["--launches", str(args.launches + 1)])
             _rocprof(out, t + "_tcc", "json", ["--pmc", "TCC_HIT", "TCC_MISS"], prog + ["--launches", "3"])
@@ -541,6 +559,7 @@ def cmd_profile_rows(args):
              f"  rocprofv3 --pmc TCC_HIT TCC_MISS --output-format json -d <out> -- {H} rows --op OP --m M --n N --chunks CHUNKS --mode MODE --launches 3",
              "  rocprofv3 --pmc FETCH_SIZE (then WRITE_SIZE) --output-format csv -d <out> -- the same",
              f"  and the same passes on `{H} copy --mib 1024` (byte-counter calibration: FETCH_SIZE x {fs:.3f}, WRITE_SIZE x {ws:.3f}).",
+             "MODE@G names group_m=G (--mode MODE --group-m G).  layernorm 64 x 1048576: without, the second launch is in dispatch order whatever the mode; with, both launches are under the mode.",
              "Roofline: HBM, 8 TB/s; algorithmic bytes 4*M*N per call (read x once, write y once).",
              "Calls repeat over the same data; up to 256 MiB of it is partly held by the 256 MB memory-side cache between calls, the 2 GiB of 32768 x 16384 are not.",
              f"The library's plain copy kernel, 1 GiB in + 1 GiB out, same session: {copy_us:.2f} us = {copy_gbs:.0f} GB/s ({100 * copy_gbs / 8000:.1f} % of 8 TB/s).",
@@ -699,7 +718,7 @@ def cmd_transpose(args):
     torch.cuda.synchronize()
     us = e0.elapsed_time(e1) * 1e3 / max(args.launches - 1, 1)
     gbs = 2.0 * args.elem_bytes * args.m * args.n / (us * 1e-6) / 1e9
-    print(f"ran {args.launches} transposes {args.m}x{args.n} ({args.elem_bytes}-byte elements) tile {args.tile} mode {args.mode} group_m {args.group_m or 4}: {us:.2f} us per launch, "
+    print(f"ran {args.launches} transposes {args.m}x{args.n} ({args.elem_bytes}-byte elements) tile {args.tile} mode {args.mode} group_m {args.group_m or 'left to the library'}: {us:.2f} us per launch, "
           f"{gbs:.0f} GB/s of 2*M*N*elem_bytes bytes ({100 * gbs / 8000:.1f} % of 8 TB/s)", flush=True)
 
 
@@ -713,12 +732,13 @@ def cmd_rows(args):
     g = torch.rand(args.n, device="cuda").to(torch.bfloat16)
     b = torch.rand(args.n, device="cuda").to(torch.bfloat16)
     mode = swz.MODES[args.mode]
+    params = dict(group_m=args.group_m) if args.group_m else {}
 
     def launch():
         if args.op == "softmax":
-            swz.softmax(x, out, chunks=args.chunks, mode=mode)
+            swz.softmax(x, out, chunks=args.chunks, mode=mode, **params)
         else:
-            swz.layernorm(x, g, b, out, eps=1e-5, chunks=args.chunks, mode=mode)
+            swz.layernorm(x, g, b, out, eps=1e-5, chunks=args.chunks, mode=mode, **params)
 
     launch()
     torch.cuda.synchronize()
@@ -909,7 +929,8 @@ def main(argv=None):
     pt.add_argument("--elem-bytes", type=int, default=2, choices=[2, 4])
     pt.add_argument("--out", required=True)
     pt.add_argument("--tile", type=int, nargs="+", default=[64, 128, 32])
-    pt.add_argument("--mode", nargs="+", default=["rr", "xcd", "xcd_groupm", "rr_skew", "xcd_skew", "xcd_groupm_skew"], choices=MODE_NAMES)
+    pt.add_argument("--mode", nargs="+", default=["rr", "xcd", "xcd_groupm", "rr_skew", "xcd_skew", "xcd_groupm_skew", "xcd_groupm_skew@4"],
+                    help="MODE or MODE@G, which names group_m=G")
     pt.add_argument("--launches", type=int, default=20)
     pt.add_argument("--table-only", action="store_true")
     pt.set_defaults(fn=cmd_profile_transpose)
@@ -940,6 +961,7 @@ def main(argv=None):
     w.add_argument("--chunks", type=int, default=8)
     w.add_argument("--mode", default="xcd", choices=MODE_NAMES)
     w.add_argument("--launches", type=int, default=10)
+    w.add_argument("--group-m", type=int, default=0)
     w.set_defaults(fn=cmd_rows)
     pk = sub.add_parser("peak")
     pk.add_argument("--iters", type=int, default=20000)

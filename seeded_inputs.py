@@ -91,10 +91,13 @@ CONFIGS = {
     "cfg5_ragged": dict(M=10000, N=7000, K=4096, seed=4, a=("uniform", 1.0), b=("uniform", 1.0), tile=(256, 256, 64)),
 }
 
-# Profiled beside them: products that the library cuts into sub-tiles.
+# Profiled beside them: products that the library computes in sub-tiles (of 32x64, 128x128, 96x128 and 192x128) and in paired tiles of 128x256.
 SUBTILE_CONFIGS = {
     "few_rows_32": dict(M=32, N=8192, K=8192, seed=5, a=("normal", 1.0), b=("normal", 8192 ** -0.5), tile=(128, 128, 64)),
     "square_2048": dict(M=2048, N=2048, K=2048, seed=6, a=("normal", 1.0), b=("normal", 2048 ** -0.5), tile=(128, 128, 64)),
+    "few_blocks_542": dict(M=542, N=4128, K=14888, seed=7, a=("normal", 1.0), b=("normal", 14888 ** -0.5), tile=(128, 128, 64)),
+    "narrow_11034": dict(M=11034, N=368, K=2048, seed=8, a=("normal", 1.0), b=("normal", 2048 ** -0.5), tile=(128, 256, 64)),
+    "short_k_8192": dict(M=8192, N=8192, K=128, seed=9, a=("normal", 1.0), b=("normal", 128 ** -0.5), tile=(256, 256, 64)),
 }
 ALL_CONFIGS = {**CONFIGS, **SUBTILE_CONFIGS}
 

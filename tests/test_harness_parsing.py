@@ -2,6 +2,8 @@
 import json
 import os
 
+import pytest
+
 from paper_2508_20258_amd import harness
 
 
@@ -243,3 +245,11 @@ def test_launched_kernel_and_its_grid_come_from_the_trace(tmp_path):
     (d / "1_kernel_trace.csv").write_text('"Kernel_Name","Start_Timestamp","End_Timestamp","Workgroup_Size_X","Grid_Size_X"\n'
                                           '"gemm<1>",2000,2500,256,65536\n"gemm<1>",1000,1500,256,512\n"copy",3000,3500,256,1024\n')
     assert harness.launched_workgroups(str(d), "gemm") == 256
+
+
+def test_mapping_with_a_named_band_height():
+    assert harness.mode_and_group("xcd_groupm_skew@4") == ("xcd_groupm_skew", 4) and harness.mode_and_group("rr") == ("rr", 0)
+    assert harness.mapping_args("xcd@4") == ["--mode", "xcd", "--group-m", "4"] and harness.mapping_args("xcd") == ["--mode", "xcd"]
+    for bad in ("xcd@", "xcd@0", "xcd@x", "@4", "grouped"):
+        with pytest.raises(ValueError):
+            harness.mode_and_group(bad)
