@@ -48,7 +48,8 @@ typedef struct {
   int32_t bm;      /* tile rows:    128 or 256 */
   int32_t bn;      /* tile columns: 128 or 256 (all four combinations; one of bm, bn given: the other takes its value) */
   int32_t bk;      /* K panel per tile step: 64 (the kernel streams it as two 32-wide halves) */
-  int32_t group_m; /* tile rows per band of the grouped raster (default 4) */
+  int32_t group_m; /* tile rows per band of the grouped raster (default 4; swz_transpose and swz_layernorm read the 0 of one that is not named as leave to
+                    * choose an order of their own in some cases, said there) */
   int32_t num_xcd; /* XCD count assumed by the renumbering (default: detected; 8 on an unpartitioned MI355X) */
   int32_t persistent; /* 0: one workgroup per tile (default); 1: persistent grid, see swz_pid_map_persistent */
   int32_t num_wg;  /* persistent grid size (default: one workgroup per compute unit, at most one per tile) */
@@ -128,8 +129,9 @@ int swz_pid_map_persistent_device(int grid_m, int grid_n, int num_xcd, int group
  *   Defaults: num_xcd detected, group_m = 4, tile 256x256x64; when the 256x256 tile grid would have at
  *   most half as many tiles as the device has compute units, 128x256x64, and at most a quarter, 128x128x64
  *   (the chip is then better filled by more and smaller tiles; the result bits do not depend on the tile shape).
- *   Small and narrow products go further: where the library chose the tile it may compute C in sub-tiles of 32x32 to
- *   128x256, one workgroup each, and then applies `mode`, num_xcd and the same band height to the grid of sub-tiles.  The
+ *   Where the library chose the tile it may go further and compute C in other blocks, one workgroup each: small and narrow products, and those that
+ *   leave a round of larger tiles half empty, in sub-tiles of 32x32 to 128x256 and 192x128 (96 rows among them), large ones of a short K (up to 352, in places
+ *   448) in blocks of 128x256, two to a compute unit.  It then applies `mode`, num_xcd and the same band height to the grid of those blocks.  The
  *   left-over tiles of a large grid's last, partial round may be computed by two or four workgroups each, on the XCD the
  *   map gives the tile unless fewer tiles than XCDs are left.  The bits are those of whole tiles.
  *   For at most 192 rows and K >= 2048 the workgroups of compute units that have no sub-tile may read A and B ahead of the others, into
@@ -176,10 +178,12 @@ int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_par
  * swz_pid_map does for that grid (`mode`, params->group_m, params->num_xcd; other fields ignored).
  *   in, out : caller-owned DEVICE pointers, 16-byte aligned, must not overlap.
  *   elem_bytes : 2 (M and N multiples of 8) or 4 (M and N multiples of 4, tile 64 only).
- *   tile    : 64 (whole 128-byte lines; the fastest, with mode SWZ_MODE_XCD_GROUPM + SWZ_MODE_SKEW), 128 (row segments of 256 bytes) or 32 (half lines, shared
+ *   tile    : 64 (whole 128-byte lines; the fastest, with mode SWZ_MODE_XCD_GROUPM + SWZ_MODE_SKEW and no group_m; SWZ_MODE_XCD_GROUPM is faster for elem_bytes 2
+ *             in a cache where rows of `out` start inside a line, and level there out of HBM), 128 (row segments of 256 bytes) or 32 (half lines, shared
  *             between neighbouring tiles: the case where the mapping decides the L2 hit rate).
  *   With tile 64, mode SWZ_MODE_XCD_GROUPM + SWZ_MODE_SKEW (6) and group_m left to the library (0) the order is the library's choice: the skewed raster
- *   that the mode names where the pitches of `in` and `out` are both multiples of 16 KiB and one of them of 64 KiB, else a sweep: all XCDs move
+ *   that the mode names, with group_m 4, where the pitches of `in` and `out` are both multiples of 16 KiB and one of them of 64 KiB, and for elem_bytes 2 where the
+ *   pitch of `in` is a multiple of 8 KiB and 24 MiB or more but less than 68 are moved, else a sweep: all XCDs move
  *   along the columns of a window of 4 * num_xcd tile rows together, every XCD in four neighbouring rows of its own (a bijection like the others; fewer rows in
  *   a low grid).  A group_m that is named always gets the raster that swz_pid_map describes.
  *   Once input plus output exceed the 256 MB memory-side cache the stores of tiles 64 and 128 are

@@ -149,12 +149,16 @@ inline bool feed_launch(int64_t M, int64_t N, int64_t K, const swz_params& r, in
 }
 
 // Whether tiles of 128x256, two to a compute unit (gemm_pair_kernel.h), compute it instead of 256x256 ones and what choose_subtile puts in their place.  Time of the
-// pair over that without, 110 products of K from 64 to 2048, log-uniform:
-//   More than half a round of 256x256 tiles: K up to 128 0.73 to 0.94, up to 352 0.80 to 0.98 (3976 x 2744 x 336 16.1 us, 14.9; 13930 x 9784 x 176 113, 105), then level and
-//   worse, as the tiles move half as many bytes again into LDS: 384 1.06, 504 to 576 1.00 to 1.13, 1024 1.05 to 1.12, 2048 1.20.
+// pair over that without, 640 products of K from 64 to 2048, log-uniform; where there are two figures, operands and C out of HBM, then out of the memory-side cache:
+//   More than half a round of 256x256 tiles: K up to 160 0.70 to 0.97 and 0.66 to 0.97, up to 352 where rows of C end on 64 bytes 0.71 to 1.00 and 0.72 to 0.98 (3976 x 2744 x 336 16.1 us,
+//   14.9); then level and worse, as the tiles move half as many bytes again into LDS: 384 1.06, 504 to 576 1.00 to 1.13, 1024 1.05 to 1.12, 2048 1.20.
+//   K from 168 to 352, rows of C that end inside 64 bytes: 0.82 to 1.17, on average 0.96, and 0.78 to 1.13, on average 0.90.  Out of HBM wide C (5 M <= 2 N) loses where 256x256 tiles fill
+//   their rounds: 1117 x 12176 x 296 18.9 us, 22.2 (out of the cache 14.9, 13.8), 2660 x 14000 x 192 33.4, 36.9 (30.1, 25.2), 3215 x 15064 x 240 47.9, 51.8 (44.3, 42.4); of 53 such
+//   products 1.01 on average there and 0.90 out of the cache (the worst of both 4327 x 14440 x 248, 1.02 and 1.13), so they stay.
 //   One and a quarter to one and a half rounds, which the finer tiles fill better: K = 400 0.87 to 0.97, 448 0.94 to 1.00, 512 0.94 to 1.02, 640 0.99 to 1.09 (up to one and
-//   a quarter, whose last tiles go in quarters: K = 400 0.97 to 1.01, 512 1.03 to 1.08).
-//   Renumbered without bands, where B comes from the memory-side cache again and again: K up to 304 0.73 to 1.02, 8192 x 8192 x 344 1.03.
+//   a quarter, whose last tiles go in quarters: K = 400 0.97 to 1.01, 512 1.03 to 1.08); 1620 x 11600 x 432 1.10 and 0.94.
+//   Renumbered without bands, where B comes from the memory-side cache again and again: K up to 304 0.71 to 1.07, on average 0.92 (4789 x 16256 x 192 61 us, 65), 8192 x 8192 x 344 1.03;
+//   round robin 0.63 to 1.12, on average 0.89 (9099 x 15104 x 216 121 us, 136).
 //   Half a round of tiles or less, where smaller sub-tiles are at work: 0.98 to 2.4.
 //   Fewer columns than half a tile: 100000 x 64 x 64 12.9 us, 8.8, x 304 18.3, 22.7; 65537 x 136 x 304 21.6, 19.2; few rows: 64 x 100000 x 304 16.3, 14.4.
 inline bool pair_wins(int64_t N, int64_t K, const swz_params& r, int64_t tiles, int mode, int cus) {

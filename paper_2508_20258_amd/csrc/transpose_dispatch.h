@@ -64,16 +64,16 @@ inline bool sweep_part_lines(int64_t N, int elem_bytes) { return elem_bytes == 4
 
 // Blocks of 256 (two bytes) or 128 rows in 512 threads for a transpose into part lines (tall), rather than 64 rows in 256 threads, and whether a thread's loads are on their way one at a time
 // (paced) or together.  us, tall / 64 rows, operands out of HBM and, where it says otherwise, out of the memory-side cache (three sets of buffers in turn):
-//   Few rows, one block either way, most of a tall one empty: two bytes 56 rows 8.3 / 6.8 (17 MiB moved), 72 rows 7.2 / 7.7, 136 rows 51 / 54 (200 MiB); four bytes 44 rows 0.89 to 1.14
+//   Few rows, one block either way, most of a tall one empty: two bytes 56 rows 8.4 / 6.8 (17 MiB moved), 72 rows 7.5 / 7.7, 136 rows 51 / 54 (200 MiB); four bytes 44 rows 0.89 to 1.14
 //   of the time, 52 rows 9.9 / 10.6 (47 MiB).
-//   Just above one block, the second nearly empty: two bytes 264 rows 8.4 / 7.1, 280 rows 7.2 / 7.4 and 4.9 / 6.1 out of the cache, but from 128 MiB on 59.7 / 54.3 (304 x 172456); four
-//   bytes 132 rows 7.5 / 6.3, 164 rows 8.5 / 7.6, 180 rows 8.6 / 7.9, 196 rows 6.6 / 8.2.
-//   Few blocks for the compute units, two bytes above 1024 rows, below 22 MiB: 1032 x 4312 7.6 / 7.3 and 5.8 / 5.4, 8200 x 536 7.4 / 7.1 and 5.5 / 4.9; up to 1024 rows 520 x 8568 7.4 / 7.4
+//   Just above one block, the second nearly empty: two bytes 264 rows 8.4 / 7.1, 280 rows 7.2 / 7.4 and 5.2 / 6.1 out of the cache, but from 128 MiB on 280 x 187240 59.7 / 54.3, 304 x 172456
+//   54.9 / 51.9; four bytes 132 rows 7.5 / 6.3, 164 x 16780 8.4 / 7.3, 180 x 16748 8.6 / 7.8, 196 x 14040 6.5 / 8.0.
+//   Few blocks for the compute units, two bytes above 1024 rows, below 22 MiB: 1032 x 4312 7.6 / 7.4 and 5.8 / 5.5, 8200 x 536 7.4 / 7.1 and 5.5 / 4.9; up to 1024 rows 520 x 8568 7.4 / 7.4
 //   and 4.9 / 5.8, 776 x 8104 8.1 / 9.1 and 5.7 / 7.1; four bytes 516 x 4316 6.6 / 6.5 and 4.4 / 5.5, 1028 x 2164 6.6 / 6.5 and 4.7 / 4.9.
-//   Paced / together, tall: two bytes 4104 x 1656 8.1 / 9.2 and 7.0 / 6.6, 2056 x 4840 10.6 / 11.7 and 9.5 / 9.8, 8200 x 1400 10.5 / 12.4 and 9.4 / 9.6, but 1032 x 13208 15.4 / 14.5
-//   and 12.6 / 10.9; four bytes 1028 x 4204 8.7 / 10.3 and 7.8 / 8.4, 2052 x 2424 9.6 / 11.1 and 8.6 / 8.5, 516 x 8380 8.6 / 10.2 and 7.5 / 7.3, but 516 x 13208 15.0 / 14.4 and
-//   13.9 / 11.6.  Outside the sizes below: together, out of the cache up to 21 % ahead of 64 rows paced, out of
-//   HBM level on average, but 8200 x 664 7.4 / 6.5, 776 x 8776 9.7 / 8.0, 392 x 22064 9.9 / 8.6.
+//   Tall and paced / together (64 rows for two bytes below 40 MiB, else tall): two bytes 4104 x 1656 7.7 / 9.3 and 7.0 / 6.6, 2056 x 4840 10.7 / 11.8 and 9.1 / 9.3, 8200 x 1400
+//   10.7 / 12.6 and 9.6 / 9.7, but 1032 x 13208 15.8 / 15.0 and 14.0 / 12.1; four bytes 1028 x 4204 8.7 / 10.1 and 7.7 / 8.1, 2052 x 2424 8.9 / 10.5 and 8.0 / 8.0, 516 x 8380 8.6 / 10.1 and
+//   7.4 / 7.3, but 516 x 13208 14.3 / 13.8 and 11.9 / 10.1.  Outside the sizes below loads together are up to 20 % ahead of one at a time out of the cache and level on average out of HBM, but
+//   two bytes 8200 x 664 8.2 / 7.2, 776 x 8776 10.2 / 8.6, 392 x 22064 10.5 / 9.1 there.
 // A launch has to hold its threads too: with one row of blocks, or two instead of three, half and three quarters as many columns fit.
 enum LineBlocks : int { kLines = 0, kLinesTall = 1, kLinesTallPaced = 2 };
 inline LineBlocks line_blocks(int64_t M, int64_t N, int elem_bytes) {

@@ -18,11 +18,12 @@
 // all tiles of one tile row write into the same TILE*2-byte wide column stripe of `out`, and when
 // the row pitch of `out` is a power of two that stripe lives in a few channels only.  The skewed
 // raster (pid_decode.h) makes tiles that run at the same time differ in their tile row as well as
-// in their tile column; measured at 16384 x 16384 it takes the 64-wide tile from 3.9 to 5.2 TB/s
-// (the 128-wide one from 4.3 to 4.7).  Where no such pitch asks for it, the tiles are swept (tile_sweep.h): us under the skewed raster -> swept, loads and occupancy as
-// they are now: two bytes 8192 x 8192 55 -> 47.5, 10048 x 7040 60 -> 52.7, 3712 x 17656 64 -> 58, 16384 x 8192 93 -> 87, 4096 x 32768 98 -> 87; four bytes 5824 x 5824
+// in their tile column; measured at 16384 x 16384, with a band height named, it takes the 64-wide tile from 4.4 to 5.9 TB/s
+// (the 128-wide one from 4.8 to 5.8).  Under the default order most sizes are swept instead (tile_sweep.h; sweep_tiles has those that are not): us under the skewed raster -> swept, loads and
+// occupancy as they are now: two bytes 16384 x 16384 183 -> 177 (6.1 TB/s), 8192 x 8192 55 -> 47.5, 10048 x 7040 60 -> 52.7, 3712 x 17656 64 -> 58, 16384 x 8192 93 -> 87, 4096 x 32768 98 -> 87; four bytes 5824 x 5824
 // 54 -> 48.8, 5800 x 5804 55 -> 51.3.  What is left to a copy (5824 x 5824 x 4 43 us) is the memory's: workgroups that copy the same blocks to the same places without
 // transposing them take 48 to 54 us by the order of the blocks, 47 to 52 with both sides of a block in one piece of 16 KiB.
+// How many loads are on their way at a time, and in how many workgroups, follows from size, pitches and order (load_pace, paced_tiles32 and line_blocks in transpose_dispatch.h).
 //
 // LDS layout: row r at byte r*(TILE*2), 16-byte chunk c in slot c ^ key(r) (same idea as the
 // GEMM's B panel; TILE*2/16 slots per row).
@@ -48,7 +49,8 @@ __device__ __forceinline__ void tr_block(int grid_m, int grid_n, int num_xcd, in
 
 // Where the 16 bytes at row m, column n of `in` are, m and n brought inside it: no branch around a load.  With one, the compiler waits for every load
 // before it issues the next, and a block's two to five loads a thread took as many trips to memory (us one at a time -> together: 1024 x 1024 x 4 B 4.0 -> 2.7,
-// 2048 x 2048 x 2 B 5.4 -> 4.6, 300 x 600 x 4 B 2.6 -> 2.2).
+// 2048 x 2048 x 2 B 5.4 -> 4.6, 300 x 600 x 4 B 2.6 -> 2.2).  Lanes beyond the edge read the edge again, out of a cache: with 8 to 24 rows of two bytes in blocks of 64 rows 2 % more time
+// than a branch takes (8 x 1441800 37.4, 38.2 us); four-byte tiles of up to 32 rows leave those loads out (LOADS below).
 template <class T>
 __device__ __forceinline__ const t_u32x4* tr_source(const T* in, int m, int n, int M, int N) {
   m = m < 0 ? 0 : m < M ? m : M - 1;
@@ -230,8 +232,8 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
 // gets columns [BM pm - s(n), BM pm - s(n) + BM), the last block of the row everything up to M (one line more at
 // most).  Its block of `in` grows by the E - 1 rows above it (E elements fill a line), which the block above reads too.  BM is 64 with 256
 // threads: 31 rows more of four bytes, 63 of two, half and all of the input once more; or 128 of four bytes and 256 of two with 512 threads, a
-// quarter more.  Part of that the L2 serves.  tall_line_blocks (swz.hip) says which: the tall blocks lose where M leaves most of one empty and where
-// there are too few of them.  s(n) differs from row
+// quarter more.  Part of that the L2 serves.  line_blocks (transpose_dispatch.h) says which: the tall blocks lose where M leaves most of one empty and where
+// there are too few of them.  PACED: a thread's loads one at a time.  s(n) differs from row
 // to row, so a lane gathers its 16 bytes element by element, four rows or eight rows of the tile at a column: the
 // transposing LDS read takes the same rows for 4 columns.
 // A wave instruction stores 8 rows x 8 chunks = 8 whole lines: lane l takes row l / 8, chunk l % 8.
@@ -242,7 +244,8 @@ __global__ __launch_bounds__(256) void transpose32_kernel(const uint32_t* __rest
 //     two bytes   10000 x 7000  75 -> 60 (4670)    8200 x 8208  67 -> 57 (4720)    30000 x 1544   49 -> 41 (4560)    3000 x 3000  10.7 -> 9.0
 //     four bytes   5800 x 5804  60 -> 56 (4810)    200 x 20000  9.5 -> 8.6         15764 x 8092  214 -> 204 (5000)
 // and with a block's loads on their way together, four-byte blocks swept: 10000 x 7000 60.5 -> 58, 5800 x 5804 56 -> 52 (5170), 15764 x 8092 209 -> 200, 5288 x 3128 x 2 B 15.1 -> 13.3.
-// Two-byte blocks are not swept: 10000 x 7000 57.5 -> 58.1, 8200 x 8200 up to 9 % slower, 5288 x 3128 13.3 -> 12.3.
+// Two-byte blocks are not swept: 10000 x 7000 57.5 -> 58.1, 8200 x 8200 up to 9 % slower, 5288 x 3128 13.3 -> 12.3; they keep the skewed raster, which is level with the plain one out of HBM
+// and slower in a cache (one set of buffers, 10000 x 7000 47.5 against 43.7 us, 173 MiB fetched against 143).
 // (tiles on line-blind boundaries 102, 110 and 82, 363 us; 60 us where both pitches are whole lines, 10048 x 7040.)  256 rows of four bytes leave a
 // compute unit two workgroups: 58 us at 5800 x 5804; with 256 threads 77.  128 columns: 60 us there, 61 at 10000 x 7000.
 
