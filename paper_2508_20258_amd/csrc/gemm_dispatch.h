@@ -34,7 +34,8 @@ constexpr int64_t kRoundNs = 2500, kWholeRoundNs = 4000;
 // pair; a partial last round of 256x256 tiles costs what its pieces make of it, see gemm_launch).  Ties go to the later
 // shape of the table.  A sub-tile has to be 5 % better than the tile, the spread of the estimate near a tie.
 // 96 and 192 rows fill a round that the powers of two leave half empty or just outgrow: 9516x544x1056 20.2 -> 16.3 us (128x256 -> 192x128), 542x4128x14888 147 -> 123
-// (128x128 -> 96x128), 11034x368x2048 29.3 -> 22.9; over the 120 products drawn for which the choice changed 0.93 of the time (see rows96_pay for those where it was more).  Not kept:
+// (128x128 -> 96x128), 11034x368x2048 29.3 -> 22.9; over the 120 products drawn for which the choice changed 0.93 of the time (see rows96_pay for those where it was more), over 150 more with K from 704 0.92 with operands out of HBM
+// and 0.91 out of the memory-side cache, where 11 and 6 of them are more than 3 % slower (7554x560x3248 45.0, 52.1 and 39.4, 37.1; 9505x592x3944 without bands 60, 69 and 55, 61).  Not kept:
 // 96x64 and 192x64, 0.95 to 1.32 of the time, as stripes of B half as wide come out of HBM at half the pace (13429x136x4744 55 -> 72); 160x128, no faster than 192x128.
 // Fitted on 60 products.  On 140 others, every shape timed (log-uniform sizes, N and K from 64 to 16384): 60 with M from 1 to
 // 16384 are on average as fast as with their best shape (worst 3.6 % behind), 80 with M from 128 to 16384 0.5 % behind (worst 13 %:
