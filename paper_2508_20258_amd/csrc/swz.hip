@@ -275,7 +275,7 @@ int launch_transpose32(const void* in, void* out, int M, int N, int gm, int gn, 
   const dim3 grid((unsigned)(gm * gn)), block(256);
   auto* i = static_cast<const uint32_t*>(in);
   auto* o = static_cast<uint32_t*>(out);
-  const size_t lds = STREAM ? 32768 : PACED || LOADS < 4 ? 0 : 12288;       // on top of the tile's 16 KB: three, eight or five workgroups to a compute unit
+  const size_t lds = PACED || LOADS < 4 ? 0 : STREAM ? 32768 : 12288;       // on top of the tile's 16 KB: eight, three or five workgroups to a compute unit
   const int skew = swz_mode_skewed(mode) ? 1 : 0;
   switch (mode & 3) {
     case SWZ_MODE_RR: return launch(swz::transpose32_kernel<kModeRR, STREAM, PACED, LOADS>, grid, block, lds, stream, i, o, M, N, gm, gn, num_xcd, group_m, skew, sweep);
@@ -585,11 +585,12 @@ int swz_transpose(const void* in, void* out, int64_t M, int64_t N, int elem_byte
   const int sweep = ours && swz::sweep_tiles(M, N, elem_bytes) ? swz_sweep_rows((int)gm, num_xcd, elem_bytes) : 0;
   if (elem_bytes == 4) {
     const int m = (int)M, n = (int)N, tm = (int)gm, tn = (int)gn;
-    if (M * N * 8 > kMemorySideCacheBytes) return launch_transpose32<true, false, 4>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
-    // one row of tiles, a quarter or half of it real: no loads for the rest, and eight workgroups to a compute unit, as each has little on its way (us, all loads and five workgroups -> these:
-    // 4 x 521008 13.6 -> 10.0, 16 x 98304 4.6 -> 4.1, 24 x 86832 5.5 -> 4.7)
-    if (M <= 16) return launch_transpose32<false, false, 1>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
-    if (M <= 32) return launch_transpose32<false, false, 2>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
+    // one row of tiles, a quarter or half of it real: no loads for the rest, and eight workgroups to a compute unit, as each has little on its way (us, all loads and five workgroups, three
+    // above 256 MiB -> these: 4 x 521008 13.6 -> 10.0, 16 x 98304 4.6 -> 4.1, 24 x 86832 5.5 -> 4.7, 32 x 1228800 61.2 -> 57.8, 32 x 3686400 176 -> 168)
+    const bool beyond = M * N * 8 > kMemorySideCacheBytes;
+    if (M <= 16 && !beyond) return launch_transpose32<false, false, 1>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
+    if (M <= 32) return (beyond ? launch_transpose32<true, false, 2> : launch_transpose32<false, false, 2>)(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
+    if (beyond) return launch_transpose32<true, false, 4>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
     if (swz::paced_tiles32(M, N)) return launch_transpose32<false, true, 4>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
     return launch_transpose32<false, false, 4>(in, out, m, n, tm, tn, num_xcd, group_m, mode, sweep, stream);
   }

@@ -717,10 +717,10 @@ def test_transpose_into_part_lines_is_bit_exact(swz, elem_bytes, M, N, offset):
 
 # the default order: windows of the sweep without a rest and with one, too few rows for a window, pitches that keep the skewed raster; loads one at a time and all at once,
 # with more and less than 32 MiB (two bytes) and 256 MiB moved, and (four bytes) with 36 to 63; one row of
-# four-byte tiles, a quarter, half and all of it real
+# four-byte tiles, a quarter, half and all of it real, and the first two also just above 256 MiB
 @pytest.mark.parametrize("elem_bytes,M,N", [(2, 2048, 64), (2, 2056, 200), (2, 4104, 1032), (2, 520, 5000), (2, 4160, 2056), (2, 4096, 4096), (2, 16384, 2048), (2, 64, 40000), (2, 8192, 8256), (2, 2112, 4096), (2, 1472, 8192),
                                             (4, 2048, 64), (4, 2116, 196), (4, 516, 2052), (4, 4100, 4100), (4, 8192, 2048), (4, 60, 30004), (4, 8256, 4160), (4, 2080, 2500), (4, 2048, 2304), (4, 32, 196604),
-                                            (4, 4, 4100), (4, 16, 8200), (4, 20, 4100), (4, 32, 1028), (4, 36, 4100), (4, 4096, 16384)])
+                                            (4, 4, 4100), (4, 16, 8200), (4, 20, 4100), (4, 32, 1028), (4, 36, 4100), (4, 4096, 16384), (4, 32, 1048580), (4, 12, 2796204)])
 def test_default_order_of_a_transpose_is_bit_exact(swz, elem_bytes, M, N):
     dtype = torch.int16 if elem_bytes == 2 else torch.int32
     g = torch.Generator(device="cuda").manual_seed(M + N)
