@@ -183,7 +183,7 @@ int swz_gemm_launch_map(int64_t M, int64_t N, int64_t K, int mode, const swz_par
  *             between neighbouring tiles: the case where the mapping decides the L2 hit rate).
  *   With tile 64, mode SWZ_MODE_XCD_GROUPM + SWZ_MODE_SKEW (6) and group_m left to the library (0) the order is the library's choice: the skewed raster
  *   that the mode names, with group_m 4, where the pitches of `in` and `out` are both multiples of 16 KiB and one of them of 64 KiB, and for elem_bytes 2 where the
- *   pitch of `in` is a multiple of 8 KiB and 24 MiB or more but less than 68 are moved, else a sweep: all XCDs move
+ *   pitch of `in` is 8 KiB or a power of two of them and 24 MiB or more but less than 68 are moved, else a sweep: all XCDs move
  *   along the columns of a window of 4 * num_xcd tile rows together, every XCD in four neighbouring rows of its own (a bijection like the others; fewer rows in
  *   a low grid).  A group_m that is named always gets the raster that swz_pid_map describes.
  *   Once input plus output exceed the 256 MB memory-side cache the stores of tiles 64 and 128 are

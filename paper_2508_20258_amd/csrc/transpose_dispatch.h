@@ -16,14 +16,18 @@ constexpr int64_t kLaunchThreads = ((int64_t)1 << 32) - 1;
 constexpr int lines_rows(int elem_bytes, bool tall) { return !tall ? 64 : elem_bytes == 2 ? 256 : 128; }
 constexpr int lines_threads(int rows) { return rows == 64 ? 256 : 512; }
 
+// Rows of n two-byte elements that are 8 KiB, or a power of two of them
+inline bool power_of_two_pitch(int64_t n) { return n >= 4096 && (n & (n - 1)) == 0; }
+
 // How many bytes the workgroups of a two-byte transpose have on their way at a time: both loads of a thread or one (paced), and LDS on top of the tile's 8 KB, which
 // holds five workgroups to a compute unit instead of eight.  us under the default mode, paced / both / both and five.  Up to 32 MiB latency counts: both, eight (2176 x 2968 7.7 / 7.5;
 // 3200 x 1440 6.0 / 5.2), but round robin from 20 MiB on paced (2176 x 2968 8.6 / 9.1).  Above, the HBM serves more
 // bytes a second the fewer are asked for, 32 to 40 KB a compute unit: 3712 x 17656 57.6 / 61.9 / 58.4; 20416 x 1912 31.7 / 34.4 / 33.2; 12416 x 2704 26.3 / 29.6 / 28.7.
 //   Rows of `out` in whole multiples of 8 KiB: fewer workgroups are better than paced ones, 8192 x 8192 49.2 / 50.8 / 47.1; 16384 x 16384 179.4 / 186.3 / 176.3 (under the bands without
 //   the skew not in odd multiples of 16 KiB, 8192 x 8192 49.7 / 51.5 / 52.0, and round robin below 56 MiB, 4096 x 2560 10.8 / 11.7 / 11.3).
-//   Rows of `in` or `out` in such multiples, under the bands and below 68 MiB: both, eight, 4096 x 4096 15.4 / 13.8 / 14.3; 2048 x 4096 9.3 / 9.0 / 8.5; 4160 x 4096 16.6 / 15.6 / 16.2;
-//   4096 x 4160 16.2 / 15.4 / 16.5; 8192 x 2048 15.6 / 14.8 / 15.4; above not, 320 x 57344 15.5 / 16.2; 1600 x 12288 16.5 / 17.2.
+//   Rows of `out` in such multiples and of `in` in whole tiles, or of `in` 8 KiB or a power of two of them, under the bands and below 68 MiB: both, eight, 4096 x 4096 15.4 / 13.8 / 14.3; 2048 x 4096 9.3 / 9.0 / 8.5; 4160 x 4096 16.6 / 15.6 / 16.2;
+//   4096 x 4160 16.2 / 15.4 / 16.5; 8192 x 2048 15.6 / 14.8 / 15.4; 24576 x 640 14.9 / 14.5 both five, eight; but part tiles 24576 x 672 15.8 both five, 16.3 eight, other rows of `in`
+//   320 x 36864 11.4 / 11.8, and above 320 x 57344 15.5 / 16.2; 1600 x 12288 16.5 / 17.2.
 // Tiles of 128, whose threads have eight loads each: all together, 1024 x 1024 4.0 us, paced 7.1 (out of the memory-side cache 3.2, 3.8), 8192 x 16384 97.5, 114, but paced without the skew
 // where both pitches alias: rows of `out` in multiples of 32 KiB and of `in` in 8, from 256 MiB on, 16384 x 16384 219, 267 together (16384 x 8192 123, 138; 16384 x 4096 62, 64; but
 // 16384 x 2048 31.9, 25.7 and 32768 x 2048 60, 56), and without the bands in multiples of 8 and 16 KiB, from 64 MiB on (4096 x 8192 29.7, 34.2; 8192 x 8192 58.9, 61.2; but 8192 x 4096
@@ -38,7 +42,7 @@ inline LoadPace load_pace(int tile, int64_t M, int64_t N, int mode) {
   const bool banded = swz_mode_grouped(mode), rr = (mode & 3) == kModeRR, out_8k = M * 2 % 8192 == 0;
   const int64_t moved = M * N * 4;
   if (tile != 64 || moved < (int64_t)(rr ? 20 : 32) << 20) return {0, 0};
-  if (banded && (out_8k || N * 2 % 8192 == 0) && moved < ((int64_t)68 << 20)) return {0, 0};
+  if (banded && ((out_8k && N % 64 == 0) || power_of_two_pitch(N)) && moved < ((int64_t)68 << 20)) return {0, 0};
   const bool few = out_8k && !(rr && moved < ((int64_t)56 << 20)) && !(banded && !swz_mode_skewed(mode) && M * 2 % 32768 == 16384);
   return {few ? 0 : 1, few ? 24576 : 0};
 }
@@ -53,11 +57,11 @@ inline bool paced_tiles32(int64_t M, int64_t N) { return M * N * 8 >= ((int64_t)
 // Which transposes under the default mode, with the band height left to the library, take the sweep of tile_sweep.h.  Time of the sweep over that of the skewed raster, loads and
 // occupancy as they are now.  Tiles: no pitch a power of two 0.84 to 1.00, on average 0.92 (40 sizes).  Both pitches multiples of 16 KiB: 8192 x 8192 x 4 B 0.99, 12288 x 8192
 // x 4 B 0.98, 16384 x 8192 x 2 B 0.94, but with one of 64 KiB 32768 x 8192 x 2 B 1.14, 16384 x 8192 x 4 B 1.13, 8192 x 16384 x 4 B 1.08, 16384 x 4096 x 4 B 1.01; 16384 x 16384
-// x 2 B (32 KiB) level.  Two bytes, rows of `in` in multiples of 8 KiB, sweep and skew: 1792 x 8192 13.9, 13.0; 2048 x 4096 8.8, 8.2; 1024 x 16384 14.9, 13.9; 4160 x 4096
-// 14.5, 14.4; but 512 x 8192 4.66, 4.81 and from 68 MiB on level, 1216 x 16384 16.5, 16.3; 2048 x 12288 20.1, 20.7.  Blocks into part lines, four bytes: 0.91 to 0.99, pitch of `in` a multiple of 8 KiB 0.98 to 1.04.
+// x 2 B (32 KiB) level.  Two bytes, rows of `in` 8 KiB or a power of two of them, sweep and skew: 1792 x 8192 13.9, 13.0; 2048 x 4096 8.8, 8.2; 1024 x 16384 14.9, 13.9; 4160 x 4096
+// 14.5, 14.4; but 512 x 8192 4.66, 4.81, other multiples of 8 KiB 64 x 184320 11.6, 12.0; 320 x 36864 11.4, 11.8, and from 68 MiB on level, 1216 x 16384 16.5, 16.3; 2048 x 12288 20.1, 20.7.  Blocks into part lines, four bytes: 0.91 to 0.99, pitch of `in` a multiple of 8 KiB 0.98 to 1.04.
 inline bool sweep_tiles(int64_t M, int64_t N, int elem_bytes) {
   const int64_t moved = 2 * M * N * elem_bytes;
-  if (elem_bytes == 2 && N * 2 % 8192 == 0 && moved >= ((int64_t)24 << 20) && moved < ((int64_t)68 << 20)) return false;
+  if (elem_bytes == 2 && power_of_two_pitch(N) && moved >= ((int64_t)24 << 20) && moved < ((int64_t)68 << 20)) return false;
   return (M | N) * elem_bytes % 16384 != 0 || (M * elem_bytes % 65536 != 0 && N * elem_bytes % 65536 != 0);
 }
 inline bool sweep_part_lines(int64_t N, int elem_bytes) { return elem_bytes == 4 && N * elem_bytes % 8192 != 0; }

@@ -39,14 +39,15 @@ def test_loads_of_tiles_of_128(rules, M, N, mode, paced):
     (1024, 1024, SKEWED, 0, 0), (2944, 2848, SKEWED, 0, 0), (2944, 2856, SKEWED, 1, 0), (5056, 5000, SKEWED, 1, 0), (5056, 5000, XCD, 1, 0),
     (4096, 4096, SKEWED, 0, 0), (2048, 4096, SKEWED, 0, 0), (4160, 4096, XCD_GROUPM, 0, 0), (4096, 4160, SKEWED, 0, 0), (4352, 4096, SKEWED, 1, 0),
     (8192, 2176, SKEWED, 0, 24576), (8192, 8192, SKEWED, 0, 24576), (8192, 8192, XCD_GROUPM, 1, 0), (16384, 16384, XCD_GROUPM, 0, 24576), (4096, 4096, XCD, 0, 24576),
-    (4160, 4096, XCD, 1, 0), (2176, 2408, RR, 0, 0), (2176, 2416, RR, 1, 0), (4096, 2560, RR, 1, 0), (4096, 4096, RR, 0, 24576)])
+    (4160, 4096, XCD, 1, 0), (2176, 2408, RR, 0, 0), (2176, 2416, RR, 1, 0), (4096, 2560, RR, 1, 0), (4096, 4096, RR, 0, 24576),
+    (24576, 672, SKEWED, 0, 24576), (24576, 640, SKEWED, 0, 0), (1408, 12288, SKEWED, 1, 0), (64, 184320, SKEWED, 1, 0), (1600, 8192, SKEWED, 0, 0)])
 def test_loads_of_tiles_of_64(rules, M, N, mode, paced, lds):
     assert (rules.paced(64, M, N, mode), rules.lds(64, M, N, mode)) == (paced, lds)
     assert (rules.paced(32, M, N, mode), rules.lds(32, M, N, mode)) == (0, 0)
 
 
 @pytest.mark.parametrize("M,N,elem_bytes,sweep", [(16384, 16384, 2, 1), (8192, 32768, 2, 0), (4096, 16384, 4, 0), (4096, 8192, 4, 1), (10048, 7040, 2, 1),
-                                                  (2048, 8192, 2, 0), (2048, 8200, 2, 1), (1536, 4096, 2, 0), (1472, 4096, 2, 1), (4288, 4096, 2, 0), (4352, 4096, 2, 1)])
+                                                  (2048, 8192, 2, 0), (2048, 8200, 2, 1), (1536, 4096, 2, 0), (1472, 4096, 2, 1), (4288, 4096, 2, 0), (4352, 4096, 2, 1), (1408, 12288, 2, 1), (64, 184320, 2, 1)])
 def test_which_tiles_are_swept(rules, M, N, elem_bytes, sweep):
     assert rules.sweep(M, N, elem_bytes) == sweep
 
